@@ -1,0 +1,53 @@
+"""The expert stand-ins on their own: every code of the fp8 format, group sizes that are and are
+not powers of two, streams that end inside a block, rows past N."""
+import numpy as np
+import pytest
+import torch
+
+from paper_2605_10670_amd import binding, synth
+
+import gpu_util as gu
+
+pytestmark = pytest.mark.gpu
+
+
+def routed_context(T, H, k=2, masked=0, **kw):
+    """Context with a layout of T tokens on 4 ranks x 2 slots, the last `masked` pairs dropped."""
+    E, R = 8, 4
+    ctx = binding.Context(num_ranks=R, slots_per_rank=2, primary_slots=2, num_logical=E, max_tokens=T,
+                          topk=k, hidden=H, **kw)
+    p2l = synth.preferred_placement(R, 2, 0)
+    ctx.update_placement(p2l)
+    idx = np.stack([np.random.default_rng(T + H + t).permutation(E)[:k] for t in range(T)])
+    idx = idx.astype(np.int32)
+    if masked:
+        idx.reshape(-1)[-masked:] = -1
+    ctx.dispatch_layout(gu.to_dev(idx), T)
+    return ctx, p2l, idx
+
+
+# 512 vectors of 8 codes per block: streams of less than one block, of exactly one and of
+# several, with 0, 1 and many vectors left over
+@pytest.mark.parametrize("T,H,group,masked", [(4, 64, 16, 1), (4, 512, 128, 0), (32, 512, 128, 5),
+                                              (12, 192, 48, 0), (44, 1152, 96, 3), (36, 192, 48, 1),
+                                              (64, 7168, 128, 7), (20, 6400, 1600, 2)])
+def test_dequant_stand_in(oracle, T, H, group, masked):
+    k = 2
+    ctx, _, _ = routed_context(T, H, k, masked, x_dtype="fp8", scale_group=group)
+    try:
+        rng = np.random.default_rng(H)
+        q = rng.permutation(np.resize(np.arange(256, dtype=np.uint8), T * k * H)).reshape(T * k, H)
+        sc = np.exp(rng.uniform(-20, 5, (T * k, H // group))).astype(np.float32)
+        sc[0, 0] = 1e-41                       # a subnormal scale
+        y = gu.dev_empty(T * k, H, "bf16", fill=0x1234)
+        ctx.expert_stub("dequant", gu.to_dev(q), y, T, recv_scale=gu.to_dev(sc))
+        N = T * k - masked
+        got = gu.to_host(y, np.uint16)
+        want = oracle.stub_dequant(q, sc, N, group)
+        nan = (q & 0x7f) == 0x7f               # both NaN codes, quiet, with the code's sign
+        assert ((want[:N] & 0x7fff) > 0x7f80)[nan[:N]].all()
+        want[nan] = 0x7fc0 | ((q[nan].astype(np.uint16) & 0x80) << 8)
+        assert np.array_equal(got[:N], want[:N])
+        assert (got[N:] == 0x1234).all(), "rows past N were written"
+    finally:
+        ctx.destroy()
