@@ -35,7 +35,9 @@ __global__ __launch_bounds__(256) void k_calibration_stream(const u32x4* __restr
 #pragma unroll
   for (int j = 0; j < WR; ++j) {
     u32x4 o = v + (uint32_t)j;
-    asm volatile("global_store_dwordx4 %0, %1, off sc0 sc1" ::"v"(&dst[j * stride + i]), "v"(o)
+    // the wait states keep the next vector instruction off the data registers of the store
+    asm volatile("global_store_dwordx4 %0, %1, off sc0 sc1\n\ts_nop 1" ::"v"(&dst[j * stride + i]),
+                 "v"(o)
                  : "memory");
   }
 }
