@@ -404,8 +404,8 @@ int eep_host_uncovered_experts(int32_t P, int32_t E, int32_t S, const int32_t* p
                                const int32_t* active);
 /* How eep_dispatch_layout tiles T tokens of R source ranks:
  * out = {tokens per rank, tiles per rank, tokens per tile (<= 128), tiles}.
- * (Batches of at most 192 tokens and 1536 pairs are laid out by a single
- * workgroup without tiles; the results are the same.) */
+ * (Batches of at most 512 tokens and 4096 pairs are laid out in one launch
+ * without tiles; the results are the same.) */
 int eep_host_tiling(int32_t T, int32_t R, int32_t out[4]);
 
 /* Placement repair after a membership change (Sec. 3.5, Sec. 5.1; worked

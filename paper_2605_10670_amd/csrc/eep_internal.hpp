@@ -36,8 +36,8 @@ inline Tiling make_tiling(int T, int R) {
   return g;
 }
 
-// LDS bytes of the map kernel: placement CSR, active mask, live-replica table,
-// per-slot token bitmaps and the tile's router indices / chosen slots.
+// The bound on table shapes that the layout accepts: LDS bytes of a tile with two ints per pair,
+// two tables per expert and six per slot.  What the kernels use today is less.
 inline size_t map_lds_bytes(int E, int P, int R, int tile_tokens, int k) {
   return sizeof(int32_t) * ((size_t)(E + 1) + P + R + E + P + (size_t)P * kBitmapWords +
                             (size_t)2 * tile_tokens * k);

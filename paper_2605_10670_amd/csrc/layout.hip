@@ -7,32 +7,37 @@
 // Sec. 3.2 (validity contract), Sec. 4.1 (contiguous per-expert receive
 // buffers as in prior work).
 //
-// Two or three launches, all tiny and latency-bound (the step's metadata is
+// One to three launches, all tiny and latency-bound (the step's metadata is
 // < 1 MB), so the design goal is a short chain of dependent memory round trips,
 // not bandwidth.  Every kernel issues all its global loads before its first
 // wait.
+//   k_layout_small  (<= 512 tokens) everything in one launch, see there.
 //   k_map_count  one workgroup per tile of <= 128 tokens of ONE source rank.
 //                Placement CSR, active mask and the tile's router indices are
-//                fetched into LDS with independent loads; the live-replica
-//                table is then built from LDS.  For every slot the kernel
-//                records a bitmap of the tile's tokens that hit it: popcount
-//                of the bitmap is the tile's count, popcount of the bits below
-//                a token is that pair's stable rank inside the tile.  No
-//                atomics on positions, so the order is deterministic.
-//   k_scan_position  (<= 64 tiles) one workgroup per tile.  Thread = slot walks
-//                the [tiles][P] count matrix in registers (coalesced, no
-//                cross-lane traffic) for the slot total and the pairs of
-//                earlier tiles; slot totals are then scanned across the
-//                workgroup; row = slot offset + pairs of earlier tiles + rank
-//                in tile.  Each workgroup repeats the small scan rather than
-//                wait for another kernel.
+//                fetched with independent loads.  For every slot the kernel
+//                records a count and a bitmap of the tile's tokens that hit it:
+//                popcount of the bits below a token is that pair's stable rank
+//                inside the tile.  No atomics on positions, so the order is
+//                deterministic.
+//   k_scan_position  (<= 64 tiles) one workgroup per tile.  Lane = slot; the
+//                workgroup's wavefronts share the rows of the [tiles][P] count
+//                matrix (coalesced) for the slot totals and the pairs of
+//                earlier tiles; one wavefront scans the totals; row = slot
+//                offset + pairs of earlier tiles + rank in tile.  Each
+//                workgroup repeats the small scan rather than wait for another
+//                kernel.
 //   k_tile_prefix + k_position  (> 64 tiles) the tile prefixes are computed once
 //                by a few workgroups, then a wide grid computes the rows.
+// Measured (a layout in a graph of 40; 32 ranks x 9 slots, top-8): T = 1024 / 4096 / 16384 in
+// 7.8 / 8.5 / 13.0 us; 9.7 / 10.5 / 14.3 while the live replicas were compacted per expert in
+// LDS, the repeat check read LDS, counts were popcounts over the bitmaps, the scan took two
+// barriers and half of k_scan_position's threads loaded the whole matrix.
 #include "eep_internal.hpp"
 
 namespace eep {
 
 constexpr int kMapThreads = 1024;
+constexpr int kMapWaves = kMapThreads / 64;
 constexpr int kPosThreads = 256;
 
 // Tile b covers tokens [t0, t0 + ntok) of source rank b / tiles_per_rank; the
@@ -53,144 +58,297 @@ __device__ inline TileRange tile_range(int b, int tokens_per_rank, int tiles_per
   return r;
 }
 
+// ---------------------------------------------------------------------------
+// Routing tables in LDS, shared by the kernels that map pairs to slots.  What
+// bounds those kernels is the chain of dependent round trips, so the tables
+// take one: every global load is issued before the first wait, the active mask
+// becomes a wave-wide ballot instead of an LDS array (R <= 64), and instead of
+// a compacted list of live replicas per expert there is one bit per entry of
+// the replica lists (`alive`), from which a pair counts and picks its replica.
+// ---------------------------------------------------------------------------
+struct RouteTables {
+  int32_t* off;     // [E+1] replica-list starts (CSR)
+  int32_t* list;    // [P] replica lists, canonical order
+  uint32_t* alive;  // [alive_words(P)] bit q: the replica in list[q] is on an active rank
+};
+
+// Bits are written 64 at a time; a pair whose expert's list starts at o <= P reads the words
+// o / 32 and o / 32 + 1, so two more words follow.
+__host__ __device__ inline int alive_words(int P) { return (P + 63) / 64 * 2 + 2; }
+__host__ __device__ inline int mask_words(int R) { return R > 64 ? (R + 31) / 32 : 0; }
+inline size_t route_table_ints(int E, int P, int R) {
+  return (size_t)(E + 1) + P + alive_words(P) + mask_words(R);
+}
+
+// Rank that owns slot p: p / S with inv_S = 1.0f / S.  (p + 0.5) / S is at least 0.5 / S away
+// from an integer and the float result at most (P / S) * 2^-23 off, so it is exact for all
+// P < 2^22; the library's limit is 2^20.
+__device__ __forceinline__ int rank_of_slot(int p, float inv_S) {
+  return (int)(((float)p + 0.5f) * inv_S);
+}
+
+// Fills the tables at `lds` (route_table_ints of it) with the whole workgroup of NT threads;
+// the caller's next barrier makes them readable.  For R > 64 the mask goes through LDS, which
+// takes one barrier here.
+template <int NT>
+__device__ __forceinline__ RouteTables load_route_tables(int32_t* lds, const int32_t* __restrict__ l2p_off,
+                                                const int32_t* __restrict__ l2p_list,
+                                                const int32_t* __restrict__ active, int E, int R,
+                                                int P, float inv_S) {
+  RouteTables rt;
+  rt.off = lds;
+  rt.list = rt.off + (E + 1);
+  rt.alive = (uint32_t*)(rt.list + P);
+  const int tid = threadIdx.x, lane = tid & 63;
+  if (R <= 64) {
+    const int a = lane < R ? active[lane] : 0;
+    const int p0 = tid < P ? l2p_list[tid] : -1;
+    for (int i = tid; i <= E; i += NT) rt.off[i] = l2p_off[i];
+    const uint64_t mask = __ballot(a != 0);
+    for (int q = tid; q - lane < P; q += NT) {  // whole wavefronts, for the ballot
+      const int p = q == tid ? p0 : q < P ? l2p_list[q] : -1;
+      if (q < P) rt.list[q] = p;
+      const uint64_t bits = __ballot(p >= 0 && ((mask >> (rank_of_slot(p, inv_S) & 63)) & 1));
+      if (lane == 0) {
+        rt.alive[(q >> 5)] = (uint32_t)bits;
+        rt.alive[(q >> 5) + 1] = (uint32_t)(bits >> 32);
+      }
+    }
+  } else {
+    uint32_t* mask = rt.alive + alive_words(P);
+    for (int r = tid; r - lane < R; r += NT) {
+      const uint64_t bits = __ballot(r < R && active[r] != 0);
+      if (lane == 0) {
+        mask[r >> 5] = (uint32_t)bits;
+        if ((r >> 5) + 1 < mask_words(R)) mask[(r >> 5) + 1] = (uint32_t)(bits >> 32);
+      }
+    }
+    for (int i = tid; i <= E; i += NT) rt.off[i] = l2p_off[i];
+    __syncthreads();
+    for (int q = tid; q - lane < P; q += NT) {
+      const int p = q < P ? l2p_list[q] : -1;
+      if (q < P) rt.list[q] = p;
+      const int r = p >= 0 ? rank_of_slot(p, inv_S) : 0;
+      const uint64_t bits = __ballot(p >= 0 && ((mask[r >> 5] >> (r & 31)) & 1));
+      if (lane == 0) {
+        rt.alive[(q >> 5)] = (uint32_t)bits;
+        rt.alive[(q >> 5) + 1] = (uint32_t)(bits >> 32);
+      }
+    }
+  }
+  if (tid < 2) rt.alive[alive_words(P) - 1 - tid] = 0;
+  return rt;
+}
+
+// The live replica that serves token t's pair with expert e (in [0, E)), or -1.
+__device__ __forceinline__ int pick_slot(const RouteTables& rt, int e, int t, int policy) {
+  const int o = rt.off[e], m = rt.off[e + 1] - o;  // m replicas, dead ones included
+  if (m <= 32) {
+    // bits o .. o + 31 of `alive`, the first m of them the expert's
+    const uint64_t two = (uint64_t)rt.alive[(o >> 5) + 1] << 32 | rt.alive[o >> 5];
+    uint32_t bits = (uint32_t)(two >> (o & 31)) & (uint32_t)((1ull << m) - 1);
+    if (bits == 0) return -1;
+    const int n = __popc(bits);
+    int sel = (policy == EEP_FIRST_LIVE || n == 1) ? 0 : n == 2 ? t & 1 : t % n;
+    for (; sel > 0; --sel) bits &= bits - 1;
+    return rt.list[o + __ffs(bits) - 1];
+  }
+  int n = 0;
+  for (int q = o; q < o + m; ++q) n += (rt.alive[q >> 5] >> (q & 31)) & 1;
+  if (n == 0) return -1;
+  int sel = policy == EEP_FIRST_LIVE ? 0 : t % n;
+  int q = o;
+  for (;; ++q)
+    if ((rt.alive[q >> 5] >> (q & 31)) & 1) {
+      if (sel == 0) break;
+      --sel;
+    }
+  return rt.list[q];
+}
+
+// Does pair j of a token repeat an earlier expert of it?  Pairs are laid out token by token,
+// one per lane from a multiple of k on, so for k a power of two <= 16 a token's pairs lie in
+// one DPP row and the earlier ones are reached without LDS; other k read the token's
+// indices (`token_idx`, k of them).
+template <int SHR>
+__device__ __forceinline__ bool earlier_lane_equals(int e, int j) {
+  const int v = __builtin_amdgcn_update_dpp(-1, e, 0x110 + SHR, 0xf, 0xf, false);  // row_shr:SHR
+  return j >= SHR && v == e;
+}
+template <int KC>
+__device__ __forceinline__ bool repeats_earlier(int e, int j, const int32_t* token_idx) {
+  bool r = false;
+  if constexpr (KC == 0) {
+    for (int jj = 0; jj < j; ++jj) r |= token_idx[jj] == e;
+  } else {
+    static_assert(KC == 1 || KC == 2 || KC == 4 || KC == 8, "pairs of a token share a DPP row");
+    if constexpr (KC > 1) r |= earlier_lane_equals<1>(e, j);
+    if constexpr (KC > 2) r |= earlier_lane_equals<2>(e, j) | earlier_lane_equals<3>(e, j);
+    if constexpr (KC > 4)
+      r |= earlier_lane_equals<4>(e, j) | earlier_lane_equals<5>(e, j) |
+           earlier_lane_equals<6>(e, j) | earlier_lane_equals<7>(e, j);
+  }
+  return r;
+}
+
 // A token can hit a slot at most once: its k logical experts are distinct
 // (repeats are masked) and a slot holds one logical expert.  So one bit per
-// (slot, token of the tile) is enough.
-template <int KC>  // KC = compile-time k (power of two) or 0 for any k
+// (slot, token of the tile) is enough: popcount of the bits below a token is
+// its stable rank in the slot.  The slot's count is kept beside the bitmap, so
+// that nobody has to walk the words for it.
+constexpr int kMaxPairsPerThread = kTileTokens * kMaxTopk / kMapThreads;
+
+// Maps this thread's pairs tid, tid + NT, ... of a batch of `npairs` (router indices at `idx`,
+// first token t0): slots to slot[] (-1: not routed), token bits to s_bm
+// ([P][stride], zeroed), counts to s_count (zeroed), dropped pairs to s_drop {uncovered, masked}
+// (zeroed).  my_e holds the indices already loaded; s_idx the same in LDS when KC == 0.  Slots of
+// the pairs [own_lo, own_hi) are written to slot_of.
+template <int KC, int NT, int U>
+__device__ __forceinline__ void map_pairs(const RouteTables& rt, const int (&my_e)[U],
+                                          const int32_t* s_idx, int (&slot)[U], uint32_t* s_bm,
+                                          int stride, int32_t* s_count, int32_t* s_drop, int npairs,
+                                          int k, int E, int t0, int policy, int own_lo,
+                                          int own_hi, int32_t* __restrict__ slot_of) {
+  const int wave0 = __builtin_amdgcn_readfirstlane(threadIdx.x & ~63);
+#pragma unroll
+  for (int u = 0; u < U; ++u) {
+    const int i = threadIdx.x + u * NT;
+    slot[u] = -1;
+    if (wave0 + u * NT >= npairs) break;  // a wavefront without pairs stays out of the others' way
+    const int tl = i / k, j = i - tl * k;
+    const int e = my_e[u];
+    const bool repeated = repeats_earlier<KC>(e, j, KC == 0 && i < npairs ? s_idx + tl * k : s_idx);
+    if (i < npairs) {
+      int p = -1;
+      if ((unsigned)e >= (unsigned)E || repeated) {
+        atomicAdd(&s_drop[1], 1);
+      } else {
+        p = pick_slot(rt, e, t0 + tl, policy);
+        if (p < 0) {
+          atomicAdd(&s_drop[0], 1);
+        } else {
+          atomicOr(&s_bm[p * stride + (tl >> 5)], 1u << (tl & 31));
+          atomicAdd(&s_count[p], 1);
+        }
+      }
+      slot[u] = p;
+      if (i >= own_lo && i < own_hi) slot_of[i] = p;
+    }
+  }
+}
+
+// Stable rank of token tl in a slot: tokens before it in the slot's bitmap.  Words are read four
+// at a time, so that their LDS latencies overlap; up to three of them lie behind the token's
+// own word and are not counted (they may belong to the next slot, or to the array behind
+// the bitmaps: the caller's LDS goes on for at least three words).
+__device__ __forceinline__ int rank_in_slot(const uint32_t* bm, int tl) {
+  const int tw = tl >> 5;
+  int r = __popc(bm[tw] & ((1u << (tl & 31)) - 1u));
+  for (int w = 0; w < tw; w += 4) {
+    uint32_t v[4];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) v[u] = bm[w + u];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) r += w + u < tw ? __popc(v[u]) : 0;
+  }
+  return r;
+}
+
+// LDS ints of the map kernel for a tile: tables, counts, bitmaps, and the router indices
+// where k is not handled lane to lane.
+inline size_t map_lds_ints(int E, int P, int R, int tile_tokens, int k) {
+  return route_table_ints(E, P, R) + P + (size_t)P * kBitmapWords + (size_t)tile_tokens * k;
+}
+
+template <int KC, int U>  // KC = compile-time k (power of two) or 0 for any k
 __global__ __launch_bounds__(kMapThreads) void k_map_count(
     const int32_t* __restrict__ topk_idx, const int32_t* __restrict__ l2p_off,
     const int32_t* __restrict__ l2p_list, const int32_t* __restrict__ active,
     int32_t* __restrict__ slot_of, int32_t* __restrict__ rank_in_tile,
     int32_t* __restrict__ cnt_tile, int32_t* __restrict__ blk_unc,
-    int32_t* __restrict__ blk_msk, int k_rt, int E, int R, int S, int P, int tokens_per_rank,
-    int tiles_per_rank, int tile_tokens, int policy) {
+    int32_t* __restrict__ blk_msk, int k_rt, int E, int R, int P, int tokens_per_rank,
+    int tiles_per_rank, int tile_tokens, int policy, float inv_S) {
   const int k = KC > 0 ? KC : k_rt;
   extern __shared__ int32_t smem[];
-  int32_t* s_off = smem;                         // [E+1] replica-list starts (CSR)
-  int32_t* s_list = s_off + (E + 1);             // [P] replica lists, canonical order
-  int32_t* s_active = s_list + P;                // [R]
-  int32_t* s_nlive = s_active + R;               // [E] live replicas of expert e
-  int32_t* s_live = s_nlive + E;                 // [P] live replicas, compacted per expert
-  uint32_t* s_bm = (uint32_t*)(s_live + P);      // [P][kBitmapWords]
-  int32_t* s_idx = (int32_t*)(s_bm + P * kBitmapWords);  // [tile_tokens*k] router indices
-  int32_t* s_slot = s_idx + tile_tokens * k;             // [tile_tokens*k] chosen slots
+  int32_t* s_count = smem;                       // [P] pairs of the tile per slot
+  uint32_t* s_bm = (uint32_t*)(s_count + P);     // [P][kBitmapWords]
+  int32_t* s_idx = (int32_t*)(s_bm + P * kBitmapWords);  // [tile_tokens*k], KC == 0 only
+  int32_t* s_tab = s_idx + (KC == 0 ? tile_tokens * k : 0);
   __shared__ int32_t s_drop[2];
 
   const int tid = threadIdx.x;
   const int b = blockIdx.x;
   const TileRange tr = tile_range(b, tokens_per_rank, tiles_per_rank, tile_tokens);
-  const int t0 = tr.t0;
   const int npairs = tr.ntok * k;
-  const int64_t g0 = (int64_t)t0 * k;
+  const int64_t g0 = (int64_t)tr.t0 * k;
 
-  // every global read of this kernel is issued here, none depends on another
-  for (int i = tid; i < npairs; i += kMapThreads) s_idx[i] = topk_idx[g0 + i];
-  for (int i = tid; i <= E; i += kMapThreads) s_off[i] = l2p_off[i];
-  for (int i = tid; i < P; i += kMapThreads) s_list[i] = l2p_list[i];
-  for (int i = tid; i < R; i += kMapThreads) s_active[i] = active[i];
-  for (int i = tid; i < P * kBitmapWords; i += kMapThreads) s_bm[i] = 0u;
-  if (tid < 2) s_drop[tid] = 0;
-  __syncthreads();
-
-  for (int e = tid; e < E; e += kMapThreads) {
-    int o = s_off[e], o1 = s_off[e + 1], n = 0;
-    for (int q = o; q < o1; ++q) {
-      int p = s_list[q];
-      if (s_active[p / S] != 0) s_live[o + n++] = p;  // failed peers are skipped
-    }
-    s_nlive[e] = n;
-  }
-  __syncthreads();
-
-  int n_unc = 0, n_msk = 0;
-  for (int i = tid; i < npairs; i += kMapThreads) {
-    int tl = i / k;
-    int j = i - tl * k;
-    int e = s_idx[i];
-    int p = -1;
-    if (e < 0 || e >= E) {
-      ++n_msk;
-    } else {
-      bool repeated = false;
-      for (int jj = 0; jj < j; ++jj) repeated |= (s_idx[tl * k + jj] == e);
-      if (repeated) {
-        ++n_msk;
-      } else {
-        int n = s_nlive[e];
-        if (n == 0) {
-          ++n_unc;
-        } else {
-          int sel = (policy == EEP_FIRST_LIVE || n == 1) ? 0 : (t0 + tl) % n;
-          p = s_live[s_off[e] + sel];
-          atomicOr(&s_bm[p * kBitmapWords + (tl >> 5)], 1u << (tl & 31));
-        }
-      }
-    }
-    s_slot[i] = p;
-    slot_of[g0 + i] = p;
-  }
-  if (n_unc) atomicAdd(&s_drop[0], n_unc);
-  if (n_msk) atomicAdd(&s_drop[1], n_msk);
-  __syncthreads();
-
-  for (int i = tid; i < npairs; i += kMapThreads) {
-    int p = s_slot[i];
-    int r = -1;
-    if (p >= 0) {
-      int tl = i / k;
-      int w = tl >> 5;
-      const uint32_t* bm = &s_bm[p * kBitmapWords];
-      r = __popc(bm[w] & ((1u << (tl & 31)) - 1u));
-      for (int ww = 0; ww < w; ++ww) r += __popc(bm[ww]);
-    }
-    rank_in_tile[g0 + i] = r;
-  }
-  for (int p = tid; p < P; p += kMapThreads) {
-    int c = 0;
+  int my_e[U], slot[U];
 #pragma unroll
-    for (int w = 0; w < kBitmapWords; ++w) c += __popc(s_bm[p * kBitmapWords + w]);
-    cnt_tile[(int64_t)b * P + p] = c;
+  for (int u = 0; u < U; ++u) {
+    const int i = tid + u * kMapThreads;
+    my_e[u] = i < npairs ? topk_idx[g0 + i] : -1;
   }
+  for (int i = tid; i < P * (kBitmapWords + 1); i += kMapThreads) s_count[i] = 0;  // and s_bm
+  if (tid < 2) s_drop[tid] = 0;
+  const RouteTables rt =
+      load_route_tables<kMapThreads>(s_tab, l2p_off, l2p_list, active, E, R, P, inv_S);
+  if constexpr (KC == 0) {
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+      if (tid + u * kMapThreads < npairs) s_idx[tid + u * kMapThreads] = my_e[u];
+  }
+  __syncthreads();
+  map_pairs<KC, kMapThreads, U>(rt, my_e, s_idx, slot, s_bm, kBitmapWords, s_count, s_drop, npairs,
+                                k, E, tr.t0, policy, 0, npairs, slot_of + g0);
+  __syncthreads();
+#pragma unroll
+  for (int u = 0; u < U; ++u) {
+    const int i = tid + u * kMapThreads;
+    if (i < npairs)
+      rank_in_tile[g0 + i] = slot[u] >= 0 ? rank_in_slot(&s_bm[slot[u] * kBitmapWords], i / k) : -1;
+  }
+  for (int p = tid; p < P; p += kMapThreads) cnt_tile[(int64_t)b * P + p] = s_count[p];
   if (tid == 0) {
     blk_unc[b] = s_drop[0];
     blk_msk[b] = s_drop[1];
   }
 }
 
-// inclusive scan inside aligned groups of `seg` lanes (seg a power of two <= 64)
-__device__ inline int seg_inclusive_scan(int v, int seg) {
-  const int sl = (threadIdx.x & 63) & (seg - 1);
-  for (int d = 1; d < seg; d <<= 1) {
-    int o = __shfl_up(v, d, 64);
-    if (sl >= d) v += o;
-  }
+// Inclusive scan across the 64 lanes of a wavefront, in DPP (no LDS round trips).
+__device__ __forceinline__ int wave_inclusive_scan(int v) {
+  v += __builtin_amdgcn_update_dpp(0, v, 0x111, 0xf, 0xf, false);  // row_shr:1
+  v += __builtin_amdgcn_update_dpp(0, v, 0x112, 0xf, 0xf, false);  // row_shr:2
+  v += __builtin_amdgcn_update_dpp(0, v, 0x114, 0xf, 0xf, false);  // row_shr:4
+  v += __builtin_amdgcn_update_dpp(0, v, 0x118, 0xf, 0xf, false);  // row_shr:8
+  v += __builtin_amdgcn_update_dpp(0, v, 0x142, 0xa, 0xf, false);  // row_bcast:15 -> rows 1, 3
+  v += __builtin_amdgcn_update_dpp(0, v, 0x143, 0xc, 0xf, false);  // row_bcast:31 -> rows 2, 3
   return v;
 }
 
-// Exclusive scan of s_count[0..P) into s_offset[0..P] by the whole workgroup
-// (NT threads, NT/64 <= 16 wavefronts).  Ends with a barrier.
-template <int NT>
-__device__ inline void block_exclusive_scan(const int32_t* s_count, int32_t* s_offset,
-                                            int32_t* s_wave, int P) {
-  const int tid = threadIdx.x;
-  const int ipt = (P + NT - 1) / NT;
-  const int lo = tid * ipt;
-  int hi = lo + ipt;
-  if (hi > P) hi = P;
-  int local = 0;
-  for (int p = lo; p < hi; ++p) local += s_count[p];
-  int incl = seg_inclusive_scan(local, 64);
-  if ((tid & 63) == 63) s_wave[tid >> 6] = incl;
-  __syncthreads();
-  int wave_base = 0;
-  for (int w = 0; w < (tid >> 6); ++w) wave_base += s_wave[w];
-  int run = wave_base + incl - local;
-  for (int p = lo; p < hi; ++p) {
-    s_offset[p] = run;
-    run += s_count[p];
+// Exclusive scan of s_count[0..n) into s_offset[0..n] by ONE wavefront, 64 values at a time
+// and kScanChunks such groups at once (their loads and scans are independent; only the running
+// sum is a chain).  The caller's next barrier makes the result readable.
+constexpr int kScanChunks = 5;
+__device__ __forceinline__ void wave_exclusive_scan(const int32_t* s_count, int32_t* s_offset, int n) {
+  const int lane = threadIdx.x & 63;
+  int run = 0;
+  for (int c0 = 0; c0 < n; c0 += 64 * kScanChunks) {
+    int v[kScanChunks], incl[kScanChunks];
+#pragma unroll
+    for (int c = 0; c < kScanChunks; ++c) {
+      const int p = c0 + c * 64 + lane;
+      v[c] = p < n ? s_count[p] : 0;
+    }
+#pragma unroll
+    for (int c = 0; c < kScanChunks; ++c) incl[c] = wave_inclusive_scan(v[c]);
+#pragma unroll
+    for (int c = 0; c < kScanChunks; ++c) {
+      const int p = c0 + c * 64 + lane;
+      if (p < n) s_offset[p] = run + incl[c] - v[c];
+      run += __builtin_amdgcn_readlane(incl[c], 63);
+    }
   }
-  if (tid == NT - 1) s_offset[P] = wave_base + incl;
-  __syncthreads();
+  if (lane == 0) s_offset[n] = run;
 }
 
 // Per-step tables every consumer needs, written once by one workgroup
@@ -225,13 +383,17 @@ __device__ inline void write_step_tables(const int32_t* s_count, const int32_t* 
 // ---------------------------------------------------------------------------
 // Few tiles (<= 64, the decode regime): scan and position fused.  Every
 // workgroup (one per tile) re-derives what it needs from the [tiles][P] count
-// matrix -- slot totals and the pairs of earlier tiles -- with thread = slot and
-// the tiles walked in registers, so that the kernel has one round of global
-// loads (two beyond 32 tiles), all issued before the first wait.
+// matrix -- slot totals and the pairs of earlier tiles -- with lane = slot and
+// the tiles shared between the wavefronts, so that a wavefront has one round of
+// loads (three sets of wavefronts at 288 slots: 11 loads at 32 tiles, 22 in two
+// rounds at 64).  Measured (T = 1024 / 4096 / 5976, whole layout): 12 loads per
+// round 7.8 / 8.5 / 8.5 us, 8 7.9 / 8.5 / 8.1, 16 8.0 / 8.6 / 8.7; 512 threads 8.4 / 9.0 / 8.3.
 // ---------------------------------------------------------------------------
-constexpr int kFusedThreads = 512;
-constexpr int kFusedPairs = 4;    // pairs of the tile kept in registers per thread
-constexpr int kTileBatch = 32;    // count-matrix rows fetched per round
+constexpr int kFusedThreads = 1024;
+constexpr int kFusedWaves = kFusedThreads / 64;
+constexpr int kFusedPairs = 2048 / kFusedThreads;  // pairs of the tile kept in registers per thread
+constexpr int kFusedBatch = 12;   // count-matrix rows fetched per round
+constexpr int kTileBatch = 32;    // count-matrix rows k_tile_prefix fetches per round
 
 template <int KC>
 __global__ __launch_bounds__(kFusedThreads) void k_scan_position(
@@ -249,7 +411,6 @@ __global__ __launch_bounds__(kFusedThreads) void k_scan_position(
   int32_t* s_count = smem;           // [P]   pairs per slot, all tiles
   int32_t* s_offset = s_count + P;   // [P+1] exclusive scan of s_count
   int32_t* s_pre = s_offset + P + 1; // [P]   pairs per slot in tiles before this one
-  __shared__ int32_t s_wave[kFusedThreads / 64];
   __shared__ int32_t s_drop[2];
   const int tid = threadIdx.x;
   const int b = blockIdx.x;
@@ -276,29 +437,46 @@ __global__ __launch_bounds__(kFusedThreads) void k_scan_position(
     if (tid == 0) version = *tbl_version + *mem_version;
   }
   if (tid < 2) s_drop[tid] = 0;
-  for (int p = tid; p < P; p += kFusedThreads) {
-    int total = 0, before = 0, src_part = 0;
-    for (int tb = 0; tb < num_tiles; tb += kTileBatch) {
-      int v[kTileBatch];
+  for (int p = tid; p < P; p += kFusedThreads) s_count[p] = s_pre[p] = 0;
+  // Wavefronts take 64 slots each, and as many sets of wavefronts as fit share the tiles; the
+  // sets' sums meet in LDS.
+  const int slot_waves = (P + 63) / 64;
+  const int sets = kFusedWaves > slot_waves ? kFusedWaves / slot_waves : 1;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  __syncthreads();
+  for (int w = wave; w < sets * slot_waves; w += kFusedWaves) {
+    const int set = w / slot_waves;
+    const int p = (w - set * slot_waves) * 64 + (tid & 63);
+    int total = 0, before = 0;
+    for (int tb = set; tb < num_tiles; tb += sets * kFusedBatch) {
+      int v[kFusedBatch];
 #pragma unroll
-      for (int u = 0; u < kTileBatch; ++u)
-        v[u] = tb + u < num_tiles ? cnt_tile[(int64_t)(tb + u) * P + p] : 0;
+      for (int u = 0; u < kFusedBatch; ++u) {
+        const int tile = tb + u * sets;
+        v[u] = tile < num_tiles && p < P ? cnt_tile[(int64_t)tile * P + p] : 0;
+      }
 #pragma unroll
-      for (int u = 0; u < kTileBatch; ++u) {
-        int tile = tb + u;
+      for (int u = 0; u < kFusedBatch; ++u) {
         total += v[u];
-        before += tile < b ? v[u] : 0;
-        src_part += (tile >= first && tile < first + tiles_per_rank) ? v[u] : 0;
+        before += tb + u * sets < b ? v[u] : 0;
       }
     }
-    s_count[p] = total;
-    s_pre[p] = before;
-    if (sub_tile == 0) cnt_src[(int64_t)src_rank * P + p] = src_part;
+    if (p < P) {
+      atomicAdd(&s_count[p], total);
+      atomicAdd(&s_pre[p], before);
+    }
   }
+  if (sub_tile == 0)  // pairs per (source rank, slot): the source rank's own tiles
+    for (int p = tid; p < P; p += kFusedThreads) {
+      int part = 0;
+      for (int t = first; t < first + tiles_per_rank; ++t) part += cnt_tile[(int64_t)t * P + p];
+      cnt_src[(int64_t)src_rank * P + p] = part;
+    }
   __syncthreads();
   if (du) atomicAdd(&s_drop[0], du);  // zeroed before the barrier, read after the scan's barriers
   if (dm) atomicAdd(&s_drop[1], dm);
-  block_exclusive_scan<kFusedThreads>(s_count, s_offset, s_wave, P);
+  if (tid < 64) wave_exclusive_scan(s_count, s_offset, P);
+  __syncthreads();
 
   const int N = s_offset[P];
 #pragma unroll
@@ -321,37 +499,62 @@ __global__ __launch_bounds__(kFusedThreads) void k_scan_position(
 }
 
 // ---------------------------------------------------------------------------
-// Small batches (T <= 192 tokens and T*k <= 1536 pairs: a few tokens per rank,
-// the low-concurrency decode regime): ONE workgroup does the whole layout in one
-// launch -- map, count, scan and position -- with a token bitmap per slot that
-// spans the whole batch.  No tiles, no second kernel.  Measured at 32 ranks,
-// top-8: the step drops from 17.3 / 18.8 / 22.7 us to 14.5 / 16.0 / 20.1 us at
-// T = 32 / 64 / 128, and by 0.7 us at T = 160 and 192; from 2 pairs per thread
-// on, the tiled two-launch path is as fast or faster, hence the limits.
+// Small batches (T <= 512 tokens and T*k <= 4096 pairs: up to 16 tokens per rank
+// at 32 ranks, the low-concurrency decode regime): the whole layout in ONE
+// launch with a token bitmap per slot that spans the batch.  Bound by latency:
+// the launch (1.9 us for an empty kernel), one round of global loads, LDS round
+// trips, and stores.  Every workgroup maps ALL pairs (1 to 4 per thread, each
+// keeps the whole count and offset table) and then writes its eighth of the
+// results, so no workgroup waits for another; one alone spent 1.4 to 2.8 us on
+// storing, mostly the [R][P] matrix of pairs per (source rank, slot).  Measured,
+// 32 ranks x 9 slots, top-8, a layout in a graph of 40: T = 32 / 128 / 256 / 384 /
+// 512 in 4.1 / 4.2 / 4.9 / 5.6 / 6.4 us with 8 workgroups, 4.1 / 4.3 / 5.2 / 6.0 / 6.6
+// with 4, 4.6 / 5.0 / 6.2 / 7.6 / 8.7 with 1.  The tiled path takes 7.7 us at 256 to
+// 1024 tokens; 8 pairs per thread (T = 768) would be no faster than that, hence the
+// limits.
 // ---------------------------------------------------------------------------
-constexpr int kSmallTokens = 192;
-constexpr int kSmallPairs = 1536;
+constexpr int kSmallBlocks = 8;
+constexpr int kSmallTokens = 512;
+constexpr int kSmallPairsPerThread = 4;
+constexpr int kSmallPairs = kMapThreads * kSmallPairsPerThread;
 
+// Row stride of the whole-batch bitmaps in words; odd, so that lanes on different slots
+// reading the same word index hit different banks.
+__host__ __device__ inline int small_stride(int T) { return ((T + 31) / 32) | 1; }
 inline size_t small_lds_bytes(int E, int P, int R, int T, int k) {
-  const int stride = ((T + 31) / 32) | 1;  // odd LDS row stride of the bitmaps
-  return sizeof(int32_t) * ((size_t)(E + 1) + P + R + E + P + P + (P + 1) + (size_t)P * stride +
-                            (size_t)2 * T * k);
+  return sizeof(int32_t) * (route_table_ints(E, P, R) + P + (P + 1) +
+                            (size_t)P * small_stride(T) + (size_t)T * k);
 }
 
-// bits [lo, hi) of a bitmap, lo < hi
-__device__ inline int popc_range(const uint32_t* bm, int lo, int hi) {
-  int c = 0;
-  for (int w = lo >> 5; w <= (hi - 1) >> 5; ++w) {
-    uint32_t m = bm[w];
-    const int base = w << 5;
-    if (lo > base) m &= ~0u << (lo - base);
-    if (hi < base + 32) m &= (1u << (hi - base)) - 1u;
-    c += __popc(m);
+// cnt[p] = tokens [lo, hi) in the bitmap of slot p, for the kSrcChunks * 64 slots from p0 on;
+// lo < hi are the same for the whole wavefront.  The slots' words are read side by side, so
+// that the LDS latencies overlap.
+template <int kSrcChunks>
+__device__ __forceinline__ void store_src_counts(const uint32_t* s_bm, int stride, int p0, int P,
+                                                 int lo, int hi, int32_t* __restrict__ cnt) {
+  const int w0 = lo >> 5, w1 = (hi - 1) >> 5;
+  int c[kSrcChunks] = {};
+  for (int w = w0; w <= w1; ++w) {
+    uint32_t m = ~0u;
+    if (w == w0) m &= ~0u << (lo & 31);
+    if (w == w1) m &= ~0u >> (31 - ((hi - 1) & 31));
+    uint32_t v[kSrcChunks];
+#pragma unroll
+    for (int u = 0; u < kSrcChunks; ++u) {
+      const int p = p0 + u * 64 + (int)(threadIdx.x & 63);
+      v[u] = s_bm[(p < P ? p : P - 1) * stride + w];
+    }
+#pragma unroll
+    for (int u = 0; u < kSrcChunks; ++u) c[u] += __popc(v[u] & m);
   }
-  return c;
+#pragma unroll
+  for (int u = 0; u < kSrcChunks; ++u) {
+    const int p = p0 + u * 64 + (int)(threadIdx.x & 63);
+    if (p < P) cnt[p] = c[u];
+  }
 }
 
-template <int KC>
+template <int KC, int U>
 __global__ __launch_bounds__(kMapThreads) void k_layout_small(
     const int32_t* __restrict__ topk_idx, const int32_t* __restrict__ l2p_off,
     const int32_t* __restrict__ l2p_list, const int32_t* __restrict__ active,
@@ -360,108 +563,78 @@ __global__ __launch_bounds__(kMapThreads) void k_layout_small(
     int32_t* __restrict__ count, int32_t* __restrict__ offset, int32_t* __restrict__ rank_count,
     int32_t* __restrict__ rank_offset, int32_t* __restrict__ cnt_src,
     int32_t* __restrict__ status, int32_t* __restrict__ step_epoch, int k_rt, int E, int R, int S,
-    int P, int T, int tokens_per_rank, int policy) {
+    int P, int T, int tokens_per_rank, int policy, float inv_S) {
   const int k = KC > 0 ? KC : k_rt;
-  const int words = (T + 31) >> 5;
-  const int stride = words | 1;  // odd: lanes on different slots reading the same word index hit different banks
+  const int stride = small_stride(T);
   const int npairs = T * k;
   extern __shared__ int32_t smem[];
-  int32_t* s_off = smem;                              // [E+1] replica-list starts (CSR)
-  int32_t* s_list = s_off + (E + 1);                  // [P] replica lists, canonical order
-  int32_t* s_active = s_list + P;                     // [R]
-  int32_t* s_nlive = s_active + R;                    // [E] live replicas of expert e
-  int32_t* s_live = s_nlive + E;                      // [P] live replicas, compacted per expert
-  int32_t* s_count = s_live + P;                      // [P] pairs per slot
-  int32_t* s_offset = s_count + P;                    // [P+1] exclusive scan of s_count
-  uint32_t* s_bm = (uint32_t*)(s_offset + P + 1);     // [P][stride] token bitmap per slot
-  int32_t* s_idx = (int32_t*)(s_bm + P * stride);     // [T*k] router indices
-  int32_t* s_slot = s_idx + npairs;                   // [T*k] chosen slots
+  int32_t* s_count = smem;                        // [P] pairs per slot
+  uint32_t* s_bm = (uint32_t*)(s_count + P);      // [P][stride] token bitmap per slot
+  int32_t* s_offset = (int32_t*)(s_bm + P * stride);  // [P+1] exclusive scan of s_count
+  int32_t* s_idx = s_offset + P + 1;              // [T*k] router indices, KC == 0 only
+  int32_t* s_tab = s_idx + (KC == 0 ? npairs : 0);
   __shared__ int32_t s_drop[2];
-  __shared__ int32_t s_wave[kMapThreads / 64];
   const int tid = threadIdx.x;
 
+  // the pairs whose results this workgroup writes
+  const int share = ((npairs + kSmallBlocks - 1) / kSmallBlocks + 63) & ~63;
+  const int own_lo = blockIdx.x * share;
+  const int own_hi = own_lo + share < npairs ? own_lo + share : npairs;
+
   // every global read of this kernel is issued here, none depends on another
-  for (int i = tid; i < npairs; i += kMapThreads) s_idx[i] = topk_idx[i];
-  for (int i = tid; i <= E; i += kMapThreads) s_off[i] = l2p_off[i];
-  for (int i = tid; i < P; i += kMapThreads) s_list[i] = l2p_list[i];
-  for (int i = tid; i < R; i += kMapThreads) s_active[i] = active[i];
-  const int version = tid == 0 ? *tbl_version + *mem_version : 0;
-  for (int i = tid; i < P * stride; i += kMapThreads) s_bm[i] = 0u;
+  int my_e[U], slot[U];
+#pragma unroll
+  for (int u = 0; u < U; ++u) {
+    const int i = tid + u * kMapThreads;
+    my_e[u] = i < npairs ? topk_idx[i] : -1;
+  }
+  const int version = blockIdx.x == 0 && tid == 0 ? *tbl_version + *mem_version : 0;
+  for (int i = tid; i < P * (stride + 1); i += kMapThreads) s_count[i] = 0;  // and s_bm
   if (tid < 2) s_drop[tid] = 0;
-  __syncthreads();
-
-  for (int e = tid; e < E; e += kMapThreads) {
-    int o = s_off[e], o1 = s_off[e + 1], n = 0;
-    for (int q = o; q < o1; ++q) {
-      int p = s_list[q];
-      if (s_active[p / S] != 0) s_live[o + n++] = p;  // failed peers are skipped
-    }
-    s_nlive[e] = n;
+  const RouteTables rt =
+      load_route_tables<kMapThreads>(s_tab, l2p_off, l2p_list, active, E, R, P, inv_S);
+  if constexpr (KC == 0) {
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+      if (tid + u * kMapThreads < npairs) s_idx[tid + u * kMapThreads] = my_e[u];
   }
   __syncthreads();
-
-  int n_unc = 0, n_msk = 0;
-  for (int i = tid; i < npairs; i += kMapThreads) {
-    int t = i / k;
-    int j = i - t * k;
-    int e = s_idx[i];
-    int p = -1;
-    if (e < 0 || e >= E) {
-      ++n_msk;
-    } else {
-      bool repeated = false;
-      for (int jj = 0; jj < j; ++jj) repeated |= (s_idx[t * k + jj] == e);
-      if (repeated) {
-        ++n_msk;
-      } else {
-        int n = s_nlive[e];
-        if (n == 0) {
-          ++n_unc;
-        } else {
-          int sel = (policy == EEP_FIRST_LIVE || n == 1) ? 0 : t % n;
-          p = s_live[s_off[e] + sel];
-          atomicOr(&s_bm[p * stride + (t >> 5)], 1u << (t & 31));
-        }
-      }
-    }
-    s_slot[i] = p;
-    slot_of[i] = p;
-  }
-  if (n_unc) atomicAdd(&s_drop[0], n_unc);
-  if (n_msk) atomicAdd(&s_drop[1], n_msk);
+  map_pairs<KC, kMapThreads, U>(rt, my_e, s_idx, slot, s_bm, stride, s_count, s_drop, npairs, k, E, 0,
+                                policy, own_lo, own_hi, slot_of);
   __syncthreads();
 
-  for (int p = tid; p < P; p += kMapThreads) {
-    int c = 0;
-    for (int w = 0; w < words; ++w) c += __popc(s_bm[p * stride + w]);
-    s_count[p] = c;
-  }
-  // pairs per (source rank, slot): the tokens of a source rank are a bit range;
-  // wavefronts take source ranks, lanes take slots
-  for (int b = tid >> 6; b < R; b += kMapThreads / 64)
-    for (int p = tid & 63; p < P; p += 64)
-      cnt_src[b * P + p] =
-          popc_range(&s_bm[p * stride], b * tokens_per_rank, (b + 1) * tokens_per_rank);
+  if (tid < 64) wave_exclusive_scan(s_count, s_offset, P);
   __syncthreads();
-  block_exclusive_scan<kMapThreads>(s_count, s_offset, s_wave, P);
 
   const int N = s_offset[P];
-  for (int i = tid; i < npairs; i += kMapThreads) {
-    int p = s_slot[i];
-    int row = -1;
-    if (p >= 0) {
-      int t = i / k;
-      const uint32_t* bm = &s_bm[p * stride];
-      int rank = __popc(bm[t >> 5] & ((1u << (t & 31)) - 1u));  // earlier tokens in this slot
-      for (int w = 0; w < (t >> 5); ++w) rank += __popc(bm[w]);
-      row = s_offset[p] + rank;
-      src_of[row] = i;
+#pragma unroll
+  for (int u = 0; u < U; ++u) {
+    const int i = tid + u * kMapThreads;
+    if (i >= own_lo && i < own_hi) {
+      const int p = slot[u];
+      int row = -1;
+      if (p >= 0) {
+        row = s_offset[p] + rank_in_slot(&s_bm[p * stride], i / k);
+        src_of[row] = i;
+      }
+      row_of[i] = row;
+      if (i >= N) src_of[i] = -1;  // rows past the last routed pair
     }
-    row_of[i] = row;
-    if (i >= N) src_of[i] = -1;  // rows past the last routed pair
   }
-  write_step_tables<kMapThreads>(s_count, s_offset, s_drop[0], s_drop[1], version, count, offset,
-                                 rank_count, rank_offset, status, step_epoch, R, S, P);
+  // pairs per (source rank, slot): the tokens of a source rank are a bit range; wavefronts
+  // take source ranks, lanes slots, five sets of 64 slots at once where there are more than one
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  for (int b = blockIdx.x * kMapWaves + wave; b < R; b += kSmallBlocks * kMapWaves) {
+    const int lo = b * tokens_per_rank, hi = lo + tokens_per_rank;
+    int32_t* cnt = cnt_src + (int64_t)b * P;
+    if (P <= 64)
+      store_src_counts<1>(s_bm, stride, 0, P, lo, hi, cnt);
+    else
+      for (int p0 = 0; p0 < P; p0 += 320) store_src_counts<5>(s_bm, stride, p0, P, lo, hi, cnt);
+  }
+  if (blockIdx.x == 0)
+    write_step_tables<kMapThreads>(s_count, s_offset, s_drop[0], s_drop[1], version, count, offset,
+                                   rank_count, rank_offset, status, step_epoch, R, S, P);
 }
 
 // ---------------------------------------------------------------------------
@@ -541,7 +714,6 @@ __global__ __launch_bounds__(kPosThreads) void k_position(
   extern __shared__ int32_t smem[];
   int32_t* s_count = smem;           // [P]
   int32_t* s_offset = s_count + P;   // [P+1]
-  __shared__ int32_t s_wave[kPosThreads / 64];
   __shared__ int32_t s_drop[2];
   const int tid = threadIdx.x;
   const int g = blockIdx.x * kPosThreads + tid;
@@ -565,7 +737,8 @@ __global__ __launch_bounds__(kPosThreads) void k_position(
   __syncthreads();
   if (du) atomicAdd(&s_drop[0], du);
   if (dm) atomicAdd(&s_drop[1], dm);
-  block_exclusive_scan<kPosThreads>(s_count, s_offset, s_wave, P);
+  if (tid < 64) wave_exclusive_scan(s_count, s_offset, P);
+  __syncthreads();
 
   // pairs per (source rank, slot): difference of the tile prefixes at the source
   // rank's first tile and at the next source rank's first tile
@@ -694,7 +867,6 @@ __global__ __launch_bounds__(kMapThreads) void k_dedup_position(
   int32_t* s_cnt = smem;           // [R]   tokens per rank, all tiles
   int32_t* s_off = s_cnt + R;      // [R+1] exclusive scan of s_cnt
   int32_t* s_pre = s_off + R + 1;  // [R]   tokens per rank in tiles before this one
-  __shared__ int32_t s_wave[kMapThreads / 64];
   const int tid = threadIdx.x;
   const int b = blockIdx.x;
   const TileRange tr = tile_range(b, tokens_per_rank, tiles_per_rank, tile_tokens);
@@ -718,7 +890,8 @@ __global__ __launch_bounds__(kMapThreads) void k_dedup_position(
     s_pre[r] = before;
   }
   __syncthreads();
-  block_exclusive_scan<kMapThreads>(s_cnt, s_off, s_wave, R);
+  if (tid < 64) wave_exclusive_scan(s_cnt, s_off, R);
+  __syncthreads();
   for (int i = tid; i < npairs; i += kMapThreads) {
     const int p = slot_of[g0 + i];
     int row_d = -1, dst = -1;
@@ -774,6 +947,18 @@ bool layout_shape_fits(int E, int P, int R, int k) {
          sizeof(int32_t) * ((size_t)3 * P + 1) <= kLayoutLdsLimit;
 }
 
+// The instantiation of a kernel family for top-k `k` and `pairs` pairs per workgroup of
+// kMapThreads threads, at most 4 per thread: a compile-time k where the lanes of a token share a
+// DPP row.
+static_assert(kMaxPairsPerThread == 4 && kSmallPairsPerThread == 4, "EEP_FOR_K's widths");
+#define EEP_FOR_K_U(KERN, U, k)                                                             \
+  ((k) == 8 ? KERN<8, U> : (k) == 4 ? KERN<4, U> : (k) == 2 ? KERN<2, U> : (k) == 1 ? KERN<1, U> \
+                                                                                    : KERN<0, U>)
+#define EEP_FOR_K(KERN, k, pairs)                                   \
+  ((pairs) <= kMapThreads       ? EEP_FOR_K_U(KERN, 1, k)           \
+   : (pairs) <= 2 * kMapThreads ? EEP_FOR_K_U(KERN, 2, k)           \
+                                : EEP_FOR_K_U(KERN, 4, k))
+
 hipError_t launch_layout(const LayoutIO& c, int T, hipStream_t st) {
   Tiling g = make_tiling(T, c.R);
   const bool k8 = c.k == 8;
@@ -783,23 +968,24 @@ hipError_t launch_layout(const LayoutIO& c, int T, hipStream_t st) {
                        c.step_epoch, c.R, c.P);
     return hipGetLastError();
   }
+  const float inv_S = 1.0f / (float)c.S;
   if (T <= kSmallTokens && T * c.k <= kSmallPairs &&
       small_lds_bytes(c.E, c.P, c.R, T, c.k) <= kLayoutLdsLimit) {
-    auto kern = k8 ? k_layout_small<8> : k_layout_small<0>;
-    hipLaunchKernelGGL(kern, dim3(1), dim3(kMapThreads), small_lds_bytes(c.E, c.P, c.R, T, c.k),
+    auto kern = EEP_FOR_K(k_layout_small, c.k, T * c.k);
+    hipLaunchKernelGGL(kern, dim3(kSmallBlocks), dim3(kMapThreads), small_lds_bytes(c.E, c.P, c.R, T, c.k),
                        st, c.topk_idx, c.l2p_off, c.l2p_list, c.active, c.tbl_version,
                        c.mem_version, c.slot_of, c.row_of, c.src_of, c.count, c.offset,
                        c.rank_count, c.rank_offset, c.cnt_src, c.status, c.step_epoch, c.k, c.E,
-                       c.R, c.S, c.P, T, g.tokens_per_rank, c.policy);
+                       c.R, c.S, c.P, T, g.tokens_per_rank, c.policy, inv_S);
     return hipGetLastError();
   }
   {
-    size_t lds = map_lds_bytes(c.E, c.P, c.R, g.tile_tokens, c.k);
-    auto kern = k8 ? k_map_count<8> : k_map_count<0>;
+    size_t lds = sizeof(int32_t) * map_lds_ints(c.E, c.P, c.R, g.tile_tokens, c.k);
+    auto kern = EEP_FOR_K(k_map_count, c.k, g.tile_tokens * c.k);
     hipLaunchKernelGGL(kern, dim3(g.num_tiles), dim3(kMapThreads), lds, st, c.topk_idx, c.l2p_off,
                        c.l2p_list, c.active, c.slot_of, c.row_of, c.cnt_tile, c.blk_unc, c.blk_msk,
-                       c.k, c.E, c.R, c.S, c.P, g.tokens_per_rank, g.tiles_per_rank, g.tile_tokens,
-                       c.policy);
+                       c.k, c.E, c.R, c.P, g.tokens_per_rank, g.tiles_per_rank, g.tile_tokens,
+                       c.policy, inv_S);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
   }

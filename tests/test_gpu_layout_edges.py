@@ -1,0 +1,63 @@
+"""dispatch_layout at the edges of its launch forms: pairs per thread (1024, 2048, 4096 pairs), the
+limit of the one-launch form (512 tokens, 4096 pairs), top-k with and without a lane form, masks in a
+register (up to 64 ranks) and in LDS, experts with more than 32 replicas, slot counts around the
+scan's groups of 64 and 320.  Every field bit-equal to the oracle, with dead ranks, masked, repeated
+and uncovered pairs."""
+import numpy as np
+import pytest
+
+from paper_2605_10670_amd import binding
+
+import gpu_util as gu
+
+pytestmark = pytest.mark.gpu
+
+# (T, k, R, S, E)
+SHAPES = [
+    (1, 1, 1, 1, 1), (32, 8, 32, 9, 256), (128, 8, 32, 9, 256), (160, 8, 32, 9, 256),
+    (256, 8, 32, 9, 256), (288, 8, 32, 9, 256), (512, 8, 32, 9, 256), (544, 8, 32, 9, 256),
+    (127, 8, 1, 20, 16), (129, 8, 3, 7, 16), (513, 8, 1, 12, 12), (512, 4, 4, 6, 16),
+    (512, 1, 8, 3, 8), (514, 2, 2, 9, 12), (500, 2, 4, 6, 16), (510, 6, 6, 5, 24), (128, 32, 4, 20, 64),
+    (132, 32, 4, 20, 64), (96, 3, 32, 2, 40), (400, 16, 16, 5, 40), (260, 8, 65, 2, 96),
+    (1300, 8, 65, 2, 96), (200, 4, 100, 3, 250), (160, 2, 8, 10, 2), (1600, 2, 8, 10, 2),
+    (64, 8, 32, 10, 300), (64, 8, 1, 321, 300), (640, 8, 64, 10, 600), (64, 5, 64, 10, 600),
+    (4096, 10, 32, 9, 256), (3000, 1, 24, 5, 96), (4160, 8, 65, 4, 200), (5976, 6, 24, 5, 96),
+    (8192, 8, 64, 3, 150),
+]
+
+
+def instance(T, k, R, S, E, seed):
+    rng = np.random.default_rng(seed)
+    P = R * S
+    p2l = rng.integers(0, E, P).astype(np.int32)
+    first = rng.permutation(P)[:min(P, E)]
+    p2l[first] = np.arange(first.size)             # most experts have at least one replica
+    p2l[rng.random(P) < 0.05] = -1
+    active = (rng.random(R) < 0.85).astype(np.int32)
+    active[rng.integers(R)] = 1
+    idx = np.argsort(rng.random((T, max(E, k))), axis=1)[:, :k].astype(np.int32)
+    idx[idx >= E] = -1
+    idx[rng.random(idx.shape) < 0.02] = E
+    if k > 1:
+        again = rng.random(T) < 0.1
+        idx[again, k - 1] = idx[again, 0]
+    return p2l, active, idx
+
+
+@pytest.mark.parametrize("policy", [binding.SPREAD, binding.FIRST_LIVE])
+@pytest.mark.parametrize("T,k,R,S,E", SHAPES)
+def test_layout_forms(oracle, T, k, R, S, E, policy):
+    S_prim = max(1, S - 1)
+    p2l, active, idx = instance(T, k, R, S, E, seed=T * 31 + R)
+    ctx = binding.Context(num_ranks=R, slots_per_rank=S, primary_slots=S_prim, num_logical=E,
+                          max_tokens=T, topk=k, hidden=64, policy=policy, strict_coverage=False)
+    try:
+        ctx.update_placement(p2l)
+        ctx.set_membership(active)
+        ctx.dispatch_layout(gu.to_dev(idx), T)
+        got = ctx.read_layout(T)
+        want = oracle.step_layout(idx, p2l, active, E, R, S, S_prim, policy)
+        gu.assert_layout_equal(got, want, T, k)
+        assert ctx.check_layout(T).tolist() == [0, 0, 0, 0]
+    finally:
+        ctx.destroy()
