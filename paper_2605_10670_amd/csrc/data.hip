@@ -17,6 +17,17 @@ typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef float f32x2 __attribute__((ext_vector_type(2)));
 typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
 
+// Workgroup index -> (token, part) without a division in front of the first load: n / d is the
+// high word of n * magic, magic = 2^32 / d rounded up, exact while n * d < 2^32 (the rounding
+// is at most d too much); a larger grid has magic 0 and divides.
+static uint32_t part_magic(int parts, int64_t grid) {
+  if (parts <= 1 || grid * parts >= ((int64_t)1 << 32)) return 0;
+  return (uint32_t)((((uint64_t)1 << 32) + parts - 1) / parts);
+}
+__device__ __forceinline__ uint32_t token_of(uint32_t n, uint32_t parts, uint32_t magic) {
+  return magic != 0 ? __umulhi(n, magic) : n / parts;
+}
+
 // ---------------------------------------------------------------------------
 // pack: recv[row_of[t, j]] = x[t].  One wavefront per token reads the row once
 // into registers (up to kPackVecs 16-byte vectors per lane per pass, every load
@@ -48,10 +59,10 @@ __device__ inline void store_through(u32x4* p, u32x4 v) {
 // indexing (2 us faster at the decode shape than the general form with parts = 1).
 template <int U, bool EXACT, bool SPLIT>
 __global__ __launch_bounds__(64) void k_pack(const u32x4* __restrict__ x,
-                                             u32x4* __restrict__ recv,
                                              const int32_t* __restrict__ row_of, int k,
-                                             int row_vecs, int parts) {
-  const int t = SPLIT ? blockIdx.x / parts : blockIdx.x;
+                                             int row_vecs, uint32_t parts, uint32_t magic,
+                                             u32x4* __restrict__ recv) {
+  const int t = SPLIT ? token_of(blockIdx.x, parts, magic) : blockIdx.x;
   const int part = SPLIT ? blockIdx.x - t * parts : 0;
   const int step = SPLIT ? parts * 64 * U : 64 * U;
   const int lane = threadIdx.x;
@@ -169,11 +180,11 @@ static hipError_t launch_pack_t(eep_ctx* c, const int32_t* rows, const void* x, 
                                 int T, int parts, hipStream_t st) {
   if (parts > 1)
     hipLaunchKernelGGL((k_pack<U, EXACT, true>), dim3((unsigned)((int64_t)T * parts)), dim3(64), 0,
-                       st, (const u32x4*)x, (u32x4*)recv_x, rows, c->k,
-                       (int)(c->x_row_bytes / 16), parts);
+                       st, (const u32x4*)x, rows, c->k, (int)(c->x_row_bytes / 16),
+                       (uint32_t)parts, part_magic(parts, (int64_t)T * parts), (u32x4*)recv_x);
   else
     hipLaunchKernelGGL((k_pack<U, EXACT, false>), dim3(T), dim3(64), 0, st, (const u32x4*)x,
-                       (u32x4*)recv_x, rows, c->k, (int)(c->x_row_bytes / 16), 1);
+                       rows, c->k, (int)(c->x_row_bytes / 16), 1u, 0u, (u32x4*)recv_x);
   return hipGetLastError();
 }
 
@@ -575,27 +586,30 @@ __device__ __forceinline__ uint32_t ranks_dropped(const DetectArgs& d, int64_t p
   return pending != 0 ? await_late_ranks(d, pair0, pending, epoch) : 0u;
 }
 
-// One wavefront per (token, part): a part is kCombineCols * 64 16-byte columns
-// of the row (2 KiB of each source row at the decode shape), so a lane has
-// kCombineCols * k independent loads in flight.  Small single-wavefront
-// workgroups measured ~10 % faster than one workgroup per token.
-constexpr int kCombineCols = 2;
-
+// One wavefront per (token, part): a part is 64 16-byte columns of the row, 1 KiB of each source
+// row, and a lane has the k loads of its column in flight.  Bound by HBM; what the kernel
+// itself decides is how soon a wavefront's loads are out, hence the order below: row indices,
+// row loads, weights.  Measured on whole steps (8 steps of 32 / 256 tokens, 4 of 4096, one of
+// 1024 with 1/32 of the pairs dropped; 7168 channels, top-8): 80.4 / 164.7 / 750 / 51.7 us; with
+// two columns per lane 82.6 / 166.4 / 756 / 52.5, four 86.9 / 169 / 763 / 56.7; two columns with a
+// bounds check around each column's loads (the second column's then waited for the first's)
+// 83.2 / 168 / 755 / 57.  Single-wavefront workgroups measured ~10 % faster than one workgroup
+// per token.
+//
 // DETECT: the wait for the ranks' signals is part of the kernel (DetectArgs above); row_of
 // is then not read-only, because dropped pairs are struck from it.
 template <bool Y_BF16, bool OUT_BF16, int K, bool DETECT>
-__global__ __launch_bounds__(64) void k_combine(const u32x4* __restrict__ y,
+__global__ __launch_bounds__(64) void k_combine(const int32_t* row_of,
+                                                const u32x4* __restrict__ y, int k, int row_vecs,
+                                                uint32_t parts, uint32_t magic,
                                                 const float* __restrict__ topk_w,
-                                                const int32_t* row_of, void* __restrict__ out,
-                                                int k, int row_vecs, int parts,
-                                                int64_t out_row_bytes, DetectArgs det) {
+                                                void* __restrict__ out, DetectArgs det) {
   constexpr int NE = YVec<Y_BF16>::kElems;
-  const int t = blockIdx.x / parts;
-  const int part = blockIdx.x - t * parts;
-  const int v0 = part * (64 * kCombineCols) + threadIdx.x;
+  const int t = token_of(blockIdx.x, parts, magic);
+  const int v = (blockIdx.x - t * parts) * 64 + threadIdx.x;
   const int32_t* rows = row_of + (int64_t)t * k;
   const float* ws = topk_w + (int64_t)t * k;
-  void* out_row = (char*)out + (int64_t)t * out_row_bytes;
+  void* out_row = (char*)out + (int64_t)t * row_vecs * (NE * (OUT_BF16 ? 2 : 4));
 
   int round_flag = 0, epoch = 0;
   if constexpr (DETECT) {
@@ -610,79 +624,73 @@ __global__ __launch_bounds__(64) void k_combine(const u32x4* __restrict__ y,
     }
     round_flag = __hip_atomic_load(det.round_ok, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   }
+  if (v >= row_vecs) return;  // never lane 0, which acts for the wavefront in the wait below
 
+  float acc[NE];
+#pragma unroll
+  for (int i = 0; i < NE; ++i) acc[i] = 0.0f;
+  uint32_t dropped = 0;  // bit j: pair j's rank was dropped in this step
   if constexpr (K > 0) {
-    // fast path: compile-time k and every pair routed -> no branch between loads
+    // compile-time k: all loads are issued before the first is used
     int r[K];
-    float w[K];
     bool all = true;
 #pragma unroll
     for (int j = 0; j < K; ++j) {
       r[j] = rows[j];
-      w[j] = ws[j];
       all &= (r[j] >= 0);
     }
-    if (all) {
-      u32x4 d[kCombineCols][K];
+    u32x4 d[K];
+    if (__builtin_expect(all, 1)) {  // every pair routed: no branch between loads
 #pragma unroll
-      for (int q = 0; q < kCombineCols; ++q) {
-        int v = v0 + q * 64;
-        if (v < row_vecs) {
-#pragma unroll
-          for (int j = 0; j < K; ++j)
-            d[q][j] = __builtin_nontemporal_load(&y[(int64_t)r[j] * row_vecs + v]);
-        }
-      }
+      for (int j = 0; j < K; ++j)
+        d[j] = __builtin_nontemporal_load(&y[(int64_t)r[j] * row_vecs + v]);
       // the look at the ranks' signals comes after the row loads have been issued, so that
       // its two dependent table lookups overlap with them; rows of a rank that turns out to
       // be dropped are loaded and not used
-      uint32_t dropped = 0;
+      if constexpr (DETECT)
+        if (round_flag != epoch) dropped = ranks_dropped(det, (int64_t)t * k, k, rows, epoch);
+      // (the weights are read here: scalar loads return in any order, so a wait for the row
+      // indices would also be one for the weights, which come from HBM)
+#pragma unroll
+      for (int j = 0; j < K; ++j)
+        if (!DETECT || !((dropped >> j) & 1u)) accumulate<Y_BF16>(acc, d[j], ws[j]);
+    } else {
+      // Some pairs have no row (a dead rank's experts before the repair, masked indices): the
+      // same, with a branch around each load and each term; r[] is uniform, so no lane
+      // diverges.  One load at a time here cost 4 us of 57 at T = 1024 with 22 % such tokens.
+#pragma unroll
+      for (int j = 0; j < K; ++j)
+        if (r[j] >= 0) d[j] = __builtin_nontemporal_load(&y[(int64_t)r[j] * row_vecs + v]);
       if constexpr (DETECT)
         if (round_flag != epoch) dropped = ranks_dropped(det, (int64_t)t * k, k, rows, epoch);
 #pragma unroll
-      for (int q = 0; q < kCombineCols; ++q) {
-        int v = v0 + q * 64;
-        if (v < row_vecs) {
-          float acc[NE];
-#pragma unroll
-          for (int i = 0; i < NE; ++i) acc[i] = 0.0f;
-#pragma unroll
-          for (int j = 0; j < K; ++j)
-            if (!DETECT || !((dropped >> j) & 1u)) accumulate<Y_BF16>(acc, d[q][j], w[j]);
-          store_out<Y_BF16, OUT_BF16>(out_row, v, acc);
-        }
-      }
-      return;
+      for (int j = 0; j < K; ++j)
+        if (r[j] >= 0 && !((dropped >> j) & 1u)) accumulate<Y_BF16>(acc, d[j], ws[j]);
     }
-  }
-  uint32_t dropped = 0;  // bit j: pair j's rank was dropped in this step
-  if constexpr (DETECT)
-    if (round_flag != epoch) dropped = ranks_dropped(det, (int64_t)t * k, k, rows, epoch);
-  for (int q = 0; q < kCombineCols; ++q) {
-    int v = v0 + q * 64;
-    if (v >= row_vecs) break;
-    float acc[NE];
-#pragma unroll
-    for (int i = 0; i < NE; ++i) acc[i] = 0.0f;
+  } else {
+    if constexpr (DETECT)
+      if (round_flag != epoch) dropped = ranks_dropped(det, (int64_t)t * k, k, rows, epoch);
     for (int j = 0; j < k; ++j) {
       int row = rows[j];
       if (row < 0 || ((dropped >> j) & 1u)) continue;
       u32x4 d = __builtin_nontemporal_load(&y[(int64_t)row * row_vecs + v]);
       accumulate<Y_BF16>(acc, d, ws[j]);
     }
-    store_out<Y_BF16, OUT_BF16>(out_row, v, acc);
   }
+  store_out<Y_BF16, OUT_BF16>(out_row, v, acc);
 }
 
 template <bool Y_BF16, bool OUT_BF16>
 static hipError_t launch_combine_t(eep_ctx* c, const void* y, const float* w, void* out, int T,
                                    hipStream_t st) {
   int row_vecs = (int)(c->y_row_bytes / 16);
-  int parts = (row_vecs + 64 * kCombineCols - 1) / (64 * kCombineCols);
+  int parts = (row_vecs + 63) / 64;
   if ((int64_t)T * parts > 0x7fffffffLL) return hipErrorInvalidValue;  // grid size limit
+  const uint32_t magic = part_magic(parts, (int64_t)T * parts);
   dim3 grid((unsigned)((int64_t)T * parts)), block(64);
   DetectArgs det = {};
-  if (c->detect_timeout_ticks > 0) {
+  const bool detect = c->detect_timeout_ticks > 0;
+  if (detect) {
     // the wait for the ranks' signals runs inside the kernel
     det.slot_of = c->slot_of; det.row_of = c->row_of; det.signal = c->signal;
     det.step_epoch = c->step_epoch; det.active = c->active; det.report = c->report;
@@ -690,24 +698,23 @@ static hipError_t launch_combine_t(eep_ctx* c, const void* y, const float* w, vo
     det.rank_count = c->rank_count; det.round_ok = c->round_ok;
     det.timeout_ticks = c->detect_timeout_ticks;
     det.max_polls = c->detect_timeout_ticks * 8 + 1024;
-    if (c->k == 8)
-      hipLaunchKernelGGL((k_combine<Y_BF16, OUT_BF16, 8, true>), grid, block, 0, st,
-                         (const u32x4*)y, w, c->row_of, out, c->k, row_vecs, parts,
-                         c->out_row_bytes, det);
-    else
-      hipLaunchKernelGGL((k_combine<Y_BF16, OUT_BF16, 0, true>), grid, block, 0, st,
-                         (const u32x4*)y, w, c->row_of, out, c->k, row_vecs, parts,
-                         c->out_row_bytes, det);
-    return hipGetLastError();
   }
-  if (c->k == 8)
-    hipLaunchKernelGGL((k_combine<Y_BF16, OUT_BF16, 8, false>), grid, block, 0, st,
-                       (const u32x4*)y, w, c->row_of, out, c->k, row_vecs, parts,
-                       c->out_row_bytes, det);
-  else
-    hipLaunchKernelGGL((k_combine<Y_BF16, OUT_BF16, 0, false>), grid, block, 0, st,
-                       (const u32x4*)y, w, c->row_of, out, c->k, row_vecs, parts,
-                       c->out_row_bytes, det);
+  switch (c->k) {
+#define EEP_COMBINE_K(CASE, K)                                                              \
+  CASE:                                                                                     \
+  hipLaunchKernelGGL((detect ? k_combine<Y_BF16, OUT_BF16, K, true>                         \
+                             : k_combine<Y_BF16, OUT_BF16, K, false>),                      \
+                     grid, block, 0, st, c->row_of, (const u32x4*)y, c->k, row_vecs,        \
+                     (uint32_t)parts, magic, w, out, det);                                  \
+  break;
+    EEP_COMBINE_K(case 8, 8)
+    EEP_COMBINE_K(case 6, 6)
+    EEP_COMBINE_K(case 4, 4)
+    EEP_COMBINE_K(case 2, 2)
+    EEP_COMBINE_K(case 1, 1)
+    EEP_COMBINE_K(default, 0)
+#undef EEP_COMBINE_K
+  }
   return hipGetLastError();
 }
 

@@ -28,7 +28,7 @@ __global__ __launch_bounds__(256) void k_signal(const int32_t* __restrict__ acti
   const int epoch = *step_epoch;
   for (int r = threadIdx.x; r < R; r += blockDim.x)
     if (active[r] != 0 && withhold[r] == 0)
-      __hip_atomic_store(&signal[r], epoch, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_AGENT);
+      __hip_atomic_store(&signal[r], epoch, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
 hipError_t launch_signal(eep_ctx* c, hipStream_t st) {
