@@ -263,11 +263,11 @@ inline size_t map_lds_ints(int E, int P, int R, int tile_tokens, int k) {
 template <int KC, int U>  // KC = compile-time k (power of two) or 0 for any k
 __global__ __launch_bounds__(kMapThreads) void k_map_count(
     const int32_t* __restrict__ topk_idx, const int32_t* __restrict__ l2p_off,
-    const int32_t* __restrict__ l2p_list, const int32_t* __restrict__ active,
-    int32_t* __restrict__ slot_of, int32_t* __restrict__ rank_in_tile,
+    const int32_t* __restrict__ l2p_list, const int32_t* __restrict__ active, int k_rt,
+    int tokens_per_rank, int tiles_per_rank, int tile_tokens, int E, int P, int R, float inv_S,
+    int policy, int32_t* __restrict__ slot_of, int32_t* __restrict__ rank_in_tile,
     int32_t* __restrict__ cnt_tile, int32_t* __restrict__ blk_unc,
-    int32_t* __restrict__ blk_msk, int k_rt, int E, int R, int P, int tokens_per_rank,
-    int tiles_per_rank, int tile_tokens, int policy, float inv_S) {
+    int32_t* __restrict__ blk_msk) {
   const int k = KC > 0 ? KC : k_rt;
   extern __shared__ int32_t smem[];
   int32_t* s_count = smem;                       // [P] pairs of the tile per slot
@@ -397,15 +397,14 @@ constexpr int kTileBatch = 32;    // count-matrix rows k_tile_prefix fetches per
 
 template <int KC>
 __global__ __launch_bounds__(kFusedThreads) void k_scan_position(
-    const int32_t* __restrict__ cnt_tile, const int32_t* __restrict__ blk_unc,
+    const int32_t* __restrict__ cnt_tile, const int32_t* __restrict__ slot_of,
+    int32_t* __restrict__ row_of, int P, int num_tiles, int k_rt, int tokens_per_rank,
+    int tiles_per_rank, int tile_tokens, const int32_t* __restrict__ blk_unc,
     const int32_t* __restrict__ blk_msk, const int32_t* __restrict__ tbl_version,
-    const int32_t* __restrict__ mem_version, const int32_t* __restrict__ slot_of,
-    int32_t* __restrict__ row_of,
-    int32_t* __restrict__ src_of, int32_t* __restrict__ count, int32_t* __restrict__ offset,
-    int32_t* __restrict__ rank_count, int32_t* __restrict__ rank_offset,
-    int32_t* __restrict__ cnt_src, int32_t* __restrict__ status,
-    int32_t* __restrict__ step_epoch, int k_rt, int num_tiles, int tokens_per_rank,
-    int tiles_per_rank, int tile_tokens, int R, int S, int P) {
+    const int32_t* __restrict__ mem_version, int R, int S, int32_t* __restrict__ src_of,
+    int32_t* __restrict__ count, int32_t* __restrict__ offset, int32_t* __restrict__ rank_count,
+    int32_t* __restrict__ rank_offset, int32_t* __restrict__ cnt_src,
+    int32_t* __restrict__ status, int32_t* __restrict__ step_epoch) {
   const int k = KC > 0 ? KC : k_rt;
   extern __shared__ int32_t smem[];
   int32_t* s_count = smem;           // [P]   pairs per slot, all tiles
@@ -557,13 +556,13 @@ __device__ __forceinline__ void store_src_counts(const uint32_t* s_bm, int strid
 template <int KC, int U>
 __global__ __launch_bounds__(kMapThreads) void k_layout_small(
     const int32_t* __restrict__ topk_idx, const int32_t* __restrict__ l2p_off,
-    const int32_t* __restrict__ l2p_list, const int32_t* __restrict__ active,
-    const int32_t* __restrict__ tbl_version, const int32_t* __restrict__ mem_version,
+    const int32_t* __restrict__ l2p_list, const int32_t* __restrict__ active, int k_rt, int T, int E,
+    int P, int R, float inv_S, const int32_t* __restrict__ tbl_version,
+    const int32_t* __restrict__ mem_version, int policy, int tokens_per_rank, int S,
     int32_t* __restrict__ slot_of, int32_t* __restrict__ row_of, int32_t* __restrict__ src_of,
     int32_t* __restrict__ count, int32_t* __restrict__ offset, int32_t* __restrict__ rank_count,
     int32_t* __restrict__ rank_offset, int32_t* __restrict__ cnt_src,
-    int32_t* __restrict__ status, int32_t* __restrict__ step_epoch, int k_rt, int E, int R, int S,
-    int P, int T, int tokens_per_rank, int policy, float inv_S) {
+    int32_t* __restrict__ status, int32_t* __restrict__ step_epoch) {
   const int k = KC > 0 ? KC : k_rt;
   const int stride = small_stride(T);
   const int npairs = T * k;
@@ -973,19 +972,19 @@ hipError_t launch_layout(const LayoutIO& c, int T, hipStream_t st) {
       small_lds_bytes(c.E, c.P, c.R, T, c.k) <= kLayoutLdsLimit) {
     auto kern = EEP_FOR_K(k_layout_small, c.k, T * c.k);
     hipLaunchKernelGGL(kern, dim3(kSmallBlocks), dim3(kMapThreads), small_lds_bytes(c.E, c.P, c.R, T, c.k),
-                       st, c.topk_idx, c.l2p_off, c.l2p_list, c.active, c.tbl_version,
-                       c.mem_version, c.slot_of, c.row_of, c.src_of, c.count, c.offset,
-                       c.rank_count, c.rank_offset, c.cnt_src, c.status, c.step_epoch, c.k, c.E,
-                       c.R, c.S, c.P, T, g.tokens_per_rank, c.policy, inv_S);
+                       st, c.topk_idx, c.l2p_off, c.l2p_list, c.active, c.k, T, c.E, c.P, c.R,
+                       inv_S, c.tbl_version, c.mem_version, c.policy, g.tokens_per_rank, c.S,
+                       c.slot_of, c.row_of, c.src_of, c.count, c.offset, c.rank_count,
+                       c.rank_offset, c.cnt_src, c.status, c.step_epoch);
     return hipGetLastError();
   }
   {
     size_t lds = sizeof(int32_t) * map_lds_ints(c.E, c.P, c.R, g.tile_tokens, c.k);
     auto kern = EEP_FOR_K(k_map_count, c.k, g.tile_tokens * c.k);
     hipLaunchKernelGGL(kern, dim3(g.num_tiles), dim3(kMapThreads), lds, st, c.topk_idx, c.l2p_off,
-                       c.l2p_list, c.active, c.slot_of, c.row_of, c.cnt_tile, c.blk_unc, c.blk_msk,
-                       c.k, c.E, c.R, c.P, g.tokens_per_rank, g.tiles_per_rank, g.tile_tokens,
-                       c.policy, inv_S);
+                       c.l2p_list, c.active, c.k, g.tokens_per_rank, g.tiles_per_rank,
+                       g.tile_tokens, c.E, c.P, c.R, inv_S, c.policy, c.slot_of, c.row_of,
+                       c.cnt_tile, c.blk_unc, c.blk_msk);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
   }
@@ -994,10 +993,10 @@ hipError_t launch_layout(const LayoutIO& c, int T, hipStream_t st) {
     size_t lds = sizeof(int32_t) * ((size_t)3 * c.P + 1);
     auto kern = k8 ? k_scan_position<8> : k_scan_position<0>;
     hipLaunchKernelGGL(kern, dim3(g.num_tiles), dim3(kFusedThreads), lds, st, c.cnt_tile,
-                       c.blk_unc, c.blk_msk, c.tbl_version, c.mem_version, c.slot_of, c.row_of,
-                       c.src_of, c.count, c.offset, c.rank_count, c.rank_offset, c.cnt_src,
-                       c.status, c.step_epoch, c.k, g.num_tiles, g.tokens_per_rank,
-                       g.tiles_per_rank, g.tile_tokens, c.R, c.S, c.P);
+                       c.slot_of, c.row_of, c.P, g.num_tiles, c.k, g.tokens_per_rank,
+                       g.tiles_per_rank, g.tile_tokens, c.blk_unc, c.blk_msk, c.tbl_version,
+                       c.mem_version, c.R, c.S, c.src_of, c.count, c.offset, c.rank_count,
+                       c.rank_offset, c.cnt_src, c.status, c.step_epoch);
     return hipGetLastError();
   }
   int tiles_per_wave = (g.num_tiles + kPrefixWaves - 1) / kPrefixWaves;
