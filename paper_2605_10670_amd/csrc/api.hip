@@ -309,7 +309,7 @@ int eep_set_membership(eep_ctx* c, const int32_t* active_host, void* stream) {
     if (o->tables == o && o->cfg.strict_coverage &&
         host_uncovered_experts(o->P, o->E, o->S, o->h_p2l.data(), a.data()) > 0)
       return EEP_ERR_COVERAGE;
-  hipError_t e = launch_patch(m->active, a.data(), c->R, m->mem_version, (hipStream_t)stream);
+  hipError_t e = launch_patch({{m->active, a.data(), c->R}}, m->mem_version, (hipStream_t)stream);
   if (e != hipSuccess) return fail_hip(c, e);
   m->h_active = a;
   return EEP_OK;
@@ -334,9 +334,10 @@ int publish_placement(eep_ctx* c, const int32_t* p2l_host, bool mask_may_be_stal
   }
   std::vector<int32_t> off(c->E + 1), list(c->P);
   host_replica_lists(c->P, c->E, c->S, c->S_prim, p2l_host, off.data(), list.data());
-  hipError_t e = launch_patch(c->p2l, p2l_host, c->P, nullptr, st);
-  if (e == hipSuccess) e = launch_patch(c->l2p_off, off.data(), c->E + 1, nullptr, st);
-  if (e == hipSuccess) e = launch_patch(c->l2p_list, list.data(), c->P, c->tbl_version, st);
+  hipError_t e = launch_patch({{c->p2l, p2l_host, c->P},
+                               {c->l2p_off, off.data(), c->E + 1},
+                               {c->l2p_list, list.data(), c->P}},
+                              c->tbl_version, st);
   if (e != hipSuccess) return fail_hip(c, e);
   c->h_p2l.assign(p2l_host, p2l_host + c->P);
   return EEP_OK;
@@ -485,7 +486,7 @@ int eep_debug_withhold_signal(eep_ctx* c, const int32_t* withhold_host, void* st
   if (!c || !withhold_host) return EEP_ERR_INVALID_ARG;
   std::vector<int32_t> w(c->R);
   for (int r = 0; r < c->R; ++r) w[r] = withhold_host[r] != 0;
-  hipError_t e = launch_patch(c->withhold, w.data(), c->R, nullptr, (hipStream_t)stream);
+  hipError_t e = launch_patch({{c->withhold, w.data(), c->R}}, nullptr, (hipStream_t)stream);
   return e == hipSuccess ? EEP_OK : fail_hip(c, e);
 }
 

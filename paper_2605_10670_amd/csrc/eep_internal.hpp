@@ -16,7 +16,11 @@ constexpr int kTileTokens = 128;
 constexpr int kBitmapWords = kTileTokens / 32;
 constexpr int kMaxTopk = 32;
 constexpr int kDedupMaxRanks = 1024;  // the de-duplicated layout keeps per-rank bitmaps in LDS
-constexpr int kPatchInts = 512;  // ints carried by value in one table-patch launch
+// Ints carried by value in one table-patch launch: with the pointers just under the 4 KB that
+// kernel arguments may take; and in a launch for a short update.
+constexpr int kPatchInts = 960;
+constexpr int kPatchSmallInts = 96;
+constexpr int kPatchParts = 3;  // arrays one update may patch together
 constexpr size_t kLayoutLdsLimit = 60 * 1024;  // the layout kernels keep their tables in LDS
 
 struct Tiling {
@@ -45,8 +49,11 @@ inline size_t map_lds_bytes(int E, int P, int R, int tile_tokens, int k) {
 
 inline int dtype_bytes(int dt) { return dt == EEP_F32 ? 4 : dt == EEP_BF16 ? 2 : 1; }
 
-struct PatchChunk {
-  int32_t v[kPatchInts];
+// One array of a table update: n values from host memory to a device address (n may be 0).
+struct PatchArray {
+  int32_t* dst;
+  const int32_t* src;
+  int n;
 };
 
 }  // namespace eep
@@ -155,8 +162,9 @@ hipError_t launch_signal(eep_ctx* c, hipStream_t st);
 // api.hip
 int publish_placement(eep_ctx* c, const int32_t* p2l_host, bool mask_may_be_stale, hipStream_t st);
 // tables.hip
-hipError_t launch_patch(int32_t* dst, const int32_t* src_host, int n, int32_t* version_dst,
-                        hipStream_t st);
+// Patches the arrays in one update, fills fill_n words with fill_value along the way.
+hipError_t launch_patch(const PatchArray (&parts)[kPatchParts], int32_t* version_dst, hipStream_t st,
+                        int32_t* fill_dst = nullptr, int fill_n = 0, int32_t fill_value = 0);
 hipError_t launch_fill(int32_t* dst, int32_t value, int64_t n, hipStream_t st);
 
 }  // namespace eep

@@ -143,17 +143,16 @@ int eep_apply_repair(eep_ctx* c, void* weights, const void* backup, int64_t slot
   }
 
   hipStream_t st = (hipStream_t)stream;
-  hipError_t e = launch_fill(c->mv_outcome, EEP_REPAIR_UNTOUCHED, P, st);
+  // the move list, with every slot's outcome set to "untouched" in the same launch
+  hipError_t e = launch_patch({{c->mv_dst, dst.data(), n_moves},
+                               {c->mv_src, src.data(), n_moves},
+                               {c->mv_expert, expert.data(), n_moves}},
+                              nullptr, st, c->mv_outcome, P, EEP_REPAIR_UNTOUCHED);
   if (e == hipSuccess && n_moves > 0) {
-    e = launch_patch(c->mv_dst, dst.data(), n_moves, nullptr, st);
-    if (e == hipSuccess) e = launch_patch(c->mv_src, src.data(), n_moves, nullptr, st);
-    if (e == hipSuccess) e = launch_patch(c->mv_expert, expert.data(), n_moves, nullptr, st);
-    if (e == hipSuccess) {
-      k_relocate<<<dim3((unsigned)(n_moves * chunks)), dim3(kMoveThreads), 0, st>>>(
-          (u32x4*)weights_dev, (const u32x4*)backup_dev, slot_vecs, (int)chunks, c->mv_dst,
-          c->mv_src, c->mv_expert, c->active, S, c->mv_outcome);
-      e = hipGetLastError();
-    }
+    k_relocate<<<dim3((unsigned)(n_moves * chunks)), dim3(kMoveThreads), 0, st>>>(
+        (u32x4*)weights_dev, (const u32x4*)backup_dev, slot_vecs, (int)chunks, c->mv_dst,
+        c->mv_src, c->mv_expert, c->active, S, c->mv_outcome);
+    e = hipGetLastError();
   }
   if (e != hipSuccess) return fail_hip(c, e);
   return publish_placement(c, new_p2l, true, st);

@@ -61,3 +61,30 @@ def test_layout_forms(oracle, T, k, R, S, E, policy):
         assert ctx.check_layout(T).tolist() == [0, 0, 0, 0]
     finally:
         ctx.destroy()
+
+
+# P + (E + 1) + P values: 96 and 97 (one short launch or one long), 960 and 961 (one long launch or
+# two), 1921 (three)
+@pytest.mark.parametrize("P,E", [(40, 15), (40, 16), (320, 319), (320, 320), (640, 640)])
+def test_placement_update_spans_launches(P, E):
+    ctx = binding.Context(num_ranks=P, slots_per_rank=1, primary_slots=1, num_logical=E,
+                          max_tokens=0, topk=1, hidden=64, strict_coverage=False)
+    try:
+        rng = np.random.default_rng(P + E)
+        version = 0
+        for _ in range(2):
+            p2l = rng.integers(-1, E, P).astype(np.int32)
+            ctx.update_placement(p2l)
+            version += 1
+            off, lst = binding.host_replica_lists(p2l, E, 1, 1)
+            assert np.array_equal(ctx.read("phys_to_logical", P), p2l)
+            assert np.array_equal(ctx.read("l2p_off", E + 1), off)
+            assert np.array_equal(ctx.read("l2p_list", P), lst)
+            active = (rng.random(P) < 0.5).astype(np.int32)
+            ctx.set_membership(active)
+            version += 1
+            assert np.array_equal(ctx.read("active", P), active)
+            ctx.dispatch_layout(None, 0)
+            assert ctx.read("status", 4)[3] == version
+    finally:
+        ctx.destroy()
