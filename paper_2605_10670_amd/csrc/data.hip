@@ -15,6 +15,7 @@ typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef float f32x2 __attribute__((ext_vector_type(2)));
+typedef uint16_t u16x2 __attribute__((ext_vector_type(2)));
 typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
 
 // Workgroup index -> (token, part) without a division in front of the first load: n / d is the
@@ -39,7 +40,9 @@ __device__ __forceinline__ uint32_t token_of(uint32_t n, uint32_t parts, uint32_
 // stores.
 // ---------------------------------------------------------------------------
 constexpr int kPackVecs = 14;
+constexpr int kRowBatch = 8;  // row indices fetched together
 constexpr int kPackSplitBelow = 1024;  // batches below this many tokens split a row over wavefronts
+constexpr int kExpandSplitBelow = 4096;  // the same for rows that are read and written once
 
 // The data registers of a store of more than 8 bytes may not be rewritten by the next two
 // wait states' vector instructions.  The compiler keeps that distance for its own stores but
@@ -49,14 +52,17 @@ __device__ inline void store_through(u32x4* p, u32x4 v) {
 }
 
 // U = 16-byte vectors per lane per pass.  EXACT: the row is a whole number of
-// passes (row_vecs % (64 * U) == 0), so no load or store needs a bounds guard
-// and the compiler keeps all U loads of a pass in flight; otherwise every
-// access is guarded (any row size).  `parts` wavefronts share a token, taking
+// passes (row_vecs % (64 * U) == 0), so no access needs a bounds check;
+// otherwise loads past the row's end read its last vector again, so that all U
+// loads of a pass are in flight here too (a branch around each would make it
+// wait for the ones before), and stores are guarded.  `parts` wavefronts share a token, taking
 // every parts-th pass each: 1 for large batches (a whole row per wavefront
 // measured fastest there), more for small ones, which would otherwise leave
 // most of the chip idle.
 // SPLIT selects at compile time: the one-wavefront-per-token form keeps its simpler
-// indexing (2 us faster at the decode shape than the general form with parts = 1).
+// indexing (2 us faster at the decode shape than the general form with parts = 1); the split
+// form, which is bound by latency, has its row indices ahead of the data (-0.1 us a step for
+// 32 to 512 tokens; +0.2 to 0.6 us in the other form at 1024 to 4096).
 template <int U, bool EXACT, bool SPLIT>
 __global__ __launch_bounds__(64) void k_pack(const u32x4* __restrict__ x,
                                              const int32_t* __restrict__ row_of, int k,
@@ -69,28 +75,52 @@ __global__ __launch_bounds__(64) void k_pack(const u32x4* __restrict__ x,
   const int32_t* rows = row_of + (int64_t)t * k;
   const u32x4* src = x + (int64_t)t * row_vecs;
   for (int v0 = part * 64 * U; v0 < row_vecs; v0 += step) {
+    int r[kRowBatch];
+    if (SPLIT) {  // the first rows, fetched ahead of the data
+#pragma unroll
+      for (int i = 0; i < kRowBatch; ++i) r[i] = rows[i < k ? i : k - 1];
+    }
     u32x4 buf[U];
 #pragma unroll
     for (int u = 0; u < U; ++u) {
       int v = v0 + u * 64 + lane;
-      if (EXACT || v < row_vecs) buf[u] = __builtin_nontemporal_load(&src[v]);
+      if (!EXACT && v >= row_vecs) v = row_vecs - 1;
+      buf[u] = __builtin_nontemporal_load(&src[v]);
     }
     // Touch every loaded register here, so that the waits for the loads sit in
     // front of the row loop and the stores of consecutive rows stream out
     // without a wait between them.
-    if (EXACT) {
 #pragma unroll
-      for (int u = 0; u < U; ++u) asm volatile("" ::"v"(buf[u]));
-    }
-    for (int j = 0; j < k; ++j) {
-      int row = rows[j];
-      if (row < 0) continue;
-      u32x4* dst = recv + (int64_t)row * row_vecs;
+    for (int u = 0; u < U; ++u) asm volatile("" ::"v"(buf[u]));
+    if (!SPLIT) {
+      for (int j = 0; j < k; ++j) {
+        int row = rows[j];
+        if (row < 0) continue;
+        u32x4* dst = recv + (int64_t)row * row_vecs;
 #pragma unroll
-      for (int u = 0; u < U; ++u) {
-        int v = v0 + u * 64 + lane;
-        if (EXACT || v < row_vecs) store_through(&dst[v], buf[u]);
+        for (int u = 0; u < U; ++u) {
+          int v = v0 + u * 64 + lane;
+          if (EXACT || v < row_vecs) store_through(&dst[v], buf[u]);
+        }
       }
+      continue;
+    }
+    for (int j0 = 0;;) {
+#pragma unroll
+      for (int i = 0; i < kRowBatch; ++i) {
+        if (j0 + i < k && r[i] >= 0) {
+          u32x4* dst = recv + (int64_t)r[i] * row_vecs;
+#pragma unroll
+          for (int u = 0; u < U; ++u) {
+            int v = v0 + u * 64 + lane;
+            if (EXACT || v < row_vecs) store_through(&dst[v], buf[u]);
+          }
+        }
+      }
+      j0 += kRowBatch;
+      if (j0 >= k) break;
+#pragma unroll
+      for (int i = 0; i < kRowBatch; ++i) r[i] = rows[j0 + i < k ? j0 + i : k - 1];
     }
   }
 }
@@ -175,6 +205,46 @@ __global__ __launch_bounds__(kScaleThreads) void k_scale_rows(
     if (pair[u] >= 0) store_through(&recv_scale[v0 + u * kScaleThreads], val[u]);
 }
 
+// How a row of row_vecs 16-byte vectors is cut into passes of 64 * u vectors, and over how many
+// wavefronts.  Large batches: one wavefront per token with the largest pass <= max_vecs that
+// divides the row (a whole 14 KiB row per wavefront at the decode shape); a row with no such
+// pass of at least half that width takes the fewest even passes and checks its end.  `split`
+// (small batches, which would leave most of the chip idle that way): a row is spread over
+// wavefronts, each taking one pass of two vectors per lane, or of the smallest larger width
+// that divides the row: measured at 32 ranks, top-8, 14 KiB rows, 2 KiB per wavefront and row is
+// about twice as fast as 1 KiB or 7 KiB pieces for 64 <= T <= 256 (1 KiB pieces are no better
+// than whole rows), and nothing differs from T = 1024 on.
+// Measured on whole steps with rows that are no whole number of passes (bf16, 2880 channels,
+// 360 vectors; T = 32 / 256 / 2048): 26 / 30 / 52 us with a bounds check around each of 14
+// accesses and one wavefront per token at every T, 9.3 / 15.7 / 42.7 us in this form.
+struct PassShape {
+  int u, parts;
+  bool exact;
+};
+static PassShape pass_shape(int row_vecs, bool split, int64_t rows, int max_vecs) {
+  const int per_lane = (row_vecs + 63) / 64;
+  PassShape s = {1, 1, row_vecs % 64 == 0};
+  if (split && per_lane > 1) {
+    s.u = 2;
+    if (s.exact)
+      while (per_lane % s.u != 0) ++s.u;  // ends at per_lane at the latest
+    if (s.u > 4) { s.u = 2; s.exact = false; }
+    s.parts = (per_lane + s.u - 1) / s.u;
+    if (rows * s.parts <= 0x7fffffffLL) return s;  // (else the grid would not fit: do not split)
+    s = {1, 1, row_vecs % 64 == 0};
+  }
+  const int passes = (per_lane + max_vecs - 1) / max_vecs;
+  const int even = (per_lane + passes - 1) / passes;
+  if (s.exact) {
+    s.u = max_vecs;
+    while (per_lane % s.u != 0) --s.u;
+    if (s.u * 2 > even) return s;
+  }
+  s.u = even;
+  s.exact = false;
+  return s;
+}
+
 template <int U, bool EXACT>
 static hipError_t launch_pack_t(eep_ctx* c, const int32_t* rows, const void* x, void* recv_x,
                                 int T, int parts, hipStream_t st) {
@@ -206,63 +276,44 @@ constexpr int kPackMultiMaxVecs = 56;     // 16-byte vectors a lane holds at onc
 static hipError_t launch_pack_payload(eep_ctx* c, const int32_t* rows, const void* x, void* recv_x,
                                       int T, hipStream_t st) {
   const int row_vecs = (int)(c->x_row_bytes / 16);
-  if (row_vecs % 64 == 0) {
-    // Large batches: one wavefront per token, the largest pass width <= kPackVecs that
-    // divides the per-lane vector count (a whole 14 KiB row per wavefront at the decode
-    // shape).  Small batches (< kPackSplitBelow tokens) would leave most of the chip idle
-    // that way, so a row is split over wavefronts, each taking one pass of the smallest
-    // width >= 2: measured at 32 ranks, top-8, 14 KiB rows, 2 KiB per wavefront and row is
-    // about twice as fast as 1 KiB or 7 KiB pieces for 64 <= T <= 256 (1 KiB pieces are
-    // no better than whole rows), and nothing differs from T = 1024 on.
-    const int per_lane = row_vecs / 64;
-    int u, parts;
-    if (T < kPackSplitBelow && per_lane > 1) {
-      u = 2;
-      while (per_lane % u != 0) ++u;  // ends at per_lane at the latest
-      if (u > kPackVecs) u = 1;       // a large prime: fall back to single vectors
-      parts = per_lane / u;
-    } else {
-      u = kPackVecs;
-      while (per_lane % u != 0) --u;
-      parts = 1;
-      // Very large batches (>= kPackMultiMinTokens) of whole-row passes: several tokens per
-      // wavefront, as many as keep >= kPackMultiMinWaves wavefronts and <= kPackMultiMaxVecs
-      // vectors per lane.
-      if (u == per_lane) {
-        int tpw = 1;
-        while (T >= kPackMultiMinTokens && tpw < 8 && T % (tpw * 2) == 0 &&
-               T / (tpw * 2) >= kPackMultiMinWaves &&
-               per_lane * tpw * 2 <= kPackMultiMaxVecs)
-          tpw *= 2;
-        if (tpw > 1) {
-          switch (tpw * 16 + u) {
+  const PassShape ps = pass_shape(row_vecs, T < kPackSplitBelow, T, kPackVecs);
+  // Very large batches (>= kPackMultiMinTokens) of whole-row passes: several tokens per
+  // wavefront, as many as keep >= kPackMultiMinWaves wavefronts and <= kPackMultiMaxVecs
+  // vectors per lane.
+  if (ps.exact && ps.u * 64 == row_vecs) {
+    int tpw = 1;
+    while (T >= kPackMultiMinTokens && tpw < 8 && T % (tpw * 2) == 0 &&
+           T / (tpw * 2) >= kPackMultiMinWaves && ps.u * tpw * 2 <= kPackMultiMaxVecs)
+      tpw *= 2;
+    if (tpw > 1) {
+      switch (tpw * 16 + ps.u) {
 #define EEP_PACK_MULTI(TPW, U) \
   case TPW * 16 + U: return launch_pack_multi_t<U, TPW>(c, rows, x, recv_x, T, st);
-            EEP_PACK_MULTI(2, 1) EEP_PACK_MULTI(2, 2) EEP_PACK_MULTI(2, 3) EEP_PACK_MULTI(2, 4)
-            EEP_PACK_MULTI(2, 5) EEP_PACK_MULTI(2, 6) EEP_PACK_MULTI(2, 7) EEP_PACK_MULTI(2, 8)
-            EEP_PACK_MULTI(2, 9) EEP_PACK_MULTI(2, 10) EEP_PACK_MULTI(2, 11) EEP_PACK_MULTI(2, 12)
-            EEP_PACK_MULTI(2, 13) EEP_PACK_MULTI(2, 14)
-            EEP_PACK_MULTI(4, 1) EEP_PACK_MULTI(4, 2) EEP_PACK_MULTI(4, 3) EEP_PACK_MULTI(4, 4)
-            EEP_PACK_MULTI(4, 5) EEP_PACK_MULTI(4, 6) EEP_PACK_MULTI(4, 7) EEP_PACK_MULTI(4, 8)
-            EEP_PACK_MULTI(4, 9) EEP_PACK_MULTI(4, 10) EEP_PACK_MULTI(4, 11) EEP_PACK_MULTI(4, 12)
-            EEP_PACK_MULTI(4, 13) EEP_PACK_MULTI(4, 14)
-            EEP_PACK_MULTI(8, 1) EEP_PACK_MULTI(8, 2) EEP_PACK_MULTI(8, 3) EEP_PACK_MULTI(8, 4)
-            EEP_PACK_MULTI(8, 5) EEP_PACK_MULTI(8, 6) EEP_PACK_MULTI(8, 7)
+        EEP_PACK_MULTI(2, 1) EEP_PACK_MULTI(2, 2) EEP_PACK_MULTI(2, 3) EEP_PACK_MULTI(2, 4)
+        EEP_PACK_MULTI(2, 5) EEP_PACK_MULTI(2, 6) EEP_PACK_MULTI(2, 7) EEP_PACK_MULTI(2, 8)
+        EEP_PACK_MULTI(2, 9) EEP_PACK_MULTI(2, 10) EEP_PACK_MULTI(2, 11) EEP_PACK_MULTI(2, 12)
+        EEP_PACK_MULTI(2, 13) EEP_PACK_MULTI(2, 14)
+        EEP_PACK_MULTI(4, 1) EEP_PACK_MULTI(4, 2) EEP_PACK_MULTI(4, 3) EEP_PACK_MULTI(4, 4)
+        EEP_PACK_MULTI(4, 5) EEP_PACK_MULTI(4, 6) EEP_PACK_MULTI(4, 7) EEP_PACK_MULTI(4, 8)
+        EEP_PACK_MULTI(4, 9) EEP_PACK_MULTI(4, 10) EEP_PACK_MULTI(4, 11) EEP_PACK_MULTI(4, 12)
+        EEP_PACK_MULTI(4, 13) EEP_PACK_MULTI(4, 14)
+        EEP_PACK_MULTI(8, 1) EEP_PACK_MULTI(8, 2) EEP_PACK_MULTI(8, 3) EEP_PACK_MULTI(8, 4)
+        EEP_PACK_MULTI(8, 5) EEP_PACK_MULTI(8, 6) EEP_PACK_MULTI(8, 7)
 #undef EEP_PACK_MULTI
-          }
-        }
       }
     }
-    switch (u) {
-#define EEP_PACK_CASE(U) \
-  case U: return launch_pack_t<U, true>(c, rows, x, recv_x, T, parts, st);
-      EEP_PACK_CASE(14) EEP_PACK_CASE(13) EEP_PACK_CASE(12) EEP_PACK_CASE(11) EEP_PACK_CASE(10)
-      EEP_PACK_CASE(9) EEP_PACK_CASE(8) EEP_PACK_CASE(7) EEP_PACK_CASE(6) EEP_PACK_CASE(5)
-      EEP_PACK_CASE(4) EEP_PACK_CASE(3) EEP_PACK_CASE(2) EEP_PACK_CASE(1)
-#undef EEP_PACK_CASE
-    }
   }
-  return launch_pack_t<kPackVecs, false>(c, rows, x, recv_x, T, 1, st);
+  switch (ps.u) {
+#define EEP_PACK_CASE(U)                                                                \
+  case U:                                                                               \
+    return ps.exact ? launch_pack_t<U, true>(c, rows, x, recv_x, T, ps.parts, st)       \
+                    : launch_pack_t<U, false>(c, rows, x, recv_x, T, ps.parts, st);
+    EEP_PACK_CASE(14) EEP_PACK_CASE(13) EEP_PACK_CASE(12) EEP_PACK_CASE(11) EEP_PACK_CASE(10)
+    EEP_PACK_CASE(9) EEP_PACK_CASE(8) EEP_PACK_CASE(7) EEP_PACK_CASE(6) EEP_PACK_CASE(5)
+    EEP_PACK_CASE(4) EEP_PACK_CASE(3) EEP_PACK_CASE(2) EEP_PACK_CASE(1)
+#undef EEP_PACK_CASE
+  }
+  return hipErrorInvalidValue;
 }
 
 static hipError_t launch_pack_any(eep_ctx* c, const int32_t* rows, const void* x,
@@ -294,38 +345,62 @@ hipError_t launch_pack_rows(eep_ctx* c, const int32_t* rows, const void* x, void
 
 // ---------------------------------------------------------------------------
 // Expansion on the destination of a de-duplicated dispatch:
-// recv[row] = recv_d[expand_of[row]] for the N routed rows.  One wavefront per
-// row; the grid covers T*k rows and reads N from device memory.
+// recv[row] = recv_d[expand_of[row]] for the N routed rows (expand_of is -1 from N
+// on).  Bound by HBM like pack, with one store per load.  Below 8192 rows, which
+// is what the chip holds in wavefronts, a wavefront has up to 7 vectors per lane in
+// flight (T = 512, 5760-byte rows, whole step: 38.8 us, with 2 40.1); from there on
+// 2, which keeps the running copies closer to address order (T = 2048, 14 KiB rows:
+// 158.5 us, with 4 160, 7 166.7, 14 168.8, and with each pass in a wavefront of its
+// own 172).  Few rows are split like a small batch in pack.
 // ---------------------------------------------------------------------------
-constexpr int kExpandVecs = 7;
+constexpr int kExpandVecs = 7, kExpandManyVecs = 2;
+constexpr int kExpandManyRows = 8192;
 
-__global__ __launch_bounds__(64) void k_expand(const u32x4* __restrict__ recv_d,
-                                               u32x4* __restrict__ recv,
-                                               const int32_t* __restrict__ expand_of,
-                                               const int32_t* __restrict__ status, int row_vecs) {
-  const int row = blockIdx.x;
-  if (row >= status[0]) return;
+template <int U, bool EXACT>
+__global__ __launch_bounds__(64) void k_expand(const int32_t* __restrict__ expand_of,
+                                               const u32x4* __restrict__ recv_d, int row_vecs,
+                                               uint32_t parts, uint32_t magic,
+                                               u32x4* __restrict__ recv) {
+  const int row = token_of(blockIdx.x, parts, magic);
   const int from = expand_of[row];
-  if (from < 0) return;
+  if (from < 0) return;  // rows past the last routed pair
   const u32x4* src = recv_d + (int64_t)from * row_vecs;
   u32x4* dst = recv + (int64_t)row * row_vecs;
-  for (int v0 = threadIdx.x; v0 < row_vecs; v0 += 64 * kExpandVecs) {
-    u32x4 buf[kExpandVecs];
+  for (int v0 = (blockIdx.x - row * parts) * 64 * U + threadIdx.x; v0 < row_vecs;
+       v0 += parts * 64 * U) {
+    u32x4 buf[U];
 #pragma unroll
-    for (int u = 0; u < kExpandVecs; ++u)
-      if (v0 + u * 64 < row_vecs) buf[u] = __builtin_nontemporal_load(&src[v0 + u * 64]);
+    for (int u = 0; u < U; ++u) {
+      int v = v0 + u * 64;
+      if (!EXACT && v >= row_vecs) v = row_vecs - 1;
+      buf[u] = __builtin_nontemporal_load(&src[v]);
+    }
 #pragma unroll
-    for (int u = 0; u < kExpandVecs; ++u)
-      if (v0 + u * 64 < row_vecs) store_through(&dst[v0 + u * 64], buf[u]);
+    for (int u = 0; u < U; ++u)
+      if (EXACT || v0 + u * 64 < row_vecs) store_through(&dst[v0 + u * 64], buf[u]);
   }
 }
 
 hipError_t launch_expand(eep_ctx* c, const void* recv_dedup, void* recv_x, int T, hipStream_t st) {
   const int64_t rows = (int64_t)T * c->k;
   if (rows == 0) return hipSuccess;
-  hipLaunchKernelGGL(k_expand, dim3((unsigned)rows), dim3(64), 0, st, (const u32x4*)recv_dedup,
-                     (u32x4*)recv_x, c->dd_expand, c->status, (int)(c->x_row_bytes / 16));
-  return hipGetLastError();
+  const int row_vecs = (int)(c->x_row_bytes / 16);
+  const PassShape ps = pass_shape(row_vecs, rows < kExpandSplitBelow, rows,
+                                  rows < kExpandManyRows ? kExpandVecs : kExpandManyVecs);
+  const uint32_t magic = part_magic(ps.parts, rows * ps.parts);
+  switch (ps.u) {
+#define EEP_EXPAND_CASE(U)                                                                     \
+  case U:                                                                                      \
+    hipLaunchKernelGGL((ps.exact ? k_expand<U, true> : k_expand<U, false>),                    \
+                       dim3((unsigned)(rows * ps.parts)), dim3(64), 0, st, c->dd_expand,       \
+                       (const u32x4*)recv_dedup, row_vecs, (uint32_t)ps.parts, magic,          \
+                       (u32x4*)recv_x);                                                        \
+    return hipGetLastError();
+    EEP_EXPAND_CASE(7) EEP_EXPAND_CASE(6) EEP_EXPAND_CASE(5) EEP_EXPAND_CASE(4)
+    EEP_EXPAND_CASE(3) EEP_EXPAND_CASE(2) EEP_EXPAND_CASE(1)
+#undef EEP_EXPAND_CASE
+  }
+  return hipErrorInvalidValue;
 }
 
 // ---------------------------------------------------------------------------

@@ -51,3 +51,29 @@ def test_dequant_stand_in(oracle, T, H, group, masked):
         assert (got[N:] == 0x1234).all(), "rows past N were written"
     finally:
         ctx.destroy()
+
+
+# row sizes around whole passes: 1 vector, one short of / exactly / one past 64 and 128 vectors, a
+# prime number of 64-vector sets above 14, an odd remainder; small batches split rows over
+# wavefronts, 1024 tokens and more do not; 8192 rows change the expansion's width
+@pytest.mark.parametrize("vecs", [1, 63, 64, 65, 128, 129, 360, 15 * 64, 17 * 64, 17 * 64 - 3])
+@pytest.mark.parametrize("T", [4, 1020, 1024])
+def test_pack_and_expand_row_shapes(T, vecs):
+    H, k = vecs * 4, 8                      # fp32 rows: 4 channels per 16-byte vector
+    ctx, _, _ = routed_context(T, H, k, 5, x_dtype="f32", y_dtype="f32", out_dtype="f32")
+    try:
+        x = torch.randint(-2**31, 2**31 - 1, (T, H), dtype=torch.int32, device="cuda")
+        recv, recv_d, recv_e = (torch.full((T * k, H), 77, dtype=torch.int32, device="cuda")
+                                for _ in range(3))
+        ctx.dispatch(x, recv, T)
+        lay = ctx.read_layout(T)
+        N = lay["N"]
+        tok = torch.from_numpy(lay["src_of"][:N] // k).long().cuda()
+        assert torch.equal(recv[:N], x[tok]) and (recv[N:] == 77).all()
+        ctx.dedup_layout(T)
+        ctx.dispatch_dedup(x, recv_d, T)
+        ctx.expand(recv_d, recv_e, T)
+        assert torch.equal(recv_e[:N], x[tok]) and (recv_e[N:] == 77).all()
+        assert (recv_d[ctx.read_dedup(T)["N_d"]:] == 77).all()
+    finally:
+        ctx.destroy()
