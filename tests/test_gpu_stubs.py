@@ -77,3 +77,61 @@ def test_pack_and_expand_row_shapes(T, vecs):
         assert (recv_d[ctx.read_dedup(T)["N_d"]:] == 77).all()
     finally:
         ctx.destroy()
+
+
+# rows of 1, 64, 65 and several passes of 64 x 16 channels; 1 to 64 lanes per group; the form with
+# a wavefront per 64 vectors (below 1024 tokens) and the one with a wavefront per token
+@pytest.mark.parametrize("T,H,group", [(4, 64, 16), (8, 1024, 16), (4, 7168, 128), (8, 1280, 64),
+                                       (12, 2048, 512), (4, 8192, 1024), (1028, 512, 64),
+                                       (1024, 7168, 128), (1024, 8192, 256)])
+def test_dispatch_quant_forms(oracle, T, H, group):
+    k = 2
+    ctx, _, _ = routed_context(T, H, k, 3, x_dtype="fp8", scale_group=group)
+    try:
+        rng = np.random.default_rng(T + H)
+        x = rng.standard_normal((T, H)).astype(np.float32)
+        x *= np.exp2(rng.integers(-130, 120, (T, H // group))).repeat(group, axis=1).astype(np.float32)
+        x[0] = np.exp2(rng.integers(-20, 4, H)).astype(np.float32)     # ties and tiny quotients
+        x[1, :group] = 0.0
+        bits = synth.f32_to_bf16_bits(x)
+        bits[2] = rng.integers(0, 0x7f80, H) | (rng.integers(0, 2, H) << 15)   # any finite bf16
+        bits[3, ::7] = 0x8000                                          # negative zeros
+        recv = gu.dev_empty(T * k, H, "fp8", fill=0x5a)
+        sc = torch.full((T * k, H // group), -7.0, device="cuda")
+        ctx.dispatch_quant(gu.to_dev(bits), recv, sc, T)
+        lay = ctx.read_layout(T)
+        q, want_sc = oracle.quantize_e4m3(bits, group)
+        N = lay["N"]
+        assert N == T * k - 3
+        tok = lay["src_of"][:N] // k
+        assert np.array_equal(recv.cpu().numpy()[:N], q[tok])
+        assert np.array_equal(sc.cpu().numpy()[:N].view(np.uint32), want_sc[tok].view(np.uint32))
+        assert (recv.cpu().numpy()[N:] == 0x5a).all() and (sc.cpu().numpy()[N:] == -7.0).all()
+    finally:
+        ctx.destroy()
+
+
+@pytest.mark.parametrize("T", [4, 1024])
+def test_dispatch_quant_with_infinities_and_nan(T):
+    """A group with an infinity has an infinite scale: finite channels become zeros, infinities the
+    NaN code; NaN channels become the NaN code and do not raise the scale."""
+    H, group, k = 512, 128, 2
+    ctx, _, _ = routed_context(T, H, k, 0, x_dtype="fp8", scale_group=group)
+    try:
+        x = np.ones((T, H), np.float32)
+        x[:, 5] = -np.inf
+        x[:, group + 3] = np.nan
+        x[:, 2 * group:3 * group] = 3e38
+        bits = synth.f32_to_bf16_bits(x)
+        bits[:, group + 3] = 0x7fc0
+        recv = gu.dev_empty(T * k, H, "fp8", fill=0)
+        sc = torch.zeros((T * k, H // group), device="cuda")
+        ctx.dispatch_quant(gu.to_dev(bits), recv, sc, T)
+        got, s = recv.cpu().numpy(), sc.cpu().numpy()
+        assert np.isinf(s[:, 0]).all() and (got[:, 5] & 0x7f == 0x7f).all()
+        assert (np.delete(got[:, :group], 5, axis=1) == 0).all()
+        assert (s[:, 1] == np.float32(1) / np.float32(448)).all() and (got[:, group + 3] == 0x7f).all()
+        assert (np.delete(got[:, group:2 * group], 3, axis=1) == 0x7e).all()
+        assert (got[:, 2 * group:3 * group] == 0x7e).all() and (got[:, 3 * group:] == 0x7e).all()
+    finally:
+        ctx.destroy()
