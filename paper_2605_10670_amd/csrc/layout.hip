@@ -958,6 +958,21 @@ static_assert(kMaxPairsPerThread == 4 && kSmallPairsPerThread == 4, "EEP_FOR_K's
    : (pairs) <= 2 * kMapThreads ? EEP_FOR_K_U(KERN, 2, k)           \
                                 : EEP_FOR_K_U(KERN, 4, k))
 
+// Does an output array overlap the router indices (a caller that gives up its indices for the
+// result)?  The one-launch form reads all of them in every workgroup while others write
+// already; in the tiled form a workgroup reads its own pairs' before it writes these.
+static bool writes_its_input(const LayoutIO& c, int T) {
+  const int64_t pairs = (int64_t)T * c.k;
+  const struct { const int32_t* p; int64_t n; } out[] = {
+      {c.slot_of, pairs}, {c.row_of, pairs}, {c.src_of, pairs}, {c.count, c.P},
+      {c.offset, c.P + 1}, {c.rank_count, c.R}, {c.rank_offset, c.R + 1},
+      {c.cnt_src, (int64_t)c.R * c.P}, {c.status, 4}};
+  const uintptr_t lo = (uintptr_t)c.topk_idx, hi = lo + pairs * sizeof(int32_t);
+  for (const auto& o : out)
+    if ((uintptr_t)o.p < hi && lo < (uintptr_t)(o.p + o.n)) return true;
+  return false;
+}
+
 hipError_t launch_layout(const LayoutIO& c, int T, hipStream_t st) {
   Tiling g = make_tiling(T, c.R);
   const bool k8 = c.k == 8;
@@ -969,7 +984,7 @@ hipError_t launch_layout(const LayoutIO& c, int T, hipStream_t st) {
   }
   const float inv_S = 1.0f / (float)c.S;
   if (T <= kSmallTokens && T * c.k <= kSmallPairs &&
-      small_lds_bytes(c.E, c.P, c.R, T, c.k) <= kLayoutLdsLimit) {
+      small_lds_bytes(c.E, c.P, c.R, T, c.k) <= kLayoutLdsLimit && !writes_its_input(c, T)) {
     auto kern = EEP_FOR_K(k_layout_small, c.k, T * c.k);
     hipLaunchKernelGGL(kern, dim3(kSmallBlocks), dim3(kMapThreads), small_lds_bytes(c.E, c.P, c.R, T, c.k),
                        st, c.topk_idx, c.l2p_off, c.l2p_list, c.active, c.k, T, c.E, c.P, c.R,

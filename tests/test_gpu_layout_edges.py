@@ -88,3 +88,22 @@ def test_placement_update_spans_launches(P, E):
             assert ctx.read("status", 4)[3] == version
     finally:
         ctx.destroy()
+
+
+@pytest.mark.parametrize("T,k", [(64, 8), (512, 8), (320, 3), (1024, 8)])
+def test_layout_over_its_router_indices(oracle, T, k):
+    """slot_of given the router indices' own memory: the caller needs them no longer."""
+    import torch
+    R, S, E = 32, 9, 256
+    p2l, active, idx = instance(T, k, R, S, E, seed=T + k)
+    off, lst = binding.host_replica_lists(p2l, E, S, S - 1)
+    sizes = dict(slot_of=T * k, row_of=T * k, src_of=T * k, count=R * S, offset=R * S + 1,
+                 rank_count=R, rank_offset=R + 1, cnt_src=R * R * S, status=4)
+    out = {n: torch.zeros(m, dtype=torch.int32, device="cuda") for n, m in sizes.items()}
+    out["slot_of"].copy_(torch.from_numpy(idx.reshape(-1)))
+    binding.dispatch_layout_noalloc(R=R, S=S, E=E, k=k, policy=binding.SPREAD,
+                                    topk_idx=out["slot_of"], active=gu.to_dev(active),
+                                    l2p_off=gu.to_dev(off), l2p_list=gu.to_dev(lst), out=out, T=T)
+    want = oracle.step_layout(idx, p2l, active, E, R, S, S - 1, binding.SPREAD)
+    for n in ("slot_of", "row_of", "src_of", "count", "offset", "cnt_src"):
+        assert np.array_equal(out[n].cpu().numpy(), want[n].reshape(-1)), n
