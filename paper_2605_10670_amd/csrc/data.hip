@@ -42,6 +42,7 @@ __device__ __forceinline__ uint32_t token_of(uint32_t n, uint32_t parts, uint32_
 constexpr int kPackVecs = 14;
 constexpr int kRowBatch = 8;  // row indices fetched together
 constexpr int kPackSplitBelow = 1024;  // batches below this many tokens split a row over wavefronts
+constexpr int kPackNarrowBelow = 512;  // ... and below this many in pieces as narrow as combine's
 constexpr int kExpandSplitBelow = 4096;  // the same for rows that are read and written once
 
 // The data registers of a store of more than 8 bytes may not be rewritten by the next two
@@ -208,12 +209,16 @@ __global__ __launch_bounds__(kScaleThreads) void k_scale_rows(
 // How a row of row_vecs 16-byte vectors is cut into passes of 64 * u vectors, and over how many
 // wavefronts.  Large batches: one wavefront per token with the largest pass <= max_vecs that
 // divides the row (a whole 14 KiB row per wavefront at the decode shape); a row with no such
-// pass of at least half that width takes the fewest even passes and checks its end.  `split`
-// (small batches, which would leave most of the chip idle that way): a row is spread over
-// wavefronts, each taking one pass of two vectors per lane, or of the smallest larger width
-// that divides the row: measured at 32 ranks, top-8, 14 KiB rows, 2 KiB per wavefront and row is
-// about twice as fast as 1 KiB or 7 KiB pieces for 64 <= T <= 256 (1 KiB pieces are no better
-// than whole rows), and nothing differs from T = 1024 on.
+// pass of at least half that width takes the fewest even passes and checks its end.  `split` > 0 (small
+// batches, which would leave most of the chip idle that way): a row is spread over wavefronts,
+// each taking one pass of `split` vectors per lane.  Pack below 512 tokens takes 1, the pieces
+// that combine reads: workgroups go to the XCDs in turn, so the piece that combine's wavefront
+// (token, part) reads is one that the same XCD's pack wrote, where combine reads the receive
+// buffer itself.  Measured (7168 channels, identity experts, one set of buffers, a graph of 8
+// steps; T = 128 / 256 / 512): 12.4 / 18.9 / 29.2 us with 1, 16.5 / 24.3 / 31.7 with 2; with a set of
+// buffers per step 8 steps of 32 / 256 tokens 77.8 / 159.4 against 79.2 / 159.5.  From 512 tokens on
+// it is 2: there 1 gains little, and with a scaling stage between (512 tokens, 2048 fp32 channels,
+// top-2) it takes 22.1 us against 19.9.
 // Measured on whole steps with rows that are no whole number of passes (bf16, 2880 channels,
 // 360 vectors; T = 32 / 256 / 2048): 26 / 30 / 52 us with a bounds check around each of 14
 // accesses and one wavefront per token at every T, 9.3 / 15.7 / 42.7 us in this form.
@@ -221,15 +226,13 @@ struct PassShape {
   int u, parts;
   bool exact;
 };
-static PassShape pass_shape(int row_vecs, bool split, int64_t rows, int max_vecs) {
+static PassShape pass_shape(int row_vecs, int split, int64_t rows, int max_vecs) {
   const int per_lane = (row_vecs + 63) / 64;
   PassShape s = {1, 1, row_vecs % 64 == 0};
-  if (split && per_lane > 1) {
-    s.u = 2;
-    if (s.exact)
-      while (per_lane % s.u != 0) ++s.u;  // ends at per_lane at the latest
-    if (s.u > 4) { s.u = 2; s.exact = false; }
-    s.parts = (per_lane + s.u - 1) / s.u;
+  if (split > 0 && per_lane > 1) {
+    s.u = split;
+    s.exact = row_vecs % (64 * split) == 0;
+    s.parts = (per_lane + split - 1) / split;
     if (rows * s.parts <= 0x7fffffffLL) return s;  // (else the grid would not fit: do not split)
     s = {1, 1, row_vecs % 64 == 0};
   }
@@ -276,7 +279,8 @@ constexpr int kPackMultiMaxVecs = 56;     // 16-byte vectors a lane holds at onc
 static hipError_t launch_pack_payload(eep_ctx* c, const int32_t* rows, const void* x, void* recv_x,
                                       int T, hipStream_t st) {
   const int row_vecs = (int)(c->x_row_bytes / 16);
-  const PassShape ps = pass_shape(row_vecs, T < kPackSplitBelow, T, kPackVecs);
+  const PassShape ps = pass_shape(row_vecs, T < kPackNarrowBelow ? 1 : T < kPackSplitBelow ? 2 : 0, T,
+                                  kPackVecs);
   // Very large batches (>= kPackMultiMinTokens) of whole-row passes: several tokens per
   // wavefront, as many as keep >= kPackMultiMinWaves wavefronts and <= kPackMultiMaxVecs
   // vectors per lane.
@@ -385,7 +389,7 @@ hipError_t launch_expand(eep_ctx* c, const void* recv_dedup, void* recv_x, int T
   const int64_t rows = (int64_t)T * c->k;
   if (rows == 0) return hipSuccess;
   const int row_vecs = (int)(c->x_row_bytes / 16);
-  const PassShape ps = pass_shape(row_vecs, rows < kExpandSplitBelow, rows,
+  const PassShape ps = pass_shape(row_vecs, rows < kExpandSplitBelow ? 2 : 0, rows,
                                   rows < kExpandManyRows ? kExpandVecs : kExpandManyVecs);
   const uint32_t magic = part_magic(ps.parts, rows * ps.parts);
   switch (ps.u) {
