@@ -130,8 +130,11 @@ int eep_create_with_workspace(const eep_config* cfg, void* workspace, int64_t wo
  * cfg->num_ranks must equal the parent's.  eep_set_membership through any
  * context of the instance updates the one shared mask (and checks the coverage
  * of every context that asked for strict_coverage); a rank dropped by one
- * context's failure detection is dropped for all.  Attached contexts must be
- * destroyed before the context that eep_create made. */
+ * context's failure detection is dropped for all, also when their steps run on
+ * different streams: a layout that runs at that moment is a valid layout of
+ * either mask, or sends some pairs by one and some by the other, never two to one
+ * row.  Graphs captured before the call stay valid.  Waits for the device.
+ * Attached contexts must be destroyed before the context that eep_create made. */
 int eep_create_attached(const eep_config* cfg, eep_ctx* parent, eep_ctx** out);
 
 /* Ends the lifetime of the stable pointers (Fig. 4, Fig. 8): graphs captured
@@ -147,7 +150,9 @@ int eep_destroy(eep_ctx* ctx);
  * Both calls only queue small kernels that overwrite table CONTENTS at their
  * fixed addresses; they do not allocate, synchronise or move any buffer, and
  * they copy the host array before returning.  A step queued later on the same
- * stream sees the new tables, one queued earlier sees the old ones.  Both may
+ * stream sees the new tables, one queued earlier sees the old ones.  An update on
+ * another stream than the step's is ordered against it by the caller (an event);
+ * only a mask that several contexts share may change while a layout runs.  Both may
  * be called while a captured graph of the per-step calls exists; the graph
  * needs no update afterwards.
  *
@@ -407,6 +412,12 @@ int eep_host_uncovered_experts(int32_t P, int32_t E, int32_t S, const int32_t* p
  * (Batches of at most 512 tokens and 4096 pairs are laid out in one launch
  * without tiles; the results are the same.) */
 int eep_host_tiling(int32_t T, int32_t R, int32_t out[4]);
+/* Workgroups of that one launch for T tokens: 8 where the instance has one context,
+ * 1 where it has several (`several_contexts` != 0: the mask may change while the
+ * layout runs) and in eep_dispatch_layout_noalloc, then for at most 384 tokens and
+ * 3072 pairs; 0 where the batch is tiled.  Negative = eep_status. */
+int eep_host_layout_workgroups(int32_t R, int32_t S, int32_t E, int32_t k, int32_t T,
+                               int32_t several_contexts);
 
 /* Placement repair after a membership change (Sec. 3.5, Sec. 5.1; worked
  * example: Fig. 5, middle panel).  Host only.  Input: what every slot holds now

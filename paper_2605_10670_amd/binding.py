@@ -102,6 +102,7 @@ def load():
         "eep_host_replica_lists": [i32, i32, i32, i32, vp, vp, vp],
         "eep_host_uncovered_experts": [i32, i32, i32, vp, vp],
         "eep_host_tiling": [i32, i32, vp],
+        "eep_host_layout_workgroups": [i32, i32, i32, i32, i32, i32],
         "eep_plan_repair": [i32, i32, i32, i32, vp, vp, vp, vp, vp, vp, vp],
         "eep_plan_transition": [i32, i32, i32, i32, vp, vp, vp, vp, vp, vp, vp, vp],
         "eep_apply_repair": [vp, vp, vp, i64, vp, vp, vp, vp],

@@ -13,6 +13,19 @@ int fail_hip(eep_ctx* c, hipError_t e) {
   return EEP_ERR_HIP;
 }
 
+// Tells launches that were captured while the instance had one context how many it has now
+// (k_layout_small).  No layout of the instance may be running meanwhile.
+hipError_t set_shared_word(eep_membership* m, int32_t several) {
+  // hipFree waits for the whole device.  (hipDeviceSynchronize would too, but fails, and spoils
+  // the capture, while any other thread captures a graph.)
+  void* block = nullptr;
+  hipError_t e = hipMalloc(&block, 256);
+  if (e == hipSuccess) e = hipFree(block);
+  if (e == hipSuccess) e = launch_fill(m->mem_version + 1, several, 1, nullptr);
+  if (e == hipSuccess) e = hipStreamSynchronize(nullptr);
+  return e;
+}
+
 bool aligned16(const void* p) { return ((uintptr_t)p & 15u) == 0; }
 
 }  // namespace
@@ -214,6 +227,7 @@ int create_impl(const eep_config* cfg, eep_ctx* parent, void* workspace, int64_t
   if (e == hipSuccess) e = launch_fill(c->row_of, -1, pairs, st);
   if (e == hipSuccess) e = launch_fill(c->src_of, -1, pairs, st);
   if (e == hipSuccess) e = hipStreamSynchronize(st);
+  if (e == hipSuccess && c->mem->members.size() == 1) e = set_shared_word(c->mem, 1);
   if (e != hipSuccess) {
     if (c->owns_slab) (void)hipFree(c->slab);
     if (!parent) delete c->mem;
@@ -289,6 +303,7 @@ int eep_destroy(eep_ctx* ctx) {
       m->members.erase(m->members.begin() + i);
       break;
     }
+  if (e == hipSuccess && m->members.size() == 1) e = set_shared_word(m, 0);
   hipError_t e2 = ctx->owns_slab ? hipFree(ctx->slab) : hipSuccess;
   if (is_root) delete m;
   delete ctx;

@@ -65,6 +65,8 @@ struct eep_membership {
   int R;
   int32_t* active;       // device [R]
   int32_t* mem_version;  // device word: membership changes (host updates + ranks dropped by kernels)
+  // [1] behind it: 1 while the instance has several contexts.  Written only while the device is
+  // idle, so that all workgroups of a launch read the same value.
   std::vector<int32_t> h_active;
   // A combine with failure detection has been queued since the last eep_read_failures: a
   // kernel may have cleared bits of `active` that h_active still shows as set.
@@ -133,12 +135,14 @@ void host_replica_lists(int P, int E, int S, int S_prim, const int32_t* p2l, int
 // array for eep_dispatch_layout_noalloc.
 struct LayoutIO {
   int R, S, P, E, k, policy;
+  bool mask_may_change;  // while the layout runs: other contexts, or nobody knows whose mask it is
   const int32_t *topk_idx, *l2p_off, *l2p_list, *active, *tbl_version, *mem_version;
   int32_t *slot_of, *row_of, *src_of, *count, *offset, *rank_count, *rank_offset, *cnt_src, *status;
   // scratch: per-tile slot counts and prefixes [tiles][P], per-tile drop counters [tiles],
   // the step counter
   int32_t *cnt_tile, *base_tile, *blk_unc, *blk_msk, *step_epoch;
 };
+int layout_small_workgroups(int E, int P, int R, int T, int k, bool solo);
 bool layout_shape_fits(int E, int P, int R, int k);  // tables fit the kernels' LDS budget
 hipError_t launch_layout(const LayoutIO& io, int T, hipStream_t st);
 hipError_t launch_layout(eep_ctx* c, const int32_t* topk_idx, int T, hipStream_t st);

@@ -507,15 +507,28 @@ __global__ __launch_bounds__(kFusedThreads) void k_scan_position(
 // results, so no workgroup waits for another; one alone spent 1.4 to 2.8 us on
 // storing, mostly the [R][P] matrix of pairs per (source rank, slot).  Measured,
 // 32 ranks x 9 slots, top-8, a layout in a graph of 40: T = 32 / 128 / 256 / 384 /
-// 512 in 4.1 / 4.2 / 4.9 / 5.6 / 6.4 us with 8 workgroups, 4.1 / 4.3 / 5.2 / 6.0 / 6.6
-// with 4, 4.6 / 5.0 / 6.2 / 7.6 / 8.7 with 1.  The tiled path takes 7.7 us at 256 to
+// 512 in 4.0 / 4.1 / 4.8 / 5.6 / 6.2 us with 8 workgroups, 4.1 / 4.3 / 5.2 / 6.0 / 6.6
+// with 4, 4.4 / 4.8 / 5.9 / 7.3 / 8.7 with 1.  The tiled path takes 7.6 us at 416 to
 // 1024 tokens; 8 pairs per thread (T = 768) would be no faster than that, hence the
 // limits.
+//
+// The eight results fit together only if all eight workgroups saw one mask.  An
+// instance of one context keeps its mask still while a layout runs: only its own
+// later calls on the stream change it.  With several contexts another one's combine
+// may drop a rank, or another one's caller may update the mask, at any moment.  So
+// there ONE workgroup does it all (each entry of the replica lists is found live or
+// dead once, and every pair, count and row follows from that), up to the size from
+// which the tiled path, where each pair is mapped once, is as fast.  The launch
+// decides by the number of contexts; a launch captured while there was one is
+// overruled by the word behind the membership version, which says that there are more
+// (0.05 to 0.1 us of the figures above).
 // ---------------------------------------------------------------------------
 constexpr int kSmallBlocks = 8;
 constexpr int kSmallTokens = 512;
 constexpr int kSmallPairsPerThread = 4;
 constexpr int kSmallPairs = kMapThreads * kSmallPairsPerThread;
+constexpr int kSoloTokens = 384;  // the limits for one workgroup: 7.3 us there, the tiled path 7.6
+constexpr int kSoloPairs = kMapThreads * 3;
 
 // Row stride of the whole-batch bitmaps in words; odd, so that lanes on different slots
 // reading the same word index hit different banks.
@@ -556,16 +569,15 @@ __device__ __forceinline__ void store_src_counts(const uint32_t* s_bm, int strid
 template <int KC, int U>
 __global__ __launch_bounds__(kMapThreads) void k_layout_small(
     const int32_t* __restrict__ topk_idx, const int32_t* __restrict__ l2p_off,
-    const int32_t* __restrict__ l2p_list, const int32_t* __restrict__ active, int k_rt, int T, int E,
-    int P, int R, float inv_S, const int32_t* __restrict__ tbl_version,
-    const int32_t* __restrict__ mem_version, int policy, int tokens_per_rank, int S,
+    const int32_t* __restrict__ l2p_list, const int32_t* __restrict__ active,
+    const int32_t* __restrict__ mem_version, int npairs, int E, int P, int R, float inv_S, int T,
+    int k_rt, int share, const int32_t* __restrict__ tbl_version, int policy, int tokens_per_rank, int S,
     int32_t* __restrict__ slot_of, int32_t* __restrict__ row_of, int32_t* __restrict__ src_of,
     int32_t* __restrict__ count, int32_t* __restrict__ offset, int32_t* __restrict__ rank_count,
     int32_t* __restrict__ rank_offset, int32_t* __restrict__ cnt_src,
     int32_t* __restrict__ status, int32_t* __restrict__ step_epoch) {
   const int k = KC > 0 ? KC : k_rt;
   const int stride = small_stride(T);
-  const int npairs = T * k;
   extern __shared__ int32_t smem[];
   int32_t* s_count = smem;                        // [P] pairs per slot
   uint32_t* s_bm = (uint32_t*)(s_count + P);      // [P][stride] token bitmap per slot
@@ -575,11 +587,6 @@ __global__ __launch_bounds__(kMapThreads) void k_layout_small(
   __shared__ int32_t s_drop[2];
   const int tid = threadIdx.x;
 
-  // the pairs whose results this workgroup writes
-  const int share = ((npairs + kSmallBlocks - 1) / kSmallBlocks + 63) & ~63;
-  const int own_lo = blockIdx.x * share;
-  const int own_hi = own_lo + share < npairs ? own_lo + share : npairs;
-
   // every global read of this kernel is issued here, none depends on another
   int my_e[U], slot[U];
 #pragma unroll
@@ -588,6 +595,7 @@ __global__ __launch_bounds__(kMapThreads) void k_layout_small(
     my_e[u] = i < npairs ? topk_idx[i] : -1;
   }
   const int version = blockIdx.x == 0 && tid == 0 ? *tbl_version + *mem_version : 0;
+  const int several = mem_version[1];  // contexts of the instance: the first workgroup does it all
   for (int i = tid; i < P * (stride + 1); i += kMapThreads) s_count[i] = 0;  // and s_bm
   if (tid < 2) s_drop[tid] = 0;
   const RouteTables rt =
@@ -597,7 +605,12 @@ __global__ __launch_bounds__(kMapThreads) void k_layout_small(
     for (int u = 0; u < U; ++u)
       if (tid + u * kMapThreads < npairs) s_idx[tid + u * kMapThreads] = my_e[u];
   }
+  // the pairs and source ranks whose results this workgroup writes
+  const int own_lo = blockIdx.x * share;
+  const int own_hi = several != 0 || own_lo + share > npairs ? npairs : own_lo + share;
+  const int ranks_at_once = several != 0 || share >= npairs ? kMapWaves : kSmallBlocks * kMapWaves;
   __syncthreads();
+  if (several != 0 && blockIdx.x > 0) return;
   map_pairs<KC, kMapThreads, U>(rt, my_e, s_idx, slot, s_bm, stride, s_count, s_drop, npairs, k, E, 0,
                                 policy, own_lo, own_hi, slot_of);
   __syncthreads();
@@ -623,7 +636,7 @@ __global__ __launch_bounds__(kMapThreads) void k_layout_small(
   // pairs per (source rank, slot): the tokens of a source rank are a bit range; wavefronts
   // take source ranks, lanes slots, five sets of 64 slots at once where there are more than one
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  for (int b = blockIdx.x * kMapWaves + wave; b < R; b += kSmallBlocks * kMapWaves) {
+  for (int b = blockIdx.x * kMapWaves + wave; b < R; b += ranks_at_once) {
     const int lo = b * tokens_per_rank, hi = lo + tokens_per_rank;
     int32_t* cnt = cnt_src + (int64_t)b * P;
     if (P <= 64)
@@ -959,8 +972,9 @@ static_assert(kMaxPairsPerThread == 4 && kSmallPairsPerThread == 4, "EEP_FOR_K's
                                 : EEP_FOR_K_U(KERN, 4, k))
 
 // Does an output array overlap the router indices (a caller that gives up its indices for the
-// result)?  The one-launch form reads all of them in every workgroup while others write
-// already; in the tiled form a workgroup reads its own pairs' before it writes these.
+// result)?  Eight workgroups read all of them while others write already; one has read
+// everything before it writes, and in the tiled form a workgroup reads its own pairs' before it
+// writes these.
 static bool writes_its_input(const LayoutIO& c, int T) {
   const int64_t pairs = (int64_t)T * c.k;
   const struct { const int32_t* p; int64_t n; } out[] = {
@@ -973,6 +987,15 @@ static bool writes_its_input(const LayoutIO& c, int T) {
   return false;
 }
 
+// Workgroups of the one-launch form for this batch; 0: the tiled form.  `solo`: more than one
+// could disagree (the mask may change while the kernel runs, or an output overlaps the input).
+int layout_small_workgroups(int E, int P, int R, int T, int k, bool solo) {
+  if (T < 1 || T > (solo ? kSoloTokens : kSmallTokens) ||
+      T * k > (solo ? kSoloPairs : kSmallPairs) || small_lds_bytes(E, P, R, T, k) > kLayoutLdsLimit)
+    return 0;
+  return solo ? 1 : kSmallBlocks;
+}
+
 hipError_t launch_layout(const LayoutIO& c, int T, hipStream_t st) {
   Tiling g = make_tiling(T, c.R);
   const bool k8 = c.k == 8;
@@ -983,12 +1006,15 @@ hipError_t launch_layout(const LayoutIO& c, int T, hipStream_t st) {
     return hipGetLastError();
   }
   const float inv_S = 1.0f / (float)c.S;
-  if (T <= kSmallTokens && T * c.k <= kSmallPairs &&
-      small_lds_bytes(c.E, c.P, c.R, T, c.k) <= kLayoutLdsLimit && !writes_its_input(c, T)) {
-    auto kern = EEP_FOR_K(k_layout_small, c.k, T * c.k);
-    hipLaunchKernelGGL(kern, dim3(kSmallBlocks), dim3(kMapThreads), small_lds_bytes(c.E, c.P, c.R, T, c.k),
-                       st, c.topk_idx, c.l2p_off, c.l2p_list, c.active, c.k, T, c.E, c.P, c.R,
-                       inv_S, c.tbl_version, c.mem_version, c.policy, g.tokens_per_rank, c.S,
+  const int small = layout_small_workgroups(c.E, c.P, c.R, T, c.k,
+                                            c.mask_may_change || writes_its_input(c, T));
+  if (small > 0) {
+    const int npairs = T * c.k;
+    auto kern = EEP_FOR_K(k_layout_small, c.k, npairs);
+    hipLaunchKernelGGL(kern, dim3(small), dim3(kMapThreads), small_lds_bytes(c.E, c.P, c.R, T, c.k),
+                       st, c.topk_idx, c.l2p_off, c.l2p_list, c.active, c.mem_version, npairs, c.E,
+                       c.P, c.R, inv_S, T, c.k, ((npairs + small - 1) / small + 63) & ~63,
+                       c.tbl_version, c.policy, g.tokens_per_rank, c.S,
                        c.slot_of, c.row_of, c.src_of, c.count, c.offset, c.rank_count,
                        c.rank_offset, c.cnt_src, c.status, c.step_epoch);
     return hipGetLastError();
@@ -1034,6 +1060,7 @@ hipError_t launch_layout(eep_ctx* c, const int32_t* topk_idx, int T, hipStream_t
   LayoutIO io;
   io.R = c->R; io.S = c->S; io.P = c->P; io.E = c->E; io.k = c->k; io.policy = c->cfg.policy;
   io.topk_idx = topk_idx;
+  io.mask_may_change = c->mem->members.size() > 1;
   io.l2p_off = c->l2p_off; io.l2p_list = c->l2p_list; io.active = c->active;
   io.tbl_version = c->tbl_version; io.mem_version = c->mem->mem_version;
   io.slot_of = c->slot_of; io.row_of = c->row_of; io.src_of = c->src_of;
@@ -1045,3 +1072,11 @@ hipError_t launch_layout(eep_ctx* c, const int32_t* topk_idx, int T, hipStream_t
 }
 
 }  // namespace eep
+
+extern "C" int eep_host_layout_workgroups(int32_t R, int32_t S, int32_t E, int32_t k, int32_t T,
+                                          int32_t several_contexts) {
+  if (R < 1 || S < 1 || E < 1 || k < 1 || k > eep::kMaxTopk || T < 0 || T % R != 0 ||
+      (int64_t)R * S > (1 << 20) || E > (1 << 20) || (int64_t)T * k > (int64_t)1 << 30)
+    return EEP_ERR_INVALID_ARG;
+  return eep::layout_small_workgroups(E, R * S, R, T, k, several_contexts != 0);
+}

@@ -21,7 +21,7 @@ constexpr int kMaxDevices = 64;
 static __device__ __align__(256) int32_t scratch[kScratchInts];
 
 // Layout of the array (ints):
-//   [0]                 a word nothing ever writes: stays 0 from load time
+//   [0], [1]            words nothing ever writes: stay 0 from load time
 //   [64]                step counter the layout kernels bump (unused by callers)
 //   [128 ...)           cnt_tile[tiles*P], base_tile[tiles*P], blk_unc[tiles], blk_msk[tiles],
 //                       each rounded up to 64 ints
@@ -90,6 +90,7 @@ int eep_dispatch_layout_noalloc(const eep_layout_shape* shape, const int32_t* to
   eep::LayoutIO io;
   io.R = R; io.S = S; io.P = P; io.E = E; io.k = k; io.policy = shape->policy;
   io.topk_idx = topk_idx;
+  io.mask_may_change = true;  // `active` may be a live instance's
   io.l2p_off = l2p_off; io.l2p_list = l2p_list; io.active = active;
   // status[3] = *table_version, or 0 without one: the kernels add two words
   io.tbl_version = table_version ? table_version : base + kZeroWord;
