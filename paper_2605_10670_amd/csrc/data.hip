@@ -734,13 +734,16 @@ __device__ __forceinline__ uint32_t await_late_ranks(const DetectArgs& d, int64_
 }
 
 // First look (plain loads) at the signals of the ranks a token's rows come from; the wait only
-// if one is missing.  Returns the bits of the pairs whose rank was dropped.
-__device__ __forceinline__ uint32_t ranks_dropped(const DetectArgs& d, int64_t pair0, int k,
-                                                  const int32_t* rows, int epoch) {
+// if one is missing.  `routed`: bit j set = the caller has found a row for pair j and will use it
+// unless it is told not to.  The rows are not read again here: another wavefront of the token
+// may have struck one meanwhile, and a struck row must be reported, not passed over.
+// Returns the bits of the pairs whose rank was dropped.
+__device__ __forceinline__ uint32_t ranks_dropped(const DetectArgs& d, int64_t pair0,
+                                                  uint32_t routed, int epoch) {
   uint32_t pending = 0;
-  for (int j = 0; j < k; ++j) {
-    const int p = d.slot_of[pair0 + j];
-    if (p >= 0 && rows[j] >= 0 && d.signal[p / d.S] != epoch) pending |= 1u << j;
+  for (uint32_t m = routed; m != 0; m &= m - 1) {
+    const int j = __ffs(m) - 1;
+    if (d.signal[d.slot_of[pair0 + j] / d.S] != epoch) pending |= 1u << j;
   }
   return pending != 0 ? await_late_ranks(d, pair0, pending, epoch) : 0u;
 }
@@ -792,14 +795,14 @@ __global__ __launch_bounds__(64) void k_combine(const int32_t* row_of,
   if constexpr (K > 0) {
     // compile-time k: all loads are issued before the first is used
     int r[K];
-    bool all = true;
+    uint32_t routed = 0;
 #pragma unroll
     for (int j = 0; j < K; ++j) {
       r[j] = rows[j];
-      all &= (r[j] >= 0);
+      routed |= (uint32_t)(r[j] >= 0) << j;
     }
     u32x4 d[K];
-    if (__builtin_expect(all, 1)) {  // every pair routed: no branch between loads
+    if (__builtin_expect(routed == (1u << K) - 1, 1)) {  // every pair routed: no branch between loads
 #pragma unroll
       for (int j = 0; j < K; ++j)
         d[j] = __builtin_nontemporal_load(&y[(int64_t)r[j] * row_vecs + v]);
@@ -807,7 +810,7 @@ __global__ __launch_bounds__(64) void k_combine(const int32_t* row_of,
       // its two dependent table lookups overlap with them; rows of a rank that turns out to
       // be dropped are loaded and not used
       if constexpr (DETECT)
-        if (round_flag != epoch) dropped = ranks_dropped(det, (int64_t)t * k, k, rows, epoch);
+        if (round_flag != epoch) dropped = ranks_dropped(det, (int64_t)t * k, routed, epoch);
       // (the weights are read here: scalar loads return in any order, so a wait for the row
       // indices would also be one for the weights, which come from HBM)
 #pragma unroll
@@ -821,16 +824,20 @@ __global__ __launch_bounds__(64) void k_combine(const int32_t* row_of,
       for (int j = 0; j < K; ++j)
         if (r[j] >= 0) d[j] = __builtin_nontemporal_load(&y[(int64_t)r[j] * row_vecs + v]);
       if constexpr (DETECT)
-        if (round_flag != epoch) dropped = ranks_dropped(det, (int64_t)t * k, k, rows, epoch);
+        if (round_flag != epoch) dropped = ranks_dropped(det, (int64_t)t * k, routed, epoch);
 #pragma unroll
       for (int j = 0; j < K; ++j)
         if (r[j] >= 0 && !((dropped >> j) & 1u)) accumulate<Y_BF16>(acc, d[j], ws[j]);
     }
   } else {
     if constexpr (DETECT)
-      if (round_flag != epoch) dropped = ranks_dropped(det, (int64_t)t * k, k, rows, epoch);
+      if (round_flag != epoch) {
+        uint32_t routed = 0;
+        for (int j = 0; j < k; ++j) routed |= (uint32_t)(rows[j] >= 0) << j;
+        dropped = ranks_dropped(det, (int64_t)t * k, routed, epoch);
+      }
     for (int j = 0; j < k; ++j) {
-      int row = rows[j];
+      int row = rows[j];  // (struck since: its rank was dropped, here or by another wavefront)
       if (row < 0 || ((dropped >> j) & 1u)) continue;
       u32x4 d = __builtin_nontemporal_load(&y[(int64_t)row * row_vecs + v]);
       accumulate<Y_BF16>(acc, d, ws[j]);
