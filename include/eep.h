@@ -284,10 +284,10 @@ int eep_expert_stub(eep_ctx* ctx, int32_t kind, const void* recv_x, const float*
  * One-GPU emulation of the paper's signal counters.  Every eep_dispatch_layout
  * advances a device-side step epoch.  The expert stage announces "the outputs of
  * rank r for this step are there" by storing the epoch into rank r's signal word
- * (release).  With detection on, the combine kernel itself polls those words:
- * before a wavefront reduces a token's rows it looks at the signal of every rank
- * the rows come from, and waits -- for at most the timeout -- for a word that
- * does not show the epoch yet.  Ranks from which the step expects nothing are
+ * (a relaxed store: the kernels that wrote the outputs have ended by then).  With
+ * detection on, the combine kernel itself polls those words: before a wavefront
+ * loads a token's rows it looks at the signal of every rank the rows come from, and
+ * waits -- for at most the timeout -- for a word that does not show the epoch yet.  Ranks from which the step expects nothing are
  * not awaited.  A rank that stays silent is dropped by the kernel: its active
  * entry is cleared in the device table, the membership version is bumped, its
  * failure is recorded, and the pairs routed to it contribute nothing to this
@@ -305,7 +305,12 @@ int eep_expert_stub(eep_ctx* ctx, int32_t kind, const void* recv_x, const float*
 int eep_set_detection(eep_ctx* ctx, int64_t timeout_ns);
 /* Producer side: marks the current step's expert outputs of every active rank as
  * arrived.  eep_expert_stub does this itself when detection is on; callers that
- * run their own expert kernels (or alias y = recv_x) queue it after them. */
+ * run their own expert kernels (or alias y = recv_x) queue it after them: on their
+ * stream, or on another behind an event.  That need not be combine's stream; a
+ * combine that is waiting already sums the outputs once they have arrived.  For
+ * that the rows of different ranks must not share a 128-byte line of y (y and the
+ * row size multiples of 128 bytes): another rank's row may have brought the line into
+ * a cache before. */
 int eep_signal_experts_done(eep_ctx* ctx, void* stream);
 /* Test knob: withhold_host[R], non-zero = that rank never signals (a silent
  * peer).  This is how a failure is injected on one GPU. */

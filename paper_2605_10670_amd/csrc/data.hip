@@ -669,11 +669,13 @@ __device__ inline void store_out(void* out_row, int v, const float (&acc)[YVec<Y
 // routed to it contribute nothing (their row_of entry becomes -1).
 // In a healthy step the first wavefront of the launch finds every expected
 // signal in place and publishes that in one word (round_ok = epoch); the others
-// read that word (one agent-scope load, issued beside the row loads) and go
+// read that word (one agent-scope load, issued beside the row indices) and go
 // straight on.  Wavefronts that run before the word is published, and all
 // wavefronts of a step in which a signal is missing, look at the signals of
-// their own rows' ranks.  Those first looks use plain loads: the signal words
-// were written by an earlier launch of the same stream.  The wait itself uses agent-scope loads,
+// their own rows' ranks, a pair per lane.  No row is loaded before one or the other has
+// said that it is there: a signal may come from another stream while the kernel
+// runs.  Those first looks use plain loads: they either see the epoch or lead to the wait.
+// The wait itself uses agent-scope loads,
 // so that a rank dropped by a wavefront on another XCD is seen at once and all
 // waiting wavefronts together spend about one time-out, not one each.  Every
 // wait is bounded by the wall clock and by a poll count.
@@ -734,18 +736,16 @@ __device__ __forceinline__ uint32_t await_late_ranks(const DetectArgs& d, int64_
 }
 
 // First look (plain loads) at the signals of the ranks a token's rows come from; the wait only
-// if one is missing.  `routed`: bit j set = the caller has found a row for pair j and will use it
-// unless it is told not to.  The rows are not read again here: another wavefront of the token
+// if one is missing.  Lane j brings the row and slot of pair j (-1: none); returns the row, or
+// -1 if its rank was dropped.  The rows are not read again here: another wavefront of the token
 // may have struck one meanwhile, and a struck row must be reported, not passed over.
-// Returns the bits of the pairs whose rank was dropped.
-__device__ __forceinline__ uint32_t ranks_dropped(const DetectArgs& d, int64_t pair0,
-                                                  uint32_t routed, int epoch) {
-  uint32_t pending = 0;
-  for (uint32_t m = routed; m != 0; m &= m - 1) {
-    const int j = __ffs(m) - 1;
-    if (d.signal[d.slot_of[pair0 + j] / d.S] != epoch) pending |= 1u << j;
-  }
-  return pending != 0 ? await_late_ranks(d, pair0, pending, epoch) : 0u;
+__device__ __forceinline__ int row_if_arrived(const DetectArgs& d, int64_t pair0, int row, int slot,
+                                              int epoch) {
+  const bool missing = row >= 0 && d.signal[slot / d.S] != epoch;
+  const uint32_t pending = (uint32_t)__ballot(missing);  // (k <= 32)
+  if (pending == 0) return row;
+  const uint32_t dropped = await_late_ranks(d, pair0, pending, epoch);
+  return threadIdx.x < 32 && ((dropped >> threadIdx.x) & 1u) ? -1 : row;
 }
 
 // One wavefront per (token, part): a part is 64 16-byte columns of the row, 1 KiB of each source
@@ -759,7 +759,8 @@ __device__ __forceinline__ uint32_t ranks_dropped(const DetectArgs& d, int64_t p
 // per token.
 //
 // DETECT: the wait for the ranks' signals is part of the kernel (DetectArgs above); row_of
-// is then not read-only, because dropped pairs are struck from it.
+// is then not read-only, because dropped pairs are struck from it, and lane j keeps the row of
+// pair j from the one time it was read.
 template <bool Y_BF16, bool OUT_BF16, int K, bool DETECT>
 __global__ __launch_bounds__(64) void k_combine(const int32_t* row_of,
                                                 const u32x4* __restrict__ y, int k, int row_vecs,
@@ -768,14 +769,20 @@ __global__ __launch_bounds__(64) void k_combine(const int32_t* row_of,
                                                 void* __restrict__ out, DetectArgs det) {
   constexpr int NE = YVec<Y_BF16>::kElems;
   const int t = token_of(blockIdx.x, parts, magic);
-  const int v = (blockIdx.x - t * parts) * 64 + threadIdx.x;
+  int v = (blockIdx.x - t * parts) * 64 + threadIdx.x;
   const int32_t* rows = row_of + (int64_t)t * k;
   const float* ws = topk_w + (int64_t)t * k;
   void* out_row = (char*)out + (int64_t)t * row_vecs * (NE * (OUT_BF16 ? 2 : 4));
 
-  int round_flag = 0, epoch = 0;
+  int my_row = -1;  // of pair threadIdx.x, with DETECT
   if constexpr (DETECT) {
-    epoch = *det.step_epoch;
+    const int64_t pair0 = (int64_t)t * k;
+    int my_slot = -1;
+    if ((int)threadIdx.x < k) {
+      my_row = rows[threadIdx.x];
+      my_slot = det.slot_of[pair0 + threadIdx.x];
+    }
+    const int epoch = *det.step_epoch;
     if (blockIdx.x == 0) {
       // the first wavefront looks at every rank that holds rows of this step
       bool ok = true;
@@ -784,38 +791,38 @@ __global__ __launch_bounds__(64) void k_combine(const int32_t* row_of,
       if (__all(ok) && threadIdx.x == 0)
         __hip_atomic_store(det.round_ok, epoch, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
-    round_flag = __hip_atomic_load(det.round_ok, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (__hip_atomic_load(det.round_ok, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != epoch)
+      my_row = row_if_arrived(det, pair0, my_row, my_slot, epoch);
   }
-  if (v >= row_vecs) return;  // never lane 0, which acts for the wavefront in the wait below
+  const auto row_at = [&](int j) { return DETECT ? __builtin_amdgcn_readlane(my_row, j) : rows[j]; };
+  const bool past_end = v >= row_vecs;
+  if constexpr (DETECT) {
+    if (past_end) v = row_vecs - 1;  // a lane with a pair's row stays, whatever its column
+  } else if (past_end) {
+    return;
+  }
 
   float acc[NE];
 #pragma unroll
   for (int i = 0; i < NE; ++i) acc[i] = 0.0f;
-  uint32_t dropped = 0;  // bit j: pair j's rank was dropped in this step
   if constexpr (K > 0) {
     // compile-time k: all loads are issued before the first is used
     int r[K];
-    uint32_t routed = 0;
+    bool all = true;
 #pragma unroll
     for (int j = 0; j < K; ++j) {
-      r[j] = rows[j];
-      routed |= (uint32_t)(r[j] >= 0) << j;
+      r[j] = row_at(j);
+      all &= (r[j] >= 0);
     }
     u32x4 d[K];
-    if (__builtin_expect(routed == (1u << K) - 1, 1)) {  // every pair routed: no branch between loads
+    if (__builtin_expect(all, 1)) {  // every pair routed: no branch between loads
 #pragma unroll
       for (int j = 0; j < K; ++j)
         d[j] = __builtin_nontemporal_load(&y[(int64_t)r[j] * row_vecs + v]);
-      // the look at the ranks' signals comes after the row loads have been issued, so that
-      // its two dependent table lookups overlap with them; rows of a rank that turns out to
-      // be dropped are loaded and not used
-      if constexpr (DETECT)
-        if (round_flag != epoch) dropped = ranks_dropped(det, (int64_t)t * k, routed, epoch);
       // (the weights are read here: scalar loads return in any order, so a wait for the row
       // indices would also be one for the weights, which come from HBM)
 #pragma unroll
-      for (int j = 0; j < K; ++j)
-        if (!DETECT || !((dropped >> j) & 1u)) accumulate<Y_BF16>(acc, d[j], ws[j]);
+      for (int j = 0; j < K; ++j) accumulate<Y_BF16>(acc, d[j], ws[j]);
     } else {
       // Some pairs have no row (a dead rank's experts before the repair, masked indices): the
       // same, with a branch around each load and each term; r[] is uniform, so no lane
@@ -823,27 +830,19 @@ __global__ __launch_bounds__(64) void k_combine(const int32_t* row_of,
 #pragma unroll
       for (int j = 0; j < K; ++j)
         if (r[j] >= 0) d[j] = __builtin_nontemporal_load(&y[(int64_t)r[j] * row_vecs + v]);
-      if constexpr (DETECT)
-        if (round_flag != epoch) dropped = ranks_dropped(det, (int64_t)t * k, routed, epoch);
 #pragma unroll
       for (int j = 0; j < K; ++j)
-        if (r[j] >= 0 && !((dropped >> j) & 1u)) accumulate<Y_BF16>(acc, d[j], ws[j]);
+        if (r[j] >= 0) accumulate<Y_BF16>(acc, d[j], ws[j]);
     }
   } else {
-    if constexpr (DETECT)
-      if (round_flag != epoch) {
-        uint32_t routed = 0;
-        for (int j = 0; j < k; ++j) routed |= (uint32_t)(rows[j] >= 0) << j;
-        dropped = ranks_dropped(det, (int64_t)t * k, routed, epoch);
-      }
     for (int j = 0; j < k; ++j) {
-      int row = rows[j];  // (struck since: its rank was dropped, here or by another wavefront)
-      if (row < 0 || ((dropped >> j) & 1u)) continue;
+      int row = row_at(j);
+      if (row < 0) continue;
       u32x4 d = __builtin_nontemporal_load(&y[(int64_t)row * row_vecs + v]);
       accumulate<Y_BF16>(acc, d, ws[j]);
     }
   }
-  store_out<Y_BF16, OUT_BF16>(out_row, v, acc);
+  if (!DETECT || !past_end) store_out<Y_BF16, OUT_BF16>(out_row, v, acc);
 }
 
 template <bool Y_BF16, bool OUT_BF16>

@@ -10,9 +10,9 @@
 //
 // Here the ranks are partitions of one GPU, so the round that can be reproduced
 // is "expert rank r has produced its outputs of this step" (producer: the expert
-// stage, which stores the step's epoch into signal[r]; k_signal below) and "combine waits for the signals of the ranks it reads from"
-// (consumer: the combine kernel itself, see await_late_ranks in data.hip).  A
-// rank that stays silent -- on one GPU only the test knob `withhold` can make
+// stage, which stores the step's epoch into signal[r]; k_signal below) and
+// "combine waits for the signals of the ranks it reads from" (consumer: the
+// combine kernel itself, see await_late_ranks in data.hip).  A rank that stays silent -- on one GPU only the test knob `withhold` can make
 // one -- is dropped by the kernel: active[r] = 0, report[r] = 1, and the pairs
 // that were routed to it lose their row.  The next step's routing already reads
 // the cleared bit; no host action and no graph change is needed for that.
