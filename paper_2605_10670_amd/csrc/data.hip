@@ -233,7 +233,7 @@ static PassShape pass_shape(int row_vecs, int split, int64_t rows, int max_vecs)
     s.u = split;
     s.exact = row_vecs % (64 * split) == 0;
     s.parts = (per_lane + split - 1) / split;
-    if (rows * s.parts <= 0x7fffffffLL) return s;  // (else the grid would not fit: do not split)
+    if (rows * s.parts <= max_blocks(64)) return s;  // (else the grid would not fit: do not split)
     s = {1, 1, row_vecs % 64 == 0};
   }
   const int passes = (per_lane + max_vecs - 1) / max_vecs;
@@ -324,13 +324,16 @@ static hipError_t launch_pack_any(eep_ctx* c, const int32_t* rows, const void* x
                                   const float* x_scale, void* recv_x, float* recv_scale, int T,
                                   hipStream_t st) {
   if (T == 0) return hipSuccess;
-  hipError_t e = launch_pack_payload(c, rows, x, recv_x, T, st);
+  hipError_t e = in_launches(T, max_blocks(64), [&](int64_t t0, int64_t n) {
+    return launch_pack_payload(c, rows + t0 * c->k, (const char*)x + t0 * c->x_row_bytes, recv_x,
+                               (int)n, st);
+  });
   if (e != hipSuccess || x_scale == nullptr) return e;
   const int scale_vecs = (int)(c->scale_row_bytes / 16);
   const int64_t vecs = (int64_t)T * c->k * scale_vecs;
   const int64_t per_block = (int64_t)kScaleThreads * kScaleVecs;
   const int64_t blocks = (vecs + per_block - 1) / per_block;
-  if (blocks > 0x7fffffffLL) return hipErrorInvalidValue;
+  if (blocks > max_blocks(kScaleThreads)) return hipErrorInvalidValue;
   hipLaunchKernelGGL(k_scale_rows, dim3((unsigned)blocks), dim3(kScaleThreads), 0, st,
                      (const u32x4*)x_scale, (u32x4*)recv_scale, c->src_of, c->status, c->k,
                      scale_vecs, vecs);
@@ -391,20 +394,22 @@ hipError_t launch_expand(eep_ctx* c, const void* recv_dedup, void* recv_x, int T
   const int row_vecs = (int)(c->x_row_bytes / 16);
   const PassShape ps = pass_shape(row_vecs, rows < kExpandSplitBelow ? 2 : 0, rows,
                                   rows < kExpandManyRows ? kExpandVecs : kExpandManyVecs);
-  const uint32_t magic = part_magic(ps.parts, rows * ps.parts);
-  switch (ps.u) {
+  return in_launches(rows, max_blocks(64) / ps.parts, [&](int64_t r0, int64_t n) {
+    const uint32_t magic = part_magic(ps.parts, n * ps.parts);
+    u32x4* to = (u32x4*)recv_x + r0 * row_vecs;
+    switch (ps.u) {
 #define EEP_EXPAND_CASE(U)                                                                     \
   case U:                                                                                      \
     hipLaunchKernelGGL((ps.exact ? k_expand<U, true> : k_expand<U, false>),                    \
-                       dim3((unsigned)(rows * ps.parts)), dim3(64), 0, st, c->dd_expand,       \
-                       (const u32x4*)recv_dedup, row_vecs, (uint32_t)ps.parts, magic,          \
-                       (u32x4*)recv_x);                                                        \
+                       dim3((unsigned)(n * ps.parts)), dim3(64), 0, st, c->dd_expand + r0,     \
+                       (const u32x4*)recv_dedup, row_vecs, (uint32_t)ps.parts, magic, to);     \
     return hipGetLastError();
-    EEP_EXPAND_CASE(7) EEP_EXPAND_CASE(6) EEP_EXPAND_CASE(5) EEP_EXPAND_CASE(4)
-    EEP_EXPAND_CASE(3) EEP_EXPAND_CASE(2) EEP_EXPAND_CASE(1)
+      EEP_EXPAND_CASE(7) EEP_EXPAND_CASE(6) EEP_EXPAND_CASE(5) EEP_EXPAND_CASE(4)
+      EEP_EXPAND_CASE(3) EEP_EXPAND_CASE(2) EEP_EXPAND_CASE(1)
 #undef EEP_EXPAND_CASE
-  }
-  return hipErrorInvalidValue;
+    }
+    return hipErrorInvalidValue;
+  });
 }
 
 // ---------------------------------------------------------------------------
@@ -604,13 +609,16 @@ hipError_t launch_pack_quant(eep_ctx* c, const void* x_bf16, void* recv_q, float
   const int out_vecs = c->H / 16;
   const int groups = c->H / c->cfg.scale_group;
   const int passes = (out_vecs + 63) / 64;
-  const bool split = T < kQuantSplitBelow && (int64_t)T * passes <= 0x7fffffffLL;
+  const bool split = T < kQuantSplitBelow && (int64_t)T * passes <= max_blocks(64);
   const int parts = split ? passes : 1;
-  hipLaunchKernelGGL((split ? k_pack_quant<1> : k_pack_quant<kQuantVecs>),
-                     dim3((unsigned)(T * parts)), dim3(64), 0, st, (const u32x4*)x_bf16, c->row_of,
-                     c->k, out_vecs, (uint32_t)parts, part_magic(parts, (int64_t)T * parts),
-                     c->cfg.scale_group / 16, groups, (u32x4*)recv_q, recv_scale);
-  return hipGetLastError();
+  return in_launches(T, max_blocks(64) / parts, [&](int64_t t0, int64_t n) {
+    hipLaunchKernelGGL((split ? k_pack_quant<1> : k_pack_quant<kQuantVecs>),
+                       dim3((unsigned)(n * parts)), dim3(64), 0, st,
+                       (const u32x4*)x_bf16 + t0 * out_vecs * 2, c->row_of + t0 * c->k, c->k,
+                       out_vecs, (uint32_t)parts, part_magic(parts, n * parts),
+                       c->cfg.scale_group / 16, groups, (u32x4*)recv_q, recv_scale);
+    return hipGetLastError();
+  });
 }
 
 // ---------------------------------------------------------------------------
@@ -850,9 +858,6 @@ static hipError_t launch_combine_t(eep_ctx* c, const void* y, const float* w, vo
                                    hipStream_t st) {
   int row_vecs = (int)(c->y_row_bytes / 16);
   int parts = (row_vecs + 63) / 64;
-  if ((int64_t)T * parts > 0x7fffffffLL) return hipErrorInvalidValue;  // grid size limit
-  const uint32_t magic = part_magic(parts, (int64_t)T * parts);
-  dim3 grid((unsigned)((int64_t)T * parts)), block(64);
   DetectArgs det = {};
   const bool detect = c->detect_timeout_ticks > 0;
   if (detect) {
@@ -864,23 +869,34 @@ static hipError_t launch_combine_t(eep_ctx* c, const void* y, const float* w, vo
     det.timeout_ticks = c->detect_timeout_ticks;
     det.max_polls = c->detect_timeout_ticks * 8 + 1024;
   }
-  switch (c->k) {
+  return in_launches(T, max_blocks(64) / parts, [&](int64_t t0, int64_t n) {
+    const dim3 grid((unsigned)(n * parts)), block(64);
+    const uint32_t magic = part_magic(parts, n * parts);
+    const int64_t p0 = t0 * c->k;
+    void* to = (char*)out + t0 * c->out_row_bytes;
+    DetectArgs d = det;
+    if (detect) {
+      d.slot_of += p0;
+      d.row_of += p0;
+    }
+    switch (c->k) {
 #define EEP_COMBINE_K(CASE, K)                                                              \
   CASE:                                                                                     \
   hipLaunchKernelGGL((detect ? k_combine<Y_BF16, OUT_BF16, K, true>                         \
                              : k_combine<Y_BF16, OUT_BF16, K, false>),                      \
-                     grid, block, 0, st, c->row_of, (const u32x4*)y, c->k, row_vecs,        \
-                     (uint32_t)parts, magic, w, out, det);                                  \
+                     grid, block, 0, st, c->row_of + p0, (const u32x4*)y, c->k, row_vecs,   \
+                     (uint32_t)parts, magic, w + p0, to, d);                                \
   break;
-    EEP_COMBINE_K(case 8, 8)
-    EEP_COMBINE_K(case 6, 6)
-    EEP_COMBINE_K(case 4, 4)
-    EEP_COMBINE_K(case 2, 2)
-    EEP_COMBINE_K(case 1, 1)
-    EEP_COMBINE_K(default, 0)
+      EEP_COMBINE_K(case 8, 8)
+      EEP_COMBINE_K(case 6, 6)
+      EEP_COMBINE_K(case 4, 4)
+      EEP_COMBINE_K(case 2, 2)
+      EEP_COMBINE_K(case 1, 1)
+      EEP_COMBINE_K(default, 0)
 #undef EEP_COMBINE_K
-  }
-  return hipGetLastError();
+    }
+    return hipGetLastError();
+  });
 }
 
 hipError_t launch_combine(eep_ctx* c, const void* y, const float* w, void* out, int T,
@@ -902,8 +918,8 @@ hipError_t launch_combine(eep_ctx* c, const void* y, const float* w, void* out, 
 __global__ __launch_bounds__(256) void k_stub_copy(const u32x4* __restrict__ recv,
                                                    u32x4* __restrict__ y,
                                                    const int32_t* __restrict__ status,
-                                                   int row_vecs) {
-  const int row = blockIdx.x;
+                                                   int row_vecs, int row0) {
+  const int row = row0 + blockIdx.x;
   if (row >= status[0]) return;
   for (int v = threadIdx.x; v < row_vecs; v += blockDim.x)
     store_through(&y[(int64_t)row * row_vecs + v],
@@ -1007,9 +1023,10 @@ __device__ __forceinline__ void dequant_block(const u32x2* q, const float* s0, u
 template <bool POW2>
 __global__ __launch_bounds__(kDequantThreads) void k_stub_dequant(
     const u32x2* __restrict__ q, const float* __restrict__ scale, u32x4* __restrict__ y,
-    const int32_t* __restrict__ status, int row_vecs, int group_vecs, int group_shift) {
+    const int32_t* __restrict__ status, int row_vecs, int group_vecs, int group_shift,
+    int64_t block0) {
   const int64_t n = (int64_t)status[0] * row_vecs;  // rows >= N are left untouched
-  const int64_t base = (int64_t)blockIdx.x * (kDequantThreads * kDequantVecs);
+  const int64_t base = (block0 + blockIdx.x) * (kDequantThreads * kDequantVecs);
   if (base >= n) return;
   const int64_t g0 = POW2 ? base >> group_shift
                           : (int64_t)((uint64_t)base / (uint32_t)group_vecs);
@@ -1026,29 +1043,31 @@ hipError_t launch_stub(eep_ctx* c, int kind, const void* recv_x, const float* re
   int64_t rows = (int64_t)T * c->k;
   if (rows == 0) return hipSuccess;
   int row_vecs = (int)(c->x_row_bytes / 16);
-  dim3 grid((unsigned)rows), block(256);
-  if (kind == EEP_STUB_IDENTITY) {
-    hipLaunchKernelGGL(k_stub_copy, grid, block, 0, st, (const u32x4*)recv_x, (u32x4*)y,
-                       c->status, row_vecs);
-  } else if (kind == EEP_STUB_SCALE) {
-    auto kern = c->cfg.x_dtype == EEP_BF16 ? k_stub_scale<true> : k_stub_scale<false>;
-    hipLaunchKernelGGL(kern, grid, block, 0, st, c->src_of, (const u32x4*)recv_x, row_vecs,
-                       c->slot_of, c->p2l, expert_scale, (u32x4*)y);
-  } else {
-    const int vecs8 = c->H / 8, group_vecs = c->cfg.scale_group / 8;
-    const int64_t per_block = kDequantThreads * kDequantVecs;
-    const int64_t blocks = (rows * vecs8 + per_block - 1) / per_block;
-    if (blocks > 0x7fffffffLL) return hipErrorInvalidValue;  // grid size limit
-    if ((group_vecs & (group_vecs - 1)) == 0)
-      hipLaunchKernelGGL(k_stub_dequant<true>, dim3((unsigned)blocks), dim3(kDequantThreads), 0, st,
-                         (const u32x2*)recv_x, recv_scale, (u32x4*)y, c->status, vecs8, group_vecs,
-                         __builtin_ctz(group_vecs));
-    else
-      hipLaunchKernelGGL(k_stub_dequant<false>, dim3((unsigned)blocks), dim3(kDequantThreads), 0,
-                         st, (const u32x2*)recv_x, recv_scale, (u32x4*)y, c->status, vecs8,
-                         group_vecs, 0);
-  }
-  return hipGetLastError();
+  const dim3 block(256);
+  if (kind != EEP_STUB_DEQUANT)
+    return in_launches(rows, max_blocks(256), [&](int64_t r0, int64_t n) {
+      const dim3 grid((unsigned)n);
+      const int64_t v0 = r0 * row_vecs;
+      if (kind == EEP_STUB_IDENTITY) {
+        hipLaunchKernelGGL(k_stub_copy, grid, block, 0, st, (const u32x4*)recv_x, (u32x4*)y,
+                           c->status, row_vecs, (int)r0);
+      } else {
+        auto kern = c->cfg.x_dtype == EEP_BF16 ? k_stub_scale<true> : k_stub_scale<false>;
+        hipLaunchKernelGGL(kern, grid, block, 0, st, c->src_of + r0, (const u32x4*)recv_x + v0,
+                           row_vecs, c->slot_of, c->p2l, expert_scale, (u32x4*)y + v0);
+      }
+      return hipGetLastError();
+    });
+  const int vecs8 = c->H / 8, group_vecs = c->cfg.scale_group / 8;
+  const int64_t per_block = kDequantThreads * kDequantVecs;
+  const bool pow2 = (group_vecs & (group_vecs - 1)) == 0;
+  return in_launches((rows * vecs8 + per_block - 1) / per_block, max_blocks(kDequantThreads),
+                     [&](int64_t b0, int64_t n) {
+    hipLaunchKernelGGL((pow2 ? k_stub_dequant<true> : k_stub_dequant<false>), dim3((unsigned)n),
+                       dim3(kDequantThreads), 0, st, (const u32x2*)recv_x, recv_scale, (u32x4*)y,
+                       c->status, vecs8, group_vecs, pow2 ? __builtin_ctz(group_vecs) : 0, b0);
+    return hipGetLastError();
+  });
 }
 
 }  // namespace eep

@@ -49,6 +49,18 @@ inline size_t map_lds_bytes(int E, int P, int R, int tile_tokens, int k) {
 
 inline int dtype_bytes(int dt) { return dt == EEP_F32 ? 4 : dt == EEP_BF16 ? 2 : 1; }
 
+// Workgroups that one launch may have: a grid of 2^32 lanes or more loses its upper bits without
+// an error.  Larger work goes in several launches.
+inline int64_t max_blocks(int threads) { return 0xffffffffLL / threads; }
+template <class Launch>  // launch(first, count) for at most `most` of `items` at a time
+inline hipError_t in_launches(int64_t items, int64_t most, Launch launch) {
+  for (int64_t first = 0; first < items; first += most) {
+    const hipError_t e = launch(first, items - first < most ? items - first : most);
+    if (e != hipSuccess) return e;
+  }
+  return hipSuccess;
+}
+
 // One array of a table update: n values from host memory to a device address (n may be 0).
 struct PatchArray {
   int32_t* dst;

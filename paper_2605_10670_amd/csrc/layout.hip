@@ -1005,6 +1005,7 @@ hipError_t launch_layout(const LayoutIO& c, int T, hipStream_t st) {
                        c.step_epoch, c.R, c.P);
     return hipGetLastError();
   }
+  if (g.num_tiles > max_blocks(kMapThreads)) return hipErrorInvalidValue;
   const float inv_S = 1.0f / (float)c.S;
   const int small = layout_small_workgroups(c.E, c.P, c.R, T, c.k,
                                             c.mask_may_change || writes_its_input(c, T));

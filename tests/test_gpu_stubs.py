@@ -135,3 +135,43 @@ def test_dispatch_quant_with_infinities_and_nan(T):
         assert (got[:, 2 * group:3 * group] == 0x7e).all() and (got[:, 3 * group:] == 0x7e).all()
     finally:
         ctx.destroy()
+
+
+def test_combine_of_more_wavefronts_than_one_launch_takes():
+    """2^25 + 1 tokens whose rows end one vector past a part: 2^26 + 2 wavefronts of 64 lanes, more
+    than the 2^32 lanes that a grid dimension may have."""
+    T, H = 2**25 + 1, 520
+    ctx = binding.Context(num_ranks=1, slots_per_rank=1, primary_slots=1, num_logical=1,
+                          max_tokens=T, topk=1, hidden=H)
+    try:
+        ctx.update_placement(np.zeros(1, np.int32))
+        y = torch.randint(0, 0x7f00, (T, H), dtype=torch.int16, device="cuda")   # finite bf16
+        out = torch.empty_like(y)
+        ctx.dispatch_layout(torch.zeros((T, 1), dtype=torch.int32, device="cuda"), T)
+        ctx.combine(y, torch.ones((T, 1), device="cuda"), out, T)
+        assert torch.equal(out, y)
+    finally:
+        ctx.destroy()
+
+
+def test_stand_ins_of_more_rows_than_one_launch_takes():
+    """2^24 + 3 rows at 256 lanes each; masked tokens at the end."""
+    T, H, masked = 2**24 + 3, 8, 2
+    ctx = binding.Context(num_ranks=1, slots_per_rank=1, primary_slots=1, num_logical=1,
+                          max_tokens=T, topk=1, hidden=H)
+    try:
+        ctx.update_placement(np.zeros(1, np.int32))
+        idx = torch.zeros((T, 1), dtype=torch.int32, device="cuda")
+        idx[-masked:] = -1
+        x = torch.randint(0, 0x7f00, (T, H), dtype=torch.int16, device="cuda")
+        recv, y = (torch.full((T, H), 77, dtype=torch.int16, device="cuda") for _ in range(2))
+        N = T - masked
+        ctx.dispatch_layout(idx, T)
+        ctx.dispatch(x, recv, T)
+        assert torch.equal(recv[:N], x[:N]) and (recv[N:] == 77).all()
+        for kind in ("identity", "scale"):
+            y.fill_(77)
+            ctx.expert_stub(kind, recv, y, T, expert_scale=torch.ones(1, device="cuda"))
+            assert torch.equal(y[:N], x[:N]) and (y[N:] == 77).all(), kind
+    finally:
+        ctx.destroy()
