@@ -529,6 +529,7 @@ constexpr int kSmallPairsPerThread = 4;
 constexpr int kSmallPairs = kMapThreads * kSmallPairsPerThread;
 constexpr int kSoloTokens = 384;  // the limits for one workgroup: 7.3 us there, the tiled path 7.6
 constexpr int kSoloPairs = kMapThreads * 3;
+constexpr uint32_t kSoloBit = 1u << 31;
 
 // Row stride of the whole-batch bitmaps in words; odd, so that lanes on different slots
 // reading the same word index hit different banks.
@@ -570,13 +571,14 @@ template <int KC, int U>
 __global__ __launch_bounds__(kMapThreads) void k_layout_small(
     const int32_t* __restrict__ topk_idx, const int32_t* __restrict__ l2p_off,
     const int32_t* __restrict__ l2p_list, const int32_t* __restrict__ active,
-    const int32_t* __restrict__ mem_version, int npairs, int E, int P, int R, float inv_S, int T,
-    int k_rt, int share, const int32_t* __restrict__ tbl_version, int policy, int tokens_per_rank, int S,
+    const int32_t* __restrict__ mem_version, uint32_t T_k, int E, int P, int R, float inv_S,
+    const int32_t* __restrict__ tbl_version, int policy, int tokens_per_rank, int S,
     int32_t* __restrict__ slot_of, int32_t* __restrict__ row_of, int32_t* __restrict__ src_of,
     int32_t* __restrict__ count, int32_t* __restrict__ offset, int32_t* __restrict__ rank_count,
     int32_t* __restrict__ rank_offset, int32_t* __restrict__ cnt_src,
     int32_t* __restrict__ status, int32_t* __restrict__ step_epoch) {
-  const int k = KC > 0 ? KC : k_rt;
+  const int T = T_k & 0xffff, k = KC > 0 ? KC : T_k >> 16 & 0xff;  // in one preloaded word
+  const int npairs = T * k;
   const int stride = small_stride(T);
   extern __shared__ int32_t smem[];
   int32_t* s_count = smem;                        // [P] pairs per slot
@@ -605,12 +607,14 @@ __global__ __launch_bounds__(kMapThreads) void k_layout_small(
     for (int u = 0; u < U; ++u)
       if (tid + u * kMapThreads < npairs) s_idx[tid + u * kMapThreads] = my_e[u];
   }
-  // the pairs and source ranks whose results this workgroup writes
-  const int own_lo = blockIdx.x * share;
-  const int own_hi = several != 0 || own_lo + share > npairs ? npairs : own_lo + share;
-  const int ranks_at_once = several != 0 || share >= npairs ? kMapWaves : kSmallBlocks * kMapWaves;
+  // the pairs [own_lo, own_hi) whose results this workgroup writes, and as which of how many; with
+  // `solo` the first one's are all, the others go along and write nothing
+  const bool solo = several != 0 || (T_k & kSoloBit) != 0;
+  const int blocks = solo ? 1 : kSmallBlocks, block = solo && blockIdx.x > 0 ? R : blockIdx.x;
+  const int share = ((npairs + kSmallBlocks - 1) / kSmallBlocks + 63) & ~63;
+  const int own_lo = solo ? (blockIdx.x > 0 ? npairs : 0) : blockIdx.x * share;
+  const int own_hi = solo || own_lo + share > npairs ? npairs : own_lo + share;
   __syncthreads();
-  if (several != 0 && blockIdx.x > 0) return;
   map_pairs<KC, kMapThreads, U>(rt, my_e, s_idx, slot, s_bm, stride, s_count, s_drop, npairs, k, E, 0,
                                 policy, own_lo, own_hi, slot_of);
   __syncthreads();
@@ -636,7 +640,7 @@ __global__ __launch_bounds__(kMapThreads) void k_layout_small(
   // pairs per (source rank, slot): the tokens of a source rank are a bit range; wavefronts
   // take source ranks, lanes slots, five sets of 64 slots at once where there are more than one
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  for (int b = blockIdx.x * kMapWaves + wave; b < R; b += ranks_at_once) {
+  for (int b = block * kMapWaves + wave; b < R; b += blocks * kMapWaves) {
     const int lo = b * tokens_per_rank, hi = lo + tokens_per_rank;
     int32_t* cnt = cnt_src + (int64_t)b * P;
     if (P <= 64)
@@ -1010,12 +1014,11 @@ hipError_t launch_layout(const LayoutIO& c, int T, hipStream_t st) {
   const int small = layout_small_workgroups(c.E, c.P, c.R, T, c.k,
                                             c.mask_may_change || writes_its_input(c, T));
   if (small > 0) {
-    const int npairs = T * c.k;
-    auto kern = EEP_FOR_K(k_layout_small, c.k, npairs);
+    auto kern = EEP_FOR_K(k_layout_small, c.k, T * c.k);
     hipLaunchKernelGGL(kern, dim3(small), dim3(kMapThreads), small_lds_bytes(c.E, c.P, c.R, T, c.k),
-                       st, c.topk_idx, c.l2p_off, c.l2p_list, c.active, c.mem_version, npairs, c.E,
-                       c.P, c.R, inv_S, T, c.k, ((npairs + small - 1) / small + 63) & ~63,
-                       c.tbl_version, c.policy, g.tokens_per_rank, c.S,
+                       st, c.topk_idx, c.l2p_off, c.l2p_list, c.active, c.mem_version,
+                       (uint32_t)T | (uint32_t)c.k << 16 | (small == 1 ? kSoloBit : 0u), c.E,
+                       c.P, c.R, inv_S, c.tbl_version, c.policy, g.tokens_per_rank, c.S,
                        c.slot_of, c.row_of, c.src_of, c.count, c.offset, c.rank_count,
                        c.rank_offset, c.cnt_src, c.status, c.step_epoch);
     return hipGetLastError();
