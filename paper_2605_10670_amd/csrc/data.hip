@@ -217,11 +217,13 @@ __global__ __launch_bounds__(kScaleThreads) void k_scale_rows(
 // buffer itself.  Measured (7168 channels, identity experts, one set of buffers, a graph of 8
 // steps; T = 128 / 256 / 512): 12.4 / 18.9 / 29.2 us with 1, 16.5 / 24.3 / 31.7 with 2; with a set of
 // buffers per step 8 steps of 32 / 256 tokens 77.8 / 159.4 against 79.2 / 159.5.  From 512 tokens on
-// it is 2: there 1 gains little, and with a scaling stage between (512 tokens, 2048 fp32 channels,
-// top-2) it takes 22.1 us against 19.9.
+// it is 2, and combine takes its pieces in pairs so that they meet in an XCD again (k_combine):
+// with 1 and a scaling stage between (512 tokens, 2048 fp32 channels, top-2) a step takes 22.4 us
+// against 19.2.
 // Measured on whole steps with rows that are no whole number of passes (bf16, 2880 channels,
 // 360 vectors; T = 32 / 256 / 2048): 26 / 30 / 52 us with a bounds check around each of 14
 // accesses and one wavefront per token at every T, 9.3 / 15.7 / 42.7 us in this form.
+static int pack_split(int T) { return T < kPackNarrowBelow ? 1 : T < kPackSplitBelow ? 2 : 0; }
 struct PassShape {
   int u, parts;
   bool exact;
@@ -279,8 +281,7 @@ constexpr int kPackMultiMaxVecs = 56;     // 16-byte vectors a lane holds at onc
 static hipError_t launch_pack_payload(eep_ctx* c, const int32_t* rows, const void* x, void* recv_x,
                                       int T, hipStream_t st) {
   const int row_vecs = (int)(c->x_row_bytes / 16);
-  const PassShape ps = pass_shape(row_vecs, T < kPackNarrowBelow ? 1 : T < kPackSplitBelow ? 2 : 0, T,
-                                  kPackVecs);
+  const PassShape ps = pass_shape(row_vecs, pack_split(T), T, kPackVecs);
   // Very large batches (>= kPackMultiMinTokens) of whole-row passes: several tokens per
   // wavefront, as many as keep >= kPackMultiMinWaves wavefronts and <= kPackMultiMaxVecs
   // vectors per lane.
@@ -766,18 +767,34 @@ __device__ __forceinline__ int row_if_arrived(const DetectArgs& d, int64_t pair0
 // 83.2 / 168 / 755 / 57.  Single-wavefront workgroups measured ~10 % faster than one workgroup
 // per token.
 //
+// `paired` > 0 (the number of tokens): the batch was packed in pieces of two parts, `parts` counts
+// such pieces, and the two wavefronts of piece m run on the XCD that wrote it (workgroups go to the
+// 8 XCDs in turn, pack's m-th to m mod 8): 16 workgroups take pieces 8g .. 8g + 7, first their first
+// parts and then their second.  Measured (identity experts, one set of buffers, whole steps of T = 512 /
+// 768 / 992 tokens): 2048 channels 20.6 / 26.6 / 29.1 us without, 15.4 / 19.0 / 22.1 with; 4096 channels
+// 28.0 / 32.1 / 35.7 and 20.5 / 28.5 / 33.5; 7168 channels 32.6 / 42.4 / 51.0 and 29.6 / 40.9 / 49.7; with a
+// scaling stage between, where nothing can meet, within 1 % either way.
+//
 // DETECT: the wait for the ranks' signals is part of the kernel (DetectArgs above); row_of
 // is then not read-only, because dropped pairs are struck from it, and lane j keeps the row of
 // pair j from the one time it was read.
 template <bool Y_BF16, bool OUT_BF16, int K, bool DETECT>
 __global__ __launch_bounds__(64) void k_combine(const int32_t* row_of,
                                                 const u32x4* __restrict__ y, int k, int row_vecs,
-                                                uint32_t parts, uint32_t magic,
+                                                uint32_t parts, uint32_t magic, int paired,
                                                 const float* __restrict__ topk_w,
                                                 void* __restrict__ out, DetectArgs det) {
   constexpr int NE = YVec<Y_BF16>::kElems;
-  const int t = token_of(blockIdx.x, parts, magic);
-  int v = (blockIdx.x - t * parts) * 64 + threadIdx.x;
+  int t, v;
+  if (paired > 0) {
+    const uint32_t piece = (blockIdx.x >> 4) * 8 + (blockIdx.x & 7);
+    t = token_of(piece, parts, magic);
+    if (t >= paired) return;
+    v = ((piece - t * parts) * 2 + ((blockIdx.x >> 3) & 1)) * 64 + threadIdx.x;
+  } else {
+    t = token_of(blockIdx.x, parts, magic);
+    v = (blockIdx.x - t * parts) * 64 + threadIdx.x;
+  }
   const int32_t* rows = row_of + (int64_t)t * k;
   const float* ws = topk_w + (int64_t)t * k;
   void* out_row = (char*)out + (int64_t)t * row_vecs * (NE * (OUT_BF16 ? 2 : 4));
@@ -858,6 +875,9 @@ static hipError_t launch_combine_t(eep_ctx* c, const void* y, const float* w, vo
                                    hipStream_t st) {
   int row_vecs = (int)(c->y_row_bytes / 16);
   int parts = (row_vecs + 63) / 64;
+  // y may be the receive buffer only if its rows are of the same size
+  const bool paired = pack_split(T) == 2 && parts > 1 && c->x_row_bytes == c->y_row_bytes;
+  if (paired) parts = (parts + 1) / 2;
   DetectArgs det = {};
   const bool detect = c->detect_timeout_ticks > 0;
   if (detect) {
@@ -870,8 +890,9 @@ static hipError_t launch_combine_t(eep_ctx* c, const void* y, const float* w, vo
     det.max_polls = c->detect_timeout_ticks * 8 + 1024;
   }
   return in_launches(T, max_blocks(64) / parts, [&](int64_t t0, int64_t n) {
-    const dim3 grid((unsigned)(n * parts)), block(64);
-    const uint32_t magic = part_magic(parts, n * parts);
+    const int64_t pieces = paired ? (n * parts + 7) / 8 * 8 : n * parts;
+    const dim3 grid((unsigned)(paired ? 2 * pieces : pieces)), block(64);
+    const uint32_t magic = part_magic(parts, pieces);
     const int64_t p0 = t0 * c->k;
     void* to = (char*)out + t0 * c->out_row_bytes;
     DetectArgs d = det;
@@ -885,7 +906,7 @@ static hipError_t launch_combine_t(eep_ctx* c, const void* y, const float* w, vo
   hipLaunchKernelGGL((detect ? k_combine<Y_BF16, OUT_BF16, K, true>                         \
                              : k_combine<Y_BF16, OUT_BF16, K, false>),                      \
                      grid, block, 0, st, c->row_of + p0, (const u32x4*)y, c->k, row_vecs,   \
-                     (uint32_t)parts, magic, w + p0, to, d);                                \
+                     (uint32_t)parts, magic, paired ? (int)n : 0, w + p0, to, d);           \
   break;
       EEP_COMBINE_K(case 8, 8)
       EEP_COMBINE_K(case 6, 6)

@@ -137,6 +137,29 @@ def test_dispatch_quant_with_infinities_and_nan(T):
         ctx.destroy()
 
 
+# row sizes of one part, of two, of an odd number and ending inside one, on both sides of the token
+# counts between which combine takes parts in pairs; small whole numbers, so every order is exact
+@pytest.mark.parametrize("vecs", [64, 65, 128, 129, 192, 360])
+@pytest.mark.parametrize("T", [508, 512, 516, 1020, 1024])
+@pytest.mark.parametrize("k,detect", [(2, False), (2, True), (3, False), (8, True)])
+def test_combine_row_shapes(T, vecs, k, detect):
+    H = vecs * 4
+    ctx, _, _ = routed_context(T, H, k, 5, x_dtype="f32", y_dtype="f32", out_dtype="f32")
+    try:
+        y = torch.randint(-99, 100, (T * k, H), device="cuda").float()
+        w = torch.randint(1, 9, (T, k), device="cuda").float()
+        out = torch.full((T + 1, H), 0.5, device="cuda")
+        if detect:
+            ctx.set_detection(200_000_000)
+            ctx.signal_experts_done()
+        ctx.combine(y, w, out, T)
+        row = torch.from_numpy(ctx.read_layout(T)["row_of"].reshape(T, k)).long().cuda()
+        want = ((w * (row >= 0)).unsqueeze(2) * y[row.clamp(min=0)]).sum(1)
+        assert torch.equal(out[:T], want) and (out[T] == 0.5).all()
+    finally:
+        ctx.destroy()
+
+
 def test_combine_of_more_wavefronts_than_one_launch_takes():
     """2^25 + 1 tokens whose rows end one vector past a part: 2^26 + 2 wavefronts of 64 lanes, more
     than the 2^32 lanes that a grid dimension may have."""
