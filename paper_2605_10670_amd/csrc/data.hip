@@ -278,34 +278,37 @@ constexpr int kPackMultiMinTokens = 8192;
 constexpr int kPackMultiMinWaves = 2048;  // two wavefronts per SIMD of the 256 CUs
 constexpr int kPackMultiMaxVecs = 56;     // 16-byte vectors a lane holds at once
 
+// Tokens per wavefront: several in very large batches (>= kPackMultiMinTokens) of whole-row
+// passes, as many as keep >= kPackMultiMinWaves wavefronts and <= kPackMultiMaxVecs vectors per lane.
+static int pack_tokens_per_wave(const PassShape& ps, int row_vecs, int T) {
+  int tpw = 1;
+  if (ps.exact && ps.u * 64 == row_vecs)
+    while (T >= kPackMultiMinTokens && tpw < 8 && T % (tpw * 2) == 0 &&
+           T / (tpw * 2) >= kPackMultiMinWaves && ps.u * tpw * 2 <= kPackMultiMaxVecs)
+      tpw *= 2;
+  return tpw;
+}
+
 static hipError_t launch_pack_payload(eep_ctx* c, const int32_t* rows, const void* x, void* recv_x,
                                       int T, hipStream_t st) {
   const int row_vecs = (int)(c->x_row_bytes / 16);
   const PassShape ps = pass_shape(row_vecs, pack_split(T), T, kPackVecs);
-  // Very large batches (>= kPackMultiMinTokens) of whole-row passes: several tokens per
-  // wavefront, as many as keep >= kPackMultiMinWaves wavefronts and <= kPackMultiMaxVecs
-  // vectors per lane.
-  if (ps.exact && ps.u * 64 == row_vecs) {
-    int tpw = 1;
-    while (T >= kPackMultiMinTokens && tpw < 8 && T % (tpw * 2) == 0 &&
-           T / (tpw * 2) >= kPackMultiMinWaves && ps.u * tpw * 2 <= kPackMultiMaxVecs)
-      tpw *= 2;
-    if (tpw > 1) {
-      switch (tpw * 16 + ps.u) {
+  const int tpw = pack_tokens_per_wave(ps, row_vecs, T);
+  if (tpw > 1) {
+    switch (tpw * 16 + ps.u) {
 #define EEP_PACK_MULTI(TPW, U) \
   case TPW * 16 + U: return launch_pack_multi_t<U, TPW>(c, rows, x, recv_x, T, st);
-        EEP_PACK_MULTI(2, 1) EEP_PACK_MULTI(2, 2) EEP_PACK_MULTI(2, 3) EEP_PACK_MULTI(2, 4)
-        EEP_PACK_MULTI(2, 5) EEP_PACK_MULTI(2, 6) EEP_PACK_MULTI(2, 7) EEP_PACK_MULTI(2, 8)
-        EEP_PACK_MULTI(2, 9) EEP_PACK_MULTI(2, 10) EEP_PACK_MULTI(2, 11) EEP_PACK_MULTI(2, 12)
-        EEP_PACK_MULTI(2, 13) EEP_PACK_MULTI(2, 14)
-        EEP_PACK_MULTI(4, 1) EEP_PACK_MULTI(4, 2) EEP_PACK_MULTI(4, 3) EEP_PACK_MULTI(4, 4)
-        EEP_PACK_MULTI(4, 5) EEP_PACK_MULTI(4, 6) EEP_PACK_MULTI(4, 7) EEP_PACK_MULTI(4, 8)
-        EEP_PACK_MULTI(4, 9) EEP_PACK_MULTI(4, 10) EEP_PACK_MULTI(4, 11) EEP_PACK_MULTI(4, 12)
-        EEP_PACK_MULTI(4, 13) EEP_PACK_MULTI(4, 14)
-        EEP_PACK_MULTI(8, 1) EEP_PACK_MULTI(8, 2) EEP_PACK_MULTI(8, 3) EEP_PACK_MULTI(8, 4)
-        EEP_PACK_MULTI(8, 5) EEP_PACK_MULTI(8, 6) EEP_PACK_MULTI(8, 7)
+      EEP_PACK_MULTI(2, 1) EEP_PACK_MULTI(2, 2) EEP_PACK_MULTI(2, 3) EEP_PACK_MULTI(2, 4)
+      EEP_PACK_MULTI(2, 5) EEP_PACK_MULTI(2, 6) EEP_PACK_MULTI(2, 7) EEP_PACK_MULTI(2, 8)
+      EEP_PACK_MULTI(2, 9) EEP_PACK_MULTI(2, 10) EEP_PACK_MULTI(2, 11) EEP_PACK_MULTI(2, 12)
+      EEP_PACK_MULTI(2, 13) EEP_PACK_MULTI(2, 14)
+      EEP_PACK_MULTI(4, 1) EEP_PACK_MULTI(4, 2) EEP_PACK_MULTI(4, 3) EEP_PACK_MULTI(4, 4)
+      EEP_PACK_MULTI(4, 5) EEP_PACK_MULTI(4, 6) EEP_PACK_MULTI(4, 7) EEP_PACK_MULTI(4, 8)
+      EEP_PACK_MULTI(4, 9) EEP_PACK_MULTI(4, 10) EEP_PACK_MULTI(4, 11) EEP_PACK_MULTI(4, 12)
+      EEP_PACK_MULTI(4, 13) EEP_PACK_MULTI(4, 14)
+      EEP_PACK_MULTI(8, 1) EEP_PACK_MULTI(8, 2) EEP_PACK_MULTI(8, 3) EEP_PACK_MULTI(8, 4)
+      EEP_PACK_MULTI(8, 5) EEP_PACK_MULTI(8, 6) EEP_PACK_MULTI(8, 7)
 #undef EEP_PACK_MULTI
-      }
     }
   }
   switch (ps.u) {
@@ -767,13 +770,14 @@ __device__ __forceinline__ int row_if_arrived(const DetectArgs& d, int64_t pair0
 // 83.2 / 168 / 755 / 57.  Single-wavefront workgroups measured ~10 % faster than one workgroup
 // per token.
 //
-// `paired` > 0 (the number of tokens): the batch was packed in pieces of two parts, `parts` counts
-// such pieces, and the two wavefronts of piece m run on the XCD that wrote it (workgroups go to the
+// `paired` > 0 (the number of tokens): the batch was packed in pieces of two parts (batches of 512
+// to 1023 tokens; whole rows of 1 to 2 KiB in larger ones), `parts` counts such pieces, and the two wavefronts of piece m run on the XCD that wrote it (workgroups go to the
 // 8 XCDs in turn, pack's m-th to m mod 8): 16 workgroups take pieces 8g .. 8g + 7, first their first
 // parts and then their second.  Measured (identity experts, one set of buffers, whole steps of T = 512 /
 // 768 / 992 tokens): 2048 channels 20.6 / 26.6 / 29.1 us without, 15.4 / 19.0 / 22.1 with; 4096 channels
-// 28.0 / 32.1 / 35.7 and 20.5 / 28.5 / 33.5; 7168 channels 32.6 / 42.4 / 51.0 and 29.6 / 40.9 / 49.7; with a
-// scaling stage between, where nothing can meet, within 1 % either way.
+// 28.0 / 32.1 / 35.7 and 20.5 / 28.5 / 33.5; 7168 channels 32.6 / 42.4 / 51.0 and 29.6 / 40.9 / 49.7;
+// 1024 channels, T = 1024 / 2048: 22.0 / 29.2 and 17.0 / 22.9; with a scaling stage between, where
+// nothing can meet, within 1 % either way.
 //
 // DETECT: the wait for the ranks' signals is part of the kernel (DetectArgs above); row_of
 // is then not read-only, because dropped pairs are struck from it, and lane j keeps the row of
@@ -875,9 +879,11 @@ static hipError_t launch_combine_t(eep_ctx* c, const void* y, const float* w, vo
                                    hipStream_t st) {
   int row_vecs = (int)(c->y_row_bytes / 16);
   int parts = (row_vecs + 63) / 64;
-  // y may be the receive buffer only if its rows are of the same size
-  const bool paired = pack_split(T) == 2 && parts > 1 && c->x_row_bytes == c->y_row_bytes;
-  if (paired) parts = (parts + 1) / 2;
+  // (y can be the receive buffer only if its rows are of the same size)
+  const PassShape packed = pass_shape(row_vecs, pack_split(T), T, kPackVecs);
+  const bool paired = c->x_row_bytes == c->y_row_bytes && parts > 1 &&
+                      (parts + 1) / 2 == packed.parts && pack_tokens_per_wave(packed, row_vecs, T) == 1;
+  if (paired) parts = packed.parts;
   DetectArgs det = {};
   const bool detect = c->detect_timeout_ticks > 0;
   if (detect) {
