@@ -895,7 +895,9 @@ static hipError_t launch_combine_t(eep_ctx* c, const void* y, const float* w, vo
     det.timeout_ticks = c->detect_timeout_ticks;
     det.max_polls = c->detect_timeout_ticks * 8 + 1024;
   }
-  return in_launches(T, max_blocks(64) / parts, [&](int64_t t0, int64_t n) {
+  // (pairs are rounded up to 8 pieces of two wavefronts)
+  const int64_t most = paired ? (max_blocks(64) - 16) / (2 * parts) : max_blocks(64) / parts;
+  return in_launches(T, most, [&](int64_t t0, int64_t n) {
     const int64_t pieces = paired ? (n * parts + 7) / 8 * 8 : n * parts;
     const dim3 grid((unsigned)(paired ? 2 * pieces : pieces)), block(64);
     const uint32_t magic = part_magic(parts, pieces);
