@@ -20,13 +20,13 @@ typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
 
 // Workgroup index -> (token, part) without a division in front of the first load: n / d is the
 // high word of n * magic, magic = 2^32 / d rounded up, exact while n * d < 2^32 (the rounding
-// is at most d too much); a larger grid has magic 0 and divides.
+// is at most d too much).  Magic 0: one part, or a grid so large that it divides.
 static uint32_t part_magic(int parts, int64_t grid) {
   if (parts <= 1 || grid * parts >= ((int64_t)1 << 32)) return 0;
   return (uint32_t)((((uint64_t)1 << 32) + parts - 1) / parts);
 }
 __device__ __forceinline__ uint32_t token_of(uint32_t n, uint32_t parts, uint32_t magic) {
-  return magic != 0 ? __umulhi(n, magic) : n / parts;
+  return magic != 0 ? __umulhi(n, magic) : parts == 1 ? n : n / parts;
 }
 
 // ---------------------------------------------------------------------------
