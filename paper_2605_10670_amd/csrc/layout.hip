@@ -128,8 +128,9 @@ __device__ __forceinline__ RouteTables load_route_tables(int32_t* lds, const int
     for (int q = tid; q - lane < P; q += NT) {
       const int p = q < P ? l2p_list[q] : -1;
       if (q < P) rt.list[q] = p;
-      const int r = p >= 0 ? rank_of_slot(p, inv_S) : 0;
-      const uint64_t bits = __ballot(p >= 0 && ((mask[r >> 5] >> (r & 31)) & 1));
+      const bool slot = (unsigned)p < (unsigned)P;  // (past the last list a caller may leave anything)
+      const int r = slot ? rank_of_slot(p, inv_S) : 0;
+      const uint64_t bits = __ballot(slot && ((mask[r >> 5] >> (r & 31)) & 1));
       if (lane == 0) {
         rt.alive[(q >> 5)] = (uint32_t)bits;
         rt.alive[(q >> 5) + 1] = (uint32_t)(bits >> 32);

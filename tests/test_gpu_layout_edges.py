@@ -107,3 +107,25 @@ def test_layout_over_its_router_indices(oracle, T, k):
     want = oracle.step_layout(idx, p2l, active, E, R, S, S - 1, binding.SPREAD)
     for n in ("slot_of", "row_of", "src_of", "count", "offset", "cnt_src"):
         assert np.array_equal(out[n].cpu().numpy(), want[n].reshape(-1)), n
+
+
+@pytest.mark.parametrize("T,R", [(130, 65), (1300, 65), (128, 32)])
+def test_what_lies_behind_the_replica_lists_is_not_used(oracle, T, R):
+    """Lists shorter than the slot count (empty slots), with arbitrary values behind them."""
+    import torch
+    k, S, E = 4, 3, 90
+    p2l, active, idx = instance(T, k, R, S, E, seed=T + R)
+    p2l[R * S // 2:] = -1
+    off, lst = binding.host_replica_lists(p2l, E, S, S - 1)
+    n = int(off[E])
+    assert n < R * S
+    lst[n:] = np.resize(np.array([2**31 - 1, -2**31, R * S, 10**6, -7], np.int32), R * S - n)
+    sizes = dict(slot_of=T * k, row_of=T * k, src_of=T * k, count=R * S, offset=R * S + 1,
+                 rank_count=R, rank_offset=R + 1, cnt_src=R * R * S, status=4)
+    out = {name: torch.zeros(m, dtype=torch.int32, device="cuda") for name, m in sizes.items()}
+    binding.dispatch_layout_noalloc(R=R, S=S, E=E, k=k, policy=binding.SPREAD, topk_idx=gu.to_dev(idx),
+                                    active=gu.to_dev(active), l2p_off=gu.to_dev(off),
+                                    l2p_list=gu.to_dev(lst), out=out, T=T)
+    want = oracle.step_layout(idx, p2l, active, E, R, S, S - 1, binding.SPREAD)
+    for name in ("slot_of", "row_of", "src_of", "count", "offset", "cnt_src"):
+        assert np.array_equal(out[name].cpu().numpy(), want[name].reshape(-1)), name
