@@ -874,6 +874,7 @@ __global__ __launch_bounds__(kMapThreads) void k_dedup_count(
 template <int KC>
 __global__ __launch_bounds__(kMapThreads) void k_dedup_position(
     const int32_t* __restrict__ slot_of, const int32_t* __restrict__ row_of,
+    const int32_t* __restrict__ src_of, const int32_t* __restrict__ offset,
     const int32_t* __restrict__ status, const int32_t* __restrict__ dd_tile,
     int32_t* __restrict__ dd_row, int32_t* __restrict__ dd_dst, int32_t* __restrict__ dd_expand,
     int32_t* __restrict__ dd_count, int32_t* __restrict__ dd_offset,
@@ -917,7 +918,14 @@ __global__ __launch_bounds__(kMapThreads) void k_dedup_position(
       row_d = s_off[r] + s_pre[r] + dd_row[g0 + i];
       if (dd_dst[g0 + i] != 0) dst = row_d;
       const int row = row_of[g0 + i];
-      if (row >= 0) dd_expand[row] = row_d;  // (a row withdrawn by failure detection stays -1)
+      if (row >= 0) {
+        dd_expand[row] = row_d;
+      } else {
+        // withdrawn by failure detection since the layout: the slot's row that still names the
+        // pair as its source gets no row of this step's (what stands there is an earlier step's)
+        for (int q = offset[p]; q < offset[p + 1]; ++q)
+          if (src_of[q] == (int)g0 + i) dd_expand[q] = -1;
+      }
     }
     dd_row[g0 + i] = row_d;
     dd_dst[g0 + i] = dst;
@@ -953,7 +961,7 @@ hipError_t launch_dedup_layout(eep_ctx* c, int T, hipStream_t st) {
   size_t lds = sizeof(int32_t) * ((size_t)3 * c->R + 1);
   auto kern = k8 ? k_dedup_position<8> : k_dedup_position<0>;
   hipLaunchKernelGGL(kern, dim3(g.num_tiles), dim3(kMapThreads), lds, st, c->slot_of, c->row_of,
-                     c->status, c->dd_tile, c->dd_row, c->dd_dst, c->dd_expand, c->dd_count,
+                     c->src_of, c->offset, c->status, c->dd_tile, c->dd_row, c->dd_dst, c->dd_expand, c->dd_count,
                      c->dd_offset, c->dd_status, c->k, c->R, c->S, g.num_tiles, g.tokens_per_rank,
                      g.tiles_per_rank, g.tile_tokens);
   return hipGetLastError();

@@ -136,3 +136,32 @@ def test_dedup_call_order_and_refusals():
         assert ei.value.code == binding.ERR_INVALID_ARG
     finally:
         ctx.destroy()
+
+
+def test_rows_withdrawn_before_the_dedup_layout(oracle):
+    """Failure detection strikes pairs between the layout and the de-duplicated one: their rows must
+    not keep the source of an earlier, larger step."""
+    wl = _workload(R=8, T=512, k=6, sp=4, sr=1, H=64)
+    T, R, S, silent = 256, wl.R, wl.S, 3
+    ctx = gu.make_context(wl, strict=False)
+    try:
+        gu.apply_tables(ctx, wl.p2l, wl.active)
+        dev = gu.DeviceStep(ctx, wl)
+        dev.layout()
+        ctx.dedup_layout(wl.T)
+        hold = np.zeros(R, np.int32)
+        hold[silent] = 1
+        ctx.debug_withhold_signal(hold)
+        ctx.set_detection(200_000)
+        ctx.dispatch_layout(dev.idx, T)
+        ctx.signal_experts_done()
+        ctx.combine(dev.recv, dev.w, dev.out, T)
+        ctx.dedup_layout(T)
+        lay = oracle.step_layout(wl.topk_idx[:T], wl.p2l, wl.active, wl.E, R, S, wl.S_prim, oracle.SPREAD)
+        want = oracle.dedup_layout(lay["slot_of"], lay["row_of"], R, S)["expand_of"]
+        gone = lay["row_of"][lay["slot_of"] // S == silent]
+        assert gone.size and (gone >= 0).all()
+        want[gone] = -1
+        assert np.array_equal(ctx.read_dedup(T)["expand_of"], want)
+    finally:
+        ctx.destroy()
