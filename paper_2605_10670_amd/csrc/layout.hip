@@ -9,8 +9,9 @@
 //
 // One to three launches, all tiny and latency-bound (the step's metadata is
 // < 1 MB), so the design goal is a short chain of dependent memory round trips,
-// not bandwidth.  Every kernel issues all its global loads before its first
-// wait.
+// not bandwidth.  Up to 64 ranks k_layout_small and k_map_count issue all their
+// global loads before their first wait; k_scan_position reads the count matrix
+// behind its first barrier, k_position the tile prefixes behind its scan.
 //   k_layout_small  (<= 512 tokens) everything in one launch, see there.
 //   k_map_count  one workgroup per tile of <= 128 tokens of ONE source rank.
 //                Placement CSR, active mask and the tile's router indices are

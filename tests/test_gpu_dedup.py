@@ -30,7 +30,7 @@ def _workload(R, T, k, sp, sr, H, failed=(), seed=0, dtype="bf16", masked=False)
 CASES = [
     dict(R=32, T=4096, k=8, sp=8, sr=1, H=256, failed=(13,)),            # decode shape, one failed rank
     dict(R=4, T=512, k=8, sp=4, sr=1, H=512, masked=True),               # 4 ranks, top-8: heavy sharing
-    dict(R=8, T=64, k=6, sp=2, sr=2, H=64, failed=(2, 5)),               # single-workgroup layout path
+    dict(R=8, T=64, k=6, sp=2, sr=2, H=64, failed=(2, 5)),               # one-launch layout path
     dict(R=32, T=16384, k=8, sp=8, sr=1, H=64, failed=(7, 20)),          # 128 tiles
     dict(R=2, T=600, k=2, sp=1, sr=3, H=8, dtype="f32"),                 # more replicas than experts
     dict(R=1, T=77, k=4, sp=8, sr=0, H=1024),                            # one rank: one row per token

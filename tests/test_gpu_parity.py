@@ -124,7 +124,7 @@ def test_many_tiles_and_odd_rank_counts(oracle, R, T):
     assert got["N"] == T * k
 
 
-@pytest.mark.parametrize("T", [96, 256])   # single-workgroup layout / tiled layout
+@pytest.mark.parametrize("T", [96, 256, 1024])   # one launch, one and two pairs a thread / tiled layout
 def test_masked_repeated_and_out_of_range_indices(oracle, T):
     wl = synth.decode(T=T, H=256)
     rng = np.random.default_rng(5)
@@ -164,10 +164,10 @@ def test_dtype_and_topk_matrix(oracle, dtypes, k):
 @pytest.mark.parametrize("shape", [
     dict(R=128, sp=2, sr=1, k=4, T=128 * 16, H=256, xd="bf16"),    # P=384 slots, many ranks
     dict(R=8, sp=8, sr=2, k=32, T=8 * 128, H=128, xd="bf16"),      # k=32: tile pairs > fused limit
-    dict(R=4, sp=4, sr=1, k=3, T=4 * 50, H=8192, xd="bf16"),       # 16 KiB rows, small batch: split in 2 KiB pieces
+    dict(R=4, sp=4, sr=1, k=3, T=4 * 50, H=8192, xd="bf16"),       # 16 KiB rows, small batch: split in 1 KiB pieces
     dict(R=4, sp=4, sr=1, k=3, T=4 * 300, H=8192, xd="bf16"),      # 16 KiB rows, large batch: two passes per wavefront
     dict(R=4, sp=4, sr=1, k=3, T=4 * 300, H=6656, xd="bf16"),      # 13 vectors per lane, one pass
-    dict(R=4, sp=4, sr=1, k=3, T=4 * 40, H=6656, xd="bf16"),       # 13 is prime: small batch split into single passes of 13
+    dict(R=4, sp=4, sr=1, k=3, T=4 * 40, H=6656, xd="bf16"),       # 13 vectors per lane, small batch: 13 pieces of 1 KiB
     dict(R=4, sp=4, sr=1, k=5, T=4 * 7, H=5000, xd="f32"),         # 20000-byte fp32 rows, ragged parts
     dict(R=2, sp=1, sr=3, k=2, T=2 * 300, H=8, xd="bf16"),         # 16-byte rows, more replicas than experts
     dict(R=4, sp=2, sr=1, k=4, T=4 * 33, H=4608, xd="bf16"),       # 9 vectors per lane (pass width 9)
@@ -751,11 +751,11 @@ def test_one_context_many_batch_sizes_in_a_row(oracle):
                                           (4, 128, 2, ()),
                                           (8, 40, 20, (2, 5)), (2, 128, 8, ()), (64, 128, 8, (0, 63)),
                                           (16, 32, 32, (7,)), (1, 128, 8, ())])
-def test_small_batches_around_the_single_workgroup_limit(oracle, policy, R, T, k, failed):
-    """Batches of at most 192 tokens and 1536 pairs are laid out by one workgroup in one
-    launch; just above either limit the tiled path runs.  Both must give the oracle's
-    layout: rank boundaries inside a bitmap word, k up to 32, failed first and last
-    ranks, one rank only."""
+def test_small_batches_laid_out_in_one_launch(oracle, policy, R, T, k, failed):
+    """Batches of at most 512 tokens and 4096 pairs are laid out in one launch.  Inside that range,
+    around the pairs that one workgroup takes in one and in two rounds (1024, 2048), the layout
+    must be the oracle's: rank boundaries inside a bitmap word, k up to 32, failed first and last
+    ranks, one rank only.  (The limits themselves: test_gpu_layout_edges.)"""
     rng = np.random.default_rng(1000 + R * 7 + T + k)
     sr, H = 2, 128
     sp = -(-max(R * 4, k) // R)

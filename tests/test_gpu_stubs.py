@@ -137,6 +137,37 @@ def test_dispatch_quant_with_infinities_and_nan(T):
         ctx.destroy()
 
 
+# more pairs than the eight row indices that a split wavefront fetches at once: one and two past
+# them, two and four sets; pieces of one vector per lane (below 512 tokens), of two (below 1024)
+# and whole rows, with and without a remainder; pairs without a row in every set
+@pytest.mark.parametrize("k", [8, 9, 10, 16, 17, 32])
+@pytest.mark.parametrize("T,vecs", [(4, 128), (508, 192), (508, 360), (512, 256), (1020, 200), (1020, 449),
+                                    (1024, 200)])
+def test_pack_of_many_pairs(T, vecs, k):
+    R, S, H = 4, 10, vecs * 4
+    ctx = binding.Context(num_ranks=R, slots_per_rank=S, primary_slots=S, num_logical=R * S,
+                          max_tokens=T, topk=k, hidden=H, x_dtype="f32", y_dtype="f32", out_dtype="f32")
+    try:
+        ctx.update_placement(synth.preferred_placement(R, S, 0))
+        rng = np.random.default_rng(T + vecs + k)
+        idx = np.argsort(rng.random((T, R * S)), axis=1)[:, :k].astype(np.int32)
+        idx[::2, 5] = -1
+        idx[1::3, k - 1] = -1
+        idx[::4, min(8, k - 1)] = -1
+        idx[T - 1] = -1
+        ctx.dispatch_layout(gu.to_dev(idx), T)
+        x = torch.randint(-2**31, 2**31 - 1, (T, H), dtype=torch.int32, device="cuda")
+        recv = torch.full((T * k, H), 77, dtype=torch.int32, device="cuda")
+        ctx.dispatch(x, recv, T)
+        lay = ctx.read_layout(T)
+        N = lay["N"]
+        assert N == (idx >= 0).sum()
+        tok = torch.from_numpy(lay["src_of"][:N] // k).long().cuda()
+        assert torch.equal(recv[:N], x[tok]) and (recv[N:] == 77).all()
+    finally:
+        ctx.destroy()
+
+
 # row sizes of one part, of two, of an odd number and ending inside one, on both sides of the token
 # counts between which combine takes parts in pairs; small whole numbers, so every order is exact
 @pytest.mark.parametrize("vecs", [64, 65, 128, 129, 192, 360])

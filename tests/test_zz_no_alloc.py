@@ -41,7 +41,7 @@ def _workload(T, failed, seed_offset):
 
 # T = 16384: 128 tiles, the three-launch path (tile prefixes in the scratch);
 # T = 4096: 32 tiles, the fused two-launch path; T = 1024: 32 tiles of 32 tokens;
-# T = 64: the single-workgroup path (no scratch besides the step counter).
+# T = 64: the one-launch path, one workgroup (no scratch besides the step counter).
 @pytest.mark.parametrize("sizes", [(16384, 4096, 64), (4096, 1024), (8192, 16384, 2048)])
 @pytest.mark.parametrize("policy", [binding.SPREAD, binding.FIRST_LIVE])
 def test_noalloc_layout_equals_the_context_entry_point(oracle, sizes, policy):
