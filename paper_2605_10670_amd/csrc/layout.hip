@@ -523,7 +523,7 @@ __global__ __launch_bounds__(kFusedThreads) void k_scan_position(
 // which the tiled path, where each pair is mapped once, is as fast.  The launch
 // decides by the number of contexts; a launch captured while there was one is
 // overruled by the word behind the membership version, which says that there are more
-// (0.05 to 0.1 us of the figures above).
+// (up to 0.1 us of the figures above).
 // ---------------------------------------------------------------------------
 constexpr int kSmallBlocks = 8;
 constexpr int kSmallTokens = 512;
@@ -599,7 +599,10 @@ __global__ __launch_bounds__(kMapThreads) void k_layout_small(
     my_e[u] = i < npairs ? topk_idx[i] : -1;
   }
   const int version = blockIdx.x == 0 && tid == 0 ? *tbl_version + *mem_version : 0;
-  const int several = mem_version[1];  // contexts of the instance: the first workgroup does it all
+  // several contexts in the instance: the first workgroup does it all.  (A vector load: a scalar one
+  // would be waited for together with every kernel argument.)
+  const int several_v =
+      __hip_atomic_load(&mem_version[1], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
   for (int i = tid; i < P * (stride + 1); i += kMapThreads) s_count[i] = 0;  // and s_bm
   if (tid < 2) s_drop[tid] = 0;
   const RouteTables rt =
@@ -611,7 +614,7 @@ __global__ __launch_bounds__(kMapThreads) void k_layout_small(
   }
   // the pairs [own_lo, own_hi) whose results this workgroup writes, and as which of how many; with
   // `solo` the first one's are all, the others go along and write nothing
-  const bool solo = several != 0 || (T_k & kSoloBit) != 0;
+  const bool solo = __builtin_amdgcn_readfirstlane(several_v) != 0 || (T_k & kSoloBit) != 0;
   const int blocks = solo ? 1 : kSmallBlocks, block = solo && blockIdx.x > 0 ? R : blockIdx.x;
   const int share = ((npairs + kSmallBlocks - 1) / kSmallBlocks + 63) & ~63;
   const int own_lo = solo ? (blockIdx.x > 0 ? npairs : 0) : blockIdx.x * share;
