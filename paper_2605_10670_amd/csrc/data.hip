@@ -362,10 +362,13 @@ hipError_t launch_pack_rows(eep_ctx* c, const int32_t* rows, const void* x, void
 // flight (T = 512, 5760-byte rows, whole step: 38.8 us, with 2 40.1); from there on
 // 2, which keeps the running copies closer to address order (T = 2048, 14 KiB rows:
 // 158.5 us, with 4 160, 7 166.7, 14 168.8, and with each pass in a wavefront of its
-// own 172).  Few rows are split like a small batch in pack.
+// own 172).  Rows beyond 16 KiB are many such passes one after the other, and there 8
+// are better (32 KiB rows, T = 1024 / 2048 / 4096: 208 / 398 / 810 us, with 2 222 / 403 /
+// 820, 4 211 / 401 / 815, 7 with a bounds check 216 / 401 / 813).  Few rows are split like a
+// small batch in pack.
 // ---------------------------------------------------------------------------
-constexpr int kExpandVecs = 7, kExpandManyVecs = 2;
-constexpr int kExpandManyRows = 8192;
+constexpr int kExpandVecs = 7, kExpandManyVecs = 2, kExpandWideVecs = 8;
+constexpr int kExpandManyRows = 8192, kExpandWideRow = 16384 / 16;
 
 template <int U, bool EXACT>
 __global__ __launch_bounds__(64) void k_expand(const int32_t* __restrict__ expand_of,
@@ -397,7 +400,9 @@ hipError_t launch_expand(eep_ctx* c, const void* recv_dedup, void* recv_x, int T
   if (rows == 0) return hipSuccess;
   const int row_vecs = (int)(c->x_row_bytes / 16);
   const PassShape ps = pass_shape(row_vecs, rows < kExpandSplitBelow ? 2 : 0, rows,
-                                  rows < kExpandManyRows ? kExpandVecs : kExpandManyVecs);
+                                  rows < kExpandManyRows       ? kExpandVecs
+                                  : row_vecs <= kExpandWideRow ? kExpandManyVecs
+                                                               : kExpandWideVecs);
   return in_launches(rows, max_blocks(64) / ps.parts, [&](int64_t r0, int64_t n) {
     const uint32_t magic = part_magic(ps.parts, n * ps.parts);
     u32x4* to = (u32x4*)recv_x + r0 * row_vecs;
@@ -408,7 +413,7 @@ hipError_t launch_expand(eep_ctx* c, const void* recv_dedup, void* recv_x, int T
                        dim3((unsigned)(n * ps.parts)), dim3(64), 0, st, c->dd_expand + r0,     \
                        (const u32x4*)recv_dedup, row_vecs, (uint32_t)ps.parts, magic, to);     \
     return hipGetLastError();
-      EEP_EXPAND_CASE(7) EEP_EXPAND_CASE(6) EEP_EXPAND_CASE(5) EEP_EXPAND_CASE(4)
+      EEP_EXPAND_CASE(8) EEP_EXPAND_CASE(7) EEP_EXPAND_CASE(6) EEP_EXPAND_CASE(5) EEP_EXPAND_CASE(4)
       EEP_EXPAND_CASE(3) EEP_EXPAND_CASE(2) EEP_EXPAND_CASE(1)
 #undef EEP_EXPAND_CASE
     }

@@ -55,8 +55,10 @@ def test_dequant_stand_in(oracle, T, H, group, masked):
 
 # row sizes around whole passes: 1 vector, one short of / exactly / one past 64 and 128 vectors, a
 # prime number of 64-vector sets above 14, an odd remainder; small batches split rows over
-# wavefronts, 1024 tokens and more do not; 8192 rows change the expansion's width
-@pytest.mark.parametrize("vecs", [1, 63, 64, 65, 128, 129, 360, 15 * 64, 17 * 64, 17 * 64 - 3])
+# wavefronts, 1024 tokens and more do not; 8192 rows change the expansion's width, and so do more
+# than 1024 vectors (16 KiB)
+@pytest.mark.parametrize("vecs", [1, 63, 64, 65, 128, 129, 360, 15 * 64, 1024, 17 * 64, 17 * 64 - 3,
+                                  24 * 64])
 @pytest.mark.parametrize("T", [4, 1020, 1024])
 def test_pack_and_expand_row_shapes(T, vecs):
     H, k = vecs * 4, 8                      # fp32 rows: 4 channels per 16-byte vector
