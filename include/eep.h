@@ -137,6 +137,22 @@ int eep_create_with_workspace(const eep_config* cfg, void* workspace, int64_t wo
  * Attached contexts must be destroyed before the context that eep_create made. */
 int eep_create_attached(const eep_config* cfg, eep_ctx* parent, eep_ctx** out);
 
+/* A second staging set of the same layer (Sec. 4.1: two staging regions overlap the
+ * communication of one round with the computation of another): a context that
+ * shares `of`'s membership AND placement tables (an update through either acts on the
+ * one set) and has layout arrays of its own.  Pair each set with receive buffers.
+ * eep_staging_fork lets side_stream wait for what is queued on `stream` and queues
+ * eep_dispatch_layout and eep_dispatch of the next step there (same arguments and
+ * errors); the caller queues the expert stage and combine of the current step, on the
+ * other set, on `stream`; eep_staging_join lets `stream` wait for side_stream.  Both
+ * may be captured.  A set is refilled only after its step was combined.  The mask may
+ * change at any step boundary, a placement update needs the pipeline drained.
+ * Waits for the device, like eep_create_attached. */
+int eep_create_staging(eep_ctx* of, eep_ctx** out);
+int eep_staging_fork(eep_ctx* ctx, const int32_t* topk_idx, const void* x, const float* x_scale,
+                     void* recv_x, float* recv_scale, int32_t T, void* stream, void* side_stream);
+int eep_staging_join(eep_ctx* ctx, void* stream, void* side_stream);
+
 /* Ends the lifetime of the stable pointers (Fig. 4, Fig. 8): graphs captured
  * with this context must not be replayed afterwards.  Waits for the device,
  * frees everything the context owns.  NULL is OK.
@@ -270,8 +286,8 @@ int eep_combine(eep_ctx* ctx, const void* y, const float* topk_w, void* out, int
                 void* stream);
 
 /* Stand-in for the expert kernels that sit between dispatch and combine in the
- * captured graph (Fig. 4).  Processes rows [0, N) only; the grid is sized for
- * T*k rows and reads N from device memory.
+ * captured graph (Fig. 4).  Computes and writes rows [0, N) only; the grid is sized
+ * for T*k rows, N is found in device memory, and any of the T*k rows may be read.
  *   IDENTITY: copies recv_x to y (callers may instead alias y = recv_x);
  *   SCALE:    expert_scale is device float[E]; x_dtype must equal y_dtype
  *             (F32 or BF16); product computed in fp32;

@@ -41,8 +41,13 @@ __device__ __forceinline__ uint32_t token_of(uint32_t n, uint32_t parts, uint32_
 // ---------------------------------------------------------------------------
 constexpr int kPackVecs = 14;
 constexpr int kRowBatch = 8;  // row indices fetched together
-constexpr int kPackSplitBelow = 1024;  // batches below this many tokens split a row over wavefronts
-constexpr int kPackNarrowBelow = 512;  // ... and below this many in pieces as narrow as combine's
+// Batches below this many tokens split a row over wavefronts, and below the second many in pieces
+// as narrow as combine's.  Counts of tokens, not of bytes: where they were checked (rows of 0.5, 1,
+// 2, 4, 5.6, 8, 14 and 16 KiB and fp32 rows of 8 and 32 KiB, T = 32 to 4096, identity and scaling
+// experts) no step is more than 1 % slower than with 2 KiB pieces below 1024 tokens and 2 KiB parts
+// in combine, and most are faster.
+constexpr int kPackSplitBelow = 1024;
+constexpr int kPackNarrowBelow = 512;
 constexpr int kExpandSplitBelow = 4096;  // the same for rows that are read and written once
 
 // The data registers of a store of more than 8 bytes may not be rewritten by the next two
@@ -478,8 +483,9 @@ __device__ inline uint32_t f32_to_e4m3(float f) {
 // Dev. 34, 1990) while nothing under- or overflows; v_cvt_pk_fp8_f32 rounds it.
 // Compared with the division and f32_to_e4m3 for EVERY pair of a finite bf16
 // maximum with its scale in [2^-100, 2^100] and a bf16 x up to it, both signs: no
-// difference.  Groups outside (infinities and NaN among them) take the
-// division.
+// code differs.  (Of the 444,868,577 pairs of one sign 1,023,886 have another quotient, all with
+// |x| < 2^-43, from residuals or quotients that underflow; it rounds to the same code.)  Groups
+// outside (infinities and NaN among them) take the division.
 // Measured, whole step with the dequantising stand-in (7168 channels, T = 32 / 256 / 4096):
 // 28.1 / 40.5 / 248 us before, 15.7 / 29.8 / 254 split by size but with divisions and with the scale
 // stores among the rows, 14.4 / 28.1 / 242.5 now.
@@ -776,13 +782,17 @@ __device__ __forceinline__ int row_if_arrived(const DetectArgs& d, int64_t pair0
 // per token.
 //
 // `paired` > 0 (the number of tokens): the batch was packed in pieces of two parts (batches of 512
-// to 1023 tokens; whole rows of 1 to 2 KiB in larger ones), `parts` counts such pieces, and the two wavefronts of piece m run on the XCD that wrote it (workgroups go to the
-// 8 XCDs in turn, pack's m-th to m mod 8): 16 workgroups take pieces 8g .. 8g + 7, first their first
-// parts and then their second.  Measured (identity experts, one set of buffers, whole steps of T = 512 /
-// 768 / 992 tokens): 2048 channels 20.6 / 26.6 / 29.1 us without, 15.4 / 19.0 / 22.1 with; 4096 channels
+// to 1023 tokens; whole rows of 1 to 2 KiB in larger ones), `parts` counts such pieces, and the
+// two wavefronts of piece m run on the XCD that wrote it (workgroups go to the 8 XCDs in turn,
+// pack's m-th to m mod 8): 16 workgroups take pieces 8g .. 8g + 7, first their first parts and
+// then their second.  Measured (identity experts, one set of buffers, whole steps of T = 512 / 768 /
+// 992 tokens): 2048 channels 20.6 / 26.6 / 29.1 us without, 15.4 / 19.0 / 22.1 with; 4096 channels
 // 28.0 / 32.1 / 35.7 and 20.5 / 28.5 / 33.5; 7168 channels 32.6 / 42.4 / 51.0 and 29.6 / 40.9 / 49.7;
 // 1024 channels, T = 1024 / 2048: 22.0 / 29.2 and 17.0 / 22.9; with a scaling stage between, where
 // nothing can meet, within 1 % either way.
+//
+// Other top-k loads one row at a time: in batches of 4 to 8 with uniform branches top-10 took 13.75 us
+// instead of 13.9 (T = 32) and 126.6 instead of 126.0 (T = 4096, 4096 channels), top-3 within 0.3 %.
 //
 // DETECT: the wait for the ranks' signals is part of the kernel (DetectArgs above); row_of
 // is then not read-only, because dropped pairs are struck from it, and lane j keeps the row of
@@ -944,10 +954,10 @@ hipError_t launch_combine(eep_ctx* c, const void* y, const float* w, void* out, 
 }
 
 // ---------------------------------------------------------------------------
-// expert stand-ins (outside the measured path): one workgroup per receive row,
-// rows >= N (read from device memory) are skipped.  Same streaming access
-// policy as pack and combine: read-once loads are non-temporal, stores write
-// through.
+// expert stand-ins: what a caller's expert kernels do between dispatch and combine, no
+// part of either.  Copy and scale take a workgroup per receive row, with the loads and
+// stores of pack (non-temporal, write-through); rows >= N are skipped.  The
+// dequantising one is a flat stream of its own, see there.
 // ---------------------------------------------------------------------------
 __global__ __launch_bounds__(256) void k_stub_copy(const u32x4* __restrict__ recv,
                                                    u32x4* __restrict__ y,
