@@ -208,6 +208,8 @@ def test_combine_of_more_wavefronts_than_one_launch_takes():
         assert torch.equal(out, y)
     finally:
         ctx.destroy()
+        y = out = None
+        torch.cuda.empty_cache()            # (70 GB)
 
 
 def test_stand_ins_of_more_rows_than_one_launch_takes():
