@@ -79,3 +79,50 @@ def test_captured_layout_outlives_a_change_of_the_number_of_contexts(oracle, T, 
         if other is not None:
             other.destroy()
         ctx.destroy()
+
+
+@pytest.mark.gpu
+def test_attaching_leaves_another_threads_capture_alone():
+    """Attaching waits for the device; it may neither fail nor spoil a capture because an unrelated
+    context is being captured meanwhile."""
+    import threading
+    import torch
+    import gpu_util as gu
+    shape = dict(num_ranks=4, slots_per_rank=2, primary_slots=2, num_logical=8, max_tokens=64, topk=2,
+                 hidden=64)
+    a, b = binding.Context(**shape), binding.Context(**shape)
+    p2l = np.arange(8, dtype=np.int32)
+    idx = gu.to_dev(np.tile(np.array([0, 1], np.int32), (64, 1)))
+    for ctx in (a, b):
+        ctx.update_placement(p2l)
+        ctx.dispatch_layout(idx, 64)
+    torch.cuda.synchronize()
+    capturing, attached, errors = threading.Event(), threading.Event(), []
+
+    def capture():
+        try:
+            stream = torch.cuda.Stream()
+            b.graph_begin(stream)
+            b.dispatch_layout(idx, 64, stream)
+            capturing.set()
+            attached.wait(60)
+            b.dispatch_layout(idx, 64, stream)
+            graph = b.graph_end(stream)
+            graph.launch(stream)
+            stream.synchronize()
+            graph.destroy()
+        except Exception as exc:
+            errors.append(repr(exc))
+            capturing.set()
+
+    thread = threading.Thread(target=capture)
+    try:
+        thread.start()
+        assert capturing.wait(60)
+        others = [binding.Context(**shape, parent=a), a.staging()]
+    finally:
+        attached.set()
+        thread.join(60)
+    assert not errors, errors
+    for ctx in others + [b, a]:
+        ctx.destroy()
