@@ -430,13 +430,14 @@ int eep_host_uncovered_experts(int32_t P, int32_t E, int32_t S, const int32_t* p
                                const int32_t* active);
 /* How eep_dispatch_layout tiles T tokens of R source ranks:
  * out = {tokens per rank, tiles per rank, tokens per tile (<= 128), tiles}.
- * (Batches of at most 512 tokens and 4096 pairs are laid out in one launch
- * without tiles; the results are the same.) */
+ * (Batches of up to 16384 pairs are mostly laid out in one launch without
+ * these tiles; the results are the same.) */
 int eep_host_tiling(int32_t T, int32_t R, int32_t out[4]);
-/* Workgroups of that one launch for T tokens: 8 where the instance has one context,
+/* Workgroups of that one launch for small batches, which take a fixed number: for at
+ * most 512 tokens and 4096 pairs 8 where the instance has one context,
  * 1 where it has several (`several_contexts` != 0: the mask may change while the
  * layout runs) and in eep_dispatch_layout_noalloc, then for at most 384 tokens and
- * 3072 pairs; 0 where the batch is tiled.  Negative = eep_status. */
+ * 3072 pairs; 0 for all others, tiled or not.  Negative = eep_status. */
 int eep_host_layout_workgroups(int32_t R, int32_t S, int32_t E, int32_t k, int32_t T,
                                int32_t several_contexts);
 

@@ -14,7 +14,7 @@ int fail_hip(eep_ctx* c, hipError_t e) {
 }
 
 // Tells launches that were captured while the instance had one context how many it has now
-// (k_layout_small).  No layout of the instance may be running meanwhile.
+// (k_layout_once).  No layout of the instance may be running meanwhile.
 hipError_t set_shared_word(eep_membership* m, int32_t several) {
   // hipFree waits for the whole device.  (hipDeviceSynchronize would too, but fails, and spoils
   // the capture, while any other thread captures a graph.)

@@ -9,10 +9,10 @@
 //
 // One to three launches, all tiny and latency-bound (the step's metadata is
 // < 1 MB), so the design goal is a short chain of dependent memory round trips,
-// not bandwidth.  Up to 64 ranks k_layout_small and k_map_count issue all their
+// not bandwidth.  Up to 64 ranks k_layout_once and k_map_count issue all their
 // global loads before their first wait; k_scan_position reads the count matrix
 // behind its first barrier, k_position the tile prefixes behind its scan.
-//   k_layout_small  (<= 512 tokens) everything in one launch, see there.
+//   k_layout_once  (<= 16384 pairs) everything in one launch, see there.
 //   k_map_count  one workgroup per tile of <= 128 tokens of ONE source rank.
 //                Placement CSR, active mask and the tile's router indices are
 //                fetched with independent loads.  For every slot the kernel
@@ -29,8 +29,8 @@
 //                kernel.
 //   k_tile_prefix + k_position  (> 64 tiles) the tile prefixes are computed once
 //                by a few workgroups, then a wide grid computes the rows.
-// Measured (a layout in a graph of 40; 32 ranks x 9 slots, top-8): T = 1024 / 4096 / 16384 in
-// 7.8 / 8.5 / 13.0 us; 9.7 / 10.5 / 14.3 while the live replicas were compacted per expert in
+// Measured (a layout in a graph of 40; 32 ranks x 9 slots, top-8): T = 1024 / 4096 / 16384 in tiles
+// 7.7 / 8.4 / 13.0 us; 9.7 / 10.5 / 14.3 while the live replicas were compacted per expert in
 // LDS, the repeat check read LDS, counts were popcounts over the bitmaps, the scan took two
 // barriers and half of k_scan_position's threads loaded the whole matrix.
 #include "eep_internal.hpp"
@@ -76,8 +76,8 @@ struct RouteTables {
 // Bits are written 64 at a time; a pair whose expert's list starts at o <= P reads the words
 // o / 32 and o / 32 + 1, so two more words follow.
 __host__ __device__ inline int alive_words(int P) { return (P + 63) / 64 * 2 + 2; }
-__host__ __device__ inline int mask_words(int R) { return R > 64 ? (R + 31) / 32 : 0; }
-inline size_t route_table_ints(int E, int P, int R) {
+__host__ __device__ inline int mask_words(int R) { return (R + 31) / 32; }
+__host__ __device__ inline size_t route_table_ints(int E, int P, int R) {
   return (size_t)(E + 1) + P + alive_words(P) + mask_words(R);
 }
 
@@ -88,59 +88,67 @@ __device__ __forceinline__ int rank_of_slot(int p, float inv_S) {
   return (int)(((float)p + 0.5f) * inv_S);
 }
 
-// Fills the tables at `lds` (route_table_ints of it) with the whole workgroup of NT threads;
-// the caller's next barrier makes them readable.  For R > 64 the mask goes through LDS, which
-// takes one barrier here.
-template <int NT>
-__device__ __forceinline__ RouteTables load_route_tables(int32_t* lds, const int32_t* __restrict__ l2p_off,
-                                                const int32_t* __restrict__ l2p_list,
-                                                const int32_t* __restrict__ active, int E, int R,
-                                                int P, float inv_S) {
-  RouteTables rt;
-  rt.off = lds;
-  rt.list = rt.off + (E + 1);
-  rt.alive = (uint32_t*)(rt.list + P);
-  const int tid = threadIdx.x, lane = tid & 63;
-  if (R <= 64) {
-    const int a = lane < R ? active[lane] : 0;
-    const int p0 = tid < P ? l2p_list[tid] : -1;
-    for (int i = tid; i <= E; i += NT) rt.off[i] = l2p_off[i];
-    const uint64_t mask = __ballot(a != 0);
-    for (int q = tid; q - lane < P; q += NT) {  // whole wavefronts, for the ballot
-      const int p = q == tid ? p0 : q < P ? l2p_list[q] : -1;
-      if (q < P) rt.list[q] = p;
-      const uint64_t bits = __ballot(p >= 0 && ((mask >> (rank_of_slot(p, inv_S) & 63)) & 1));
-      if (lane == 0) {
-        rt.alive[(q >> 5)] = (uint32_t)bits;
-        rt.alive[(q >> 5) + 1] = (uint32_t)(bits >> 32);
-      }
-    }
-  } else {
-    uint32_t* mask = rt.alive + alive_words(P);
-    for (int r = tid; r - lane < R; r += NT) {
-      const uint64_t bits = __ballot(r < R && active[r] != 0);
-      if (lane == 0) {
-        mask[r >> 5] = (uint32_t)bits;
-        if ((r >> 5) + 1 < mask_words(R)) mask[(r >> 5) + 1] = (uint32_t)(bits >> 32);
-      }
-    }
-    for (int i = tid; i <= E; i += NT) rt.off[i] = l2p_off[i];
-    __syncthreads();
-    for (int q = tid; q - lane < P; q += NT) {
-      const int p = q < P ? l2p_list[q] : -1;
-      if (q < P) rt.list[q] = p;
-      const bool slot = (unsigned)p < (unsigned)P;  // (past the last list a caller may leave anything)
-      const int r = slot ? rank_of_slot(p, inv_S) : 0;
-      const uint64_t bits = __ballot(slot && ((mask[r >> 5] >> (r & 31)) & 1));
-      if (lane == 0) {
-        rt.alive[(q >> 5)] = (uint32_t)bits;
-        rt.alive[(q >> 5) + 1] = (uint32_t)(bits >> 32);
-      }
-    }
+// Fills the tables at `lds` (route_table_ints of it) with the whole workgroup of nt threads, in
+// two steps: `fetch` at the very start of a kernel, so that its loads are out before anything is
+// waited for, and `fill`; the caller's next barrier makes the tables readable.  LARGE: more than 64 ranks
+// (the mask goes through LDS, which takes one barrier here) or tables of more than nt words.
+inline bool large_tables(int E, int P, int R, int threads) { return R > 64 || P > threads || E >= threads; }
+template <bool LARGE>
+struct RouteTableLoad {
+  const int32_t *l2p_off, *l2p_list, *active;
+  int E, R, P, nt, a, p, o;
+  __device__ __forceinline__ void fetch() {
+    const int tid = threadIdx.x, lane = tid & 63;
+    a = active[lane < R ? lane : R - 1];
+    p = l2p_list[tid < P ? tid : P - 1];
+    o = l2p_off[tid < E ? tid : E];
   }
-  if (tid < 2) rt.alive[alive_words(P) - 1 - tid] = 0;
-  return rt;
-}
+  __device__ __forceinline__ RouteTables fill(int32_t* lds, float inv_S) const {
+    RouteTables rt;
+    rt.off = lds;
+    rt.list = rt.off + (E + 1);
+    rt.alive = (uint32_t*)(rt.list + P);
+    const int tid = threadIdx.x, lane = tid & 63;
+    if constexpr (!LARGE) {
+      if (tid <= E) rt.off[tid] = o;
+      const uint64_t mask = __ballot(lane < R && a != 0);
+      const bool slot = tid < P && p >= 0;
+      if (tid < P) rt.list[tid] = p;
+      const uint64_t bits = __ballot(slot && ((mask >> (rank_of_slot(p, inv_S) & 63)) & 1));
+      if (lane == 0 && tid < P) {
+        rt.alive[tid >> 5] = (uint32_t)bits;
+        rt.alive[(tid >> 5) + 1] = (uint32_t)(bits >> 32);
+      }
+    } else {
+      uint32_t* mask = rt.alive + alive_words(P);
+#pragma nounroll
+      for (int r = tid; r - lane < R; r += nt) {
+        const uint64_t bits = __ballot(r < R && active[r] != 0);
+        if (lane == 0) {
+          mask[r >> 5] = (uint32_t)bits;
+          if ((r >> 5) + 1 < mask_words(R)) mask[(r >> 5) + 1] = (uint32_t)(bits >> 32);
+        }
+      }
+#pragma nounroll
+      for (int i = tid; i <= E; i += nt) rt.off[i] = i == tid ? o : l2p_off[i];
+      __syncthreads();
+#pragma nounroll
+      for (int q = tid; q - lane < P; q += nt) {  // whole wavefronts, for the ballot
+        const int v = q == tid ? p : q < P ? l2p_list[q] : -1;
+        if (q < P) rt.list[q] = v;
+        const bool slot = q < P && (unsigned)v < (unsigned)P;  // (past the last list a caller may leave anything)
+        const int r = slot ? rank_of_slot(v, inv_S) : 0;
+        const uint64_t bits = __ballot(slot && ((mask[r >> 5] >> (r & 31)) & 1));
+        if (lane == 0) {
+          rt.alive[(q >> 5)] = (uint32_t)bits;
+          rt.alive[(q >> 5) + 1] = (uint32_t)(bits >> 32);
+        }
+      }
+    }
+    if (tid < 2) rt.alive[alive_words(P) - 1 - tid] = 0;
+    return rt;
+  }
+};
 
 // The live replica that serves token t's pair with expert e (in [0, E)), or -1.
 __device__ __forceinline__ int pick_slot(const RouteTables& rt, int e, int t, int policy) {
@@ -177,18 +185,48 @@ __device__ __forceinline__ bool earlier_lane_equals(int e, int j) {
   const int v = __builtin_amdgcn_update_dpp(-1, e, 0x110 + SHR, 0xf, 0xf, false);  // row_shr:SHR
   return j >= SHR && v == e;
 }
+// x ^ the value CTRL away, lane to lane inside groups of 8
+template <int CTRL>
+__device__ __forceinline__ uint32_t lane_xor(int from, int e) {
+  return (uint32_t)(__builtin_amdgcn_update_dpp(0, from, CTRL, 0xf, 0xf, false) ^ e);
+}
 template <int KC>
 __device__ __forceinline__ bool repeats_earlier(int e, int j, const int32_t* token_idx) {
   bool r = false;
   if constexpr (KC == 0) {
-    for (int jj = 0; jj < j; ++jj) r |= token_idx[jj] == e;
-  } else {
-    static_assert(KC == 1 || KC == 2 || KC == 4 || KC == 8, "pairs of a token share a DPP row");
-    if constexpr (KC > 1) r |= earlier_lane_equals<1>(e, j);
-    if constexpr (KC > 2) r |= earlier_lane_equals<2>(e, j) | earlier_lane_equals<3>(e, j);
-    if constexpr (KC > 4)
-      r |= earlier_lane_equals<4>(e, j) | earlier_lane_equals<5>(e, j) |
-           earlier_lane_equals<6>(e, j) | earlier_lane_equals<7>(e, j);
+    // four at a time, so that their latencies overlap (up to three words behind the token's are read)
+#pragma nounroll
+    for (int jj = 0; jj < j; jj += 4) {
+      int v[4];
+#pragma unroll
+      for (int u = 0; u < 4; ++u) v[u] = token_idx[jj + u];
+#pragma unroll
+      for (int u = 0; u < 4; ++u) r |= jj + u < j && v[u] == e;
+    }
+  } else if constexpr (KC > 1) {
+    static_assert(KC == 2 || KC == 4 || KC == 8, "pairs of a token share a DPP row");
+    // first whether any two of the token's lanes are equal (quad_perm 1032, 2301, 3210; the other
+    // quad by way of row_half_mirror), which is rarely so
+    uint32_t least = lane_xor<0xB1>(e, e);
+    if constexpr (KC > 2) least = min(least, min(lane_xor<0x4E>(e, e), lane_xor<0x1B>(e, e)));
+    if constexpr (KC > 4) {
+      const int m = __builtin_amdgcn_update_dpp(0, e, 0x141, 0xf, 0xf, false);
+      least = min(least, min((uint32_t)(m ^ e), lane_xor<0xB1>(m, e)));
+      least = min(least, min(lane_xor<0x4E>(m, e), lane_xor<0x1B>(m, e)));
+    }
+    if (__builtin_expect(__any(least == 0), 0)) {
+      r = earlier_lane_equals<1>(e, j);
+      if constexpr (KC > 2) {
+        r |= earlier_lane_equals<2>(e, j);
+        r |= earlier_lane_equals<3>(e, j);
+      }
+      if constexpr (KC > 4) {
+        r |= earlier_lane_equals<4>(e, j);
+        r |= earlier_lane_equals<5>(e, j);
+        r |= earlier_lane_equals<6>(e, j);
+        r |= earlier_lane_equals<7>(e, j);
+      }
+    }
   }
   return r;
 }
@@ -203,14 +241,13 @@ constexpr int kMaxPairsPerThread = kTileTokens * kMaxTopk / kMapThreads;
 // Maps this thread's pairs tid, tid + NT, ... of a batch of `npairs` (router indices at `idx`,
 // first token t0): slots to slot[] (-1: not routed), token bits to s_bm
 // ([P][stride], zeroed), counts to s_count (zeroed), dropped pairs to s_drop {uncovered, masked}
-// (zeroed).  my_e holds the indices already loaded; s_idx the same in LDS when KC == 0.  Slots of
-// the pairs [own_lo, own_hi) are written to slot_of.
+// (zeroed).  my_e holds the indices already loaded; s_idx the same in LDS when KC == 0.
 template <int KC, int NT, int U>
 __device__ __forceinline__ void map_pairs(const RouteTables& rt, const int (&my_e)[U],
                                           const int32_t* s_idx, int (&slot)[U], uint32_t* s_bm,
                                           int stride, int32_t* s_count, int32_t* s_drop, int npairs,
-                                          int k, int E, int t0, int policy, int own_lo,
-                                          int own_hi, int32_t* __restrict__ slot_of) {
+                                          int k, int E, int t0, int policy,
+                                          int32_t* __restrict__ slot_of) {
   const int wave0 = __builtin_amdgcn_readfirstlane(threadIdx.x & ~63);
 #pragma unroll
   for (int u = 0; u < U; ++u) {
@@ -234,7 +271,7 @@ __device__ __forceinline__ void map_pairs(const RouteTables& rt, const int (&my_
         }
       }
       slot[u] = p;
-      if (i >= own_lo && i < own_hi) slot_of[i] = p;
+      slot_of[i] = p;
     }
   }
 }
@@ -262,7 +299,7 @@ inline size_t map_lds_ints(int E, int P, int R, int tile_tokens, int k) {
   return route_table_ints(E, P, R) + P + (size_t)P * kBitmapWords + (size_t)tile_tokens * k;
 }
 
-template <int KC, int U>  // KC = compile-time k (power of two) or 0 for any k
+template <int KC, int U, bool LARGE>  // KC = compile-time k (power of two) or 0 for any k
 __global__ __launch_bounds__(kMapThreads) void k_map_count(
     const int32_t* __restrict__ topk_idx, const int32_t* __restrict__ l2p_off,
     const int32_t* __restrict__ l2p_list, const int32_t* __restrict__ active, int k_rt,
@@ -290,10 +327,12 @@ __global__ __launch_bounds__(kMapThreads) void k_map_count(
     const int i = tid + u * kMapThreads;
     my_e[u] = i < npairs ? topk_idx[g0 + i] : -1;
   }
+  RouteTableLoad<LARGE> tables = {l2p_off, l2p_list, active, E, R, P, kMapThreads};
+  tables.fetch();
+#pragma nounroll
   for (int i = tid; i < P * (kBitmapWords + 1); i += kMapThreads) s_count[i] = 0;  // and s_bm
   if (tid < 2) s_drop[tid] = 0;
-  const RouteTables rt =
-      load_route_tables<kMapThreads>(s_tab, l2p_off, l2p_list, active, E, R, P, inv_S);
+  const RouteTables rt = tables.fill(s_tab, inv_S);
   if constexpr (KC == 0) {
 #pragma unroll
     for (int u = 0; u < U; ++u)
@@ -301,7 +340,7 @@ __global__ __launch_bounds__(kMapThreads) void k_map_count(
   }
   __syncthreads();
   map_pairs<KC, kMapThreads, U>(rt, my_e, s_idx, slot, s_bm, kBitmapWords, s_count, s_drop, npairs,
-                                k, E, tr.t0, policy, 0, npairs, slot_of + g0);
+                                k, E, tr.t0, policy, slot_of + g0);
   __syncthreads();
 #pragma unroll
   for (int u = 0; u < U; ++u) {
@@ -327,11 +366,12 @@ __device__ __forceinline__ int wave_inclusive_scan(int v) {
   return v;
 }
 
-// Exclusive scan of s_count[0..n) into s_offset[0..n] by ONE wavefront, 64 values at a time
+// Exclusive scan of value(0..n) into s_offset[0..n] by ONE wavefront, 64 values at a time
 // and kScanChunks such groups at once (their loads and scans are independent; only the running
 // sum is a chain).  The caller's next barrier makes the result readable.
 constexpr int kScanChunks = 5;
-__device__ __forceinline__ void wave_exclusive_scan(const int32_t* s_count, int32_t* s_offset, int n) {
+template <class Value>
+__device__ __forceinline__ void wave_exclusive_scan(Value value, int32_t* s_offset, int n) {
   const int lane = threadIdx.x & 63;
   int run = 0;
   for (int c0 = 0; c0 < n; c0 += 64 * kScanChunks) {
@@ -339,7 +379,7 @@ __device__ __forceinline__ void wave_exclusive_scan(const int32_t* s_count, int3
 #pragma unroll
     for (int c = 0; c < kScanChunks; ++c) {
       const int p = c0 + c * 64 + lane;
-      v[c] = p < n ? s_count[p] : 0;
+      v[c] = p < n ? value(p) : 0;
     }
 #pragma unroll
     for (int c = 0; c < kScanChunks; ++c) incl[c] = wave_inclusive_scan(v[c]);
@@ -355,8 +395,7 @@ __device__ __forceinline__ void wave_exclusive_scan(const int32_t* s_count, int3
 
 // Per-step tables every consumer needs, written once by one workgroup
 // (`count` may be null when another kernel has already written it).
-template <int NT>
-__device__ inline void write_step_tables(const int32_t* s_count, const int32_t* s_offset,
+__device__ inline void write_step_tables(int nt, const int32_t* s_offset,
                                          int dropped_unc, int dropped_msk, int version,
                                          int32_t* __restrict__ count, int32_t* __restrict__ offset,
                                          int32_t* __restrict__ rank_count,
@@ -364,11 +403,13 @@ __device__ inline void write_step_tables(const int32_t* s_count, const int32_t* 
                                          int32_t* __restrict__ status,
                                          int32_t* __restrict__ step_epoch, int R, int S, int P) {
   const int tid = threadIdx.x;
-  for (int p = tid; p <= P; p += NT) {
+#pragma nounroll
+  for (int p = tid; p <= P; p += nt) {
     offset[p] = s_offset[p];
-    if (count != nullptr && p < P) count[p] = s_count[p];
+    if (count != nullptr && p < P) count[p] = s_offset[p + 1] - s_offset[p];
   }
-  for (int r = tid; r < R; r += NT) {
+#pragma nounroll
+  for (int r = tid; r < R; r += nt) {
     rank_offset[r] = s_offset[r * S];
     rank_count[r] = s_offset[(r + 1) * S] - s_offset[r * S];
   }
@@ -476,7 +517,7 @@ __global__ __launch_bounds__(kFusedThreads) void k_scan_position(
   __syncthreads();
   if (du) atomicAdd(&s_drop[0], du);  // zeroed before the barrier, read after the scan's barriers
   if (dm) atomicAdd(&s_drop[1], dm);
-  if (tid < 64) wave_exclusive_scan(s_count, s_offset, P);
+  if (tid < 64) wave_exclusive_scan([=](int p) { return s_count[p]; }, s_offset, P);
   __syncthreads();
 
   const int N = s_offset[P];
@@ -495,26 +536,35 @@ __global__ __launch_bounds__(kFusedThreads) void k_scan_position(
     }
   }
   if (b == 0)
-    write_step_tables<kFusedThreads>(s_count, s_offset, s_drop[0], s_drop[1], version, count,
+    write_step_tables(kFusedThreads, s_offset, s_drop[0], s_drop[1], version, count,
                                      offset, rank_count, rank_offset, status, step_epoch, R, S, P);
 }
 
 // ---------------------------------------------------------------------------
-// Small batches (T <= 512 tokens and T*k <= 4096 pairs: up to 16 tokens per rank
-// at 32 ranks, the low-concurrency decode regime): the whole layout in ONE
-// launch with a token bitmap per slot that spans the batch.  Bound by latency:
-// the launch (1.9 us for an empty kernel), one round of global loads, LDS round
-// trips, and stores.  Every workgroup maps ALL pairs (1 to 4 per thread, each
-// keeps the whole count and offset table) and then writes its eighth of the
-// results, so no workgroup waits for another; one alone spent 1.4 to 2.8 us on
-// storing, mostly the [R][P] matrix of pairs per (source rank, slot).  Measured,
-// 32 ranks x 9 slots, top-8, a layout in a graph of 40: T = 32 / 128 / 256 / 384 /
-// 512 in 4.0 / 4.1 / 4.8 / 5.6 / 6.2 us with 8 workgroups, 4.1 / 4.3 / 5.2 / 6.0 / 6.6
-// with 4, 4.4 / 4.8 / 5.9 / 7.3 / 8.7 with 1.  The tiled path takes 7.6 us at 416 to
-// 1024 tokens; 8 pairs per thread (T = 768) would be no faster than that, hence the
-// limits.
+// The whole layout in ONE launch, for batches up to 16384 pairs.  A workgroup owns a
+// share of the tokens, whole source ranks.  It counts the pairs per slot of ALL tokens,
+// those ahead of its share, its own and those behind it apart, so it needs nothing from
+// the others; then it places its own.  Bound by latency and by instructions: the launch
+// (1.9 us for an empty kernel), one round of global loads, LDS round trips, and, as every
+// workgroup maps all pairs, the instructions per pair.  Hence a lane takes a whole token,
+// whose indices it compares in registers, the routing of an expert is one word that is
+// prepared once (`build_entries`), pairs without a slot have a sink to be counted in instead
+// of a branch, and what does not wait for the scan stands between its barriers.  Batches of
+// up to 512 pairs are a pair to a lane: there the chain counts, not the sum.
 //
-// The eight results fit together only if all eight workgroups saw one mask.  An
+// Measured (a layout in a graph of 40; 32 ranks x 9 slots, top-8), in brackets with a pair to
+// a lane, branches, and beyond 512 tokens a second launch for scan and rows: T = 32 / 256 / 512
+// 3.9 / 4.3 / 4.6 us (3.9 / 4.8 / 6.2), 768 / 1024 / 1536 / 2048 4.9 / 5.1 / 5.6 / 6.0 (7.6 / 7.7 / 7.8 / 7.9),
+// 3072 / 4096 7.3 / 8.6 (8.1 / 8.4); with a Zipf router, whose hot slots' counts are one LDS word
+// for many lanes, 2048 7.2 (7.7), 4096 10.7 (8.1).  T = 1024 of 64 ranks x 9 slots 5.8 (12.0), top-2 of
+// 32 ranks 4.0 (7.4), top-6 of 24 ranks 4.2 (7.8).  So up to 16384 pairs; and no share may have more
+// than 2048 pairs, of which 4 ranks or fewer are soon short (2 ranks, top-8: T = 512 5.3 (5.9), T = 1024,
+// 4096 pairs to a share, 8.5 (7.3)).  Shares of about 64 tokens; 512 threads, 1024 for more than
+// 1024 items (T = 256 / 1024 / 2048: 4.3 / 5.1 / 6.2 with 512, 4.6 / 5.0 / 6.0 with 1024).
+//
+// Up to 512 tokens and 4096 pairs there are 8 workgroups, however many ranks.
+//
+// The workgroups' results fit together only if all of them saw one mask.  An
 // instance of one context keeps its mask still while a layout runs: only its own
 // later calls on the stream change it.  With several contexts another one's combine
 // may drop a rank, or another one's caller may update the mask, at any moment.  So
@@ -522,141 +572,373 @@ __global__ __launch_bounds__(kFusedThreads) void k_scan_position(
 // dead once, and every pair, count and row follows from that), up to the size from
 // which the tiled path, where each pair is mapped once, is as fast.  The launch
 // decides by the number of contexts; a launch captured while there was one is
-// overruled by the word behind the membership version, which says that there are more
-// (up to 0.1 us of the figures above).
+// overruled by the word behind the membership version, which says that there are more:
+// its first workgroup then takes the shares one after the other.
 // ---------------------------------------------------------------------------
-constexpr int kSmallBlocks = 8;
+constexpr int kSmallBlocks = 8;  // and where they apply:
 constexpr int kSmallTokens = 512;
-constexpr int kSmallPairsPerThread = 4;
-constexpr int kSmallPairs = kMapThreads * kSmallPairsPerThread;
-constexpr int kSoloTokens = 384;  // the limits for one workgroup: 7.3 us there, the tiled path 7.6
-constexpr int kSoloPairs = kMapThreads * 3;
-constexpr uint32_t kSoloBit = 1u << 31;
+constexpr int kSmallPairs = 4096;
+constexpr int kSoloTokens = 384;  // the limits for one workgroup
+constexpr int kSoloPairs = 3072;
+constexpr int kOnceThreads = 1024;
+constexpr int kOnceMaxK = 10;  // compile-time top-k, a token to a lane, up to here
+constexpr int kPairPairs = 512;  // a pair to a lane up to here
+constexpr int kOncePairs = 16384, kSharePairs = 2048, kShareTokens = 64;
 
-// Row stride of the whole-batch bitmaps in words; odd, so that lanes on different slots
-// reading the same word index hit different banks.
-__host__ __device__ inline int small_stride(int T) { return ((T + 31) / 32) | 1; }
-inline size_t small_lds_bytes(int E, int P, int R, int T, int k) {
-  return sizeof(int32_t) * (route_table_ints(E, P, R) + P + (P + 1) +
-                            (size_t)P * small_stride(T) + (size_t)T * k);
+// Element i of a small global array: a 32-bit offset from a scalar address, which takes no 64-bit
+// arithmetic per lane.
+template <class T>
+__device__ __forceinline__ T& at(T* p, uint32_t i) {
+  return *(T*)((char*)p + (uint32_t)(i * (uint32_t)sizeof(T)));
 }
 
-// cnt[p] = tokens [lo, hi) in the bitmap of slot p, for the kSrcChunks * 64 slots from p0 on;
-// lo < hi are the same for the whole wavefront.  The slots' words are read side by side, so
-// that the LDS latencies overlap.
-template <int kSrcChunks>
-__device__ __forceinline__ void store_src_counts(const uint32_t* s_bm, int stride, int p0, int P,
-                                                 int lo, int hi, int32_t* __restrict__ cnt) {
-  const int w0 = lo >> 5, w1 = (hi - 1) >> 5;
-  int c[kSrcChunks] = {};
-  for (int w = w0; w <= w1; ++w) {
-    uint32_t m = ~0u;
-    if (w == w0) m &= ~0u << (lo & 31);
-    if (w == w1) m &= ~0u >> (31 - ((hi - 1) & 31));
-    uint32_t v[kSrcChunks];
-#pragma unroll
-    for (int u = 0; u < kSrcChunks; ++u) {
-      const int p = p0 + u * 64 + (int)(threadIdx.x & 63);
-      v[u] = s_bm[(p < P ? p : P - 1) * stride + w];
+__device__ __forceinline__ int vector_load(const int32_t* p) {
+  return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+}
+
+// What an expert's pairs need to know, one word per expert: the slot of its pairs from even tokens
+// and << 12 that of those from odd ones.  Pairs without a row go to two sinks behind the P slots, and
+// are counted there: P for experts without a live replica, P + 1 for what is no expert or a repeat.
+constexpr uint32_t kEntryMany = 1u << 24;  // more live ones to spread over: list start, count << 12
+constexpr int kEntrySlots = 1 << 12;       // slots, sinks and counts stay below this
+constexpr int kSinks = 2;
+
+// Writes the entries of all experts, and for those with more than two live replicas to choose from
+// the live ones to the front of the list.  The caller's next barrier makes both readable.
+template <bool LARGE>
+__device__ __forceinline__ void build_entries(const RouteTables& rt, uint32_t* entries, int E, int P,
+                                              int policy, int nt) {
+#pragma nounroll
+  for (int e = threadIdx.x; e <= E; e += nt) {  // (one pass unless LARGE)
+    uint32_t even = P + 1, odd = P + 1, many = 0;  // (entry E: not an expert)
+    if (e < E) {
+      const int o = rt.off[e], m = rt.off[e + 1] - o;
+      const uint64_t two = (uint64_t)rt.alive[(o >> 5) + 1] << 32 | rt.alive[o >> 5];
+      const uint32_t bits = (uint32_t)(two >> (o & 31)) & (uint32_t)((1ull << (m & 63)) - 1);
+      const uint32_t rest = policy == EEP_FIRST_LIVE ? 0 : bits & (bits - 1);
+      even = odd = P;
+      if (__builtin_expect(m > 32 || (rest & (rest - 1)) != 0, 0)) {
+        int n = 0;
+#pragma nounroll
+        for (int q = o; q < o + m; ++q)
+          if ((rt.alive[q >> 5] >> (q & 31)) & 1) rt.list[o + n++] = rt.list[q];
+        if (n > 0) {
+          many = kEntryMany;
+          even = o;
+          odd = policy == EEP_FIRST_LIVE ? 1 : n;
+        }
+      } else if (bits != 0) {
+        even = odd = rt.list[o + __ffs(bits) - 1];
+        if (rest != 0) odd = rt.list[o + __ffs(rest) - 1];
+      }
     }
-#pragma unroll
-    for (int u = 0; u < kSrcChunks; ++u) c[u] += __popc(v[u] & m);
-  }
-#pragma unroll
-  for (int u = 0; u < kSrcChunks; ++u) {
-    const int p = p0 + u * 64 + (int)(threadIdx.x & 63);
-    if (p < P) cnt[p] = c[u];
+    entries[e] = many | odd << 12 | even;
+    if (!LARGE) break;
   }
 }
 
-template <int KC, int U>
-__global__ __launch_bounds__(kMapThreads) void k_layout_small(
+// Does a token name an expert twice?
+template <uint32_t N>
+__device__ __forceinline__ bool any_repeats(const int (&e)[N]) {
+  uint32_t least = ~0u;
+#pragma unroll
+  for (uint32_t j = 1; j < N; ++j) {
+#pragma unroll
+    for (uint32_t i = 0; i < j; ++i) least = min(least, (uint32_t)(e[i] ^ e[j]));
+  }
+  return N > 1 && least == 0;
+}
+
+// The slots (or sinks) p[] of token t's pairs with the experts e[].
+template <uint32_t N>
+__device__ __forceinline__ void map_token(const RouteTables& rt, const uint32_t* entries, int E, int P,
+                                          int (&e)[N], bool repeats, int t, int (&p)[N]) {
+  uint32_t all = 0;
+#pragma unroll
+  for (uint32_t j = 0; j < N; ++j) p[j] = entries[(uint32_t)e[j] < (uint32_t)E ? e[j] : E];
+#pragma unroll
+  for (uint32_t j = 0; j < N; ++j) all |= p[j];
+  if (__builtin_expect(__any(all >= kEntryMany), 0)) {
+    // t % n by way of t / n in float, which is exact: (t + 0.5) / n is at least 0.5 / n away from an
+    // integer, and t < 2^20
+#pragma unroll
+    for (uint32_t j = 0; j < N; ++j) {
+      const int lo = p[j] & (kEntrySlots - 1), hi = p[j] >> 12 & (kEntrySlots - 1);
+      const int q = (int)(((float)t + 0.5f) * __builtin_amdgcn_rcpf((float)hi));
+      int s = t & 1 ? hi : lo;
+      if ((uint32_t)p[j] >= kEntryMany) s = rt.list[lo + t - q * hi];
+      p[j] = s;
+    }
+  } else {
+    const int shift = t & 1 ? 12 : 0;
+#pragma unroll
+    for (uint32_t j = 0; j < N; ++j) p[j] = (uint32_t)p[j] >> shift & (kEntrySlots - 1);
+  }
+  if (__builtin_expect(__any(repeats), 0)) {  // (a router's choices never do)
+#pragma unroll
+    for (uint32_t j = 1; j < N; ++j) {
+      asm volatile("" : "+v"(e[j]));  // (or the comparisons would be kept from above)
+#pragma unroll
+      for (uint32_t i = 0; i < j; ++i) p[j] = e[i] == e[j] ? P + 1 : p[j];
+    }
+  }
+}
+
+// Bits [lo, hi) of a bitmap, lo < hi.
+__device__ __forceinline__ int bits_between(const uint32_t* bm, int lo, int hi) {
+  const int w0 = lo >> 5, w1 = (hi - 1) >> 5;
+  int c = -__popc(bm[w0] & ~(~0u << (lo & 31)));
+#pragma nounroll
+  for (int w = w0; w < w1; ++w) c += __popc(bm[w]);
+  return c + __popc(bm[w1] & ~0u >> (31 - ((hi - 1) & 31)));
+}
+
+// Row stride of a share's token bitmaps in words; odd, so that lanes on different slots reading
+// the same word index hit different banks.
+__host__ __device__ inline int share_stride(int tokens) { return ((tokens + 31) / 32) | 1; }
+constexpr int kRegions = 3;  // tokens ahead of the share, its own, behind it
+// Words that start at zero: counts and bitmaps, a whole number of 16 bytes.
+__host__ __device__ inline uint32_t once_zeros(uint32_t P, uint32_t stride) {
+  return ((P + kSinks) * (kRegions + stride) + 3) / 4 * 4;
+}
+inline size_t once_lds_bytes(int E, int P, int R, int T, int tokens, int k) {
+  return sizeof(int32_t) * (once_zeros(P, share_stride(tokens)) + route_table_ints(E, P, R) +
+                            (k > kOnceMaxK ? (size_t)T * k : E + 1) + (P + 1) + (size_t)tokens * k);
+}
+
+// Exclusive scan of the slots' totals into s_offset[0..P]: the wavefronts, the last one first, take
+// 64 slots each and add up what lies ahead of these for themselves, so that nothing has to be
+// exchanged.  The caller's next barrier makes the result readable.
+template <class Total>
+__device__ __forceinline__ void scan_totals(Total total, int32_t* s_offset, int P, int wave,
+                                            int waves) {
+  const int lane = threadIdx.x & 63, chunks = (P >> 6) + 1;
+#pragma nounroll
+  for (int c = waves - 1 - wave; c < chunks; c += waves) {
+    int ahead = 0;
+#pragma unroll 4
+    for (int i = 0; i < c; ++i) ahead += total(i * 64 + lane);
+    const int p = c * 64 + lane, v = p < P ? total(p) : 0;
+    const int incl = wave_inclusive_scan(v);
+    ahead = __builtin_amdgcn_readlane(wave_inclusive_scan(ahead), 63);
+    if (p <= P) s_offset[p] = ahead + incl - v;
+  }
+}
+
+// A value that the compiler knows nothing about: what follows from it is computed where it is used.
+__device__ __forceinline__ int opaque(int x) {
+  asm volatile("" : "+s"(x));
+  return x;
+}
+
+// KC: compile-time k, or 0 for any.  TOKEN: a lane takes a token, otherwise a pair.
+// Four words hold the shape (T and tokens per rank; E and P; R and the source ranks of a share; S,
+// policy << 12, k << 13, wavefronts << 19), so that it arrives in registers with the first pointers.
+template <int KC, bool TOKEN, bool LARGE>
+__global__ __launch_bounds__(kOnceThreads) void k_layout_once(
     const int32_t* __restrict__ topk_idx, const int32_t* __restrict__ l2p_off,
     const int32_t* __restrict__ l2p_list, const int32_t* __restrict__ active,
-    const int32_t* __restrict__ mem_version, uint32_t T_k, int E, int P, int R, float inv_S,
-    const int32_t* __restrict__ tbl_version, int policy, int tokens_per_rank, int S,
-    int32_t* __restrict__ slot_of, int32_t* __restrict__ row_of, int32_t* __restrict__ src_of,
+    const int32_t* __restrict__ mem_version, uint32_t T_rank, uint32_t E_P, uint32_t R_share,
+    uint32_t S_policy_k_waves, const int32_t* __restrict__ tbl_version, int32_t* __restrict__ slot_of,
+    int32_t* __restrict__ row_of, int32_t* __restrict__ src_of, int32_t* __restrict__ cnt_src,
     int32_t* __restrict__ count, int32_t* __restrict__ offset, int32_t* __restrict__ rank_count,
-    int32_t* __restrict__ rank_offset, int32_t* __restrict__ cnt_src,
-    int32_t* __restrict__ status, int32_t* __restrict__ step_epoch) {
-  const int T = T_k & 0xffff, k = KC > 0 ? KC : T_k >> 16 & 0xff;  // in one preloaded word
-  const int npairs = T * k;
-  const int stride = small_stride(T);
-  extern __shared__ int32_t smem[];
-  int32_t* s_count = smem;                        // [P] pairs per slot
-  uint32_t* s_bm = (uint32_t*)(s_count + P);      // [P][stride] token bitmap per slot
-  int32_t* s_offset = (int32_t*)(s_bm + P * stride);  // [P+1] exclusive scan of s_count
-  int32_t* s_idx = s_offset + P + 1;              // [T*k] router indices, KC == 0 only
-  int32_t* s_tab = s_idx + (KC == 0 ? npairs : 0);
-  __shared__ int32_t s_drop[2];
-  const int tid = threadIdx.x;
-
-  // every global read of this kernel is issued here, none depends on another
-  int my_e[U], slot[U];
-#pragma unroll
-  for (int u = 0; u < U; ++u) {
-    const int i = tid + u * kMapThreads;
-    my_e[u] = i < npairs ? topk_idx[i] : -1;
-  }
-  const int version = blockIdx.x == 0 && tid == 0 ? *tbl_version + *mem_version : 0;
+    int32_t* __restrict__ rank_offset, int32_t* __restrict__ status,
+    int32_t* __restrict__ step_epoch) {
+  constexpr uint32_t N = TOKEN ? KC : 1;
+  const uint32_t T = T_rank & 0xffff, tokens_per_rank = T_rank >> 16;
+  const uint32_t E = E_P & 0xffff, R = R_share & 0xffff, ranks = R_share >> 16;
+  const uint32_t S = S_policy_k_waves & 0xfff, policy = S_policy_k_waves >> 12 & 1;
+  const uint32_t k = KC > 0 ? KC : S_policy_k_waves >> 13 & 63;
+  const uint32_t waves = S_policy_k_waves >> 19, nt = waves * 64;
+  const uint32_t tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const uint32_t per_item = TOKEN ? 1 : k, items = T * per_item;
+  const auto load = [&](uint32_t i, int (&e)[N]) { __builtin_memcpy(e, &at(topk_idx, i * N), sizeof(e)); };
+  // i / k; a k that is not known by way of float, which is exact: (i + 0.5) / k is at least 0.5 / k away
+  // from an integer, and i < 2^16
+  const float inv_k = __builtin_amdgcn_rcpf((float)k);
+  const auto token_at = [=](uint32_t i) { return KC > 0 ? i / k : (uint32_t)(((float)i + 0.5f) * inv_k); };
+  // The first round's tokens from the last thread down: the first threads have the tables to do.
+  uint32_t item = TOKEN ? nt - 1 - tid : tid;
+  int e[N];
+  load(item < items ? item : items - 1, e);
+  RouteTableLoad<LARGE> tables = {l2p_off, l2p_list, active, (int)E, (int)R, (int)(E_P >> 16), (int)nt};
+  tables.fetch();
   // several contexts in the instance: the first workgroup does it all.  (A vector load: a scalar one
   // would be waited for together with every kernel argument.)
-  const int several_v =
-      __hip_atomic_load(&mem_version[1], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-  for (int i = tid; i < P * (stride + 1); i += kMapThreads) s_count[i] = 0;  // and s_bm
-  if (tid < 2) s_drop[tid] = 0;
-  const RouteTables rt =
-      load_route_tables<kMapThreads>(s_tab, l2p_off, l2p_list, active, E, R, P, inv_S);
+  const int several_v = vector_load(&mem_version[1]);
+
+  extern __shared__ __align__(16) int32_t smem[];
+  const uint32_t tokens = ranks * tokens_per_rank, stride = share_stride(tokens);
+  const uint32_t zeros = once_zeros(E_P >> 16, stride);
+  int32_t* s_tab = smem + zeros;
+#pragma nounroll
+  for (uint32_t i = tid * 4; i < zeros; i += nt * 4) *(int4*)(smem + i) = make_int4(0, 0, 0, 0);
+  const RouteTables rt = tables.fill(s_tab, __builtin_amdgcn_rcpf((float)S));
+  uint32_t* s_entry = (uint32_t*)(s_tab + route_table_ints(E, E_P >> 16, R));  // [E+1]
   if constexpr (KC == 0) {
-#pragma unroll
-    for (int u = 0; u < U; ++u)
-      if (tid + u * kMapThreads < npairs) s_idx[tid + u * kMapThreads] = my_e[u];
+    int32_t* s_idx = (int32_t*)s_entry;  // [T*k] router indices
+#pragma nounroll
+    for (uint32_t i = tid; i < items; i += nt) s_idx[i] = i == tid ? e[0] : at(topk_idx, i);
   }
-  // the pairs [own_lo, own_hi) whose results this workgroup writes, and as which of how many; with
-  // `solo` the first one's are all, the others go along and write nothing
-  const bool solo = __builtin_amdgcn_readfirstlane(several_v) != 0 || (T_k & kSoloBit) != 0;
-  const int blocks = solo ? 1 : kSmallBlocks, block = solo && blockIdx.x > 0 ? R : blockIdx.x;
-  const int share = ((npairs + kSmallBlocks - 1) / kSmallBlocks + 63) & ~63;
-  const int own_lo = solo ? (blockIdx.x > 0 ? npairs : 0) : blockIdx.x * share;
-  const int own_hi = solo || own_lo + share > npairs ? npairs : own_lo + share;
+  const bool alone = ranks < R && __builtin_amdgcn_readfirstlane(several_v) != 0;
+  uint32_t share = blockIdx.x;
+  if (share > 0 && (alone || share * ranks >= R)) return;
   __syncthreads();
-  map_pairs<KC, kMapThreads, U>(rt, my_e, s_idx, slot, s_bm, stride, s_count, s_drop, npairs, k, E, 0,
-                                policy, own_lo, own_hi, slot_of);
-  __syncthreads();
+  bool repeats = false;
+  if constexpr (TOKEN) {
+    build_entries<LARGE>(rt, s_entry, E, E_P >> 16, policy, nt);
+    repeats = any_repeats(e);
+    __syncthreads();
+  }
 
-  if (tid < 64) wave_exclusive_scan(s_count, s_offset, P);
-  __syncthreads();
-
-  const int N = s_offset[P];
-#pragma unroll
-  for (int u = 0; u < U; ++u) {
-    const int i = tid + u * kMapThreads;
-    if (i >= own_lo && i < own_hi) {
-      const int p = slot[u];
-      int row = -1;
-      if (p >= 0) {
-        row = s_offset[p] + rank_in_slot(&s_bm[p * stride], i / k);
-        src_of[row] = i;
+  // One round, over the whole batch; alone, a second one for every share, over its tokens.
+  uint32_t end = items, lo = alone ? T : share * tokens;
+  int rows = 0;
+  for (uint32_t round = 0;; ++round) {
+    // (Opaque, or whatever follows from it would be computed ahead of the loop by every wavefront.)
+    const uint32_t P = opaque(E_P >> 16), P2 = P + kSinks;
+    int32_t* const s_cnt = smem;                          // [kRegions][P2] pairs per slot
+    uint32_t* const s_bm = (uint32_t*)(smem + kRegions * P2);  // [P2][stride] bitmap of the share's tokens per slot
+    int32_t* const s_offset = smem + opaque(zeros + route_table_ints(E, P, R) +
+                                            (KC > 0 ? E + 1 : items));  // [P+1] exclusive scan of the totals
+    int32_t* const s_slot = s_offset + P + 1;             // [tokens*k] slots of the share's pairs
+    const uint32_t hi = min(lo + tokens, T);
+#pragma nounroll
+    while (item < end) {
+      const uint32_t now = item;
+      item += nt;
+      int next[N];
+      if (item < end) load(item, next);
+      int p[N];
+      uint32_t t = now, j0 = 0;
+      if constexpr (TOKEN) {
+        map_token<N>(rt, s_entry, E, P, e, repeats, t, p);
+      } else {
+        t = token_at(now);
+        j0 = now - t * k;
+        p[0] = P + 1;
+        const bool again = repeats_earlier<KC>(e[0], j0, (int32_t*)s_entry + t * k);  // (all lanes)
+        if ((uint32_t)e[0] < E && !again) {
+          p[0] = pick_slot(rt, e[0], t, policy);
+          if (p[0] < 0) p[0] = P;
+        }
       }
-      row_of[i] = row;
-      if (i >= N) src_of[i] = -1;  // rows past the last routed pair
+      // counted in the token's region, and if the token is the share's own, kept
+      const bool own = t >= lo && t < hi;
+      int32_t* cnt = s_cnt + (own ? P2 : t < lo ? 0 : 2 * P2);
+#pragma unroll
+      for (uint32_t j = 0; j < N; ++j) atomicAdd(&cnt[p[j]], 1);
+      if (own) {
+        const uint32_t tl = t - lo;
+        uint32_t* bm = s_bm + (tl >> 5);
+        int32_t* to = s_slot + tl * k + j0;
+        const uint32_t bit = 1u << (tl & 31);
+#pragma unroll
+        for (uint32_t j = 0; j < N; ++j) to[j] = p[j];
+#pragma unroll
+        for (uint32_t j = 0; j < N; ++j) {
+          atomicOr(&bm[__umul24(p[j], stride)], bit);
+        }
+      }
+      if (item < end) {
+#pragma unroll
+        for (uint32_t j = 0; j < N; ++j) e[j] = next[j];
+        if constexpr (TOKEN) repeats = any_repeats(e);
+      }
     }
+    __syncthreads();
+    // Between two barriers: the scan, and what does not need it.
+    const uint32_t n = lo < T ? (hi - lo) * k : 0, g0 = lo * k;
+    const auto total = [=](uint32_t p) { return s_cnt[p] + s_cnt[P2 + p] + s_cnt[2 * P2 + p]; };
+    int dead = 0, masked = 0, version = 0;
+    if (round == 0) {
+      scan_totals(total, s_offset, P, wave, waves);
+      if (share == 0) {
+        dead = total(P);
+        masked = total(P + 1);
+        version = vector_load(tbl_version) + vector_load(mem_version);
+      }
+    }
+    // pairs per (source rank, slot): the tokens of a source rank are a bit range
+    if (n > 0) {
+      const uint32_t rank0 = share * ranks, mine = min(R - rank0, ranks);
+#pragma nounroll
+      for (uint32_t p = tid; p < P; p += nt) {
+        const uint32_t* bm = &s_bm[__umul24(p, stride)];
+        uint32_t to = rank0 * P + p;
+        if (tokens <= 64) {
+          uint64_t bits = bm[0];
+          if (stride > 1) bits |= (uint64_t)bm[1] << 32;
+          const uint64_t mask = ~0ull >> (64 - tokens_per_rank);
+#pragma nounroll
+          for (uint32_t b = 0; b < mine; ++b, to += P) {
+            at(cnt_src, to) = __popcll(bits & mask);
+            bits >>= tokens_per_rank;
+          }
+        } else {
+#pragma nounroll
+          for (uint32_t b = 0; b < mine; ++b, to += P)
+            at(cnt_src, to) = bits_between(bm, b * tokens_per_rank, (b + 1) * tokens_per_rank);
+        }
+      }
+    }
+    uint32_t p = P;
+    int row = -1;
+    const auto place = [&](uint32_t i) {  // slot of the share's pair i, its row less the slot's offset
+      p = s_slot[i];
+      row = s_cnt[p] + rank_in_slot(&s_bm[p * stride], token_at(i));
+    };
+    if (tid < n) place(tid);
+    __syncthreads();
+    if (round == 0) rows = s_offset[P];
+#pragma nounroll
+    for (uint32_t i = tid; i < n;) {
+      const uint32_t g = g0 + i;
+      int slot = -1;
+      if (p < P) {
+        slot = p;
+        row += s_offset[p];
+        at(src_of, row) = g;
+      } else {
+        row = -1;
+      }
+      at(slot_of, g) = slot;
+      at(row_of, g) = row;
+      if ((int)g >= rows) at(src_of, g) = -1;  // rows past the last routed pair
+      i += nt;
+      if (i < n) place(i);
+    }
+    if (share == 0 && round == 0)
+      write_step_tables(nt, s_offset, dead, masked, version, count, offset, rank_count,
+                                      rank_offset, status, step_epoch, R, S, P);
+    share = round;
+    lo = share * tokens;
+    if (!alone || lo >= T) break;
+    __syncthreads();
+#pragma nounroll
+    for (uint32_t q = tid; q < P2; q += nt) {
+      s_cnt[q] = round == 0 ? 0 : s_cnt[q] + s_cnt[P2 + q];  // now the pairs of the shares so far
+      s_cnt[P2 + q] = 0;
+    }
+#pragma nounroll
+    for (uint32_t q = tid; q < P2 * stride; q += nt) s_bm[q] = 0;
+    item = lo * per_item + tid;
+    end = min(lo + tokens, T) * per_item;
+    if (item < end) {
+      load(item, e);
+      if constexpr (TOKEN) repeats = any_repeats(e);
+    }
+    __syncthreads();
   }
-  // pairs per (source rank, slot): the tokens of a source rank are a bit range; wavefronts
-  // take source ranks, lanes slots, five sets of 64 slots at once where there are more than one
-  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  for (int b = block * kMapWaves + wave; b < R; b += blocks * kMapWaves) {
-    const int lo = b * tokens_per_rank, hi = lo + tokens_per_rank;
-    int32_t* cnt = cnt_src + (int64_t)b * P;
-    if (P <= 64)
-      store_src_counts<1>(s_bm, stride, 0, P, lo, hi, cnt);
-    else
-      for (int p0 = 0; p0 < P; p0 += 320) store_src_counts<5>(s_bm, stride, p0, P, lo, hi, cnt);
-  }
-  if (blockIdx.x == 0)
-    write_step_tables<kMapThreads>(s_count, s_offset, s_drop[0], s_drop[1], version, count, offset,
-                                   rank_count, rank_offset, status, step_epoch, R, S, P);
 }
+
+// What a bitmap of the whole batch would take: the bound for the forms of 8 workgroups and of one.
+inline size_t small_lds_bytes(int E, int P, int R, int T, int k) {
+  return sizeof(int32_t) * (route_table_ints(E, P, R) + P + (P + 1) +
+                            (size_t)P * share_stride(T) + (size_t)T * k);
+}
+// Source ranks in a share, for about `shares` of them.
+static int share_ranks(int R, int shares) { return shares > 0 ? (R + shares - 1) / shares : R; }
 
 // ---------------------------------------------------------------------------
 // Many tiles (> 64, the prefill regime): three launches.
@@ -758,7 +1040,7 @@ __global__ __launch_bounds__(kPosThreads) void k_position(
   __syncthreads();
   if (du) atomicAdd(&s_drop[0], du);
   if (dm) atomicAdd(&s_drop[1], dm);
-  if (tid < 64) wave_exclusive_scan(s_count, s_offset, P);
+  if (tid < 64) wave_exclusive_scan([=](int p) { return s_count[p]; }, s_offset, P);
   __syncthreads();
 
   // pairs per (source rank, slot): difference of the tile prefixes at the source
@@ -785,7 +1067,7 @@ __global__ __launch_bounds__(kPosThreads) void k_position(
     if (g >= N) src_of[g] = -1;  // rows past the last routed pair
   }
   if (blockIdx.x == 0)
-    write_step_tables<kPosThreads>(s_count, s_offset, s_drop[0], s_drop[1], version, nullptr,
+    write_step_tables(kPosThreads, s_offset, s_drop[0], s_drop[1], version, nullptr,
                                    offset, rank_count, rank_offset, status, step_epoch, R, S, P);
 }
 
@@ -912,7 +1194,7 @@ __global__ __launch_bounds__(kMapThreads) void k_dedup_position(
     s_pre[r] = before;
   }
   __syncthreads();
-  if (tid < 64) wave_exclusive_scan(s_cnt, s_off, R);
+  if (tid < 64) wave_exclusive_scan([=](int r) { return s_cnt[r]; }, s_off, R);
   __syncthreads();
   for (int i = tid; i < npairs; i += kMapThreads) {
     const int p = slot_of[g0 + i];
@@ -979,14 +1261,36 @@ bool layout_shape_fits(int E, int P, int R, int k) {
 // The instantiation of a kernel family for top-k `k` and `pairs` pairs per workgroup of
 // kMapThreads threads, at most 4 per thread: a compile-time k where the lanes of a token share a
 // DPP row.
-static_assert(kMaxPairsPerThread == 4 && kSmallPairsPerThread == 4, "EEP_FOR_K's widths");
-#define EEP_FOR_K_U(KERN, U, k)                                                             \
-  ((k) == 8 ? KERN<8, U> : (k) == 4 ? KERN<4, U> : (k) == 2 ? KERN<2, U> : (k) == 1 ? KERN<1, U> \
-                                                                                    : KERN<0, U>)
-#define EEP_FOR_K(KERN, k, pairs)                                   \
-  ((pairs) <= kMapThreads       ? EEP_FOR_K_U(KERN, 1, k)           \
-   : (pairs) <= 2 * kMapThreads ? EEP_FOR_K_U(KERN, 2, k)           \
-                                : EEP_FOR_K_U(KERN, 4, k))
+static_assert(kMaxPairsPerThread == 4, "widths of map_count_for");
+template <int U, bool WIDE>
+static auto map_count_for_k(int k) {
+  return k == 8 ? k_map_count<8, U, WIDE> : k == 4 ? k_map_count<4, U, WIDE>
+       : k == 2 ? k_map_count<2, U, WIDE> : k == 1 ? k_map_count<1, U, WIDE> : k_map_count<0, U, WIDE>;
+}
+template <bool WIDE>
+static auto map_count_for(int k, int pairs) {
+  return pairs <= kMapThreads ? map_count_for_k<1, WIDE>(k)
+       : pairs <= 2 * kMapThreads ? map_count_for_k<2, WIDE>(k) : map_count_for_k<4, WIDE>(k);
+}
+template <bool LARGE>
+static decltype(&k_layout_once<0, false, LARGE>) layout_once_for(int k, bool token) {
+  if (!token) return k == 8 ? k_layout_once<8, false, LARGE> : k == 4 ? k_layout_once<4, false, LARGE>
+                   : k == 2 ? k_layout_once<2, false, LARGE> : k == 1 ? k_layout_once<1, false, LARGE>
+                                                              : k_layout_once<0, false, LARGE>;
+  switch (k) {
+    case 1: return k_layout_once<1, true, LARGE>;
+    case 2: return k_layout_once<2, true, LARGE>;
+    case 3: return k_layout_once<3, true, LARGE>;
+    case 4: return k_layout_once<4, true, LARGE>;
+    case 5: return k_layout_once<5, true, LARGE>;
+    case 6: return k_layout_once<6, true, LARGE>;
+    case 7: return k_layout_once<7, true, LARGE>;
+    case 8: return k_layout_once<8, true, LARGE>;
+    case 9: return k_layout_once<9, true, LARGE>;
+    case 10: return k_layout_once<10, true, LARGE>;
+    default: return k_layout_once<0, false, LARGE>;
+  }
+}
 
 // Does an output array overlap the router indices (a caller that gives up its indices for the
 // result)?  Eight workgroups read all of them while others write already; one has read
@@ -1008,7 +1312,9 @@ static bool writes_its_input(const LayoutIO& c, int T) {
 // could disagree (the mask may change while the kernel runs, or an output overlaps the input).
 int layout_small_workgroups(int E, int P, int R, int T, int k, bool solo) {
   if (T < 1 || T > (solo ? kSoloTokens : kSmallTokens) ||
-      T * k > (solo ? kSoloPairs : kSmallPairs) || small_lds_bytes(E, P, R, T, k) > kLayoutLdsLimit)
+      T * k > (solo ? kSoloPairs : kSmallPairs) || P + kSinks > kEntrySlots ||
+      small_lds_bytes(E, P, R, T, k) > kLayoutLdsLimit ||
+      once_lds_bytes(E, P, R, T, share_ranks(R, solo ? 1 : kSmallBlocks) * (T / R), k) > kLayoutLdsLimit)
     return 0;
   return solo ? 1 : kSmallBlocks;
 }
@@ -1024,21 +1330,36 @@ hipError_t launch_layout(const LayoutIO& c, int T, hipStream_t st) {
   }
   if (g.num_tiles > max_blocks(kMapThreads)) return hipErrorInvalidValue;
   const float inv_S = 1.0f / (float)c.S;
-  const int small = layout_small_workgroups(c.E, c.P, c.R, T, c.k,
-                                            c.mask_may_change || writes_its_input(c, T));
-  if (small > 0) {
-    auto kern = EEP_FOR_K(k_layout_small, c.k, T * c.k);
-    hipLaunchKernelGGL(kern, dim3(small), dim3(kMapThreads), small_lds_bytes(c.E, c.P, c.R, T, c.k),
-                       st, c.topk_idx, c.l2p_off, c.l2p_list, c.active, c.mem_version,
-                       (uint32_t)T | (uint32_t)c.k << 16 | (small == 1 ? kSoloBit : 0u), c.E,
-                       c.P, c.R, inv_S, c.tbl_version, c.policy, g.tokens_per_rank, c.S,
-                       c.slot_of, c.row_of, c.src_of, c.count, c.offset, c.rank_count,
-                       c.rank_offset, c.cnt_src, c.status, c.step_epoch);
+  const bool solo = c.mask_may_change || writes_its_input(c, T);
+  const int small = layout_small_workgroups(c.E, c.P, c.R, T, c.k, solo);
+  int ranks = share_ranks(c.R, small), grid = small;
+  if (small == 0) {
+    ranks = g.tokens_per_rank < kShareTokens ? kShareTokens / g.tokens_per_rank : 1;
+    if (!solo && c.k <= kOnceMaxK && (int64_t)T * c.k <= kOncePairs &&
+        ranks * g.tokens_per_rank * c.k <= kSharePairs && c.P + kSinks <= kEntrySlots &&
+        once_lds_bytes(c.E, c.P, c.R, T, ranks * g.tokens_per_rank, c.k) <= kLayoutLdsLimit)
+      grid = (c.R + ranks - 1) / ranks;
+  }
+  if (grid > 0) {
+    const bool token = c.k <= kOnceMaxK && !(T * c.k <= kPairPairs && (c.k & (c.k - 1)) == 0);
+    int nt = c.P > c.E ? c.P : c.E + 1;  // threads: for the tables, and for the items
+    const int most = (token ? T : 2 * T * c.k) > kOnceThreads ? kOnceThreads : kOnceThreads / 2;
+    nt = nt < most ? most : nt < kOnceThreads ? (nt + 63) / 64 * 64 : kOnceThreads;
+    auto kern = large_tables(c.E, c.P, c.R, nt) ? layout_once_for<true>(c.k, token) : layout_once_for<false>(c.k, token);
+    hipLaunchKernelGGL(kern, dim3(grid), dim3(nt),
+                       once_lds_bytes(c.E, c.P, c.R, T, ranks * g.tokens_per_rank, c.k), st, c.topk_idx,
+                       c.l2p_off, c.l2p_list, c.active, c.mem_version,
+                       (uint32_t)T | (uint32_t)g.tokens_per_rank << 16, (uint32_t)c.E | (uint32_t)c.P << 16,
+                       (uint32_t)c.R | (uint32_t)ranks << 16,
+                       (uint32_t)c.S | (uint32_t)c.policy << 12 | (uint32_t)c.k << 13 | (uint32_t)(nt / 64) << 19,
+                       c.tbl_version, c.slot_of, c.row_of,
+                       c.src_of, c.cnt_src, c.count, c.offset, c.rank_count, c.rank_offset, c.status,
+                       c.step_epoch);
     return hipGetLastError();
   }
   {
     size_t lds = sizeof(int32_t) * map_lds_ints(c.E, c.P, c.R, g.tile_tokens, c.k);
-    auto kern = EEP_FOR_K(k_map_count, c.k, g.tile_tokens * c.k);
+    auto kern = large_tables(c.E, c.P, c.R, kMapThreads) ? map_count_for<true>(c.k, g.tile_tokens * c.k) : map_count_for<false>(c.k, g.tile_tokens * c.k);
     hipLaunchKernelGGL(kern, dim3(g.num_tiles), dim3(kMapThreads), lds, st, c.topk_idx, c.l2p_off,
                        c.l2p_list, c.active, c.k, g.tokens_per_rank, g.tiles_per_rank,
                        g.tile_tokens, c.E, c.P, c.R, inv_S, c.policy, c.slot_of, c.row_of,
