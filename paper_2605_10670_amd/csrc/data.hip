@@ -57,35 +57,25 @@ __device__ inline void store_through(u32x4* p, u32x4 v) {
   asm volatile("global_store_dwordx4 %0, %1, off sc0 sc1\n\ts_nop 1" ::"v"(p), "v"(v) : "memory");
 }
 
-// U = 16-byte vectors per lane per pass.  EXACT: the row is a whole number of
+// The same to a byte offset from a scalar address.
+__device__ __forceinline__ void store_through_at(void* base, uint32_t offset, u32x4 v) {
+  asm volatile("global_store_dwordx4 %0, %1, %2 sc0 sc1\n\ts_nop 1" ::"v"(offset), "v"(v), "s"(base) : "memory");
+}
+
+// One wavefront per token.  U = 16-byte vectors per lane per pass.  EXACT: the row is a whole number of
 // passes (row_vecs % (64 * U) == 0), so no access needs a bounds check;
 // otherwise loads past the row's end read its last vector again, so that all U
 // loads of a pass are in flight here too (a branch around each would make it
-// wait for the ones before), and stores are guarded.  `parts` wavefronts share a token, taking
-// every parts-th pass each: 1 for large batches (a whole row per wavefront
-// measured fastest there), more for small ones, which would otherwise leave
-// most of the chip idle.
-// SPLIT selects at compile time: the one-wavefront-per-token form keeps its simpler
-// indexing (2 us faster at the decode shape than the general form with parts = 1); the split
-// form, which is bound by latency, has its row indices ahead of the data (-0.1 us a step for
-// 32 to 512 tokens; +0.2 to 0.6 us in the other form at 1024 to 4096).
-template <int U, bool EXACT, bool SPLIT>
+// wait for the ones before), and stores are guarded.
+template <int U, bool EXACT>
 __global__ __launch_bounds__(64) void k_pack(const u32x4* __restrict__ x,
                                              const int32_t* __restrict__ row_of, int k,
-                                             int row_vecs, uint32_t parts, uint32_t magic,
-                                             u32x4* __restrict__ recv) {
-  const int t = SPLIT ? token_of(blockIdx.x, parts, magic) : blockIdx.x;
-  const int part = SPLIT ? blockIdx.x - t * parts : 0;
-  const int step = SPLIT ? parts * 64 * U : 64 * U;
+                                             int row_vecs, u32x4* __restrict__ recv) {
+  const int t = blockIdx.x;
   const int lane = threadIdx.x;
   const int32_t* rows = row_of + (int64_t)t * k;
   const u32x4* src = x + (int64_t)t * row_vecs;
-  for (int v0 = part * 64 * U; v0 < row_vecs; v0 += step) {
-    int r[kRowBatch];
-    if (SPLIT) {  // the first rows, fetched ahead of the data
-#pragma unroll
-      for (int i = 0; i < kRowBatch; ++i) r[i] = rows[i < k ? i : k - 1];
-    }
+  for (int v0 = 0; v0 < row_vecs; v0 += 64 * U) {
     u32x4 buf[U];
 #pragma unroll
     for (int u = 0; u < U; ++u) {
@@ -98,37 +88,92 @@ __global__ __launch_bounds__(64) void k_pack(const u32x4* __restrict__ x,
     // without a wait between them.
 #pragma unroll
     for (int u = 0; u < U; ++u) asm volatile("" ::"v"(buf[u]));
-    if (!SPLIT) {
-      for (int j = 0; j < k; ++j) {
-        int row = rows[j];
-        if (row < 0) continue;
-        u32x4* dst = recv + (int64_t)row * row_vecs;
+    for (int j = 0; j < k; ++j) {
+      int row = rows[j];
+      if (row < 0) continue;
+      u32x4* dst = recv + (int64_t)row * row_vecs;
 #pragma unroll
-        for (int u = 0; u < U; ++u) {
-          int v = v0 + u * 64 + lane;
-          if (EXACT || v < row_vecs) store_through(&dst[v], buf[u]);
-        }
+      for (int u = 0; u < U; ++u) {
+        int v = v0 + u * 64 + lane;
+        if (EXACT || v < row_vecs) store_through(&dst[v], buf[u]);
       }
-      continue;
-    }
-    for (int j0 = 0;;) {
-#pragma unroll
-      for (int i = 0; i < kRowBatch; ++i) {
-        if (j0 + i < k && r[i] >= 0) {
-          u32x4* dst = recv + (int64_t)r[i] * row_vecs;
-#pragma unroll
-          for (int u = 0; u < U; ++u) {
-            int v = v0 + u * 64 + lane;
-            if (EXACT || v < row_vecs) store_through(&dst[v], buf[u]);
-          }
-        }
-      }
-      j0 += kRowBatch;
-      if (j0 >= k) break;
-#pragma unroll
-      for (int i = 0; i < kRowBatch; ++i) r[i] = rows[j0 + i < k ? j0 + i : k - 1];
     }
   }
+}
+
+// Small batches, which would leave most of the chip idle that way: one wavefront per piece of 64 * U
+// vectors of a token's row, and for fp8 payloads (SCALES) one more for its scale row.  Bound by
+// latency, that is by the instructions of a wavefront, some 5 cycles each, and by the launch: k is a
+// compile-time number up to kSplitMaxK, whose row indices are one scalar load, the data load comes
+// before them, and a store takes its row from a scalar address.  Measured on whole steps in a graph of 8
+// (7168 channels, top-8): T = 32 / 256 in 10.2 / 21.5 us with 5 scalar instructions to an index and 18 to
+// a store, 10.05 / 21.35 now; with fp8 payloads, whose scale rows were a launch of their own behind
+// (k_scale_rows), T = 32 / 128 / 512 / 1000 in 16.3 / 19.9 / 42.4 / 70.7 us, 13.2 / 17.2 / 38.6 / 67.0 now.
+constexpr int kSplitMaxK = 8;
+
+template <int U, bool EXACT, int K, bool SCALES>
+__global__ __launch_bounds__(64) void k_pack_split(const u32x4* __restrict__ x,
+                                                   const int32_t* __restrict__ row_of, int k_rt,
+                                                   uint32_t row_vecs, uint32_t parts, uint32_t magic,
+                                                   u32x4* __restrict__ recv,
+                                                   const u32x4* __restrict__ x_scale,
+                                                   u32x4* __restrict__ recv_scale, uint32_t scale_vecs) {
+  const int k = K > 0 ? K : k_rt;
+  const uint32_t t = token_of(blockIdx.x, parts, magic);
+  const uint32_t part = blockIdx.x - t * parts, lane = threadIdx.x;
+  const int32_t* rows = row_of + (int64_t)t * k;
+  // f(row) for the token's rows, with the data in `touch` waited for ahead of the first, so that no
+  // store waits for the one before
+  const auto for_rows = [&](auto touch, auto f) {
+    if constexpr (K > 0) {
+      int r[K];
+#pragma unroll
+      for (int j = 0; j < K; ++j) r[j] = rows[j];
+      touch();
+#pragma unroll
+      for (int j = 0; j < K; ++j)
+        if (r[j] >= 0) f(r[j]);
+    } else {
+      for (int j0 = 0; j0 < k; j0 += kRowBatch) {
+        int r[kRowBatch];
+#pragma unroll
+        for (int i = 0; i < kRowBatch; ++i) r[i] = rows[j0 + i < k ? j0 + i : k - 1];
+        touch();
+#pragma unroll
+        for (int i = 0; i < kRowBatch; ++i)
+          if (j0 + i < k && r[i] >= 0) f(r[i]);
+      }
+    }
+  };
+  if (SCALES && part == parts - 1) {  // the scale row, a vector per lane and pass
+    for (uint32_t v0 = 0; v0 < scale_vecs; v0 += 64) {
+      const uint32_t v = v0 + lane < scale_vecs ? v0 + lane : scale_vecs - 1;
+      const u32x4 d = x_scale[(int64_t)t * scale_vecs + v];
+      for_rows([&]() { asm volatile("" ::"v"(d)); }, [&](int row) {
+        if (v0 + lane < scale_vecs)
+          store_through_at((char*)recv_scale + (int64_t)row * (scale_vecs * 16), v * 16, d);
+      });
+    }
+    return;
+  }
+  const u32x4* src = x + (int64_t)t * row_vecs;
+  const uint32_t v0 = part * (64 * U) + lane;
+  u32x4 buf[U];
+#pragma unroll
+  for (int u = 0; u < U; ++u) {
+    uint32_t v = v0 + u * 64;
+    if (!EXACT && v >= row_vecs) v = row_vecs - 1;
+    buf[u] = __builtin_nontemporal_load(&src[v]);
+  }
+  for_rows([&]() {
+#pragma unroll
+    for (int u = 0; u < U; ++u) asm volatile("" ::"v"(buf[u]));
+  }, [&](int row) {
+    char* dst = (char*)recv + (int64_t)row * (row_vecs * 16);
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+      if (EXACT || v0 + u * 64 < row_vecs) store_through_at(dst, (v0 + u * 64) * 16, buf[u]);
+  });
 }
 
 // Several tokens per wavefront: all TPW * U loads of the wavefront are issued
@@ -178,33 +223,38 @@ __global__ __launch_bounds__(64) void k_pack_multi(const u32x4* __restrict__ x,
 // Measured at T = 16384 inside the step (payload, scales, combine in a loop):
 // token-ordered scatter with one token per wavefront +27 us, with four tokens
 // per wavefront +20 us, this form +10 us, for 33 MB; 224-byte rows scattered
-// among the payload's write stream are what is expensive, not the launch.
+// among the payload's write stream are what is expensive there, not the launch; in small batches,
+// where it is the launch, k_pack_split moves them.
 constexpr int kScaleThreads = 256;
 constexpr int kScaleVecs = 4;  // vectors per thread, each an independent chain of lookups
                                // (measured at T = 16384: 2 per thread -1.5 us, 4 -3 us, 8 +5 us
                                // against one vector per thread)
 
-// max_vecs = T * k * scale_vecs (every row the buffers hold); the rows of this step end at
-// status[0], which is read beside the first lookups rather than ahead of them.
+// max_vecs = T * k * scale_vecs (every row the buffers hold), first: the launch's first one; the rows of this
+// step end at status[0], which is read beside the first lookups rather than ahead of them.  row_magic: for
+// the vector's row, as in token_of, 0 where there are too many vectors for it.
+template <int K>
 __global__ __launch_bounds__(kScaleThreads) void k_scale_rows(
     const u32x4* __restrict__ x_scale, u32x4* __restrict__ recv_scale,
-    const int32_t* __restrict__ src_of, const int32_t* __restrict__ status, int k, int scale_vecs,
-    int64_t max_vecs) {
+    const int32_t* __restrict__ src_of, const int32_t* __restrict__ status, int k_rt,
+    uint32_t scale_vecs, uint32_t row_magic, int64_t max_vecs) {
+  const uint32_t k = K > 0 ? K : k_rt;
   const int64_t v0 = (int64_t)blockIdx.x * (kScaleThreads * kScaleVecs) + threadIdx.x;
-  int pair[kScaleVecs], col[kScaleVecs];
+  int pair[kScaleVecs];
+  uint32_t col[kScaleVecs];
 #pragma unroll
   for (int u = 0; u < kScaleVecs; ++u) {
-    const int64_t v = v0 + u * kScaleThreads;
-    const int row = (int)(v / scale_vecs);
-    col[u] = (int)(v - (int64_t)row * scale_vecs);
-    pair[u] = v < max_vecs ? src_of[row] : -1;
+    const int64_t v = v0 + u * kScaleThreads < max_vecs ? v0 + u * kScaleThreads : max_vecs - 1;
+    const uint32_t row = row_magic != 0 ? __umulhi((uint32_t)v, row_magic) : (uint32_t)(v / scale_vecs);
+    col[u] = (uint32_t)v - row * scale_vecs;
+    pair[u] = src_of[row];
   }
   const int64_t n_vecs = (int64_t)status[0] * scale_vecs;  // rows >= N are left untouched
   u32x4 val[kScaleVecs];
 #pragma unroll
   for (int u = 0; u < kScaleVecs; ++u) {
     if (v0 + u * kScaleThreads >= n_vecs) pair[u] = -1;
-    if (pair[u] >= 0) val[u] = x_scale[(int64_t)(pair[u] / k) * scale_vecs + col[u]];
+    if (pair[u] >= 0) val[u] = x_scale[(int64_t)((uint32_t)pair[u] / k) * scale_vecs + col[u]];
   }
 #pragma unroll
   for (int u = 0; u < kScaleVecs; ++u)
@@ -257,14 +307,27 @@ static PassShape pass_shape(int row_vecs, int split, int64_t rows, int max_vecs)
 
 template <int U, bool EXACT>
 static hipError_t launch_pack_t(eep_ctx* c, const int32_t* rows, const void* x, void* recv_x,
-                                int T, int parts, hipStream_t st) {
-  if (parts > 1)
-    hipLaunchKernelGGL((k_pack<U, EXACT, true>), dim3((unsigned)((int64_t)T * parts)), dim3(64), 0,
-                       st, (const u32x4*)x, rows, c->k, (int)(c->x_row_bytes / 16),
-                       (uint32_t)parts, part_magic(parts, (int64_t)T * parts), (u32x4*)recv_x);
-  else
-    hipLaunchKernelGGL((k_pack<U, EXACT, false>), dim3(T), dim3(64), 0, st, (const u32x4*)x,
-                       rows, c->k, (int)(c->x_row_bytes / 16), 1u, 0u, (u32x4*)recv_x);
+                                int T, hipStream_t st) {
+  hipLaunchKernelGGL((k_pack<U, EXACT>), dim3(T), dim3(64), 0, st, (const u32x4*)x, rows, c->k,
+                     (int)(c->x_row_bytes / 16), (u32x4*)recv_x);
+  return hipGetLastError();
+}
+
+template <int U, bool EXACT, bool SCALES>
+static hipError_t launch_pack_split_t(eep_ctx* c, const int32_t* rows, const void* x,
+                                      const float* x_scale, void* recv_x, float* recv_scale, int T,
+                                      int parts, hipStream_t st) {
+  static const decltype(&k_pack_split<U, EXACT, 0, SCALES>) of[kSplitMaxK + 1] = {
+      k_pack_split<U, EXACT, 0, SCALES>, k_pack_split<U, EXACT, 1, SCALES>,
+      k_pack_split<U, EXACT, 2, SCALES>, k_pack_split<U, EXACT, 3, SCALES>,
+      k_pack_split<U, EXACT, 4, SCALES>, k_pack_split<U, EXACT, 5, SCALES>,
+      k_pack_split<U, EXACT, 6, SCALES>, k_pack_split<U, EXACT, 7, SCALES>,
+      k_pack_split<U, EXACT, 8, SCALES>};
+  const int64_t grid = (int64_t)T * parts;
+  hipLaunchKernelGGL(of[c->k <= kSplitMaxK ? c->k : 0], dim3((unsigned)grid), dim3(64), 0, st,
+                     (const u32x4*)x, rows, c->k, (uint32_t)(c->x_row_bytes / 16), (uint32_t)parts,
+                     part_magic(parts, grid), (u32x4*)recv_x, (const u32x4*)x_scale,
+                     (u32x4*)recv_scale, (uint32_t)(c->scale_row_bytes / 16));
   return hipGetLastError();
 }
 
@@ -294,10 +357,26 @@ static int pack_tokens_per_wave(const PassShape& ps, int row_vecs, int T) {
   return tpw;
 }
 
-static hipError_t launch_pack_payload(eep_ctx* c, const int32_t* rows, const void* x, void* recv_x,
-                                      int T, hipStream_t st) {
+// (x_scale null: no scale rows, or not here)
+static hipError_t launch_pack_payload(eep_ctx* c, const int32_t* rows, const void* x,
+                                      const float* x_scale, void* recv_x, float* recv_scale, int T,
+                                      hipStream_t st) {
   const int row_vecs = (int)(c->x_row_bytes / 16);
   const PassShape ps = pass_shape(row_vecs, pack_split(T), T, kPackVecs);
+  if (x_scale != nullptr || ps.parts > 1) {
+#define EEP_PACK_SPLIT(U, SCALES)                                                                 \
+  return ps.exact ? launch_pack_split_t<U, true, SCALES>(c, rows, x, x_scale, recv_x, recv_scale, \
+                                                         T, ps.parts + SCALES, st)                \
+                  : launch_pack_split_t<U, false, SCALES>(c, rows, x, x_scale, recv_x, recv_scale, \
+                                                          T, ps.parts + SCALES, st)
+    if (x_scale != nullptr) {
+      if (ps.u == 1) EEP_PACK_SPLIT(1, true);
+      EEP_PACK_SPLIT(2, true);
+    }
+    if (ps.u == 1) EEP_PACK_SPLIT(1, false);
+    EEP_PACK_SPLIT(2, false);
+#undef EEP_PACK_SPLIT
+  }
   const int tpw = pack_tokens_per_wave(ps, row_vecs, T);
   if (tpw > 1) {
     switch (tpw * 16 + ps.u) {
@@ -319,8 +398,8 @@ static hipError_t launch_pack_payload(eep_ctx* c, const int32_t* rows, const voi
   switch (ps.u) {
 #define EEP_PACK_CASE(U)                                                                \
   case U:                                                                               \
-    return ps.exact ? launch_pack_t<U, true>(c, rows, x, recv_x, T, ps.parts, st)       \
-                    : launch_pack_t<U, false>(c, rows, x, recv_x, T, ps.parts, st);
+    return ps.exact ? launch_pack_t<U, true>(c, rows, x, recv_x, T, st)                 \
+                    : launch_pack_t<U, false>(c, rows, x, recv_x, T, st);
     EEP_PACK_CASE(14) EEP_PACK_CASE(13) EEP_PACK_CASE(12) EEP_PACK_CASE(11) EEP_PACK_CASE(10)
     EEP_PACK_CASE(9) EEP_PACK_CASE(8) EEP_PACK_CASE(7) EEP_PACK_CASE(6) EEP_PACK_CASE(5)
     EEP_PACK_CASE(4) EEP_PACK_CASE(3) EEP_PACK_CASE(2) EEP_PACK_CASE(1)
@@ -333,19 +412,24 @@ static hipError_t launch_pack_any(eep_ctx* c, const int32_t* rows, const void* x
                                   const float* x_scale, void* recv_x, float* recv_scale, int T,
                                   hipStream_t st) {
   if (T == 0) return hipSuccess;
+  // Small batches: the scale rows go with the payload, in wavefronts of their own.
+  const bool together = x_scale != nullptr && T < kPackSplitBelow &&
+                        pass_shape((int)(c->x_row_bytes / 16), pack_split(T), T, kPackVecs).u <= 2;
   hipError_t e = in_launches(T, max_blocks(64), [&](int64_t t0, int64_t n) {
-    return launch_pack_payload(c, rows + t0 * c->k, (const char*)x + t0 * c->x_row_bytes, recv_x,
-                               (int)n, st);
+    return launch_pack_payload(c, rows + t0 * c->k, (const char*)x + t0 * c->x_row_bytes,
+                               together ? x_scale : nullptr, recv_x, recv_scale, (int)n, st);
   });
-  if (e != hipSuccess || x_scale == nullptr) return e;
+  if (e != hipSuccess || x_scale == nullptr || together) return e;
   const int scale_vecs = (int)(c->scale_row_bytes / 16);
   const int64_t vecs = (int64_t)T * c->k * scale_vecs;
   const int64_t per_block = (int64_t)kScaleThreads * kScaleVecs;
   const int64_t blocks = (vecs + per_block - 1) / per_block;
   if (blocks > max_blocks(kScaleThreads)) return hipErrorInvalidValue;
-  hipLaunchKernelGGL(k_scale_rows, dim3((unsigned)blocks), dim3(kScaleThreads), 0, st,
-                     (const u32x4*)x_scale, (u32x4*)recv_scale, c->src_of, c->status, c->k,
-                     scale_vecs, vecs);
+  // (row = v * magic >> 32 is exact while vecs * scale_vecs < 2^32)
+  const uint32_t magic = scale_vecs > 1 ? part_magic(scale_vecs, vecs) : 0;
+  hipLaunchKernelGGL((c->k == 8 ? k_scale_rows<8> : k_scale_rows<0>), dim3((unsigned)blocks),
+                     dim3(kScaleThreads), 0, st, (const u32x4*)x_scale, (u32x4*)recv_scale, c->src_of,
+                     c->status, c->k, (uint32_t)scale_vecs, magic, vecs);
   return hipGetLastError();
 }
 
