@@ -7,6 +7,8 @@
 // every kernel is bound by HBM traffic, so the design rules are 16-byte
 // accesses, whole 64-lane wavefronts on contiguous 1 KiB spans, each input byte
 // read once, and enough independent loads in flight per lane.
+#include <type_traits>
+
 #include "eep_internal.hpp"
 
 namespace eep {
@@ -875,12 +877,16 @@ __device__ __forceinline__ int row_if_arrived(const DetectArgs& d, int64_t pair0
 // 1024 channels, T = 1024 / 2048: 22.0 / 29.2 and 17.0 / 22.9; with a scaling stage between, where
 // nothing can meet, within 1 % either way.
 //
-// Other top-k loads one row at a time: in batches of 4 to 8 with uniform branches top-10 took 13.75 us
-// instead of 13.9 (T = 32) and 126.6 instead of 126.0 (T = 4096, 4096 channels), top-3 within 0.3 %.
+// k is a compile-time number up to kCombineMaxK; a larger one goes in batches of 8 and 4 rows.  One row at a
+// time, each behind its index, top-10 took (whole steps, 4096 channels, T = 32 / 256) 12.5 / 16.9 us instead
+// of 9.7 / 15.5, top-3 9.2 / 10.4 instead of 8.7 / 9.9, top-5 of 512 tokens 21.9 instead of 21.1; at 4096
+// tokens, where other wavefronts fill the time, 124.8 instead of 123.0 and the same.
 //
 // DETECT: the wait for the ranks' signals is part of the kernel (DetectArgs above); row_of
 // is then not read-only, because dropped pairs are struck from it, and lane j keeps the row of
 // pair j from the one time it was read.
+constexpr int kCombineMaxK = 10;
+
 template <bool Y_BF16, bool OUT_BF16, int K, bool DETECT>
 __global__ __launch_bounds__(64) void k_combine(const int32_t* row_of,
                                                 const u32x4* __restrict__ y, int k, int row_vecs,
@@ -963,12 +969,36 @@ __global__ __launch_bounds__(64) void k_combine(const int32_t* row_of,
         if (r[j] >= 0) accumulate<Y_BF16>(acc, d[j], ws[j]);
     }
   } else {
-    for (int j = 0; j < k; ++j) {
-      int row = row_at(j);
-      if (row < 0) continue;
-      u32x4 d = __builtin_nontemporal_load(&y[(int64_t)row * row_vecs + v]);
-      accumulate<Y_BF16>(acc, d, ws[j]);
+    const auto batch = [&](auto size, int j0) {
+      constexpr int B = decltype(size)::value;
+      int r[B];
+      bool all = true;
+#pragma unroll
+      for (int i = 0; i < B; ++i) {
+        r[i] = row_at(j0 + i);
+        all &= r[i] >= 0;
+      }
+      u32x4 d[B];
+      if (__builtin_expect(all, 1)) {
+#pragma unroll
+        for (int i = 0; i < B; ++i) d[i] = __builtin_nontemporal_load(&y[(int64_t)r[i] * row_vecs + v]);
+#pragma unroll
+        for (int i = 0; i < B; ++i) accumulate<Y_BF16>(acc, d[i], ws[j0 + i]);
+      } else {
+        for (int i = 0; i < B; ++i) {
+          const int row = row_at(j0 + i);
+          if (row < 0) continue;
+          accumulate<Y_BF16>(acc, __builtin_nontemporal_load(&y[(int64_t)row * row_vecs + v]), ws[j0 + i]);
+        }
+      }
+    };
+    int j = 0;
+    for (; j + 8 <= k; j += 8) batch(std::integral_constant<int, 8>(), j);
+    if (j + 4 <= k) {
+      batch(std::integral_constant<int, 4>(), j);
+      j += 4;
     }
+    for (; j < k; ++j) batch(std::integral_constant<int, 1>(), j);
   }
   if (!DETECT || !past_end) store_out<Y_BF16, OUT_BF16>(out_row, v, acc);
 }
@@ -1015,11 +1045,10 @@ static hipError_t launch_combine_t(eep_ctx* c, const void* y, const float* w, vo
                      grid, block, 0, st, c->row_of + p0, (const u32x4*)y, c->k, row_vecs,   \
                      (uint32_t)parts, magic, paired ? (int)n : 0, w + p0, to, d);           \
   break;
-      EEP_COMBINE_K(case 8, 8)
-      EEP_COMBINE_K(case 6, 6)
-      EEP_COMBINE_K(case 4, 4)
-      EEP_COMBINE_K(case 2, 2)
-      EEP_COMBINE_K(case 1, 1)
+      EEP_COMBINE_K(case 1, 1) EEP_COMBINE_K(case 2, 2) EEP_COMBINE_K(case 3, 3)
+      EEP_COMBINE_K(case 4, 4) EEP_COMBINE_K(case 5, 5) EEP_COMBINE_K(case 6, 6)
+      EEP_COMBINE_K(case 7, 7) EEP_COMBINE_K(case 8, 8) EEP_COMBINE_K(case 9, 9)
+      EEP_COMBINE_K(case 10, 10)
       EEP_COMBINE_K(default, 0)
 #undef EEP_COMBINE_K
     }
