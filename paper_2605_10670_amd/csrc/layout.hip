@@ -542,7 +542,7 @@ __global__ __launch_bounds__(kFusedThreads) void k_scan_position(
 
 // ---------------------------------------------------------------------------
 // The whole layout in ONE launch, for batches up to 16384 pairs.  A workgroup owns a
-// share of the tokens, whole source ranks.  It counts the pairs per slot of ALL tokens,
+// share of the tokens.  It counts the pairs per slot of ALL tokens,
 // those ahead of its share, its own and those behind it apart, so it needs nothing from
 // the others; then it places its own.  Bound by latency and by instructions: the launch
 // (1.9 us for an empty kernel), one round of global loads, LDS round trips, and, as every
@@ -557,9 +557,12 @@ __global__ __launch_bounds__(kFusedThreads) void k_scan_position(
 // 3.9 / 4.3 / 4.6 us (3.9 / 4.8 / 6.2), 768 / 1024 / 1536 / 2048 4.9 / 5.1 / 5.6 / 6.0 (7.6 / 7.7 / 7.8 / 7.9),
 // 3072 / 4096 7.3 / 8.6 (8.1 / 8.4); with a Zipf router, whose hot slots' counts are one LDS word
 // for many lanes, 2048 7.2 (7.7), 4096 10.7 (8.1).  T = 1024 of 64 ranks x 9 slots 5.8 (12.0), top-2 of
-// 32 ranks 4.0 (7.4), top-6 of 24 ranks 4.2 (7.8).  So up to 16384 pairs; and no share may have more
-// than 2048 pairs, of which 4 ranks or fewer are soon short (2 ranks, top-8: T = 512 5.3 (5.9), T = 1024,
-// 4096 pairs to a share, 8.5 (7.3)).  Shares of about 64 tokens; 512 threads, 1024 for more than
+// 32 ranks 4.0 (7.4), top-6 of 24 ranks 4.2 (7.8).  So up to 16384 pairs.  Shares of about 64 tokens, whole
+// source ranks or, where a rank has at least 768 pairs, a part of one, whose first then also counts the
+// rank's other tokens for the rank's totals: 8 ranks, T = 1024 / 2048 5.4 / 6.4 (whole ranks 5.5 / 7.3; two
+// launches 8.0 / 8.2), 2 ranks, T = 512 / 1024 / 2048 4.5 / 5.4 / 6.8 (5.4 / 7.1 / - ; 5.9 / 7.2 / 7.8), 4 ranks,
+// top-3, T = 1024 4.2 (4.6; 7.2); with fewer pairs it costs as much as it gives (32 ranks, top-2, T = 4096, 256
+// pairs to a rank: 5.5 in parts, 5.1).  512 threads, 1024 for more than
 // 1024 items (T = 256 / 1024 / 2048: 4.3 / 5.1 / 6.2 with 512, 4.6 / 5.0 / 6.0 with 1024).
 //
 // Up to 512 tokens and 4096 pairs there are 8 workgroups, however many ranks.
@@ -583,7 +586,7 @@ constexpr int kSoloPairs = 3072;
 constexpr int kOnceThreads = 1024;
 constexpr int kOnceMaxK = 10;  // compile-time top-k, a token to a lane, up to here
 constexpr int kPairPairs = 512;  // a pair to a lane up to here
-constexpr int kOncePairs = 16384, kSharePairs = 2048, kShareTokens = 64;
+constexpr int kOncePairs = 16384, kShareTokens = 64, kPartPairs = 768;
 
 // Element i of a small global array: a 32-bit offset from a scalar address, which takes no 64-bit
 // arithmetic per lane.
@@ -696,13 +699,19 @@ __device__ __forceinline__ int bits_between(const uint32_t* bm, int lo, int hi) 
 // Row stride of a share's token bitmaps in words; odd, so that lanes on different slots reading
 // the same word index hit different banks.
 __host__ __device__ inline int share_stride(int tokens) { return ((tokens + 31) / 32) | 1; }
-constexpr int kRegions = 3;  // tokens ahead of the share, its own, behind it
+// Counts per slot: tokens ahead of the share, its own, those behind it, and of these the ones that belong
+// to the share's source rank where that is several shares and this its first.
+__host__ __device__ constexpr int regions(bool parts) { return parts ? 4 : 3; }
+// Tokens of a share: `ranks` whole source ranks, or one of `subs` parts of one.
+__host__ __device__ inline uint32_t share_tokens(uint32_t tokens_per_rank, uint32_t ranks, uint32_t subs) {
+  return subs == 1 ? ranks * tokens_per_rank : (tokens_per_rank + subs - 1) / subs;
+}
 // Words that start at zero: counts and bitmaps, a whole number of 16 bytes.
-__host__ __device__ inline uint32_t once_zeros(uint32_t P, uint32_t stride) {
-  return ((P + kSinks) * (kRegions + stride) + 3) / 4 * 4;
+__host__ __device__ inline uint32_t once_zeros(uint32_t P, uint32_t stride, bool parts) {
+  return ((P + kSinks) * (regions(parts) + stride) + 3) / 4 * 4;
 }
 inline size_t once_lds_bytes(int E, int P, int R, int T, int tokens, int k) {
-  return sizeof(int32_t) * (once_zeros(P, share_stride(tokens)) + route_table_ints(E, P, R) +
+  return sizeof(int32_t) * (once_zeros(P, share_stride(tokens), true) + route_table_ints(E, P, R) +
                             (k > kOnceMaxK ? (size_t)T * k : E + 1) + (P + 1) + (size_t)tokens * k);
 }
 
@@ -731,15 +740,16 @@ __device__ __forceinline__ int opaque(int x) {
   return x;
 }
 
-// KC: compile-time k, or 0 for any.  TOKEN: a lane takes a token, otherwise a pair.
+// KC: compile-time k, or 0 for any.  TOKEN: a lane takes a token, otherwise a pair.  PARTS: a share is a part
+// of a source rank, one of `subs`, otherwise `ranks` whole ones.
 // Four words hold the shape (T and tokens per rank; E and P; R and the source ranks of a share; S,
-// policy << 12, k << 13, wavefronts << 19), so that it arrives in registers with the first pointers.
-template <int KC, bool TOKEN, bool LARGE>
+// policy << 12, k << 13, wavefronts << 19, shares in a rank << 24), so that it arrives in registers with the first pointers.
+template <int KC, bool TOKEN, bool LARGE, bool PARTS>
 __global__ __launch_bounds__(kOnceThreads) void k_layout_once(
     const int32_t* __restrict__ topk_idx, const int32_t* __restrict__ l2p_off,
     const int32_t* __restrict__ l2p_list, const int32_t* __restrict__ active,
     const int32_t* __restrict__ mem_version, uint32_t T_rank, uint32_t E_P, uint32_t R_share,
-    uint32_t S_policy_k_waves, const int32_t* __restrict__ tbl_version, int32_t* __restrict__ slot_of,
+    uint32_t S_policy_k_waves_subs, const int32_t* __restrict__ tbl_version, int32_t* __restrict__ slot_of,
     int32_t* __restrict__ row_of, int32_t* __restrict__ src_of, int32_t* __restrict__ cnt_src,
     int32_t* __restrict__ count, int32_t* __restrict__ offset, int32_t* __restrict__ rank_count,
     int32_t* __restrict__ rank_offset, int32_t* __restrict__ status,
@@ -747,9 +757,10 @@ __global__ __launch_bounds__(kOnceThreads) void k_layout_once(
   constexpr uint32_t N = TOKEN ? KC : 1;
   const uint32_t T = T_rank & 0xffff, tokens_per_rank = T_rank >> 16;
   const uint32_t E = E_P & 0xffff, R = R_share & 0xffff, ranks = R_share >> 16;
-  const uint32_t S = S_policy_k_waves & 0xfff, policy = S_policy_k_waves >> 12 & 1;
-  const uint32_t k = KC > 0 ? KC : S_policy_k_waves >> 13 & 63;
-  const uint32_t waves = S_policy_k_waves >> 19, nt = waves * 64;
+  const uint32_t S = S_policy_k_waves_subs & 0xfff, policy = S_policy_k_waves_subs >> 12 & 1;
+  const uint32_t k = KC > 0 ? KC : S_policy_k_waves_subs >> 13 & 63;
+  const uint32_t waves = S_policy_k_waves_subs >> 19 & 31, nt = waves * 64;
+  const uint32_t subs = PARTS ? S_policy_k_waves_subs >> 24 : 1;
   const uint32_t tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const uint32_t per_item = TOKEN ? 1 : k, items = T * per_item;
   const auto load = [&](uint32_t i, int (&e)[N]) { __builtin_memcpy(e, &at(topk_idx, i * N), sizeof(e)); };
@@ -768,8 +779,8 @@ __global__ __launch_bounds__(kOnceThreads) void k_layout_once(
   const int several_v = vector_load(&mem_version[1]);
 
   extern __shared__ __align__(16) int32_t smem[];
-  const uint32_t tokens = ranks * tokens_per_rank, stride = share_stride(tokens);
-  const uint32_t zeros = once_zeros(E_P >> 16, stride);
+  const uint32_t tokens = share_tokens(tokens_per_rank, ranks, subs), stride = share_stride(tokens);
+  const uint32_t zeros = once_zeros(E_P >> 16, stride, PARTS);
   int32_t* s_tab = smem + zeros;
 #pragma nounroll
   for (uint32_t i = tid * 4; i < zeros; i += nt * 4) *(int4*)(smem + i) = make_int4(0, 0, 0, 0);
@@ -780,9 +791,15 @@ __global__ __launch_bounds__(kOnceThreads) void k_layout_once(
 #pragma nounroll
     for (uint32_t i = tid; i < items; i += nt) s_idx[i] = i == tid ? e[0] : at(topk_idx, i);
   }
-  const bool alone = ranks < R && __builtin_amdgcn_readfirstlane(several_v) != 0;
+  const bool alone = (PARTS || ranks < R) && __builtin_amdgcn_readfirstlane(several_v) != 0;
   uint32_t share = blockIdx.x;
-  if (share > 0 && (alone || share * ranks >= R)) return;
+  // PARTS: the share's rank (share / subs, by way of float), and which of the rank's shares it is
+  const auto rank_of_part = [&]() {
+    return (uint32_t)__builtin_amdgcn_readfirstlane(
+        (uint32_t)(((float)share + 0.5f) * __builtin_amdgcn_rcpf((float)subs)));
+  };
+  uint32_t rank0 = PARTS ? rank_of_part() : 0, sub = share - rank0 * subs;
+  if (share > 0 && (alone || (PARTS ? rank0 : share * ranks) >= R)) return;
   __syncthreads();
   bool repeats = false;
   if constexpr (TOKEN) {
@@ -792,17 +809,24 @@ __global__ __launch_bounds__(kOnceThreads) void k_layout_once(
   }
 
   // One round, over the whole batch; alone, a second one for every share, over its tokens.
-  uint32_t end = items, lo = alone ? T : share * tokens;
+  uint32_t lo = T;
+  const auto first_token = [&]() {
+    return !PARTS ? share * tokens
+                  : min(rank0 * tokens_per_rank + sub * tokens, (rank0 + 1) * tokens_per_rank);
+  };
+  const auto last_token = [&]() { return min(lo + tokens, PARTS ? (rank0 + 1) * tokens_per_rank : T); };
+  uint32_t end = items;
+  if (!alone) lo = first_token();
   int rows = 0;
   for (uint32_t round = 0;; ++round) {
     // (Opaque, or whatever follows from it would be computed ahead of the loop by every wavefront.)
     const uint32_t P = opaque(E_P >> 16), P2 = P + kSinks;
-    int32_t* const s_cnt = smem;                          // [kRegions][P2] pairs per slot
-    uint32_t* const s_bm = (uint32_t*)(smem + kRegions * P2);  // [P2][stride] bitmap of the share's tokens per slot
+    int32_t* const s_cnt = smem;                          // [regions][P2] pairs per slot
+    uint32_t* const s_bm = (uint32_t*)(smem + regions(PARTS) * P2);  // [P2][stride] bitmap of the share's tokens per slot
     int32_t* const s_offset = smem + opaque(zeros + route_table_ints(E, P, R) +
                                             (KC > 0 ? E + 1 : items));  // [P+1] exclusive scan of the totals
     int32_t* const s_slot = s_offset + P + 1;             // [tokens*k] slots of the share's pairs
-    const uint32_t hi = min(lo + tokens, T);
+    const uint32_t hi = !PARTS ? min(lo + tokens, T) : lo < T ? last_token() : T;
 #pragma nounroll
     while (item < end) {
       const uint32_t now = item;
@@ -828,6 +852,10 @@ __global__ __launch_bounds__(kOnceThreads) void k_layout_once(
       int32_t* cnt = s_cnt + (own ? P2 : t < lo ? 0 : 2 * P2);
 #pragma unroll
       for (uint32_t j = 0; j < N; ++j) atomicAdd(&cnt[p[j]], 1);
+      if (PARTS && sub == 0 && !alone && t >= hi && t < (rank0 + 1) * tokens_per_rank) {
+#pragma unroll
+        for (uint32_t j = 0; j < N; ++j) atomicAdd(&s_cnt[3 * P2 + p[j]], 1);
+      }
       if (own) {
         const uint32_t tl = t - lo;
         uint32_t* bm = s_bm + (tl >> 5);
@@ -861,12 +889,17 @@ __global__ __launch_bounds__(kOnceThreads) void k_layout_once(
     }
     // pairs per (source rank, slot): the tokens of a source rank are a bit range
     if (n > 0) {
-      const uint32_t rank0 = share * ranks, mine = min(R - rank0, ranks);
+      const uint32_t rank = PARTS ? rank0 : share * ranks, mine = min(R - rank, ranks);
 #pragma nounroll
       for (uint32_t p = tid; p < P; p += nt) {
         const uint32_t* bm = &s_bm[__umul24(p, stride)];
-        uint32_t to = rank0 * P + p;
-        if (tokens <= 64) {
+        uint32_t to = rank * P + p;
+        if constexpr (PARTS) {
+          if (alone)
+            at(cnt_src, to) = s_cnt[P2 + p] + (sub == 0 ? 0 : at(cnt_src, to));
+          else if (sub == 0)
+            at(cnt_src, to) = s_cnt[P2 + p] + s_cnt[3 * P2 + p];
+        } else if (tokens <= 64) {
           uint64_t bits = bm[0];
           if (stride > 1) bits |= (uint64_t)bm[1] << 32;
           const uint64_t mask = ~0ull >> (64 - tokens_per_rank);
@@ -912,8 +945,12 @@ __global__ __launch_bounds__(kOnceThreads) void k_layout_once(
       write_step_tables(nt, s_offset, dead, masked, version, count, offset, rank_count,
                                       rank_offset, status, step_epoch, R, S, P);
     share = round;
-    lo = share * tokens;
-    if (!alone || lo >= T) break;
+    if constexpr (PARTS) {
+      rank0 = rank_of_part();
+      sub = share - rank0 * subs;
+    }
+    if (!alone || (PARTS ? rank0 : share * ranks) >= R) break;
+    lo = first_token();
     __syncthreads();
 #pragma nounroll
     for (uint32_t q = tid; q < P2; q += nt) {
@@ -923,7 +960,7 @@ __global__ __launch_bounds__(kOnceThreads) void k_layout_once(
 #pragma nounroll
     for (uint32_t q = tid; q < P2 * stride; q += nt) s_bm[q] = 0;
     item = lo * per_item + tid;
-    end = min(lo + tokens, T) * per_item;
+    end = last_token() * per_item;
     if (item < end) {
       load(item, e);
       if constexpr (TOKEN) repeats = any_repeats(e);
@@ -937,8 +974,20 @@ inline size_t small_lds_bytes(int E, int P, int R, int T, int k) {
   return sizeof(int32_t) * (route_table_ints(E, P, R) + P + (P + 1) +
                             (size_t)P * share_stride(T) + (size_t)T * k);
 }
-// Source ranks in a share, for about `shares` of them.
-static int share_ranks(int R, int shares) { return shares > 0 ? (R + shares - 1) / shares : R; }
+// What a share holds: source ranks, or a part of one.
+struct ShareSize {
+  int ranks, subs;
+  int tokens(int tokens_per_rank) const { return (int)share_tokens(tokens_per_rank, ranks, subs); }
+  int count(int R) const { return subs > 1 ? R * subs : (R + ranks - 1) / ranks; }
+};
+// For at most `shares` of them, or (0) of about kShareTokens tokens.
+static ShareSize share_size(int E, int P, int R, int tokens_per_rank, int k, int shares) {
+  ShareSize s = {shares > 0 ? (R + shares - 1) / shares : kShareTokens / tokens_per_rank,
+                 shares > 0 ? shares / R : (tokens_per_rank + kShareTokens / 2) / kShareTokens};
+  if (s.ranks < 1) s.ranks = 1;
+  if (s.subs < 1 || tokens_per_rank * k < kPartPairs || large_tables(E, P, R, kOnceThreads)) s.subs = 1;
+  return s;
+}
 
 // ---------------------------------------------------------------------------
 // Many tiles (> 64, the prefill regime): three launches.
@@ -1373,23 +1422,23 @@ static auto map_count_for(int k, int pairs) {
   return pairs <= kMapThreads ? map_count_for_k<1, WIDE>(k)
        : pairs <= 2 * kMapThreads ? map_count_for_k<2, WIDE>(k) : map_count_for_k<4, WIDE>(k);
 }
-template <bool LARGE>
-static decltype(&k_layout_once<0, false, LARGE>) layout_once_for(int k, bool token) {
-  if (!token) return k == 8 ? k_layout_once<8, false, LARGE> : k == 4 ? k_layout_once<4, false, LARGE>
-                   : k == 2 ? k_layout_once<2, false, LARGE> : k == 1 ? k_layout_once<1, false, LARGE>
-                                                              : k_layout_once<0, false, LARGE>;
+template <bool LARGE, bool PARTS>
+static decltype(&k_layout_once<0, false, LARGE, PARTS>) layout_once_for(int k, bool token) {
+  if (!token) return k == 8 ? k_layout_once<8, false, LARGE, PARTS> : k == 4 ? k_layout_once<4, false, LARGE, PARTS>
+                   : k == 2 ? k_layout_once<2, false, LARGE, PARTS> : k == 1 ? k_layout_once<1, false, LARGE, PARTS>
+                                                              : k_layout_once<0, false, LARGE, PARTS>;
   switch (k) {
-    case 1: return k_layout_once<1, true, LARGE>;
-    case 2: return k_layout_once<2, true, LARGE>;
-    case 3: return k_layout_once<3, true, LARGE>;
-    case 4: return k_layout_once<4, true, LARGE>;
-    case 5: return k_layout_once<5, true, LARGE>;
-    case 6: return k_layout_once<6, true, LARGE>;
-    case 7: return k_layout_once<7, true, LARGE>;
-    case 8: return k_layout_once<8, true, LARGE>;
-    case 9: return k_layout_once<9, true, LARGE>;
-    case 10: return k_layout_once<10, true, LARGE>;
-    default: return k_layout_once<0, false, LARGE>;
+    case 1: return k_layout_once<1, true, LARGE, PARTS>;
+    case 2: return k_layout_once<2, true, LARGE, PARTS>;
+    case 3: return k_layout_once<3, true, LARGE, PARTS>;
+    case 4: return k_layout_once<4, true, LARGE, PARTS>;
+    case 5: return k_layout_once<5, true, LARGE, PARTS>;
+    case 6: return k_layout_once<6, true, LARGE, PARTS>;
+    case 7: return k_layout_once<7, true, LARGE, PARTS>;
+    case 8: return k_layout_once<8, true, LARGE, PARTS>;
+    case 9: return k_layout_once<9, true, LARGE, PARTS>;
+    case 10: return k_layout_once<10, true, LARGE, PARTS>;
+    default: return k_layout_once<0, false, LARGE, PARTS>;
   }
 }
 
@@ -1415,7 +1464,7 @@ int layout_small_workgroups(int E, int P, int R, int T, int k, bool solo) {
   if (T < 1 || T > (solo ? kSoloTokens : kSmallTokens) ||
       T * k > (solo ? kSoloPairs : kSmallPairs) || P + kSinks > kEntrySlots ||
       small_lds_bytes(E, P, R, T, k) > kLayoutLdsLimit ||
-      once_lds_bytes(E, P, R, T, share_ranks(R, solo ? 1 : kSmallBlocks) * (T / R), k) > kLayoutLdsLimit)
+      once_lds_bytes(E, P, R, T, share_size(E, P, R, T / R, k, solo ? 1 : kSmallBlocks).tokens(T / R), k) > kLayoutLdsLimit)
     return 0;
   return solo ? 1 : kSmallBlocks;
 }
@@ -1433,26 +1482,28 @@ hipError_t launch_layout(const LayoutIO& c, int T, hipStream_t st) {
   const float inv_S = 1.0f / (float)c.S;
   const bool solo = c.mask_may_change || writes_its_input(c, T);
   const int small = layout_small_workgroups(c.E, c.P, c.R, T, c.k, solo);
-  int ranks = share_ranks(c.R, small), grid = small;
-  if (small == 0) {
-    ranks = g.tokens_per_rank < kShareTokens ? kShareTokens / g.tokens_per_rank : 1;
-    if (!solo && c.k <= kOnceMaxK && (int64_t)T * c.k <= kOncePairs &&
-        ranks * g.tokens_per_rank * c.k <= kSharePairs && c.P + kSinks <= kEntrySlots &&
-        once_lds_bytes(c.E, c.P, c.R, T, ranks * g.tokens_per_rank, c.k) <= kLayoutLdsLimit)
-      grid = (c.R + ranks - 1) / ranks;
-  }
+  const ShareSize share = share_size(c.E, c.P, c.R, g.tokens_per_rank, c.k, small);
+  int grid = small;
+  if (small == 0 && !solo && c.k <= kOnceMaxK && (int64_t)T * c.k <= kOncePairs &&
+      c.P + kSinks <= kEntrySlots && share.subs < 256 &&
+      once_lds_bytes(c.E, c.P, c.R, T, share.tokens(g.tokens_per_rank), c.k) <= kLayoutLdsLimit)
+    grid = share.count(c.R);
   if (grid > 0) {
     const bool token = c.k <= kOnceMaxK && !(T * c.k <= kPairPairs && (c.k & (c.k - 1)) == 0);
     int nt = c.P > c.E ? c.P : c.E + 1;  // threads: for the tables, and for the items
     const int most = (token ? T : 2 * T * c.k) > kOnceThreads ? kOnceThreads : kOnceThreads / 2;
     nt = nt < most ? most : nt < kOnceThreads ? (nt + 63) / 64 * 64 : kOnceThreads;
-    auto kern = large_tables(c.E, c.P, c.R, nt) ? layout_once_for<true>(c.k, token) : layout_once_for<false>(c.k, token);
+    const bool large = large_tables(c.E, c.P, c.R, nt);
+    auto kern = large ? layout_once_for<true, false>(c.k, token)
+                : share.subs > 1 ? layout_once_for<false, true>(c.k, token)
+                                 : layout_once_for<false, false>(c.k, token);
     hipLaunchKernelGGL(kern, dim3(grid), dim3(nt),
-                       once_lds_bytes(c.E, c.P, c.R, T, ranks * g.tokens_per_rank, c.k), st, c.topk_idx,
+                       once_lds_bytes(c.E, c.P, c.R, T, share.tokens(g.tokens_per_rank), c.k), st, c.topk_idx,
                        c.l2p_off, c.l2p_list, c.active, c.mem_version,
                        (uint32_t)T | (uint32_t)g.tokens_per_rank << 16, (uint32_t)c.E | (uint32_t)c.P << 16,
-                       (uint32_t)c.R | (uint32_t)ranks << 16,
-                       (uint32_t)c.S | (uint32_t)c.policy << 12 | (uint32_t)c.k << 13 | (uint32_t)(nt / 64) << 19,
+                       (uint32_t)c.R | (uint32_t)share.ranks << 16,
+                       (uint32_t)c.S | (uint32_t)c.policy << 12 | (uint32_t)c.k << 13 | (uint32_t)(nt / 64) << 19 |
+                           (uint32_t)share.subs << 24,
                        c.tbl_version, c.slot_of, c.row_of,
                        c.src_of, c.cnt_src, c.count, c.offset, c.rank_count, c.rank_offset, c.status,
                        c.step_epoch);

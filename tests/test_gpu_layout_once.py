@@ -1,5 +1,5 @@
-"""The one-launch layout at the edges of its rules: 16384 pairs and 2048 pairs to a share and the next
-size, shares of one and of several source ranks, every compile-time top-k, batches that a lane takes
+"""The one-launch layout at the edges of its rules: 16384 pairs and the next size, shares of one and of
+several source ranks and of a part of one (the last part short or empty), every compile-time top-k, batches that a lane takes
 several tokens of, tables larger than a workgroup, experts with none, two, three and more than 32 live
 replicas.  Every field bit-equal to the oracle, with dead ranks, masked, repeated and uncovered pairs;
 and the same after the instance got a second context, when one workgroup does it all."""
@@ -18,7 +18,7 @@ SHAPES = [
     (2048, 8, 32, 9, 256), (2080, 8, 32, 9, 256), (1638, 10, 2, 9, 16), (1600, 10, 32, 3, 90),
     (1816, 9, 8, 4, 30), (585, 7, 65, 3, 130), (1024, 5, 4, 6, 16), (512, 4, 1, 9, 8), (516, 4, 1, 9, 8),
     (8192, 2, 16, 6, 40), (5456, 3, 11, 4, 20), (16384, 1, 64, 2, 100), (600, 2, 150, 8, 1100),
-    (64, 8, 32, 9, 256), (72, 8, 24, 9, 200), (1360, 12, 16, 4, 32), (720, 6, 48, 4, 12), (700, 4, 20, 40, 9),
+    (64, 8, 32, 9, 256), (72, 8, 24, 9, 200), (194, 8, 2, 9, 16), (770, 10, 2, 9, 16), (26, 32, 1, 40, 32), (82, 10, 1, 12, 11), (1360, 12, 16, 4, 32), (720, 6, 48, 4, 12), (700, 4, 20, 40, 9),
 ]
 
 
