@@ -1,5 +1,5 @@
-"""ctypes binding of libeep.so (include/eep.h).  Argument marshalling only:
-every step of the path runs in the library's HIP kernels.  Device buffers are
+"""Binding of libeep.so (include/eep.h): ctypes, and native/marshal.cpp for the per-step calls.
+Argument marshalling only: every step of the path runs in the library's HIP kernels.  Device buffers are
 torch tensors (or raw integer addresses); streams are raw hipStream_t handles
 (`torch.cuda.Stream.cuda_stream`).
 """
@@ -53,12 +53,14 @@ class _LayoutOut(ctypes.Structure):
 
 
 _lib = None
+_call = None        # native/marshal.cpp: call(address, kinds, arguments...) -> return code
+_address = {}       # of the entry points that are called through it
 
 
 def load():
     """Load libeep.so, building it first if it does not exist; raises if that fails
     (there is no fallback path)."""
-    global _lib
+    global _lib, _call
     if _lib is not None:
         return _lib
     if not os.path.exists(LIB_PATH):
@@ -126,6 +128,19 @@ def load():
         fn = getattr(lib, name)
         fn.argtypes = argtypes
         fn.restype = ctypes.c_int
+    for name in sig:
+        _address[name] = ctypes.cast(getattr(lib, name), ctypes.c_void_p).value
+    try:
+        from . import _marshal
+    except ImportError:
+        try:
+            from . import build as _build
+            _build.build_marshal()
+            from . import _marshal
+        except Exception as exc:
+            raise RuntimeError(f"_marshal.so is missing and could not be built ({exc}); "
+                               "there is no fallback path") from exc
+    _call = _marshal.call
     lib.eep_noalloc_scratch_needed.argtypes = [i32, i32, i32]
     lib.eep_noalloc_scratch_needed.restype = i64
     lib.eep_strerror.argtypes = [ctypes.c_int]
@@ -286,7 +301,9 @@ class Graph:
         self._h = handle
 
     def launch(self, stream):
-        _check(load().eep_graph_launch(self._h, _stream(stream)), "eep_graph_launch")
+        code = _call(_address["eep_graph_launch"], "hs", self._h.value if self._h else 0, stream)
+        if code != OK:
+            _check(code, "eep_graph_launch")
 
     def counters(self):
         c = (ctypes.c_int64 * 3)()
@@ -390,35 +407,33 @@ class Context:
         return out
 
     # -- per-step calls ------------------------------------------------------
+    def _step(self, name, kinds, *args):
+        code = _call(_address[name], kinds, self._h.value or 0, *args)
+        if code != OK:
+            _check(code, name, self._h)
+
     def dispatch_layout(self, topk_idx, T, stream=None):
-        _check(load().eep_dispatch_layout(self._h, _ptr(topk_idx), T, _stream(stream)),
-               "eep_dispatch_layout", self._h)
+        self._step("eep_dispatch_layout", "hpis", topk_idx, T, stream)
 
     def dispatch(self, x, recv_x, T, x_scale=None, recv_scale=None, stream=None):
-        _check(load().eep_dispatch(self._h, _ptr(x), _ptr(x_scale), _ptr(recv_x),
-                                   _ptr(recv_scale), T, _stream(stream)), "eep_dispatch", self._h)
+        self._step("eep_dispatch", "hppppis", x, x_scale, recv_x, recv_scale, T, stream)
 
     def dispatch_quant(self, x_bf16, recv_x, recv_scale, T, stream=None):
-        _check(load().eep_dispatch_quant(self._h, _ptr(x_bf16), _ptr(recv_x), _ptr(recv_scale), T,
-                                         _stream(stream)), "eep_dispatch_quant", self._h)
+        self._step("eep_dispatch_quant", "hpppis", x_bf16, recv_x, recv_scale, T, stream)
 
     def combine(self, y, topk_w, out, T, stream=None):
-        _check(load().eep_combine(self._h, _ptr(y), _ptr(topk_w), _ptr(out), T, _stream(stream)),
-               "eep_combine", self._h)
+        self._step("eep_combine", "hpppis", y, topk_w, out, T, stream)
 
     def expert_stub(self, kind, recv_x, y, T, recv_scale=None, expert_scale=None, stream=None):
         kind = STUBS[kind] if isinstance(kind, str) else kind
-        _check(load().eep_expert_stub(self._h, kind, _ptr(recv_x), _ptr(recv_scale),
-                                      _ptr(expert_scale), _ptr(y), T, _stream(stream)),
-               "eep_expert_stub", self._h)
+        self._step("eep_expert_stub", "hippppis", kind, recv_x, recv_scale, expert_scale, y, T, stream)
 
     # -- GPU-side failure detection -------------------------------------------
     def set_detection(self, timeout_ns):
         _check(load().eep_set_detection(self._h, int(timeout_ns)), "eep_set_detection", self._h)
 
     def signal_experts_done(self, stream=None):
-        _check(load().eep_signal_experts_done(self._h, _stream(stream)),
-               "eep_signal_experts_done", self._h)
+        self._step("eep_signal_experts_done", "hs", stream)
 
     def debug_withhold_signal(self, withhold, stream=None):
         w = np.ascontiguousarray(withhold, np.int32)
@@ -467,15 +482,13 @@ class Context:
 
     # -- de-duplicated dispatch ------------------------------------------------
     def dedup_layout(self, T, stream=None):
-        _check(load().eep_dedup_layout(self._h, T, _stream(stream)), "eep_dedup_layout", self._h)
+        self._step("eep_dedup_layout", "his", T, stream)
 
     def dispatch_dedup(self, x, recv_dedup, T, stream=None):
-        _check(load().eep_dispatch_dedup(self._h, _ptr(x), _ptr(recv_dedup), T, _stream(stream)),
-               "eep_dispatch_dedup", self._h)
+        self._step("eep_dispatch_dedup", "hppis", x, recv_dedup, T, stream)
 
     def expand(self, recv_dedup, recv_x, T, stream=None):
-        _check(load().eep_expand(self._h, _ptr(recv_dedup), _ptr(recv_x), T, _stream(stream)),
-               "eep_expand", self._h)
+        self._step("eep_expand", "hppis", recv_dedup, recv_x, T, stream)
 
     def read_dedup(self, T, stream=None):
         fields = ["dedup_count", "dedup_offset", "dedup_row", "dedup_dst", "expand_of", "status"]

@@ -1,7 +1,9 @@
-"""Compile the HIP sources under csrc/ into paper_2605_10670_amd/libeep.so for gfx950."""
+"""Compile the HIP sources under csrc/ into paper_2605_10670_amd/libeep.so for gfx950, and
+native/marshal.cpp into the extension module that binding.py makes its per-step calls through."""
 import glob
 import os
 import subprocess
+import sysconfig
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
@@ -23,9 +25,21 @@ FLAGS = [
 ]
 
 
+MARSHAL = os.path.join(HERE, "_marshal.so")
+
+
+def build_marshal() -> str:
+    cmd = [os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall", "-Wextra",
+           "-Wno-missing-field-initializers", "-I", sysconfig.get_path("include"), "-o", MARSHAL,
+           os.path.join(HERE, "native", "marshal.cpp")]
+    subprocess.run(cmd, check=True)
+    return MARSHAL
+
+
 def build() -> str:
     cmd = [HIPCC] + FLAGS + ["-o", LIB] + SOURCES
     subprocess.run(cmd, check=True)
+    build_marshal()
     return LIB
 
 
