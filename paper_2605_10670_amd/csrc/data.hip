@@ -877,7 +877,7 @@ __device__ __forceinline__ int row_if_arrived(const DetectArgs& d, int64_t pair0
 // 1024 channels, T = 1024 / 2048: 22.0 / 29.2 and 17.0 / 22.9; with a scaling stage between, where
 // nothing can meet, within 1 % either way.
 //
-// k is a compile-time number up to kCombineMaxK; a larger one goes in batches of 8 and 4 rows.  One row at a
+// k is a compile-time number up to 10; a larger one goes in batches of 8 and 4 rows.  One row at a
 // time, each behind its index, top-10 took (whole steps, 4096 channels, T = 32 / 256) 12.5 / 16.9 us instead
 // of 9.7 / 15.5, top-3 9.2 / 10.4 instead of 8.7 / 9.9, top-5 of 512 tokens 21.9 instead of 21.1; at 4096
 // tokens, where other wavefronts fill the time, 124.8 instead of 123.0 and the same.
@@ -885,8 +885,6 @@ __device__ __forceinline__ int row_if_arrived(const DetectArgs& d, int64_t pair0
 // DETECT: the wait for the ranks' signals is part of the kernel (DetectArgs above); row_of
 // is then not read-only, because dropped pairs are struck from it, and lane j keeps the row of
 // pair j from the one time it was read.
-constexpr int kCombineMaxK = 10;
-
 template <bool Y_BF16, bool OUT_BF16, int K, bool DETECT>
 __global__ __launch_bounds__(64) void k_combine(const int32_t* row_of,
                                                 const u32x4* __restrict__ y, int k, int row_vecs,

@@ -38,7 +38,6 @@
 namespace eep {
 
 constexpr int kMapThreads = 1024;
-constexpr int kMapWaves = kMapThreads / 64;
 constexpr int kPosThreads = 256;
 
 // Tile b covers tokens [t0, t0 + ntok) of source rank b / tiles_per_rank; the
