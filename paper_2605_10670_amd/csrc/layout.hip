@@ -553,7 +553,7 @@ __global__ __launch_bounds__(kFusedThreads) void k_scan_position(
 //
 // Measured (a layout in a graph of 40; 32 ranks x 9 slots, top-8), in brackets with a pair to
 // a lane, branches, and beyond 512 tokens a second launch for scan and rows: T = 32 / 256 / 512
-// 3.9 / 4.3 / 4.6 us (3.9 / 4.8 / 6.2), 768 / 1024 / 1536 / 2048 4.9 / 5.1 / 5.6 / 6.0 (7.6 / 7.7 / 7.8 / 7.9),
+// 4.0 / 4.5 / 4.7 us (3.9 / 4.8 / 6.2), 768 / 1024 / 1536 / 2048 5.0 / 5.3 / 5.7 / 6.2 (7.6 / 7.7 / 7.8 / 7.9),
 // 3072 / 4096 7.3 / 8.6 (8.1 / 8.4); with a Zipf router, whose hot slots' counts are one LDS word
 // for many lanes, 2048 7.2 (7.7), 4096 10.7 (8.1).  T = 1024 of 64 ranks x 9 slots 5.8 (12.0), top-2 of
 // 32 ranks 4.0 (7.4), top-6 of 24 ranks 4.2 (7.8).  So up to 16384 pairs.  Shares of about 64 tokens, whole
@@ -575,7 +575,11 @@ __global__ __launch_bounds__(kFusedThreads) void k_scan_position(
 // which the tiled path, where each pair is mapped once, is as fast.  The launch
 // decides by the number of contexts; a launch captured while there was one is
 // overruled by the word behind the membership version, which says that there are more:
-// its first workgroup then takes the shares one after the other.
+// its first workgroup then does it all, as many shares at once as fit in LDS: T = 32 / 256 / 512 / 1024 /
+// 2048 5.0 / 8.7 / 11.2 / 19.6 / 30 us (15.8 / 16.9 / 18.4 / 32.6 / 61 with one share after the other, which
+// made the launches of one context 0.1 us faster).  One workgroup for the whole batch is an instance
+// of its own (SOLO), with a pair to a lane up to 2048 pairs and 1024 threads, which share its source ranks'
+// counts: T = 32 / 128 / 256 / 384 4.3 / 5.6 / 6.7 / 7.5 us (4.9 / 7.3 / 8.3 / 9.7 without).
 // ---------------------------------------------------------------------------
 constexpr int kSmallBlocks = 8;  // and where they apply:
 constexpr int kSmallTokens = 512;
@@ -584,7 +588,7 @@ constexpr int kSoloTokens = 384;  // the limits for one workgroup
 constexpr int kSoloPairs = 3072;
 constexpr int kOnceThreads = 1024;
 constexpr int kOnceMaxK = 10;  // compile-time top-k, a token to a lane, up to here
-constexpr int kPairPairs = 512;  // a pair to a lane up to here
+constexpr int kPairPairs = 512, kSoloPairPairs = 2048;  // a pair to a lane up to here
 constexpr int kOncePairs = 16384, kShareTokens = 64, kPartPairs = 768;
 
 // Element i of a small global array: a 32-bit offset from a scalar address, which takes no 64-bit
@@ -709,9 +713,15 @@ __host__ __device__ inline uint32_t share_tokens(uint32_t tokens_per_rank, uint3
 __host__ __device__ inline uint32_t once_zeros(uint32_t P, uint32_t stride, bool parts) {
   return ((P + kSinks) * (regions(parts) + stride) + 3) / 4 * 4;
 }
-inline size_t once_lds_bytes(int E, int P, int R, int T, int tokens, int k) {
-  return sizeof(int32_t) * (once_zeros(P, share_stride(tokens), true) + route_table_ints(E, P, R) +
-                            (k > kOnceMaxK ? (size_t)T * k : E + 1) + (P + 1) + (size_t)tokens * k);
+// Where the last of it ends: what starts at zero, tables, entries or router indices, offsets, a share's slots.
+__host__ __device__ inline uint32_t once_end(uint32_t zeros, uint32_t tables, uint32_t entries, uint32_t P, uint32_t pairs) {
+  return (zeros + tables + entries + (P + 1) + pairs + 3) / 4 * 4;
+}
+// `alone`: the tokens that a workgroup alone takes at once, whose counts and bitmaps are behind the rest; or 0.
+inline size_t once_lds_bytes(int E, int P, int R, int T, int tokens, int alone, int k) {
+  return sizeof(int32_t) * ((size_t)once_end(once_zeros(P, share_stride(tokens), true), route_table_ints(E, P, R),
+                                             k > kOnceMaxK ? T * k : E + 1, P, (alone > 0 ? alone : tokens) * k) +
+                            (alone > 0 ? once_zeros(P, share_stride(alone), true) : 0));
 }
 
 // Exclusive scan of the slots' totals into s_offset[0..P]: the wavefronts, the last one first, take
@@ -740,10 +750,10 @@ __device__ __forceinline__ int opaque(int x) {
 }
 
 // KC: compile-time k, or 0 for any.  TOKEN: a lane takes a token, otherwise a pair.  PARTS: a share is a part
-// of a source rank, one of `subs`, otherwise `ranks` whole ones.
-// Four words hold the shape (T and tokens per rank; E and P; R and the source ranks of a share; S,
-// policy << 12, k << 13, wavefronts << 19, shares in a rank << 24), so that it arrives in registers with the first pointers.
-template <int KC, bool TOKEN, bool LARGE, bool PARTS>
+// of a source rank, one of `subs`, otherwise `ranks` whole ones.  SOLO: a share is the whole batch.
+// Four words hold the shape (T and tokens per rank; E and P; R, the source ranks of a share << 12 and
+// how many shares at once a workgroup alone takes << 24; S, policy << 12, k << 13, wavefronts << 19, shares in a rank << 24), so that it arrives in registers with the first pointers.
+template <int KC, bool TOKEN, bool LARGE, bool PARTS, bool SOLO>
 __global__ __launch_bounds__(kOnceThreads) void k_layout_once(
     const int32_t* __restrict__ topk_idx, const int32_t* __restrict__ l2p_off,
     const int32_t* __restrict__ l2p_list, const int32_t* __restrict__ active,
@@ -755,7 +765,8 @@ __global__ __launch_bounds__(kOnceThreads) void k_layout_once(
     int32_t* __restrict__ step_epoch) {
   constexpr uint32_t N = TOKEN ? KC : 1;
   const uint32_t T = T_rank & 0xffff, tokens_per_rank = T_rank >> 16;
-  const uint32_t E = E_P & 0xffff, R = R_share & 0xffff, ranks = R_share >> 16;
+  const uint32_t E = E_P & 0xffff, R = R_share & 0xfff;
+  uint32_t width = R_share >> 12 & 0xfff;  // source ranks of a share
   const uint32_t S = S_policy_k_waves_subs & 0xfff, policy = S_policy_k_waves_subs >> 12 & 1;
   const uint32_t k = KC > 0 ? KC : S_policy_k_waves_subs >> 13 & 63;
   const uint32_t waves = S_policy_k_waves_subs >> 19 & 31, nt = waves * 64;
@@ -778,8 +789,8 @@ __global__ __launch_bounds__(kOnceThreads) void k_layout_once(
   const int several_v = vector_load(&mem_version[1]);
 
   extern __shared__ __align__(16) int32_t smem[];
-  const uint32_t tokens = share_tokens(tokens_per_rank, ranks, subs), stride = share_stride(tokens);
-  const uint32_t zeros = once_zeros(E_P >> 16, stride, PARTS);
+  const uint32_t part = share_tokens(tokens_per_rank, width, subs);
+  const uint32_t zeros = once_zeros(E_P >> 16, share_stride(part), PARTS);
   int32_t* s_tab = smem + zeros;
 #pragma nounroll
   for (uint32_t i = tid * 4; i < zeros; i += nt * 4) *(int4*)(smem + i) = make_int4(0, 0, 0, 0);
@@ -790,7 +801,7 @@ __global__ __launch_bounds__(kOnceThreads) void k_layout_once(
 #pragma nounroll
     for (uint32_t i = tid; i < items; i += nt) s_idx[i] = i == tid ? e[0] : at(topk_idx, i);
   }
-  const bool alone = (PARTS || ranks < R) && __builtin_amdgcn_readfirstlane(several_v) != 0;
+  const bool alone = !SOLO && (PARTS || width < R) && __builtin_amdgcn_readfirstlane(several_v) != 0;
   uint32_t share = blockIdx.x;
   // PARTS: the share's rank (share / subs, by way of float), and which of the rank's shares it is
   const auto rank_of_part = [&]() {
@@ -798,7 +809,17 @@ __global__ __launch_bounds__(kOnceThreads) void k_layout_once(
         (uint32_t)(((float)share + 0.5f) * __builtin_amdgcn_rcpf((float)subs)));
   };
   uint32_t rank0 = PARTS ? rank_of_part() : 0, sub = share - rank0 * subs;
-  if (share > 0 && (alone || (PARTS ? rank0 : share * ranks) >= R)) return;
+  if (share > 0 && (alone || (PARTS ? rank0 : share * width) >= R)) return;
+  uint32_t base = 0;  // where the counts and bitmaps are
+  if (!PARTS && alone && (R_share >> 24) > 1) {  // as many shares at once as there is LDS for, behind the rest
+    width *= R_share >> 24;
+    const uint32_t P = E_P >> 16, many = width * tokens_per_rank;
+    base = once_end(zeros, route_table_ints(E, P, R), KC > 0 ? E + 1 : items, P, many * k);
+    const uint32_t end = base + once_zeros(P, share_stride(many), false);
+#pragma nounroll
+    for (uint32_t i = base + tid * 4; i < end; i += nt * 4) *(int4*)(smem + i) = make_int4(0, 0, 0, 0);
+  }
+  const bool rounds = alone && (PARTS || width < R);
   __syncthreads();
   bool repeats = false;
   if constexpr (TOKEN) {
@@ -807,21 +828,25 @@ __global__ __launch_bounds__(kOnceThreads) void k_layout_once(
     __syncthreads();
   }
 
-  // One round, over the whole batch; alone, a second one for every share, over its tokens.
+  // One round, over the whole batch; alone with several shares, a second one for each, over its tokens.
   uint32_t lo = T;
   const auto first_token = [&]() {
-    return !PARTS ? share * tokens
-                  : min(rank0 * tokens_per_rank + sub * tokens, (rank0 + 1) * tokens_per_rank);
+    return !PARTS ? share * width * tokens_per_rank
+                  : min(rank0 * tokens_per_rank + sub * part, (rank0 + 1) * tokens_per_rank);
   };
-  const auto last_token = [&]() { return min(lo + tokens, PARTS ? (rank0 + 1) * tokens_per_rank : T); };
+  const auto last_token = [&]() {
+    return PARTS ? min(lo + part, (rank0 + 1) * tokens_per_rank) : min(lo + width * tokens_per_rank, T);
+  };
   uint32_t end = items;
-  if (!alone) lo = first_token();
+  if (!rounds) lo = first_token();
   int rows = 0;
   for (uint32_t round = 0;; ++round) {
     // (Opaque, or whatever follows from it would be computed ahead of the loop by every wavefront.)
     const uint32_t P = opaque(E_P >> 16), P2 = P + kSinks;
-    int32_t* const s_cnt = smem;                          // [regions][P2] pairs per slot
-    uint32_t* const s_bm = (uint32_t*)(smem + regions(PARTS) * P2);  // [P2][stride] bitmap of the share's tokens per slot
+    const uint32_t ranks = PARTS ? 1 : opaque(width), tokens = PARTS ? part : ranks * tokens_per_rank;
+    const uint32_t stride = share_stride(tokens);
+    int32_t* const s_cnt = smem + base;                   // [regions][P2] pairs per slot
+    uint32_t* const s_bm = (uint32_t*)(s_cnt + regions(PARTS) * P2);  // [P2][stride] bitmap of the share's tokens per slot
     int32_t* const s_offset = smem + opaque(zeros + route_table_ints(E, P, R) +
                                             (KC > 0 ? E + 1 : items));  // [P+1] exclusive scan of the totals
     int32_t* const s_slot = s_offset + P + 1;             // [tokens*k] slots of the share's pairs
@@ -889,28 +914,50 @@ __global__ __launch_bounds__(kOnceThreads) void k_layout_once(
     // pairs per (source rank, slot): the tokens of a source rank are a bit range
     if (n > 0) {
       const uint32_t rank = PARTS ? rank0 : share * ranks, mine = min(R - rank, ranks);
+      if (SOLO && tokens > 64) {
+        // Many in a row: wavefronts share the source ranks of 64 slots, if there are enough wavefronts.
+        const float inv = __builtin_amdgcn_rcpf((float)((P + 63) >> 6)), w = (float)(tid >> 6) + 0.5f;
+        const uint32_t groups = max((uint32_t)(((float)waves + 0.5f) * inv), 1u), group = (uint32_t)(w * inv);
+        const uint32_t b0 = group, first = tid - group * ((P + 63) & ~63u);
+        if (group < groups) {
 #pragma nounroll
-      for (uint32_t p = tid; p < P; p += nt) {
-        const uint32_t* bm = &s_bm[__umul24(p, stride)];
-        uint32_t to = rank * P + p;
-        if constexpr (PARTS) {
-          if (alone)
-            at(cnt_src, to) = s_cnt[P2 + p] + (sub == 0 ? 0 : at(cnt_src, to));
-          else if (sub == 0)
-            at(cnt_src, to) = s_cnt[P2 + p] + s_cnt[3 * P2 + p];
-        } else if (tokens <= 64) {
-          uint64_t bits = bm[0];
-          if (stride > 1) bits |= (uint64_t)bm[1] << 32;
-          const uint64_t mask = ~0ull >> (64 - tokens_per_rank);
-#pragma nounroll
-          for (uint32_t b = 0; b < mine; ++b, to += P) {
-            at(cnt_src, to) = __popcll(bits & mask);
-            bits >>= tokens_per_rank;
+          for (uint32_t p = first; p < P; p += nt) {
+            const uint32_t* bm = &s_bm[__umul24(p, stride)];
+#pragma unroll 2
+            for (uint32_t b = b0; b < mine; b += groups) {
+              const uint32_t from = b * tokens_per_rank;
+              // up to 32 tokens are in two words (what is behind the row's last one is masked)
+              const uint64_t two = (uint64_t)bm[(from >> 5) + 1] << 32 | bm[from >> 5];
+              at(cnt_src, (rank + b) * P + p) =
+                  tokens_per_rank <= 32 ? __popcll(two >> (from & 31) & (~0ull >> (64 - tokens_per_rank)))
+                                        : bits_between(bm, from, from + tokens_per_rank);
+            }
           }
-        } else {
+        }
+      } else {
 #pragma nounroll
-          for (uint32_t b = 0; b < mine; ++b, to += P)
-            at(cnt_src, to) = bits_between(bm, b * tokens_per_rank, (b + 1) * tokens_per_rank);
+        for (uint32_t p = tid; p < P; p += nt) {
+          const uint32_t* bm = &s_bm[__umul24(p, stride)];
+          uint32_t to = rank * P + p;
+          if constexpr (PARTS) {
+            if (alone)
+              at(cnt_src, to) = s_cnt[P2 + p] + (sub == 0 ? 0 : at(cnt_src, to));
+            else if (sub == 0)
+              at(cnt_src, to) = s_cnt[P2 + p] + s_cnt[3 * P2 + p];
+          } else if (tokens <= 64) {
+            uint64_t bits = bm[0];
+            if (stride > 1) bits |= (uint64_t)bm[1] << 32;
+            const uint64_t mask = ~0ull >> (64 - tokens_per_rank);
+#pragma nounroll
+            for (uint32_t b = 0; b < mine; ++b, to += P) {
+              at(cnt_src, to) = __popcll(bits & mask);
+              bits >>= tokens_per_rank;
+            }
+          } else {
+#pragma nounroll
+            for (uint32_t b = 0; b < mine; ++b, to += P)
+              at(cnt_src, to) = bits_between(bm, b * tokens_per_rank, (b + 1) * tokens_per_rank);
+          }
         }
       }
     }
@@ -948,7 +995,7 @@ __global__ __launch_bounds__(kOnceThreads) void k_layout_once(
       rank0 = rank_of_part();
       sub = share - rank0 * subs;
     }
-    if (!alone || (PARTS ? rank0 : share * ranks) >= R) break;
+    if (!rounds || (PARTS ? rank0 : share * ranks) >= R) break;
     lo = first_token();
     __syncthreads();
 #pragma nounroll
@@ -1421,23 +1468,23 @@ static auto map_count_for(int k, int pairs) {
   return pairs <= kMapThreads ? map_count_for_k<1, WIDE>(k)
        : pairs <= 2 * kMapThreads ? map_count_for_k<2, WIDE>(k) : map_count_for_k<4, WIDE>(k);
 }
-template <bool LARGE, bool PARTS>
-static decltype(&k_layout_once<0, false, LARGE, PARTS>) layout_once_for(int k, bool token) {
-  if (!token) return k == 8 ? k_layout_once<8, false, LARGE, PARTS> : k == 4 ? k_layout_once<4, false, LARGE, PARTS>
-                   : k == 2 ? k_layout_once<2, false, LARGE, PARTS> : k == 1 ? k_layout_once<1, false, LARGE, PARTS>
-                                                              : k_layout_once<0, false, LARGE, PARTS>;
+template <bool LARGE, bool PARTS, bool SOLO>
+static decltype(&k_layout_once<0, false, LARGE, PARTS, SOLO>) layout_once_for(int k, bool token) {
+  if (!token) return k == 8 ? k_layout_once<8, false, LARGE, PARTS, SOLO> : k == 4 ? k_layout_once<4, false, LARGE, PARTS, SOLO>
+                   : k == 2 ? k_layout_once<2, false, LARGE, PARTS, SOLO> : k == 1 ? k_layout_once<1, false, LARGE, PARTS, SOLO>
+                                                              : k_layout_once<0, false, LARGE, PARTS, SOLO>;
   switch (k) {
-    case 1: return k_layout_once<1, true, LARGE, PARTS>;
-    case 2: return k_layout_once<2, true, LARGE, PARTS>;
-    case 3: return k_layout_once<3, true, LARGE, PARTS>;
-    case 4: return k_layout_once<4, true, LARGE, PARTS>;
-    case 5: return k_layout_once<5, true, LARGE, PARTS>;
-    case 6: return k_layout_once<6, true, LARGE, PARTS>;
-    case 7: return k_layout_once<7, true, LARGE, PARTS>;
-    case 8: return k_layout_once<8, true, LARGE, PARTS>;
-    case 9: return k_layout_once<9, true, LARGE, PARTS>;
-    case 10: return k_layout_once<10, true, LARGE, PARTS>;
-    default: return k_layout_once<0, false, LARGE, PARTS>;
+    case 1: return k_layout_once<1, true, LARGE, PARTS, SOLO>;
+    case 2: return k_layout_once<2, true, LARGE, PARTS, SOLO>;
+    case 3: return k_layout_once<3, true, LARGE, PARTS, SOLO>;
+    case 4: return k_layout_once<4, true, LARGE, PARTS, SOLO>;
+    case 5: return k_layout_once<5, true, LARGE, PARTS, SOLO>;
+    case 6: return k_layout_once<6, true, LARGE, PARTS, SOLO>;
+    case 7: return k_layout_once<7, true, LARGE, PARTS, SOLO>;
+    case 8: return k_layout_once<8, true, LARGE, PARTS, SOLO>;
+    case 9: return k_layout_once<9, true, LARGE, PARTS, SOLO>;
+    case 10: return k_layout_once<10, true, LARGE, PARTS, SOLO>;
+    default: return k_layout_once<0, false, LARGE, PARTS, SOLO>;
   }
 }
 
@@ -1463,7 +1510,7 @@ int layout_small_workgroups(int E, int P, int R, int T, int k, bool solo) {
   if (T < 1 || T > (solo ? kSoloTokens : kSmallTokens) ||
       T * k > (solo ? kSoloPairs : kSmallPairs) || P + kSinks > kEntrySlots ||
       small_lds_bytes(E, P, R, T, k) > kLayoutLdsLimit ||
-      once_lds_bytes(E, P, R, T, share_size(E, P, R, T / R, k, solo ? 1 : kSmallBlocks).tokens(T / R), k) > kLayoutLdsLimit)
+      once_lds_bytes(E, P, R, T, share_size(E, P, R, T / R, k, solo ? 1 : kSmallBlocks).tokens(T / R), 0, k) > kLayoutLdsLimit)
     return 0;
   return solo ? 1 : kSmallBlocks;
 }
@@ -1485,22 +1532,29 @@ hipError_t launch_layout(const LayoutIO& c, int T, hipStream_t st) {
   int grid = small;
   if (small == 0 && !solo && c.k <= kOnceMaxK && (int64_t)T * c.k <= kOncePairs &&
       c.P + kSinks <= kEntrySlots && share.subs < 256 &&
-      once_lds_bytes(c.E, c.P, c.R, T, share.tokens(g.tokens_per_rank), c.k) <= kLayoutLdsLimit)
+      once_lds_bytes(c.E, c.P, c.R, T, share.tokens(g.tokens_per_rank), 0, c.k) <= kLayoutLdsLimit)
     grid = share.count(c.R);
   if (grid > 0) {
-    const bool token = c.k <= kOnceMaxK && !(T * c.k <= kPairPairs && (c.k & (c.k - 1)) == 0);
+    const bool token = c.k <= kOnceMaxK && !(T * c.k <= (solo ? kSoloPairPairs : kPairPairs) && (c.k & (c.k - 1)) == 0);
     int nt = c.P > c.E ? c.P : c.E + 1;  // threads: for the tables, and for the items
-    const int most = (token ? T : 2 * T * c.k) > kOnceThreads ? kOnceThreads : kOnceThreads / 2;
+    const int most = solo || (token ? T : 2 * T * c.k) > kOnceThreads ? kOnceThreads : kOnceThreads / 2;
     nt = nt < most ? most : nt < kOnceThreads ? (nt + 63) / 64 * 64 : kOnceThreads;
+    // shares at once for a workgroup alone: all of them, or what fits beside the rest
+    const int tokens = share.tokens(g.tokens_per_rank);
+    int at_once = share.subs > 1 ? 0 : std::min((c.R + share.ranks - 1) / share.ranks, 255);
+    size_t lds;
+    while ((lds = once_lds_bytes(c.E, c.P, c.R, T, tokens, at_once > 1 ? tokens * at_once : 0, c.k)) > kLayoutLdsLimit &&
+           at_once > 1)
+      at_once /= 2;
     const bool large = large_tables(c.E, c.P, c.R, nt);
-    auto kern = large ? layout_once_for<true, false>(c.k, token)
-                : share.subs > 1 ? layout_once_for<false, true>(c.k, token)
-                                 : layout_once_for<false, false>(c.k, token);
-    hipLaunchKernelGGL(kern, dim3(grid), dim3(nt),
-                       once_lds_bytes(c.E, c.P, c.R, T, share.tokens(g.tokens_per_rank), c.k), st, c.topk_idx,
+    auto kern = large ? layout_once_for<true, false, false>(c.k, token)
+                : solo ? layout_once_for<false, false, true>(c.k, token)
+                : share.subs > 1 ? layout_once_for<false, true, false>(c.k, token)
+                                 : layout_once_for<false, false, false>(c.k, token);
+    hipLaunchKernelGGL(kern, dim3(grid), dim3(nt), lds, st, c.topk_idx,
                        c.l2p_off, c.l2p_list, c.active, c.mem_version,
                        (uint32_t)T | (uint32_t)g.tokens_per_rank << 16, (uint32_t)c.E | (uint32_t)c.P << 16,
-                       (uint32_t)c.R | (uint32_t)share.ranks << 16,
+                       (uint32_t)c.R | (uint32_t)share.ranks << 12 | (uint32_t)at_once << 24,
                        (uint32_t)c.S | (uint32_t)c.policy << 12 | (uint32_t)c.k << 13 | (uint32_t)(nt / 64) << 19 |
                            (uint32_t)share.subs << 24,
                        c.tbl_version, c.slot_of, c.row_of,

@@ -2,7 +2,8 @@
 several source ranks and of a part of one (the last part short or empty), every compile-time top-k, batches that a lane takes
 several tokens of, tables larger than a workgroup, experts with none, two, three and more than 32 live
 replicas.  Every field bit-equal to the oracle, with dead ranks, masked, repeated and uncovered pairs;
-and the same after the instance got a second context, when one workgroup does it all."""
+and the same after the instance got a second context, when one workgroup does it all: of a launch
+captured before, and of one made then."""
 import numpy as np
 import pytest
 
@@ -19,6 +20,7 @@ SHAPES = [
     (1816, 9, 8, 4, 30), (585, 7, 65, 3, 130), (1024, 5, 4, 6, 16), (512, 4, 1, 9, 8), (516, 4, 1, 9, 8),
     (8192, 2, 16, 6, 40), (5456, 3, 11, 4, 20), (16384, 1, 64, 2, 100), (600, 2, 150, 8, 1100),
     (64, 8, 32, 9, 256), (72, 8, 24, 9, 200), (194, 8, 2, 9, 16), (770, 10, 2, 9, 16), (26, 32, 1, 40, 32), (82, 10, 1, 12, 11), (1360, 12, 16, 4, 32), (720, 6, 48, 4, 12), (700, 4, 20, 40, 9),
+    (256, 8, 32, 9, 256), (384, 8, 12, 9, 64), (360, 8, 9, 9, 64), (384, 3, 128, 4, 200),
 ]
 
 
@@ -59,6 +61,12 @@ def test_layout_once(oracle, shape, policy):
             graph.launch(stream)
             stream.synchronize()
             check(ctx, oracle, idx, p2l, mask, shape, policy)
+            changed = mask.copy()
+            changed[0] ^= R > 1
+            ctx.set_membership(changed, stream)
+            ctx.dispatch_layout(dev, T, stream)            # launched with two contexts
+            stream.synchronize()
+            check(ctx, oracle, idx, p2l, changed, shape, policy)
         graph.destroy()
     finally:
         if other is not None:
