@@ -171,10 +171,13 @@ __global__ __launch_bounds__(64) void k_pack_split(const u32x4* __restrict__ x,
 #pragma unroll
     for (int u = 0; u < U; ++u) asm volatile("" ::"v"(buf[u]));
   }, [&](int row) {
-    char* dst = (char*)recv + (int64_t)row * (row_vecs * 16);
+    // (a row of 4 GiB and more, which the general k takes, is 64 bits of bytes)
+    char* dst = K > 0 ? (char*)recv + (int64_t)row * (row_vecs * 16)
+                      : (char*)recv + ((int64_t)row * row_vecs + (v0 - lane)) * 16;
 #pragma unroll
     for (int u = 0; u < U; ++u)
-      if (EXACT || v0 + u * 64 < row_vecs) store_through_at(dst, (v0 + u * 64) * 16, buf[u]);
+      if (EXACT || v0 + u * 64 < row_vecs)
+        store_through_at(dst, ((K > 0 ? v0 : lane) + u * 64) * 16, buf[u]);
   });
 }
 
@@ -326,7 +329,8 @@ static hipError_t launch_pack_split_t(eep_ctx* c, const int32_t* rows, const voi
       k_pack_split<U, EXACT, 6, SCALES>, k_pack_split<U, EXACT, 7, SCALES>,
       k_pack_split<U, EXACT, 8, SCALES>};
   const int64_t grid = (int64_t)T * parts;
-  hipLaunchKernelGGL(of[c->k <= kSplitMaxK ? c->k : 0], dim3((unsigned)grid), dim3(64), 0, st,
+  const bool compiled = c->k <= kSplitMaxK && c->x_row_bytes < (int64_t)1 << 32;  // (32-bit offsets there)
+  hipLaunchKernelGGL(of[compiled ? c->k : 0], dim3((unsigned)grid), dim3(64), 0, st,
                      (const u32x4*)x, rows, c->k, (uint32_t)(c->x_row_bytes / 16), (uint32_t)parts,
                      part_magic(parts, grid), (u32x4*)recv_x, (const u32x4*)x_scale,
                      (u32x4*)recv_scale, (uint32_t)(c->scale_row_bytes / 16));
