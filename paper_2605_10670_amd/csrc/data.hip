@@ -59,9 +59,17 @@ __device__ inline void store_through(u32x4* p, u32x4 v) {
   asm volatile("global_store_dwordx4 %0, %1, off sc0 sc1\n\ts_nop 1" ::"v"(p), "v"(v) : "memory");
 }
 
-// The same to a byte offset from a scalar address.
-__device__ __forceinline__ void store_through_at(void* base, uint32_t offset, u32x4 v) {
-  asm volatile("global_store_dwordx4 %0, %1, %2 sc0 sc1\n\ts_nop 1" ::"v"(offset), "v"(v), "s"(base) : "memory");
+// The same to `offset` bytes behind base + row, both scalar.  A vector memory instruction may not read
+// a scalar register within five wait states of a vector instruction that wrote it (v_readfirstlane, or
+// a spilled register's v_readlane); the compiler does not keep that distance for asm either, so
+// the address is added up by scalar instructions that are part of it.
+__device__ __forceinline__ void store_through_at(void* base, int64_t row, uint32_t offset, u32x4 v) {
+  asm volatile(
+      "s_add_u32 s98, %2, %4\n\ts_addc_u32 s99, %3, %5\n\t"
+      "global_store_dwordx4 %0, %1, s[98:99] sc0 sc1\n\ts_nop 1" ::"v"(offset), "v"(v),
+      "s"((uint32_t)(uintptr_t)base), "s"((uint32_t)((uintptr_t)base >> 32)), "s"((uint32_t)row),
+      "s"((uint32_t)((uint64_t)row >> 32))
+      : "memory", "scc", "s98", "s99");
 }
 
 // One wavefront per token.  U = 16-byte vectors per lane per pass.  EXACT: the row is a whole number of
@@ -153,7 +161,7 @@ __global__ __launch_bounds__(64) void k_pack_split(const u32x4* __restrict__ x,
       const u32x4 d = x_scale[(int64_t)t * scale_vecs + v];
       for_rows([&]() { asm volatile("" ::"v"(d)); }, [&](int row) {
         if (v0 + lane < scale_vecs)
-          store_through_at((char*)recv_scale + (int64_t)row * (scale_vecs * 16), v * 16, d);
+          store_through_at(recv_scale, (int64_t)row * (scale_vecs * 16), v * 16, d);
       });
     }
     return;
@@ -172,12 +180,11 @@ __global__ __launch_bounds__(64) void k_pack_split(const u32x4* __restrict__ x,
     for (int u = 0; u < U; ++u) asm volatile("" ::"v"(buf[u]));
   }, [&](int row) {
     // (a row of 4 GiB and more, which the general k takes, is 64 bits of bytes)
-    char* dst = K > 0 ? (char*)recv + (int64_t)row * (row_vecs * 16)
-                      : (char*)recv + ((int64_t)row * row_vecs + (v0 - lane)) * 16;
+    const int64_t at = K > 0 ? (int64_t)row * (row_vecs * 16) : ((int64_t)row * row_vecs + (v0 - lane)) * 16;
 #pragma unroll
     for (int u = 0; u < U; ++u)
       if (EXACT || v0 + u * 64 < row_vecs)
-        store_through_at(dst, ((K > 0 ? v0 : lane) + u * 64) * 16, buf[u]);
+        store_through_at(recv, at, ((K > 0 ? v0 : lane) + u * 64) * 16, buf[u]);
   });
 }
 
