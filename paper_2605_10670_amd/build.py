@@ -25,20 +25,31 @@ FLAGS = [
 ]
 
 
-MARSHAL = os.path.join(HERE, "_marshal.so")
+# (with the interpreter's tag, so that no other one loads it)
+MARSHAL = os.path.join(HERE, "_marshal" + sysconfig.get_config_var("EXT_SUFFIX"))
+
+
+def _compile(cmd, out):
+    """Run `cmd` with an output name of this process's own and move the result into place whole: another
+    process may be about to load `out`, or be building it too."""
+    own = f"{out}.{os.getpid()}.so"
+    try:
+        subprocess.run(cmd + ["-o", own], check=True)
+        os.replace(own, out)
+    finally:
+        if os.path.exists(own):
+            os.remove(own)
+    return out
 
 
 def build_marshal() -> str:
-    cmd = [os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall", "-Wextra",
-           "-Wno-missing-field-initializers", "-I", sysconfig.get_path("include"), "-o", MARSHAL,
-           os.path.join(HERE, "native", "marshal.cpp")]
-    subprocess.run(cmd, check=True)
-    return MARSHAL
+    return _compile([os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall", "-Wextra",
+                     "-Wno-missing-field-initializers", "-I", sysconfig.get_path("include"),
+                     os.path.join(HERE, "native", "marshal.cpp")], MARSHAL)
 
 
 def build() -> str:
-    cmd = [HIPCC] + FLAGS + ["-o", LIB] + SOURCES
-    subprocess.run(cmd, check=True)
+    _compile([HIPCC] + FLAGS + SOURCES, LIB)
     build_marshal()
     return LIB
 
