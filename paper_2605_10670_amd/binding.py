@@ -53,14 +53,33 @@ class _LayoutOut(ctypes.Structure):
 
 
 _lib = None
-_call = None        # native/marshal.cpp: call(address, kinds, arguments...) -> return code
-_address = {}       # of the entry points that are called through it
+_address = {}       # of the entry points that are called through _call
+
+
+def _call(*args):
+    """native/marshal.cpp: call(address, kinds, arguments...) -> return code.  Loaded, and built if it is
+    not there, by the first per-step call, so that what is host only does without it."""
+    global _call
+    try:
+        from . import _marshal
+    except ImportError:
+        try:
+            import importlib
+            from . import build as _build
+            _build.build_marshal()
+            importlib.invalidate_caches()
+            from . import _marshal
+        except Exception as exc:
+            raise RuntimeError(f"the _marshal module is missing and could not be built ({exc}); "
+                               "there is no fallback path") from exc
+    _call = _marshal.call
+    return _call(*args)
 
 
 def load():
     """Load libeep.so, building it first if it does not exist; raises if that fails
     (there is no fallback path)."""
-    global _lib, _call
+    global _lib
     if _lib is not None:
         return _lib
     if not os.path.exists(LIB_PATH):
@@ -130,17 +149,6 @@ def load():
         fn.restype = ctypes.c_int
     for name in sig:
         _address[name] = ctypes.cast(getattr(lib, name), ctypes.c_void_p).value
-    try:
-        from . import _marshal
-    except ImportError:
-        try:
-            from . import build as _build
-            _build.build_marshal()
-            from . import _marshal
-        except Exception as exc:
-            raise RuntimeError(f"_marshal.so is missing and could not be built ({exc}); "
-                               "there is no fallback path") from exc
-    _call = _marshal.call
     lib.eep_noalloc_scratch_needed.argtypes = [i32, i32, i32]
     lib.eep_noalloc_scratch_needed.restype = i64
     lib.eep_strerror.argtypes = [ctypes.c_int]
