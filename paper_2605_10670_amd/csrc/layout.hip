@@ -9,10 +9,11 @@
 //
 // One to three launches, all tiny and latency-bound (the step's metadata is
 // < 1 MB), so the design goal is a short chain of dependent memory round trips,
-// not bandwidth.  Up to 64 ranks k_layout_once and k_map_count issue all their
+// not bandwidth.  Up to 64 ranks the one-launch forms and k_map_count issue all their
 // global loads before their first wait; k_scan_position reads the count matrix
 // behind its first barrier, k_position the tile prefixes behind its scan.
-//   k_layout_once  (<= 16384 pairs) everything in one launch, see there.
+//   k_layout_small  (<= 512 tokens and 4096 pairs) everything in one launch, see there.
+//   k_layout_once  (<= 16384 pairs) the same for larger batches, see there.
 //   k_map_count  one workgroup per tile of <= 128 tokens of ONE source rank.
 //                Placement CSR, active mask and the tile's router indices are
 //                fetched with independent loads.  For every slot the kernel
@@ -33,6 +34,8 @@
 // 7.7 / 8.4 / 13.0 us; 9.7 / 10.5 / 14.3 while the live replicas were compacted per expert in
 // LDS, the repeat check read LDS, counts were popcounts over the bitmaps, the scan took two
 // barriers and half of k_scan_position's threads loaded the whole matrix.
+#include <type_traits>
+
 #include "eep_internal.hpp"
 
 namespace eep {
@@ -193,15 +196,20 @@ template <int KC>
 __device__ __forceinline__ bool repeats_earlier(int e, int j, const int32_t* token_idx) {
   bool r = false;
   if constexpr (KC == 0) {
-    // four at a time, so that their latencies overlap (up to three words behind the token's are read)
+    // eight and then four at a time, so that their latencies overlap (up to three words behind the
+    // token's are read): top-32, 64 tokens 6.6 us, four at a time 7.1
+    const auto look = [&](int jj, auto n) {
+      constexpr int N = decltype(n)::value;
+      int v[N];
+#pragma unroll
+      for (int u = 0; u < N; ++u) v[u] = token_idx[jj + u];
+#pragma unroll
+      for (int u = 0; u < N; ++u) r |= jj + u < j && v[u] == e;
+    };
+    int jj = 0;
 #pragma nounroll
-    for (int jj = 0; jj < j; jj += 4) {
-      int v[4];
-#pragma unroll
-      for (int u = 0; u < 4; ++u) v[u] = token_idx[jj + u];
-#pragma unroll
-      for (int u = 0; u < 4; ++u) r |= jj + u < j && v[u] == e;
-    }
+    for (; jj + 4 < j; jj += 8) look(jj, std::integral_constant<int, 8>());
+    if (jj < j) look(jj, std::integral_constant<int, 4>());
   } else if constexpr (KC > 1) {
     static_assert(KC == 2 || KC == 4 || KC == 8, "pairs of a token share a DPP row");
     // first whether any two of the token's lanes are equal (quad_perm 1032, 2301, 3210; the other
@@ -237,22 +245,23 @@ __device__ __forceinline__ bool repeats_earlier(int e, int j, const int32_t* tok
 // that nobody has to walk the words for it.
 constexpr int kMaxPairsPerThread = kTileTokens * kMaxTopk / kMapThreads;
 
-// Maps this thread's pairs tid, tid + NT, ... of a batch of `npairs` (router indices at `idx`,
-// first token t0): slots to slot[] (-1: not routed), token bits to s_bm
+// Maps this thread's pairs tid, tid + kMapThreads, ... of a batch of `npairs` (first token t0):
+// slots to slot[] (-1: not routed), token bits to s_bm
 // ([P][stride], zeroed), counts to s_count (zeroed), dropped pairs to s_drop {uncovered, masked}
-// (zeroed).  my_e holds the indices already loaded; s_idx the same in LDS when KC == 0.
-template <int KC, int NT, int U>
+// (zeroed).  my_e holds the router indices already loaded; s_idx the same in LDS when KC == 0.  Slots of
+// the pairs [own_lo, own_hi) are written to slot_of.
+template <int KC, int U>
 __device__ __forceinline__ void map_pairs(const RouteTables& rt, const int (&my_e)[U],
                                           const int32_t* s_idx, int (&slot)[U], uint32_t* s_bm,
                                           int stride, int32_t* s_count, int32_t* s_drop, int npairs,
-                                          int k, int E, int t0, int policy,
-                                          int32_t* __restrict__ slot_of) {
+                                          int k, int E, int t0, int policy, int own_lo,
+                                          int own_hi, int32_t* __restrict__ slot_of) {
   const int wave0 = __builtin_amdgcn_readfirstlane(threadIdx.x & ~63);
 #pragma unroll
   for (int u = 0; u < U; ++u) {
-    const int i = threadIdx.x + u * NT;
+    const int i = threadIdx.x + u * kMapThreads;
     slot[u] = -1;
-    if (wave0 + u * NT >= npairs) break;  // a wavefront without pairs stays out of the others' way
+    if (wave0 + u * kMapThreads >= npairs) break;  // a wavefront without pairs stays out of the others' way
     const int tl = i / k, j = i - tl * k;
     const int e = my_e[u];
     const bool repeated = repeats_earlier<KC>(e, j, KC == 0 && i < npairs ? s_idx + tl * k : s_idx);
@@ -270,7 +279,7 @@ __device__ __forceinline__ void map_pairs(const RouteTables& rt, const int (&my_
         }
       }
       slot[u] = p;
-      slot_of[i] = p;
+      if (i >= own_lo && i < own_hi) slot_of[i] = p;
     }
   }
 }
@@ -338,8 +347,8 @@ __global__ __launch_bounds__(kMapThreads) void k_map_count(
       if (tid + u * kMapThreads < npairs) s_idx[tid + u * kMapThreads] = my_e[u];
   }
   __syncthreads();
-  map_pairs<KC, kMapThreads, U>(rt, my_e, s_idx, slot, s_bm, kBitmapWords, s_count, s_drop, npairs,
-                                k, E, tr.t0, policy, slot_of + g0);
+  map_pairs<KC, U>(rt, my_e, s_idx, slot, s_bm, kBitmapWords, s_count, s_drop, npairs, k, E, tr.t0,
+                   policy, 0, npairs, slot_of + g0);
   __syncthreads();
 #pragma unroll
   for (int u = 0; u < U; ++u) {
@@ -540,6 +549,172 @@ __global__ __launch_bounds__(kFusedThreads) void k_scan_position(
 }
 
 // ---------------------------------------------------------------------------
+// Small batches (at most 512 tokens and 4096 pairs) in ONE launch with a token bitmap per slot that spans
+// the batch, a pair to a lane.  Bound by latency: the launch (1.9 us for an empty kernel), one round of
+// global loads, LDS round trips, and stores.  Every workgroup maps ALL pairs (1 to 4 per thread, each
+// keeps the whole count and offset table) and then writes its eighth of the results, so no
+// workgroup waits for another; one alone spent 1.4 to 2.8 us on storing, mostly the [R][P] matrix of pairs per
+// (source rank, slot).
+//
+// Where k_layout_once below could do it too, this takes at most a pair to a thread (kFewPairsOfK), and
+// half of that without a compile-time k (kFewPairs).  Measured (a layout in a graph of 40; 32 ranks x 9 slots, in
+// brackets that one): top-8, T = 32 / 64 / 96 / 128 3.7 / 3.7 / 3.7 / 3.8 us (4.0 / 4.1 / 4.4 / 4.4), T = 192 / 256 /
+// 384 / 512 4.4 / 4.6 / 5.3 / 5.8 (4.4 / 4.4 / 4.6 / 4.7); top-4, T = 128 / 384 / 512 3.6 / 4.3 / 4.4 (3.9 / 4.1 / 4.2);
+// top-5, T = 32 / 96 / 192 3.9 / 3.95 / 4.2 (4.1 / 4.0 / 4.1); top-3, T = 160 / 256 4.0 / 4.1 (4.0 / 4.0); 64 ranks,
+// top-8, T = 128 / 256 4.5 / 5.4 (5.2 / 5.2).  Beyond these it takes more than top-10, and tables that do not
+// fit there (8 ranks x 265 slots, T = 32: 8.5 us, in tiles 12.6).
+//
+// The eight results fit together only if all eight workgroups saw one mask.  An
+// instance of one context keeps its mask still while a layout runs: only its own
+// later calls on the stream change it.  With several contexts another one's combine
+// may drop a rank, or another one's caller may update the mask, at any moment.  So
+// there ONE workgroup does it all (each entry of the replica lists is found live or
+// dead once, and every pair, count and row follows from that), up to the size from
+// which the tiled path, where each pair is mapped once, is as fast: T = 32 / 128 / 256 / 384
+// 4.1 / 4.4 / 5.7 / 7.2 us, in tiles 7.5.  The launch
+// decides by the number of contexts; a launch captured while there was one is
+// overruled by the word behind the membership version, which says that there are more.
+// ---------------------------------------------------------------------------
+constexpr int kSmallBlocks = 8;
+constexpr int kSmallTokens = 512;
+constexpr int kSmallPairsPerThread = 4;
+constexpr int kSmallPairs = kMapThreads * kSmallPairsPerThread;
+constexpr int kSoloTokens = 384;  // the limits for one workgroup
+constexpr int kSoloPairs = kMapThreads * 3;
+constexpr int kFewPairs = 512, kFewPairsOfK = 1024;  // up to these not for k_layout_once
+constexpr uint32_t kSoloBit = 1u << 31;
+
+__device__ __forceinline__ int vector_load(const int32_t* p) {
+  return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+}
+
+// Row stride of token bitmaps in words; odd, so that lanes on different slots reading
+// the same word index hit different banks.
+__host__ __device__ inline int token_stride(int tokens) { return ((tokens + 31) / 32) | 1; }
+inline size_t small_lds_bytes(int E, int P, int R, int T, int k) {
+  return sizeof(int32_t) * (route_table_ints(E, P, R) + P + (P + 1) +
+                            (size_t)P * token_stride(T) + (size_t)T * k);
+}
+
+// cnt[p] = tokens [lo, hi) in the bitmap of slot p, for the kSrcChunks * 64 slots from p0 on;
+// lo < hi are the same for the whole wavefront.  The slots' words are read side by side, so
+// that the LDS latencies overlap.
+template <int kSrcChunks>
+__device__ __forceinline__ void store_src_counts(const uint32_t* s_bm, int stride, int p0, int P,
+                                                 int lo, int hi, int32_t* __restrict__ cnt) {
+  const int w0 = lo >> 5, w1 = (hi - 1) >> 5;
+  int c[kSrcChunks] = {};
+  for (int w = w0; w <= w1; ++w) {
+    uint32_t m = ~0u;
+    if (w == w0) m &= ~0u << (lo & 31);
+    if (w == w1) m &= ~0u >> (31 - ((hi - 1) & 31));
+    uint32_t v[kSrcChunks];
+#pragma unroll
+    for (int u = 0; u < kSrcChunks; ++u) {
+      const int p = p0 + u * 64 + (int)(threadIdx.x & 63);
+      v[u] = s_bm[(p < P ? p : P - 1) * stride + w];
+    }
+#pragma unroll
+    for (int u = 0; u < kSrcChunks; ++u) c[u] += __popc(v[u] & m);
+  }
+#pragma unroll
+  for (int u = 0; u < kSrcChunks; ++u) {
+    const int p = p0 + u * 64 + (int)(threadIdx.x & 63);
+    if (p < P) cnt[p] = c[u];
+  }
+}
+
+template <int KC, int U, bool LARGE>
+__global__ __launch_bounds__(kMapThreads) void k_layout_small(
+    const int32_t* __restrict__ topk_idx, const int32_t* __restrict__ l2p_off,
+    const int32_t* __restrict__ l2p_list, const int32_t* __restrict__ active,
+    const int32_t* __restrict__ mem_version, uint32_t T_k, int E, int P, int R, float inv_S,
+    const int32_t* __restrict__ tbl_version, int policy, int tokens_per_rank, int S,
+    int32_t* __restrict__ slot_of, int32_t* __restrict__ row_of, int32_t* __restrict__ src_of,
+    int32_t* __restrict__ count, int32_t* __restrict__ offset, int32_t* __restrict__ rank_count,
+    int32_t* __restrict__ rank_offset, int32_t* __restrict__ cnt_src,
+    int32_t* __restrict__ status, int32_t* __restrict__ step_epoch) {
+  const int T = T_k & 0xffff, k = KC > 0 ? KC : T_k >> 16 & 0xff;  // in one preloaded word
+  const int npairs = T * k;
+  const int stride = token_stride(T);
+  extern __shared__ int32_t smem[];
+  int32_t* s_count = smem;                        // [P] pairs per slot
+  uint32_t* s_bm = (uint32_t*)(s_count + P);      // [P][stride] token bitmap per slot
+  int32_t* s_offset = (int32_t*)(s_bm + P * stride);  // [P+1] exclusive scan of s_count
+  int32_t* s_idx = s_offset + P + 1;              // [T*k] router indices, KC == 0 only
+  int32_t* s_tab = s_idx + (KC == 0 ? npairs : 0);
+  __shared__ int32_t s_drop[2];
+  const int tid = threadIdx.x;
+
+  // every global read of this kernel is issued here, none depends on another
+  int my_e[U], slot[U];
+#pragma unroll
+  for (int u = 0; u < U; ++u) {
+    const int i = tid + u * kMapThreads;
+    my_e[u] = i < npairs ? topk_idx[i] : -1;
+  }
+  const int version = blockIdx.x == 0 && tid == 0 ? *tbl_version + *mem_version : 0;
+  // several contexts in the instance: the first workgroup does it all.  (A vector load: a scalar one
+  // would be waited for together with every kernel argument.)
+  const int several_v = vector_load(&mem_version[1]);
+  RouteTableLoad<LARGE> tables = {l2p_off, l2p_list, active, E, R, P, kMapThreads};
+  tables.fetch();
+#pragma nounroll
+  for (int i = tid; i < P * (stride + 1); i += kMapThreads) s_count[i] = 0;  // and s_bm
+  if (tid < 2) s_drop[tid] = 0;
+  const RouteTables rt = tables.fill(s_tab, inv_S);
+  if constexpr (KC == 0) {
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+      if (tid + u * kMapThreads < npairs) s_idx[tid + u * kMapThreads] = my_e[u];
+  }
+  // the pairs [own_lo, own_hi) whose results this workgroup writes, and as which of how many; with
+  // `solo` the first one's are all, the others go along and write nothing
+  const bool solo = __builtin_amdgcn_readfirstlane(several_v) != 0 || (T_k & kSoloBit) != 0;
+  const int blocks = solo ? 1 : kSmallBlocks, block = solo && blockIdx.x > 0 ? R : blockIdx.x;
+  const int share = ((npairs + kSmallBlocks - 1) / kSmallBlocks + 63) & ~63;
+  const int own_lo = solo ? (blockIdx.x > 0 ? npairs : 0) : blockIdx.x * share;
+  const int own_hi = solo || own_lo + share > npairs ? npairs : own_lo + share;
+  __syncthreads();
+  map_pairs<KC, U>(rt, my_e, s_idx, slot, s_bm, stride, s_count, s_drop, npairs, k, E, 0, policy, own_lo,
+                   own_hi, slot_of);
+  __syncthreads();
+
+  if (tid < 64) wave_exclusive_scan([=](int p) { return s_count[p]; }, s_offset, P);
+  __syncthreads();
+
+  const int N = s_offset[P];
+#pragma unroll
+  for (int u = 0; u < U; ++u) {
+    const int i = tid + u * kMapThreads;
+    if (i >= own_lo && i < own_hi) {
+      const int p = slot[u];
+      int row = -1;
+      if (p >= 0) {
+        row = s_offset[p] + rank_in_slot(&s_bm[p * stride], i / k);
+        src_of[row] = i;
+      }
+      row_of[i] = row;
+      if (i >= N) src_of[i] = -1;  // rows past the last routed pair
+    }
+  }
+  // pairs per (source rank, slot): the tokens of a source rank are a bit range; wavefronts
+  // take source ranks, lanes slots, five sets of 64 slots at once where there are more than one
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  for (int b = block * (kMapThreads / 64) + wave; b < R; b += blocks * (kMapThreads / 64)) {
+    const int lo = b * tokens_per_rank, hi = lo + tokens_per_rank;
+    int32_t* cnt = cnt_src + (int64_t)b * P;
+    if (P <= 64)
+      store_src_counts<1>(s_bm, stride, 0, P, lo, hi, cnt);
+    else
+      for (int p0 = 0; p0 < P; p0 += 320) store_src_counts<5>(s_bm, stride, p0, P, lo, hi, cnt);
+  }
+  if (blockIdx.x == 0)
+    write_step_tables(kMapThreads, s_offset, s_drop[0], s_drop[1], version, count, offset, rank_count,
+                      rank_offset, status, step_epoch, R, S, P);
+}
+
+// ---------------------------------------------------------------------------
 // The whole layout in ONE launch, for batches up to 16384 pairs.  A workgroup owns a
 // share of the tokens.  It counts the pairs per slot of ALL tokens,
 // those ahead of its share, its own and those behind it apart, so it needs nothing from
@@ -548,47 +723,29 @@ __global__ __launch_bounds__(kFusedThreads) void k_scan_position(
 // workgroup maps all pairs, the instructions per pair.  Hence a lane takes a whole token,
 // whose indices it compares in registers, the routing of an expert is one word that is
 // prepared once (`build_entries`), pairs without a slot have a sink to be counted in instead
-// of a branch, and what does not wait for the scan stands between its barriers.  Batches of
-// up to 512 pairs are a pair to a lane: there the chain counts, not the sum.
+// of a branch, and what does not wait for the scan stands between its barriers.
 //
-// Measured (a layout in a graph of 40; 32 ranks x 9 slots, top-8), in brackets with a pair to
-// a lane, branches, and beyond 512 tokens a second launch for scan and rows: T = 32 / 256 / 512
-// 4.0 / 4.5 / 4.7 us (3.9 / 4.8 / 6.2), 768 / 1024 / 1536 / 2048 5.0 / 5.3 / 5.7 / 6.2 (7.6 / 7.7 / 7.8 / 7.9),
+// Measured (a layout in a graph of 40; 32 ranks x 9 slots, top-8), in brackets k_layout_small, and beyond 512
+// tokens tiles: T = 256 / 512 4.4 / 4.7 us (4.6 / 5.8), 768 / 1024 / 1536 / 2048 5.1 / 5.3 / 5.7 / 6.1 (7.6 / 7.7 / 7.8 / 7.9),
 // 3072 / 4096 7.3 / 8.6 (8.1 / 8.4); with a Zipf router, whose hot slots' counts are one LDS word
-// for many lanes, 2048 7.2 (7.7), 4096 10.7 (8.1).  T = 1024 of 64 ranks x 9 slots 5.8 (12.0), top-2 of
-// 32 ranks 4.0 (7.4), top-6 of 24 ranks 4.2 (7.8).  So up to 16384 pairs.  Shares of about 64 tokens, whole
+// for many lanes, 2048 7.2 (7.8), 4096 10.7 (8.1).  T = 1024 of 64 ranks x 9 slots 5.8 (12.0), top-2 of
+// 32 ranks 4.1 (7.4), top-6 of 24 ranks 4.2 (7.8).  So up to 16384 pairs.  Shares of about 64 tokens, whole
 // source ranks or, where a rank has at least 768 pairs, a part of one, whose first then also counts the
-// rank's other tokens for the rank's totals: 8 ranks, T = 1024 / 2048 5.4 / 6.4 (whole ranks 5.5 / 7.3; two
-// launches 8.0 / 8.2), 2 ranks, T = 512 / 1024 / 2048 4.5 / 5.4 / 6.8 (5.4 / 7.1 / - ; 5.9 / 7.2 / 7.8), 4 ranks,
+// rank's other tokens for the rank's totals: 8 ranks, T = 1024 / 2048 5.3 / 6.3 (whole ranks 5.5 / 7.3; two
+// launches 8.0 / 8.1), 2 ranks, T = 512 / 1024 / 2048 4.6 / 5.6 / 6.8 (5.4 / 7.1 / - ; 5.9 / 7.2 / 7.8), 4 ranks,
 // top-3, T = 1024 4.2 (4.6; 7.2); with fewer pairs it costs as much as it gives (32 ranks, top-2, T = 4096, 256
-// pairs to a rank: 5.5 in parts, 5.1).  512 threads, 1024 for more than
-// 1024 items (T = 256 / 1024 / 2048: 4.3 / 5.1 / 6.2 with 512, 4.6 / 5.0 / 6.0 with 1024).
+// pairs to a rank: 5.5 in parts, 5.2).  512 threads, 1024 for more than 1024 tokens (T = 256 / 1024 / 2048: 0.3 /
+// -0.1 / -0.2 us with 1024 against 512).
 //
 // Up to 512 tokens and 4096 pairs there are 8 workgroups, however many ranks.
 //
-// The workgroups' results fit together only if all of them saw one mask.  An
-// instance of one context keeps its mask still while a layout runs: only its own
-// later calls on the stream change it.  With several contexts another one's combine
-// may drop a rank, or another one's caller may update the mask, at any moment.  So
-// there ONE workgroup does it all (each entry of the replica lists is found live or
-// dead once, and every pair, count and row follows from that), up to the size from
-// which the tiled path, where each pair is mapped once, is as fast.  The launch
-// decides by the number of contexts; a launch captured while there was one is
-// overruled by the word behind the membership version, which says that there are more:
-// its first workgroup then does it all, as many shares at once as fit in LDS: T = 32 / 256 / 512 / 1024 /
-// 2048 5.0 / 8.7 / 11.2 / 19.6 / 30 us (15.8 / 16.9 / 18.4 / 32.6 / 61 with one share after the other, which
-// made the launches of one context 0.1 us faster).  One workgroup for the whole batch is an instance
-// of its own (SOLO), with a pair to a lane up to 2048 pairs and 1024 threads, which share its source ranks'
-// counts: T = 32 / 128 / 256 / 384 4.3 / 5.6 / 6.7 / 7.5 us (4.9 / 7.3 / 8.3 / 9.7 without).
+// Only for an instance of one context, see k_layout_small.  A launch captured while there was one is overruled by
+// the word behind the membership version, which says that there are more:
+// its first workgroup then does it all, as many shares at once as fit in LDS: T = 256 / 512 / 1024 /
+// 2048 8.6 / 11.1 / 19.3 / 29.9 us (16.9 / 18.4 / 32.6 / 61 with one share after the other).
 // ---------------------------------------------------------------------------
-constexpr int kSmallBlocks = 8;  // and where they apply:
-constexpr int kSmallTokens = 512;
-constexpr int kSmallPairs = 4096;
-constexpr int kSoloTokens = 384;  // the limits for one workgroup
-constexpr int kSoloPairs = 3072;
 constexpr int kOnceThreads = 1024;
 constexpr int kOnceMaxK = 10;  // compile-time top-k, a token to a lane, up to here
-constexpr int kPairPairs = 512, kSoloPairPairs = 2048;  // a pair to a lane up to here
 constexpr int kOncePairs = 16384, kShareTokens = 64, kPartPairs = 768;
 
 // Element i of a small global array: a 32-bit offset from a scalar address, which takes no 64-bit
@@ -596,10 +753,6 @@ constexpr int kOncePairs = 16384, kShareTokens = 64, kPartPairs = 768;
 template <class T>
 __device__ __forceinline__ T& at(T* p, uint32_t i) {
   return *(T*)((char*)p + (uint32_t)(i * (uint32_t)sizeof(T)));
-}
-
-__device__ __forceinline__ int vector_load(const int32_t* p) {
-  return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
 }
 
 // What an expert's pairs need to know, one word per expert: the slot of its pairs from even tokens
@@ -699,9 +852,6 @@ __device__ __forceinline__ int bits_between(const uint32_t* bm, int lo, int hi) 
   return c + __popc(bm[w1] & ~0u >> (31 - ((hi - 1) & 31)));
 }
 
-// Row stride of a share's token bitmaps in words; odd, so that lanes on different slots reading
-// the same word index hit different banks.
-__host__ __device__ inline int share_stride(int tokens) { return ((tokens + 31) / 32) | 1; }
 // Counts per slot: tokens ahead of the share, its own, those behind it, and of these the ones that belong
 // to the share's source rank where that is several shares and this its first.
 __host__ __device__ constexpr int regions(bool parts) { return parts ? 4 : 3; }
@@ -713,15 +863,15 @@ __host__ __device__ inline uint32_t share_tokens(uint32_t tokens_per_rank, uint3
 __host__ __device__ inline uint32_t once_zeros(uint32_t P, uint32_t stride, bool parts) {
   return ((P + kSinks) * (regions(parts) + stride) + 3) / 4 * 4;
 }
-// Where the last of it ends: what starts at zero, tables, entries or router indices, offsets, a share's slots.
-__host__ __device__ inline uint32_t once_end(uint32_t zeros, uint32_t tables, uint32_t entries, uint32_t P, uint32_t pairs) {
-  return (zeros + tables + entries + (P + 1) + pairs + 3) / 4 * 4;
+// Where the last of it ends: what starts at zero, tables, entries, offsets, a share's slots.
+__host__ __device__ inline uint32_t once_end(uint32_t zeros, uint32_t tables, uint32_t E, uint32_t P, uint32_t pairs) {
+  return (zeros + tables + (E + 1) + (P + 1) + pairs + 3) / 4 * 4;
 }
 // `alone`: the tokens that a workgroup alone takes at once, whose counts and bitmaps are behind the rest; or 0.
-inline size_t once_lds_bytes(int E, int P, int R, int T, int tokens, int alone, int k) {
-  return sizeof(int32_t) * ((size_t)once_end(once_zeros(P, share_stride(tokens), true), route_table_ints(E, P, R),
-                                             k > kOnceMaxK ? T * k : E + 1, P, (alone > 0 ? alone : tokens) * k) +
-                            (alone > 0 ? once_zeros(P, share_stride(alone), true) : 0));
+inline size_t once_lds_bytes(int E, int P, int R, int tokens, int alone, int k) {
+  return sizeof(int32_t) * ((size_t)once_end(once_zeros(P, token_stride(tokens), true), route_table_ints(E, P, R),
+                                             E, P, (alone > 0 ? alone : tokens) * k) +
+                            (alone > 0 ? once_zeros(P, token_stride(alone), true) : 0));
 }
 
 // Exclusive scan of the slots' totals into s_offset[0..P]: the wavefronts, the last one first, take
@@ -749,39 +899,31 @@ __device__ __forceinline__ int opaque(int x) {
   return x;
 }
 
-// KC: compile-time k, or 0 for any.  TOKEN: a lane takes a token, otherwise a pair.  PARTS: a share is a part
-// of a source rank, one of `subs`, otherwise `ranks` whole ones.  SOLO: a share is the whole batch.
+// K: top-k.  PARTS: a share is a part of a source rank, one of `subs`, otherwise `ranks` whole ones.
 // Four words hold the shape (T and tokens per rank; E and P; R, the source ranks of a share << 12 and
-// how many shares at once a workgroup alone takes << 24; S, policy << 12, k << 13, wavefronts << 19, shares in a rank << 24), so that it arrives in registers with the first pointers.
-template <int KC, bool TOKEN, bool LARGE, bool PARTS, bool SOLO>
+// how many shares at once a workgroup alone takes << 24; S, policy << 12, wavefronts << 13, shares in a rank << 18), so that it arrives in registers with the first pointers.
+template <uint32_t K, bool LARGE, bool PARTS>
 __global__ __launch_bounds__(kOnceThreads) void k_layout_once(
     const int32_t* __restrict__ topk_idx, const int32_t* __restrict__ l2p_off,
     const int32_t* __restrict__ l2p_list, const int32_t* __restrict__ active,
     const int32_t* __restrict__ mem_version, uint32_t T_rank, uint32_t E_P, uint32_t R_share,
-    uint32_t S_policy_k_waves_subs, const int32_t* __restrict__ tbl_version, int32_t* __restrict__ slot_of,
+    uint32_t S_policy_waves_subs, const int32_t* __restrict__ tbl_version, int32_t* __restrict__ slot_of,
     int32_t* __restrict__ row_of, int32_t* __restrict__ src_of, int32_t* __restrict__ cnt_src,
     int32_t* __restrict__ count, int32_t* __restrict__ offset, int32_t* __restrict__ rank_count,
     int32_t* __restrict__ rank_offset, int32_t* __restrict__ status,
     int32_t* __restrict__ step_epoch) {
-  constexpr uint32_t N = TOKEN ? KC : 1;
   const uint32_t T = T_rank & 0xffff, tokens_per_rank = T_rank >> 16;
   const uint32_t E = E_P & 0xffff, R = R_share & 0xfff;
   uint32_t width = R_share >> 12 & 0xfff;  // source ranks of a share
-  const uint32_t S = S_policy_k_waves_subs & 0xfff, policy = S_policy_k_waves_subs >> 12 & 1;
-  const uint32_t k = KC > 0 ? KC : S_policy_k_waves_subs >> 13 & 63;
-  const uint32_t waves = S_policy_k_waves_subs >> 19 & 31, nt = waves * 64;
-  const uint32_t subs = PARTS ? S_policy_k_waves_subs >> 24 : 1;
+  const uint32_t S = S_policy_waves_subs & 0xfff, policy = S_policy_waves_subs >> 12 & 1;
+  const uint32_t waves = S_policy_waves_subs >> 13 & 31, nt = waves * 64;
+  const uint32_t subs = PARTS ? S_policy_waves_subs >> 18 : 1;
   const uint32_t tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const uint32_t per_item = TOKEN ? 1 : k, items = T * per_item;
-  const auto load = [&](uint32_t i, int (&e)[N]) { __builtin_memcpy(e, &at(topk_idx, i * N), sizeof(e)); };
-  // i / k; a k that is not known by way of float, which is exact: (i + 0.5) / k is at least 0.5 / k away
-  // from an integer, and i < 2^16
-  const float inv_k = __builtin_amdgcn_rcpf((float)k);
-  const auto token_at = [=](uint32_t i) { return KC > 0 ? i / k : (uint32_t)(((float)i + 0.5f) * inv_k); };
+  const auto load = [&](uint32_t t, int (&e)[K]) { __builtin_memcpy(e, &at(topk_idx, t * K), sizeof(e)); };
   // The first round's tokens from the last thread down: the first threads have the tables to do.
-  uint32_t item = TOKEN ? nt - 1 - tid : tid;
-  int e[N];
-  load(item < items ? item : items - 1, e);
+  uint32_t t = nt - 1 - tid;
+  int e[K];
+  load(t < T ? t : T - 1, e);
   RouteTableLoad<LARGE> tables = {l2p_off, l2p_list, active, (int)E, (int)R, (int)(E_P >> 16), (int)nt};
   tables.fetch();
   // several contexts in the instance: the first workgroup does it all.  (A vector load: a scalar one
@@ -790,18 +932,13 @@ __global__ __launch_bounds__(kOnceThreads) void k_layout_once(
 
   extern __shared__ __align__(16) int32_t smem[];
   const uint32_t part = share_tokens(tokens_per_rank, width, subs);
-  const uint32_t zeros = once_zeros(E_P >> 16, share_stride(part), PARTS);
+  const uint32_t zeros = once_zeros(E_P >> 16, token_stride(part), PARTS);
   int32_t* s_tab = smem + zeros;
 #pragma nounroll
   for (uint32_t i = tid * 4; i < zeros; i += nt * 4) *(int4*)(smem + i) = make_int4(0, 0, 0, 0);
   const RouteTables rt = tables.fill(s_tab, __builtin_amdgcn_rcpf((float)S));
   uint32_t* s_entry = (uint32_t*)(s_tab + route_table_ints(E, E_P >> 16, R));  // [E+1]
-  if constexpr (KC == 0) {
-    int32_t* s_idx = (int32_t*)s_entry;  // [T*k] router indices
-#pragma nounroll
-    for (uint32_t i = tid; i < items; i += nt) s_idx[i] = i == tid ? e[0] : at(topk_idx, i);
-  }
-  const bool alone = !SOLO && (PARTS || width < R) && __builtin_amdgcn_readfirstlane(several_v) != 0;
+  const bool alone = (PARTS || width < R) && __builtin_amdgcn_readfirstlane(several_v) != 0;
   uint32_t share = blockIdx.x;
   // PARTS: the share's rank (share / subs, by way of float), and which of the rank's shares it is
   const auto rank_of_part = [&]() {
@@ -814,19 +951,16 @@ __global__ __launch_bounds__(kOnceThreads) void k_layout_once(
   if (!PARTS && alone && (R_share >> 24) > 1) {  // as many shares at once as there is LDS for, behind the rest
     width *= R_share >> 24;
     const uint32_t P = E_P >> 16, many = width * tokens_per_rank;
-    base = once_end(zeros, route_table_ints(E, P, R), KC > 0 ? E + 1 : items, P, many * k);
-    const uint32_t end = base + once_zeros(P, share_stride(many), false);
+    base = once_end(zeros, route_table_ints(E, P, R), E, P, many * K);
+    const uint32_t end = base + once_zeros(P, token_stride(many), false);
 #pragma nounroll
     for (uint32_t i = base + tid * 4; i < end; i += nt * 4) *(int4*)(smem + i) = make_int4(0, 0, 0, 0);
   }
   const bool rounds = alone && (PARTS || width < R);
   __syncthreads();
-  bool repeats = false;
-  if constexpr (TOKEN) {
-    build_entries<LARGE>(rt, s_entry, E, E_P >> 16, policy, nt);
-    repeats = any_repeats(e);
-    __syncthreads();
-  }
+  build_entries<LARGE>(rt, s_entry, E, E_P >> 16, policy, nt);
+  bool repeats = any_repeats(e);
+  __syncthreads();
 
   // One round, over the whole batch; alone with several shares, a second one for each, over its tokens.
   uint32_t lo = T;
@@ -837,70 +971,57 @@ __global__ __launch_bounds__(kOnceThreads) void k_layout_once(
   const auto last_token = [&]() {
     return PARTS ? min(lo + part, (rank0 + 1) * tokens_per_rank) : min(lo + width * tokens_per_rank, T);
   };
-  uint32_t end = items;
+  uint32_t end = T;
   if (!rounds) lo = first_token();
   int rows = 0;
   for (uint32_t round = 0;; ++round) {
     // (Opaque, or whatever follows from it would be computed ahead of the loop by every wavefront.)
     const uint32_t P = opaque(E_P >> 16), P2 = P + kSinks;
     const uint32_t ranks = PARTS ? 1 : opaque(width), tokens = PARTS ? part : ranks * tokens_per_rank;
-    const uint32_t stride = share_stride(tokens);
+    const uint32_t stride = token_stride(tokens);
     int32_t* const s_cnt = smem + base;                   // [regions][P2] pairs per slot
     uint32_t* const s_bm = (uint32_t*)(s_cnt + regions(PARTS) * P2);  // [P2][stride] bitmap of the share's tokens per slot
-    int32_t* const s_offset = smem + opaque(zeros + route_table_ints(E, P, R) +
-                                            (KC > 0 ? E + 1 : items));  // [P+1] exclusive scan of the totals
-    int32_t* const s_slot = s_offset + P + 1;             // [tokens*k] slots of the share's pairs
+    int32_t* const s_offset = smem + opaque(zeros + route_table_ints(E, P, R) + E + 1);  // [P+1] exclusive scan of the totals
+    int32_t* const s_slot = s_offset + P + 1;             // [tokens*K] slots of the share's pairs
     const uint32_t hi = !PARTS ? min(lo + tokens, T) : lo < T ? last_token() : T;
 #pragma nounroll
-    while (item < end) {
-      const uint32_t now = item;
-      item += nt;
-      int next[N];
-      if (item < end) load(item, next);
-      int p[N];
-      uint32_t t = now, j0 = 0;
-      if constexpr (TOKEN) {
-        map_token<N>(rt, s_entry, E, P, e, repeats, t, p);
-      } else {
-        t = token_at(now);
-        j0 = now - t * k;
-        p[0] = P + 1;
-        const bool again = repeats_earlier<KC>(e[0], j0, (int32_t*)s_entry + t * k);  // (all lanes)
-        if ((uint32_t)e[0] < E && !again) {
-          p[0] = pick_slot(rt, e[0], t, policy);
-          if (p[0] < 0) p[0] = P;
-        }
-      }
+    while (t < end) {
+      const uint32_t now = t;
+      t += nt;
+      int next[K];
+      if (t < end) load(t, next);
+      int p[K];
+      map_token<K>(rt, s_entry, E, P, e, repeats, now, p);
       // counted in the token's region, and if the token is the share's own, kept
-      const bool own = t >= lo && t < hi;
-      int32_t* cnt = s_cnt + (own ? P2 : t < lo ? 0 : 2 * P2);
+      const bool own = now >= lo && now < hi;
+      int32_t* cnt = s_cnt + (own ? P2 : now < lo ? 0 : 2 * P2);
 #pragma unroll
-      for (uint32_t j = 0; j < N; ++j) atomicAdd(&cnt[p[j]], 1);
-      if (PARTS && sub == 0 && !alone && t >= hi && t < (rank0 + 1) * tokens_per_rank) {
+      for (uint32_t j = 0; j < K; ++j) atomicAdd(&cnt[p[j]], 1);
+      if (PARTS && sub == 0 && !alone && now >= hi && now < (rank0 + 1) * tokens_per_rank) {
 #pragma unroll
-        for (uint32_t j = 0; j < N; ++j) atomicAdd(&s_cnt[3 * P2 + p[j]], 1);
+        for (uint32_t j = 0; j < K; ++j) atomicAdd(&s_cnt[3 * P2 + p[j]], 1);
       }
       if (own) {
-        const uint32_t tl = t - lo;
+        const uint32_t tl = now - lo;
         uint32_t* bm = s_bm + (tl >> 5);
-        int32_t* to = s_slot + tl * k + j0;
+        int32_t* to = s_slot + tl * K;
         const uint32_t bit = 1u << (tl & 31);
 #pragma unroll
-        for (uint32_t j = 0; j < N; ++j) to[j] = p[j];
+        for (uint32_t j = 0; j < K; ++j) to[j] = p[j];
 #pragma unroll
-        for (uint32_t j = 0; j < N; ++j) {
+        for (uint32_t j = 0; j < K; ++j) {
           atomicOr(&bm[__umul24(p[j], stride)], bit);
         }
       }
-      if (item < end) {
+      if (t < end) {
 #pragma unroll
-        for (uint32_t j = 0; j < N; ++j) e[j] = next[j];
-        if constexpr (TOKEN) repeats = any_repeats(e);
+        for (uint32_t j = 0; j < K; ++j) e[j] = next[j];
+        repeats = any_repeats(e);
       }
     }
     __syncthreads();
     // Between two barriers: the scan, and what does not need it.
-    const uint32_t n = lo < T ? (hi - lo) * k : 0, g0 = lo * k;
+    const uint32_t n = lo < T ? (hi - lo) * K : 0, g0 = lo * K;
     const auto total = [=](uint32_t p) { return s_cnt[p] + s_cnt[P2 + p] + s_cnt[2 * P2 + p]; };
     int dead = 0, masked = 0, version = 0;
     if (round == 0) {
@@ -914,50 +1035,28 @@ __global__ __launch_bounds__(kOnceThreads) void k_layout_once(
     // pairs per (source rank, slot): the tokens of a source rank are a bit range
     if (n > 0) {
       const uint32_t rank = PARTS ? rank0 : share * ranks, mine = min(R - rank, ranks);
-      if (SOLO && tokens > 64) {
-        // Many in a row: wavefronts share the source ranks of 64 slots, if there are enough wavefronts.
-        const float inv = __builtin_amdgcn_rcpf((float)((P + 63) >> 6)), w = (float)(tid >> 6) + 0.5f;
-        const uint32_t groups = max((uint32_t)(((float)waves + 0.5f) * inv), 1u), group = (uint32_t)(w * inv);
-        const uint32_t b0 = group, first = tid - group * ((P + 63) & ~63u);
-        if (group < groups) {
 #pragma nounroll
-          for (uint32_t p = first; p < P; p += nt) {
-            const uint32_t* bm = &s_bm[__umul24(p, stride)];
-#pragma unroll 2
-            for (uint32_t b = b0; b < mine; b += groups) {
-              const uint32_t from = b * tokens_per_rank;
-              // up to 32 tokens are in two words (what is behind the row's last one is masked)
-              const uint64_t two = (uint64_t)bm[(from >> 5) + 1] << 32 | bm[from >> 5];
-              at(cnt_src, (rank + b) * P + p) =
-                  tokens_per_rank <= 32 ? __popcll(two >> (from & 31) & (~0ull >> (64 - tokens_per_rank)))
-                                        : bits_between(bm, from, from + tokens_per_rank);
-            }
+      for (uint32_t p = tid; p < P; p += nt) {
+        const uint32_t* bm = &s_bm[__umul24(p, stride)];
+        uint32_t to = rank * P + p;
+        if constexpr (PARTS) {
+          if (alone)
+            at(cnt_src, to) = s_cnt[P2 + p] + (sub == 0 ? 0 : at(cnt_src, to));
+          else if (sub == 0)
+            at(cnt_src, to) = s_cnt[P2 + p] + s_cnt[3 * P2 + p];
+        } else if (tokens <= 64) {
+          uint64_t bits = bm[0];
+          if (stride > 1) bits |= (uint64_t)bm[1] << 32;
+          const uint64_t mask = ~0ull >> (64 - tokens_per_rank);
+#pragma nounroll
+          for (uint32_t b = 0; b < mine; ++b, to += P) {
+            at(cnt_src, to) = __popcll(bits & mask);
+            bits >>= tokens_per_rank;
           }
-        }
-      } else {
+        } else {
 #pragma nounroll
-        for (uint32_t p = tid; p < P; p += nt) {
-          const uint32_t* bm = &s_bm[__umul24(p, stride)];
-          uint32_t to = rank * P + p;
-          if constexpr (PARTS) {
-            if (alone)
-              at(cnt_src, to) = s_cnt[P2 + p] + (sub == 0 ? 0 : at(cnt_src, to));
-            else if (sub == 0)
-              at(cnt_src, to) = s_cnt[P2 + p] + s_cnt[3 * P2 + p];
-          } else if (tokens <= 64) {
-            uint64_t bits = bm[0];
-            if (stride > 1) bits |= (uint64_t)bm[1] << 32;
-            const uint64_t mask = ~0ull >> (64 - tokens_per_rank);
-#pragma nounroll
-            for (uint32_t b = 0; b < mine; ++b, to += P) {
-              at(cnt_src, to) = __popcll(bits & mask);
-              bits >>= tokens_per_rank;
-            }
-          } else {
-#pragma nounroll
-            for (uint32_t b = 0; b < mine; ++b, to += P)
-              at(cnt_src, to) = bits_between(bm, b * tokens_per_rank, (b + 1) * tokens_per_rank);
-          }
+          for (uint32_t b = 0; b < mine; ++b, to += P)
+            at(cnt_src, to) = bits_between(bm, b * tokens_per_rank, (b + 1) * tokens_per_rank);
         }
       }
     }
@@ -965,7 +1064,7 @@ __global__ __launch_bounds__(kOnceThreads) void k_layout_once(
     int row = -1;
     const auto place = [&](uint32_t i) {  // slot of the share's pair i, its row less the slot's offset
       p = s_slot[i];
-      row = s_cnt[p] + rank_in_slot(&s_bm[p * stride], token_at(i));
+      row = s_cnt[p] + rank_in_slot(&s_bm[p * stride], i / K);
     };
     if (tid < n) place(tid);
     __syncthreads();
@@ -1005,21 +1104,16 @@ __global__ __launch_bounds__(kOnceThreads) void k_layout_once(
     }
 #pragma nounroll
     for (uint32_t q = tid; q < P2 * stride; q += nt) s_bm[q] = 0;
-    item = lo * per_item + tid;
-    end = last_token() * per_item;
-    if (item < end) {
-      load(item, e);
-      if constexpr (TOKEN) repeats = any_repeats(e);
+    t = lo + tid;
+    end = last_token();
+    if (t < end) {
+      load(t, e);
+      repeats = any_repeats(e);
     }
     __syncthreads();
   }
 }
 
-// What a bitmap of the whole batch would take: the bound for the forms of 8 workgroups and of one.
-inline size_t small_lds_bytes(int E, int P, int R, int T, int k) {
-  return sizeof(int32_t) * (route_table_ints(E, P, R) + P + (P + 1) +
-                            (size_t)P * share_stride(T) + (size_t)T * k);
-}
 // What a share holds: source ranks, or a part of one.
 struct ShareSize {
   int ranks, subs;
@@ -1468,30 +1562,28 @@ static auto map_count_for(int k, int pairs) {
   return pairs <= kMapThreads ? map_count_for_k<1, WIDE>(k)
        : pairs <= 2 * kMapThreads ? map_count_for_k<2, WIDE>(k) : map_count_for_k<4, WIDE>(k);
 }
-template <bool LARGE, bool PARTS, bool SOLO>
-static decltype(&k_layout_once<0, false, LARGE, PARTS, SOLO>) layout_once_for(int k, bool token) {
-  if (!token) return k == 8 ? k_layout_once<8, false, LARGE, PARTS, SOLO> : k == 4 ? k_layout_once<4, false, LARGE, PARTS, SOLO>
-                   : k == 2 ? k_layout_once<2, false, LARGE, PARTS, SOLO> : k == 1 ? k_layout_once<1, false, LARGE, PARTS, SOLO>
-                                                              : k_layout_once<0, false, LARGE, PARTS, SOLO>;
-  switch (k) {
-    case 1: return k_layout_once<1, true, LARGE, PARTS, SOLO>;
-    case 2: return k_layout_once<2, true, LARGE, PARTS, SOLO>;
-    case 3: return k_layout_once<3, true, LARGE, PARTS, SOLO>;
-    case 4: return k_layout_once<4, true, LARGE, PARTS, SOLO>;
-    case 5: return k_layout_once<5, true, LARGE, PARTS, SOLO>;
-    case 6: return k_layout_once<6, true, LARGE, PARTS, SOLO>;
-    case 7: return k_layout_once<7, true, LARGE, PARTS, SOLO>;
-    case 8: return k_layout_once<8, true, LARGE, PARTS, SOLO>;
-    case 9: return k_layout_once<9, true, LARGE, PARTS, SOLO>;
-    case 10: return k_layout_once<10, true, LARGE, PARTS, SOLO>;
-    default: return k_layout_once<0, false, LARGE, PARTS, SOLO>;
-  }
+template <bool LARGE>
+static auto small_for(int k, int pairs) {
+#define EEP_SMALL(U)                                                                              \
+  (k == 8 ? k_layout_small<8, U, LARGE> : k == 4 ? k_layout_small<4, U, LARGE>                    \
+   : k == 2 ? k_layout_small<2, U, LARGE> : k == 1 ? k_layout_small<1, U, LARGE> : k_layout_small<0, U, LARGE>)
+  return pairs <= kMapThreads ? EEP_SMALL(1) : pairs <= 2 * kMapThreads ? EEP_SMALL(2) : EEP_SMALL(4);
+#undef EEP_SMALL
+}
+template <bool LARGE, bool PARTS>
+static auto once_for(int k) {
+  static const decltype(&k_layout_once<1, LARGE, PARTS>) of[kOnceMaxK] = {
+      k_layout_once<1, LARGE, PARTS>, k_layout_once<2, LARGE, PARTS>, k_layout_once<3, LARGE, PARTS>,
+      k_layout_once<4, LARGE, PARTS>, k_layout_once<5, LARGE, PARTS>, k_layout_once<6, LARGE, PARTS>,
+      k_layout_once<7, LARGE, PARTS>, k_layout_once<8, LARGE, PARTS>, k_layout_once<9, LARGE, PARTS>,
+      k_layout_once<10, LARGE, PARTS>};
+  return of[k - 1];
 }
 
 // Does an output array overlap the router indices (a caller that gives up its indices for the
-// result)?  Eight workgroups read all of them while others write already; one has read
-// everything before it writes, and in the tiled form a workgroup reads its own pairs' before it
-// writes these.
+// result)?  The workgroups of a one-launch form read all of them while others write already; one alone
+// has read everything before it writes, and in the tiled form a workgroup reads its own pairs'
+// before it writes these.
 static bool writes_its_input(const LayoutIO& c, int T) {
   const int64_t pairs = (int64_t)T * c.k;
   const struct { const int32_t* p; int64_t n; } out[] = {
@@ -1504,13 +1596,11 @@ static bool writes_its_input(const LayoutIO& c, int T) {
   return false;
 }
 
-// Workgroups of the one-launch form for this batch; 0: the tiled form.  `solo`: more than one
-// could disagree (the mask may change while the kernel runs, or an output overlaps the input).
+// Workgroups of a one-launch form for a small batch; 0: larger, or its tables do not fit.  `solo`: more
+// than one could disagree (the mask may change while the kernel runs, or an output overlaps the input).
 int layout_small_workgroups(int E, int P, int R, int T, int k, bool solo) {
   if (T < 1 || T > (solo ? kSoloTokens : kSmallTokens) ||
-      T * k > (solo ? kSoloPairs : kSmallPairs) || P + kSinks > kEntrySlots ||
-      small_lds_bytes(E, P, R, T, k) > kLayoutLdsLimit ||
-      once_lds_bytes(E, P, R, T, share_size(E, P, R, T / R, k, solo ? 1 : kSmallBlocks).tokens(T / R), 0, k) > kLayoutLdsLimit)
+      T * k > (solo ? kSoloPairs : kSmallPairs) || small_lds_bytes(E, P, R, T, k) > kLayoutLdsLimit)
     return 0;
   return solo ? 1 : kSmallBlocks;
 }
@@ -1529,37 +1619,41 @@ hipError_t launch_layout(const LayoutIO& c, int T, hipStream_t st) {
   const bool solo = c.mask_may_change || writes_its_input(c, T);
   const int small = layout_small_workgroups(c.E, c.P, c.R, T, c.k, solo);
   const ShareSize share = share_size(c.E, c.P, c.R, g.tokens_per_rank, c.k, small);
-  int grid = small;
-  if (small == 0 && !solo && c.k <= kOnceMaxK && (int64_t)T * c.k <= kOncePairs &&
-      c.P + kSinks <= kEntrySlots && share.subs < 256 &&
-      once_lds_bytes(c.E, c.P, c.R, T, share.tokens(g.tokens_per_rank), 0, c.k) <= kLayoutLdsLimit)
-    grid = share.count(c.R);
-  if (grid > 0) {
-    const bool token = c.k <= kOnceMaxK && !(T * c.k <= (solo ? kSoloPairPairs : kPairPairs) && (c.k & (c.k - 1)) == 0);
-    int nt = c.P > c.E ? c.P : c.E + 1;  // threads: for the tables, and for the items
-    const int most = solo || (token ? T : 2 * T * c.k) > kOnceThreads ? kOnceThreads : kOnceThreads / 2;
+  const int tokens = share.tokens(g.tokens_per_rank);
+  const bool has_k = c.k == 1 || c.k == 2 || c.k == 4 || c.k == 8;  // an instance of k_layout_small
+  const bool few = small > 0 && T * c.k <= (has_k ? kFewPairsOfK : kFewPairs);
+  if (!solo && !few && c.k <= kOnceMaxK && (int64_t)T * c.k <= kOncePairs && c.P + kSinks <= kEntrySlots &&
+      share.subs < 256 && once_lds_bytes(c.E, c.P, c.R, tokens, 0, c.k) <= kLayoutLdsLimit) {
+    int nt = c.P > c.E ? c.P : c.E + 1;  // threads: for the tables, and for the tokens
+    const int most = T > kOnceThreads ? kOnceThreads : kOnceThreads / 2;
     nt = nt < most ? most : nt < kOnceThreads ? (nt + 63) / 64 * 64 : kOnceThreads;
     // shares at once for a workgroup alone: all of them, or what fits beside the rest
-    const int tokens = share.tokens(g.tokens_per_rank);
     int at_once = share.subs > 1 ? 0 : std::min((c.R + share.ranks - 1) / share.ranks, 255);
     size_t lds;
-    while ((lds = once_lds_bytes(c.E, c.P, c.R, T, tokens, at_once > 1 ? tokens * at_once : 0, c.k)) > kLayoutLdsLimit &&
+    while ((lds = once_lds_bytes(c.E, c.P, c.R, tokens, at_once > 1 ? tokens * at_once : 0, c.k)) > kLayoutLdsLimit &&
            at_once > 1)
       at_once /= 2;
-    const bool large = large_tables(c.E, c.P, c.R, nt);
-    auto kern = large ? layout_once_for<true, false, false>(c.k, token)
-                : solo ? layout_once_for<false, false, true>(c.k, token)
-                : share.subs > 1 ? layout_once_for<false, true, false>(c.k, token)
-                                 : layout_once_for<false, false, false>(c.k, token);
-    hipLaunchKernelGGL(kern, dim3(grid), dim3(nt), lds, st, c.topk_idx,
+    auto kern = large_tables(c.E, c.P, c.R, nt) ? once_for<true, false>(c.k)
+                : share.subs > 1 ? once_for<false, true>(c.k) : once_for<false, false>(c.k);
+    hipLaunchKernelGGL(kern, dim3(small > 0 ? small : share.count(c.R)), dim3(nt), lds, st, c.topk_idx,
                        c.l2p_off, c.l2p_list, c.active, c.mem_version,
                        (uint32_t)T | (uint32_t)g.tokens_per_rank << 16, (uint32_t)c.E | (uint32_t)c.P << 16,
                        (uint32_t)c.R | (uint32_t)share.ranks << 12 | (uint32_t)at_once << 24,
-                       (uint32_t)c.S | (uint32_t)c.policy << 12 | (uint32_t)c.k << 13 | (uint32_t)(nt / 64) << 19 |
-                           (uint32_t)share.subs << 24,
+                       (uint32_t)c.S | (uint32_t)c.policy << 12 | (uint32_t)(nt / 64) << 13 |
+                           (uint32_t)share.subs << 18,
                        c.tbl_version, c.slot_of, c.row_of,
                        c.src_of, c.cnt_src, c.count, c.offset, c.rank_count, c.rank_offset, c.status,
                        c.step_epoch);
+    return hipGetLastError();
+  }
+  if (small > 0) {
+    auto kern = large_tables(c.E, c.P, c.R, kMapThreads) ? small_for<true>(c.k, T * c.k) : small_for<false>(c.k, T * c.k);
+    hipLaunchKernelGGL(kern, dim3(small), dim3(kMapThreads), small_lds_bytes(c.E, c.P, c.R, T, c.k),
+                       st, c.topk_idx, c.l2p_off, c.l2p_list, c.active, c.mem_version,
+                       (uint32_t)T | (uint32_t)c.k << 16 | (solo ? kSoloBit : 0u), c.E,
+                       c.P, c.R, inv_S, c.tbl_version, c.policy, g.tokens_per_rank, c.S,
+                       c.slot_of, c.row_of, c.src_of, c.count, c.offset, c.rank_count,
+                       c.rank_offset, c.cnt_src, c.status, c.step_epoch);
     return hipGetLastError();
   }
   {
