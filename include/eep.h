@@ -433,7 +433,7 @@ int eep_host_uncovered_experts(int32_t P, int32_t E, int32_t S, const int32_t* p
  * (Batches of up to 16384 pairs are mostly laid out in one launch without
  * these tiles; the results are the same.) */
 int eep_host_tiling(int32_t T, int32_t R, int32_t out[4]);
-/* Workgroups of that one launch for small batches, which take a fixed number: for at
+/* Workgroups that one launch divides small batches between at most: for at
  * most 512 tokens and 4096 pairs 8 where the instance has one context,
  * 1 where it has several (`several_contexts` != 0: the mask may change while the
  * layout runs) and in eep_dispatch_layout_noalloc, then for at most 384 tokens and

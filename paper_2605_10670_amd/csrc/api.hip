@@ -133,7 +133,8 @@ int create_impl(const eep_config* cfg, eep_ctx* parent, void* workspace, int64_t
   int64_t total = 0;
   for (int i = 0; i < EEP_V_NUM_FIELDS; ++i) total += round_up(n[i] > 0 ? n[i] : 1);
   const int64_t n_tile = (int64_t)c->max_tiles * c->P;
-  total += 2 * round_up(n_tile) + 2 * round_up(c->max_tiles) + 5 * round_up(1) +
+  const int64_t n_epoch = kAgreeMask + 2 * mask_words(c->R);  // the step counter and what stands behind it
+  total += 2 * round_up(n_tile) + 2 * round_up(c->max_tiles) + 4 * round_up(1) + round_up(n_epoch) +
            3 * round_up(c->R) + 4 * round_up(c->P);
   const int64_t n_dd_tile = (int64_t)c->max_tiles * c->R;
   total += 3 * round_up(pairs > 0 ? pairs : 1) + round_up(c->R) + round_up(c->R + 1) +
@@ -179,7 +180,7 @@ int create_impl(const eep_config* cfg, eep_ctx* parent, void* workspace, int64_t
   c->blk_msk = cur;   cur += round_up(c->max_tiles);
   c->tbl_version = cur; cur += round_up(1);
   c->mem_version_word = cur; cur += round_up(1);
-  c->step_epoch = cur;  cur += round_up(1);
+  c->step_epoch = cur;  cur += round_up(n_epoch);
   c->round_ok = cur;    cur += round_up(1);
   c->check_bad = cur;   cur += round_up(1);
   c->signal = cur;      cur += round_up(c->R);

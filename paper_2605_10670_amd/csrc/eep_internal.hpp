@@ -21,6 +21,10 @@ constexpr int kDedupMaxRanks = 1024;  // the de-duplicated layout keeps per-rank
 constexpr int kPatchInts = 960;
 constexpr int kPatchSmallInts = 96;
 constexpr int kPatchParts = 3;  // arrays one update may patch together
+// Behind a context's step counter, for the workgroups of a layout launch that agree on a mask (k_layout_once):
+// how many of them have it, and the mask, 32 entries and a 1 to every 8 bytes.  All zero between launches.
+constexpr int kAgreeCount = 1, kAgreeMask = 2;
+__host__ __device__ inline int mask_words(int R) { return (R + 31) / 32; }
 constexpr size_t kLayoutLdsLimit = 60 * 1024;  // the layout kernels keep their tables in LDS
 
 struct Tiling {

@@ -78,7 +78,6 @@ struct RouteTables {
 // Bits are written 64 at a time; a pair whose expert's list starts at o <= P reads the words
 // o / 32 and o / 32 + 1, so two more words follow.
 __host__ __device__ inline int alive_words(int P) { return (P + 63) / 64 * 2 + 2; }
-__host__ __device__ inline int mask_words(int R) { return (R + 31) / 32; }
 __host__ __device__ inline size_t route_table_ints(int E, int P, int R) {
   return (size_t)(E + 1) + P + alive_words(P) + mask_words(R);
 }
@@ -94,6 +93,12 @@ __device__ __forceinline__ int rank_of_slot(int p, float inv_S) {
 // two steps: `fetch` at the very start of a kernel, so that its loads are out before anything is
 // waited for, and `fill`; the caller's next barrier makes the tables readable.  LARGE: more than 64 ranks
 // (the mask goes through LDS, which takes one barrier here) or tables of more than nt words.
+// `agree` may replace the mask: it is called with the 64-bit mask, or (LARGE) with its words in LDS, and the
+// whole workgroup.
+struct OwnMask {
+  __device__ __forceinline__ uint64_t operator()(uint64_t mask) const { return mask; }
+  __device__ __forceinline__ void operator()(uint32_t*) const {}
+};
 inline bool large_tables(int E, int P, int R, int threads) { return R > 64 || P > threads || E >= threads; }
 template <bool LARGE>
 struct RouteTableLoad {
@@ -105,7 +110,8 @@ struct RouteTableLoad {
     p = l2p_list[tid < P ? tid : P - 1];
     o = l2p_off[tid < E ? tid : E];
   }
-  __device__ __forceinline__ RouteTables fill(int32_t* lds, float inv_S) const {
+  template <class Agree = OwnMask>
+  __device__ __forceinline__ RouteTables fill(int32_t* lds, float inv_S, Agree agree = Agree()) const {
     RouteTables rt;
     rt.off = lds;
     rt.list = rt.off + (E + 1);
@@ -113,7 +119,7 @@ struct RouteTableLoad {
     const int tid = threadIdx.x, lane = tid & 63;
     if constexpr (!LARGE) {
       if (tid <= E) rt.off[tid] = o;
-      const uint64_t mask = __ballot(lane < R && a != 0);
+      const uint64_t mask = agree(__ballot(lane < R && a != 0));
       const bool slot = tid < P && p >= 0;
       if (tid < P) rt.list[tid] = p;
       const uint64_t bits = __ballot(slot && ((mask >> (rank_of_slot(p, inv_S) & 63)) & 1));
@@ -134,6 +140,7 @@ struct RouteTableLoad {
 #pragma nounroll
       for (int i = tid; i <= E; i += nt) rt.off[i] = i == tid ? o : l2p_off[i];
       __syncthreads();
+      agree(mask);
 #pragma nounroll
       for (int q = tid; q - lane < P; q += nt) {  // whole wavefronts, for the ballot
         const int v = q == tid ? p : q < P ? l2p_list[q] : -1;
@@ -556,12 +563,12 @@ __global__ __launch_bounds__(kFusedThreads) void k_scan_position(
 // workgroup waits for another; one alone spent 1.4 to 2.8 us on storing, mostly the [R][P] matrix of pairs per
 // (source rank, slot).
 //
-// Where k_layout_once below could do it too, this takes at most a pair to a thread (kFewPairsOfK), and
-// half of that without a compile-time k (kFewPairs).  Measured (a layout in a graph of 40; 32 ranks x 9 slots, in
-// brackets that one): top-8, T = 32 / 64 / 96 / 128 3.7 / 3.7 / 3.7 / 3.8 us (4.0 / 4.1 / 4.4 / 4.4), T = 192 / 256 /
-// 384 / 512 4.4 / 4.6 / 5.3 / 5.8 (4.4 / 4.4 / 4.6 / 4.7); top-4, T = 128 / 384 / 512 3.6 / 4.3 / 4.4 (3.9 / 4.1 / 4.2);
-// top-5, T = 32 / 96 / 192 3.9 / 3.95 / 4.2 (4.1 / 4.0 / 4.1); top-3, T = 160 / 256 4.0 / 4.1 (4.0 / 4.0); 64 ranks,
-// top-8, T = 128 / 256 4.5 / 5.4 (5.2 / 5.2).  Beyond these it takes more than top-10, and tables that do not
+// Where k_layout_once below could do it too, this takes batches of up to 128 tokens (kFewTokens), two
+// wavefronts in that form, with a compile-time k.  Measured (a layout in a graph of 40; 32 ranks x 9 slots, in
+// brackets that one): top-8, T = 32 / 64 / 96 / 128 3.6 / 3.7 / 3.7 / 3.8 us (3.9 each), T = 192 / 256 / 512
+// 4.4 / 4.6 / 5.8 (4.1 / 4.2 / 4.4); top-4, T = 64 / 128 / 256 3.6 / 3.7 / 3.8 (3.8 each); top-2, T = 64 / 128 / 512
+// 3.6 / 3.6 / 3.9 (3.6 / 3.6 / 3.65); without a compile-time k, top-6, T = 32 / 64 4.1 / 4.15 (3.8 each); 64 ranks,
+// top-8, T = 64 / 128 4.4 / 4.5 (4.6 each).  Beyond these it takes more than top-10, and tables that do not
 // fit there (8 ranks x 265 slots, T = 32: 8.5 us, in tiles 12.6).
 //
 // The eight results fit together only if all eight workgroups saw one mask.  An
@@ -581,7 +588,7 @@ constexpr int kSmallPairsPerThread = 4;
 constexpr int kSmallPairs = kMapThreads * kSmallPairsPerThread;
 constexpr int kSoloTokens = 384;  // the limits for one workgroup
 constexpr int kSoloPairs = kMapThreads * 3;
-constexpr int kFewPairs = 512, kFewPairsOfK = 1024;  // up to these not for k_layout_once
+constexpr int kFewTokens = 128;  // up to here not for k_layout_once
 constexpr uint32_t kSoloBit = 1u << 31;
 
 __device__ __forceinline__ int vector_load(const int32_t* p) {
@@ -726,7 +733,7 @@ __global__ __launch_bounds__(kMapThreads) void k_layout_small(
 // of a branch, and what does not wait for the scan stands between its barriers.
 //
 // Measured (a layout in a graph of 40; 32 ranks x 9 slots, top-8), in brackets k_layout_small, and beyond 512
-// tokens tiles: T = 256 / 512 4.4 / 4.7 us (4.6 / 5.8), 768 / 1024 / 1536 / 2048 5.1 / 5.3 / 5.7 / 6.1 (7.6 / 7.7 / 7.8 / 7.9),
+// tokens tiles: T = 256 / 512 4.2 / 4.4 us (4.6 / 5.8), 768 / 1024 / 1536 / 2048 4.7 / 4.9 / 5.4 / 5.8 (7.6 / 7.7 / 7.8 / 7.9),
 // 3072 / 4096 7.3 / 8.6 (8.1 / 8.4); with a Zipf router, whose hot slots' counts are one LDS word
 // for many lanes, 2048 7.2 (7.8), 4096 10.7 (8.1).  T = 1024 of 64 ranks x 9 slots 5.8 (12.0), top-2 of
 // 32 ranks 4.1 (7.4), top-6 of 24 ranks 4.2 (7.8).  So up to 16384 pairs.  Shares of about 64 tokens, whole
@@ -739,10 +746,12 @@ __global__ __launch_bounds__(kMapThreads) void k_layout_small(
 //
 // Up to 512 tokens and 4096 pairs there are 8 workgroups, however many ranks.
 //
-// Only for an instance of one context, see k_layout_small.  A launch captured while there was one is overruled by
-// the word behind the membership version, which says that there are more:
-// its first workgroup then does it all, as many shares at once as fit in LDS: T = 256 / 512 / 1024 /
-// 2048 8.6 / 11.1 / 19.3 / 29.9 us (16.9 / 18.4 / 32.6 / 61 with one share after the other).
+// The workgroups' results fit together only if all of them saw one mask, see k_layout_small.  Launches are made for
+// an instance of one context, which keeps its mask still.  One captured then and replayed when there are more
+// learns it from the word behind the membership version; its workgroups use the mask that the first one read
+// (agree_on), for a barrier and a round trip or two through memory more: T = 256 / 512 / 1024 / 2048
+// 5.1 / 5.5 / 6.2 / 7.1 us.  (All of it done by the first workgroup took 8.6 / 11.1 / 19.3 / 29.9, and 65 for 2048 tokens of
+// 8 ranks, and the loop over shares that it needed cost every launch 0.1 to 0.3 us.)
 // ---------------------------------------------------------------------------
 constexpr int kOnceThreads = 1024;
 constexpr int kOnceMaxK = 10;  // compile-time top-k, a token to a lane, up to here
@@ -863,15 +872,10 @@ __host__ __device__ inline uint32_t share_tokens(uint32_t tokens_per_rank, uint3
 __host__ __device__ inline uint32_t once_zeros(uint32_t P, uint32_t stride, bool parts) {
   return ((P + kSinks) * (regions(parts) + stride) + 3) / 4 * 4;
 }
-// Where the last of it ends: what starts at zero, tables, entries, offsets, a share's slots.
-__host__ __device__ inline uint32_t once_end(uint32_t zeros, uint32_t tables, uint32_t E, uint32_t P, uint32_t pairs) {
-  return (zeros + tables + (E + 1) + (P + 1) + pairs + 3) / 4 * 4;
-}
-// `alone`: the tokens that a workgroup alone takes at once, whose counts and bitmaps are behind the rest; or 0.
-inline size_t once_lds_bytes(int E, int P, int R, int tokens, int alone, int k) {
-  return sizeof(int32_t) * ((size_t)once_end(once_zeros(P, token_stride(tokens), true), route_table_ints(E, P, R),
-                                             E, P, (alone > 0 ? alone : tokens) * k) +
-                            (alone > 0 ? once_zeros(P, token_stride(alone), true) : 0));
+// What starts at zero, tables, entries, offsets, a share's slots.
+inline size_t once_lds_bytes(int E, int P, int R, int tokens, int k, bool parts) {
+  return sizeof(int32_t) * ((size_t)once_zeros(P, token_stride(tokens), parts) + route_table_ints(E, P, R) +
+                            (E + 1) + (P + 1) + (size_t)tokens * k);
 }
 
 // Exclusive scan of the slots' totals into s_offset[0..P]: the wavefronts, the last one first, take
@@ -893,224 +897,208 @@ __device__ __forceinline__ void scan_totals(Total total, int32_t* s_offset, int 
   }
 }
 
-// A value that the compiler knows nothing about: what follows from it is computed where it is used.
-__device__ __forceinline__ int opaque(int x) {
-  asm volatile("" : "+s"(x));
-  return x;
+// One word of the mask that all workgroups of a launch use where it may change meanwhile: the one that the first
+// workgroup read, which it passes on in *word together with a 1.  It waits for nobody, so every other workgroup's
+// wait ends; the bound (some seconds) is for a device that stops in between.
+constexpr int kAgreePolls = 1 << 22;
+__device__ __forceinline__ uint32_t agree_on(uint64_t* word, uint32_t mine) {
+  uint64_t v = (uint64_t)1 << 32 | mine;
+  if (blockIdx.x == 0) {
+    __hip_atomic_store(word, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    __builtin_amdgcn_s_waitcnt(0x0f70);  // vmcnt(0): it is there before this workgroup counts itself
+    return mine;
+  }
+  for (int polls = 0; polls < kAgreePolls; ++polls) {
+    v = __hip_atomic_load(word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (v >> 32 != 0) return (uint32_t)v;
+    __builtin_amdgcn_s_sleep(1);
+  }
+  return mine;
 }
 
 // K: top-k.  PARTS: a share is a part of a source rank, one of `subs`, otherwise `ranks` whole ones.
-// Four words hold the shape (T and tokens per rank; E and P; R, the source ranks of a share << 12 and
-// how many shares at once a workgroup alone takes << 24; S, policy << 12, wavefronts << 13, shares in a rank << 18), so that it arrives in registers with the first pointers.
+// Four words hold the shape (T and tokens per rank; E and P; R and the source ranks of a share << 12;
+// S, policy << 12, wavefronts << 13, shares in a rank << 18), so that it arrives in registers with the first pointers.
 template <uint32_t K, bool LARGE, bool PARTS>
 __global__ __launch_bounds__(kOnceThreads) void k_layout_once(
     const int32_t* __restrict__ topk_idx, const int32_t* __restrict__ l2p_off,
     const int32_t* __restrict__ l2p_list, const int32_t* __restrict__ active,
-    const int32_t* __restrict__ mem_version, uint32_t T_rank, uint32_t E_P, uint32_t R_share,
+    const int32_t* __restrict__ mem_version, uint32_t T_rank, uint32_t E_P, uint32_t R_ranks,
     uint32_t S_policy_waves_subs, const int32_t* __restrict__ tbl_version, int32_t* __restrict__ slot_of,
     int32_t* __restrict__ row_of, int32_t* __restrict__ src_of, int32_t* __restrict__ cnt_src,
     int32_t* __restrict__ count, int32_t* __restrict__ offset, int32_t* __restrict__ rank_count,
     int32_t* __restrict__ rank_offset, int32_t* __restrict__ status,
     int32_t* __restrict__ step_epoch) {
   const uint32_t T = T_rank & 0xffff, tokens_per_rank = T_rank >> 16;
-  const uint32_t E = E_P & 0xffff, R = R_share & 0xfff;
-  uint32_t width = R_share >> 12 & 0xfff;  // source ranks of a share
+  const uint32_t E = E_P & 0xffff, P = E_P >> 16, P2 = P + kSinks;
+  const uint32_t R = R_ranks & 0xfff, ranks = PARTS ? 1 : R_ranks >> 12;
   const uint32_t S = S_policy_waves_subs & 0xfff, policy = S_policy_waves_subs >> 12 & 1;
   const uint32_t waves = S_policy_waves_subs >> 13 & 31, nt = waves * 64;
   const uint32_t subs = PARTS ? S_policy_waves_subs >> 18 : 1;
   const uint32_t tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const auto load = [&](uint32_t t, int (&e)[K]) { __builtin_memcpy(e, &at(topk_idx, t * K), sizeof(e)); };
-  // The first round's tokens from the last thread down: the first threads have the tables to do.
+  // The first tokens from the last thread down: the first threads have the tables to do.
   uint32_t t = nt - 1 - tid;
   int e[K];
   load(t < T ? t : T - 1, e);
-  RouteTableLoad<LARGE> tables = {l2p_off, l2p_list, active, (int)E, (int)R, (int)(E_P >> 16), (int)nt};
+  RouteTableLoad<LARGE> tables = {l2p_off, l2p_list, active, (int)E, (int)R, (int)P, (int)nt};
   tables.fetch();
-  // several contexts in the instance: the first workgroup does it all.  (A vector load: a scalar one
-  // would be waited for together with every kernel argument.)
+  // several contexts in the instance.  (A vector load: a scalar one would be waited for together with
+  // every kernel argument.)
   const int several_v = vector_load(&mem_version[1]);
 
   extern __shared__ __align__(16) int32_t smem[];
-  const uint32_t part = share_tokens(tokens_per_rank, width, subs);
-  const uint32_t zeros = once_zeros(E_P >> 16, token_stride(part), PARTS);
-  int32_t* s_tab = smem + zeros;
+  const uint32_t tokens = share_tokens(tokens_per_rank, ranks, subs), stride = token_stride(tokens);
+  const uint32_t zeros = once_zeros(P, stride, PARTS);
+  int32_t* const s_cnt = smem;                                      // [regions][P2] pairs per slot
+  uint32_t* const s_bm = (uint32_t*)(s_cnt + regions(PARTS) * P2);  // [P2][stride] bitmap of the share's tokens per slot
+  int32_t* const s_tab = smem + zeros;
+  uint32_t* const s_entry = (uint32_t*)(s_tab + route_table_ints(E, P, R));  // [E+1]
+  int32_t* const s_offset = (int32_t*)s_entry + E + 1;              // [P+1] exclusive scan of the totals
+  int32_t* const s_slot = s_offset + P + 1;                         // [tokens*K] slots of the share's pairs
+  __shared__ uint32_t s_agreed[2];
 #pragma nounroll
   for (uint32_t i = tid * 4; i < zeros; i += nt * 4) *(int4*)(smem + i) = make_int4(0, 0, 0, 0);
-  const RouteTables rt = tables.fill(s_tab, __builtin_amdgcn_rcpf((float)S));
-  uint32_t* s_entry = (uint32_t*)(s_tab + route_table_ints(E, E_P >> 16, R));  // [E+1]
-  const bool alone = (PARTS || width < R) && __builtin_amdgcn_readfirstlane(several_v) != 0;
-  uint32_t share = blockIdx.x;
+  struct {
+    uint64_t* words;
+    bool several;
+    uint32_t R;
+    uint32_t* s_agreed;
+    __device__ __forceinline__ uint64_t operator()(uint64_t mask) const {
+      if (!several) return mask;
+      const uint32_t tid = threadIdx.x;
+      if (tid < (uint32_t)mask_words(R)) s_agreed[tid] = agree_on(words + tid, (uint32_t)(mask >> (tid * 32)));
+      __syncthreads();
+      return (uint64_t)(R > 32 ? s_agreed[1] : 0) << 32 | s_agreed[0];
+    }
+    __device__ __forceinline__ void operator()(uint32_t* mask) const {
+      if (!several) return;
+      const uint32_t tid = threadIdx.x;
+      if (tid < (uint32_t)mask_words(R)) mask[tid] = agree_on(words + tid, mask[tid]);
+      __syncthreads();
+    }
+  } agree = {(uint64_t*)(step_epoch + kAgreeMask), __builtin_amdgcn_readfirstlane(several_v) != 0, R, s_agreed};
+  const RouteTables rt = tables.fill(s_tab, __builtin_amdgcn_rcpf((float)S), agree);
+  int before = 0;  // workgroups that had the mask before this one
+  if (agree.several && tid == 0)
+    before = __hip_atomic_fetch_add(step_epoch + kAgreeCount, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  const uint32_t share = blockIdx.x;
   // PARTS: the share's rank (share / subs, by way of float), and which of the rank's shares it is
-  const auto rank_of_part = [&]() {
-    return (uint32_t)__builtin_amdgcn_readfirstlane(
-        (uint32_t)(((float)share + 0.5f) * __builtin_amdgcn_rcpf((float)subs)));
-  };
-  uint32_t rank0 = PARTS ? rank_of_part() : 0, sub = share - rank0 * subs;
-  if (share > 0 && (alone || (PARTS ? rank0 : share * width) >= R)) return;
-  uint32_t base = 0;  // where the counts and bitmaps are
-  if (!PARTS && alone && (R_share >> 24) > 1) {  // as many shares at once as there is LDS for, behind the rest
-    width *= R_share >> 24;
-    const uint32_t P = E_P >> 16, many = width * tokens_per_rank;
-    base = once_end(zeros, route_table_ints(E, P, R), E, P, many * K);
-    const uint32_t end = base + once_zeros(P, token_stride(many), false);
-#pragma nounroll
-    for (uint32_t i = base + tid * 4; i < end; i += nt * 4) *(int4*)(smem + i) = make_int4(0, 0, 0, 0);
-  }
-  const bool rounds = alone && (PARTS || width < R);
+  const uint32_t rank0 = !PARTS ? share * ranks : __builtin_amdgcn_readfirstlane(
+      (uint32_t)(((float)share + 0.5f) * __builtin_amdgcn_rcpf((float)subs)));
+  const uint32_t sub = PARTS ? share - rank0 * subs : 0, rank_end = (rank0 + 1) * tokens_per_rank;
+  const uint32_t lo = PARTS ? min(rank0 * tokens_per_rank + sub * tokens, rank_end) : rank0 * tokens_per_rank;
+  const uint32_t hi = min(lo + tokens, PARTS ? rank_end : T);
   __syncthreads();
-  build_entries<LARGE>(rt, s_entry, E, E_P >> 16, policy, nt);
+  build_entries<LARGE>(rt, s_entry, E, P, policy, nt);
   bool repeats = any_repeats(e);
   __syncthreads();
-
-  // One round, over the whole batch; alone with several shares, a second one for each, over its tokens.
-  uint32_t lo = T;
-  const auto first_token = [&]() {
-    return !PARTS ? share * width * tokens_per_rank
-                  : min(rank0 * tokens_per_rank + sub * part, (rank0 + 1) * tokens_per_rank);
-  };
-  const auto last_token = [&]() {
-    return PARTS ? min(lo + part, (rank0 + 1) * tokens_per_rank) : min(lo + width * tokens_per_rank, T);
-  };
-  uint32_t end = T;
-  if (!rounds) lo = first_token();
-  int rows = 0;
-  for (uint32_t round = 0;; ++round) {
-    // (Opaque, or whatever follows from it would be computed ahead of the loop by every wavefront.)
-    const uint32_t P = opaque(E_P >> 16), P2 = P + kSinks;
-    const uint32_t ranks = PARTS ? 1 : opaque(width), tokens = PARTS ? part : ranks * tokens_per_rank;
-    const uint32_t stride = token_stride(tokens);
-    int32_t* const s_cnt = smem + base;                   // [regions][P2] pairs per slot
-    uint32_t* const s_bm = (uint32_t*)(s_cnt + regions(PARTS) * P2);  // [P2][stride] bitmap of the share's tokens per slot
-    int32_t* const s_offset = smem + opaque(zeros + route_table_ints(E, P, R) + E + 1);  // [P+1] exclusive scan of the totals
-    int32_t* const s_slot = s_offset + P + 1;             // [tokens*K] slots of the share's pairs
-    const uint32_t hi = !PARTS ? min(lo + tokens, T) : lo < T ? last_token() : T;
 #pragma nounroll
-    while (t < end) {
-      const uint32_t now = t;
-      t += nt;
-      int next[K];
-      if (t < end) load(t, next);
-      int p[K];
-      map_token<K>(rt, s_entry, E, P, e, repeats, now, p);
-      // counted in the token's region, and if the token is the share's own, kept
-      const bool own = now >= lo && now < hi;
-      int32_t* cnt = s_cnt + (own ? P2 : now < lo ? 0 : 2 * P2);
+  while (t < T) {
+    const uint32_t now = t;
+    t += nt;
+    int next[K];
+    if (t < T) load(t, next);
+    int p[K];
+    map_token<K>(rt, s_entry, E, P, e, repeats, now, p);
+    // counted in the token's region, and if the token is the share's own, kept
+    const bool own = now >= lo && now < hi;
+    int32_t* cnt = s_cnt + (own ? P2 : now < lo ? 0 : 2 * P2);
 #pragma unroll
-      for (uint32_t j = 0; j < K; ++j) atomicAdd(&cnt[p[j]], 1);
-      if (PARTS && sub == 0 && !alone && now >= hi && now < (rank0 + 1) * tokens_per_rank) {
+    for (uint32_t j = 0; j < K; ++j) atomicAdd(&cnt[p[j]], 1);
+    if (PARTS && sub == 0 && now >= hi && now < rank_end) {
 #pragma unroll
-        for (uint32_t j = 0; j < K; ++j) atomicAdd(&s_cnt[3 * P2 + p[j]], 1);
-      }
-      if (own) {
-        const uint32_t tl = now - lo;
-        uint32_t* bm = s_bm + (tl >> 5);
-        int32_t* to = s_slot + tl * K;
-        const uint32_t bit = 1u << (tl & 31);
+      for (uint32_t j = 0; j < K; ++j) atomicAdd(&s_cnt[3 * P2 + p[j]], 1);
+    }
+    if (own) {
+      const uint32_t tl = now - lo;
+      uint32_t* bm = s_bm + (tl >> 5);
+      int32_t* to = s_slot + tl * K;
+      const uint32_t bit = 1u << (tl & 31);
 #pragma unroll
-        for (uint32_t j = 0; j < K; ++j) to[j] = p[j];
+      for (uint32_t j = 0; j < K; ++j) to[j] = p[j];
 #pragma unroll
-        for (uint32_t j = 0; j < K; ++j) {
-          atomicOr(&bm[__umul24(p[j], stride)], bit);
-        }
+      for (uint32_t j = 0; j < K; ++j) {
+        atomicOr(&bm[__umul24(p[j], stride)], bit);
       }
-      if (t < end) {
+    }
+    if (t < T) {
 #pragma unroll
-        for (uint32_t j = 0; j < K; ++j) e[j] = next[j];
-        repeats = any_repeats(e);
-      }
-    }
-    __syncthreads();
-    // Between two barriers: the scan, and what does not need it.
-    const uint32_t n = lo < T ? (hi - lo) * K : 0, g0 = lo * K;
-    const auto total = [=](uint32_t p) { return s_cnt[p] + s_cnt[P2 + p] + s_cnt[2 * P2 + p]; };
-    int dead = 0, masked = 0, version = 0;
-    if (round == 0) {
-      scan_totals(total, s_offset, P, wave, waves);
-      if (share == 0) {
-        dead = total(P);
-        masked = total(P + 1);
-        version = vector_load(tbl_version) + vector_load(mem_version);
-      }
-    }
-    // pairs per (source rank, slot): the tokens of a source rank are a bit range
-    if (n > 0) {
-      const uint32_t rank = PARTS ? rank0 : share * ranks, mine = min(R - rank, ranks);
-#pragma nounroll
-      for (uint32_t p = tid; p < P; p += nt) {
-        const uint32_t* bm = &s_bm[__umul24(p, stride)];
-        uint32_t to = rank * P + p;
-        if constexpr (PARTS) {
-          if (alone)
-            at(cnt_src, to) = s_cnt[P2 + p] + (sub == 0 ? 0 : at(cnt_src, to));
-          else if (sub == 0)
-            at(cnt_src, to) = s_cnt[P2 + p] + s_cnt[3 * P2 + p];
-        } else if (tokens <= 64) {
-          uint64_t bits = bm[0];
-          if (stride > 1) bits |= (uint64_t)bm[1] << 32;
-          const uint64_t mask = ~0ull >> (64 - tokens_per_rank);
-#pragma nounroll
-          for (uint32_t b = 0; b < mine; ++b, to += P) {
-            at(cnt_src, to) = __popcll(bits & mask);
-            bits >>= tokens_per_rank;
-          }
-        } else {
-#pragma nounroll
-          for (uint32_t b = 0; b < mine; ++b, to += P)
-            at(cnt_src, to) = bits_between(bm, b * tokens_per_rank, (b + 1) * tokens_per_rank);
-        }
-      }
-    }
-    uint32_t p = P;
-    int row = -1;
-    const auto place = [&](uint32_t i) {  // slot of the share's pair i, its row less the slot's offset
-      p = s_slot[i];
-      row = s_cnt[p] + rank_in_slot(&s_bm[p * stride], i / K);
-    };
-    if (tid < n) place(tid);
-    __syncthreads();
-    if (round == 0) rows = s_offset[P];
-#pragma nounroll
-    for (uint32_t i = tid; i < n;) {
-      const uint32_t g = g0 + i;
-      int slot = -1;
-      if (p < P) {
-        slot = p;
-        row += s_offset[p];
-        at(src_of, row) = g;
-      } else {
-        row = -1;
-      }
-      at(slot_of, g) = slot;
-      at(row_of, g) = row;
-      if ((int)g >= rows) at(src_of, g) = -1;  // rows past the last routed pair
-      i += nt;
-      if (i < n) place(i);
-    }
-    if (share == 0 && round == 0)
-      write_step_tables(nt, s_offset, dead, masked, version, count, offset, rank_count,
-                                      rank_offset, status, step_epoch, R, S, P);
-    share = round;
-    if constexpr (PARTS) {
-      rank0 = rank_of_part();
-      sub = share - rank0 * subs;
-    }
-    if (!rounds || (PARTS ? rank0 : share * ranks) >= R) break;
-    lo = first_token();
-    __syncthreads();
-#pragma nounroll
-    for (uint32_t q = tid; q < P2; q += nt) {
-      s_cnt[q] = round == 0 ? 0 : s_cnt[q] + s_cnt[P2 + q];  // now the pairs of the shares so far
-      s_cnt[P2 + q] = 0;
-    }
-#pragma nounroll
-    for (uint32_t q = tid; q < P2 * stride; q += nt) s_bm[q] = 0;
-    t = lo + tid;
-    end = last_token();
-    if (t < end) {
-      load(t, e);
+      for (uint32_t j = 0; j < K; ++j) e[j] = next[j];
       repeats = any_repeats(e);
     }
-    __syncthreads();
+  }
+  __syncthreads();
+  // Between two barriers: the scan, and what does not need it.
+  const uint32_t n = (hi - lo) * K, g0 = lo * K;
+  const auto total = [=](uint32_t p) { return s_cnt[p] + s_cnt[P2 + p] + s_cnt[2 * P2 + p]; };
+  scan_totals(total, s_offset, P, wave, waves);
+  int dead = 0, masked = 0, version = 0;
+  if (share == 0) {
+    dead = total(P);
+    masked = total(P + 1);
+    version = vector_load(tbl_version) + vector_load(mem_version);
+  }
+  // pairs per (source rank, slot): the tokens of a source rank are a bit range
+  if (sub == 0) {
+    const uint32_t mine = min(R - rank0, ranks);
+#pragma nounroll
+    for (uint32_t p = tid; p < P; p += nt) {
+      const uint32_t* bm = &s_bm[__umul24(p, stride)];
+      uint32_t to = rank0 * P + p;
+      if constexpr (PARTS) {
+        at(cnt_src, to) = s_cnt[P2 + p] + s_cnt[3 * P2 + p];
+      } else if (tokens <= 64) {
+        uint64_t bits = bm[0];
+        if (stride > 1) bits |= (uint64_t)bm[1] << 32;
+        const uint64_t mask = ~0ull >> (64 - tokens_per_rank);
+#pragma nounroll
+        for (uint32_t b = 0; b < mine; ++b, to += P) {
+          at(cnt_src, to) = __popcll(bits & mask);
+          bits >>= tokens_per_rank;
+        }
+      } else {
+#pragma nounroll
+        for (uint32_t b = 0; b < mine; ++b, to += P)
+          at(cnt_src, to) = bits_between(bm, b * tokens_per_rank, (b + 1) * tokens_per_rank);
+      }
+    }
+  }
+  uint32_t p = P;
+  int row = -1;
+  const auto place = [&](uint32_t i) {  // slot of the share's pair i, its row less the slot's offset
+    p = s_slot[i];
+    row = s_cnt[p] + rank_in_slot(&s_bm[p * stride], i / K);
+  };
+  if (tid < n) place(tid);
+  __syncthreads();
+  const int rows = s_offset[P];
+#pragma nounroll
+  for (uint32_t i = tid; i < n;) {
+    const uint32_t g = g0 + i;
+    int slot = -1;
+    if (p < P) {
+      slot = p;
+      row += s_offset[p];
+      at(src_of, row) = g;
+    } else {
+      row = -1;
+    }
+    at(slot_of, g) = slot;
+    at(row_of, g) = row;
+    if ((int)g >= rows) at(src_of, g) = -1;  // rows past the last routed pair
+    i += nt;
+    if (i < n) place(i);
+  }
+  if (share == 0)
+    write_step_tables(nt, s_offset, dead, masked, version, count, offset, rank_count, rank_offset, status,
+                      step_epoch, R, S, P);
+  if (agree.several && wave == 0 && __builtin_amdgcn_readfirstlane(before) == (int)gridDim.x - 1) {
+    // every workgroup has the mask: zeros again for the next launch
+#pragma nounroll
+    for (uint32_t i = tid; i < (uint32_t)mask_words(R); i += 64)
+      __hip_atomic_store(agree.words + i, (uint64_t)0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (tid == 0) __hip_atomic_store(step_epoch + kAgreeCount, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   }
 }
 
@@ -1621,24 +1609,19 @@ hipError_t launch_layout(const LayoutIO& c, int T, hipStream_t st) {
   const ShareSize share = share_size(c.E, c.P, c.R, g.tokens_per_rank, c.k, small);
   const int tokens = share.tokens(g.tokens_per_rank);
   const bool has_k = c.k == 1 || c.k == 2 || c.k == 4 || c.k == 8;  // an instance of k_layout_small
-  const bool few = small > 0 && T * c.k <= (has_k ? kFewPairsOfK : kFewPairs);
+  const bool few = small > 0 && has_k && T <= kFewTokens;
   if (!solo && !few && c.k <= kOnceMaxK && (int64_t)T * c.k <= kOncePairs && c.P + kSinks <= kEntrySlots &&
-      share.subs < 256 && once_lds_bytes(c.E, c.P, c.R, tokens, 0, c.k) <= kLayoutLdsLimit) {
+      once_lds_bytes(c.E, c.P, c.R, tokens, c.k, share.subs > 1) <= kLayoutLdsLimit) {
     int nt = c.P > c.E ? c.P : c.E + 1;  // threads: for the tables, and for the tokens
     const int most = T > kOnceThreads ? kOnceThreads : kOnceThreads / 2;
     nt = nt < most ? most : nt < kOnceThreads ? (nt + 63) / 64 * 64 : kOnceThreads;
-    // shares at once for a workgroup alone: all of them, or what fits beside the rest
-    int at_once = share.subs > 1 ? 0 : std::min((c.R + share.ranks - 1) / share.ranks, 255);
-    size_t lds;
-    while ((lds = once_lds_bytes(c.E, c.P, c.R, tokens, at_once > 1 ? tokens * at_once : 0, c.k)) > kLayoutLdsLimit &&
-           at_once > 1)
-      at_once /= 2;
     auto kern = large_tables(c.E, c.P, c.R, nt) ? once_for<true, false>(c.k)
                 : share.subs > 1 ? once_for<false, true>(c.k) : once_for<false, false>(c.k);
-    hipLaunchKernelGGL(kern, dim3(small > 0 ? small : share.count(c.R)), dim3(nt), lds, st, c.topk_idx,
+    hipLaunchKernelGGL(kern, dim3(share.count(c.R)), dim3(nt),
+                       once_lds_bytes(c.E, c.P, c.R, tokens, c.k, share.subs > 1), st, c.topk_idx,
                        c.l2p_off, c.l2p_list, c.active, c.mem_version,
                        (uint32_t)T | (uint32_t)g.tokens_per_rank << 16, (uint32_t)c.E | (uint32_t)c.P << 16,
-                       (uint32_t)c.R | (uint32_t)share.ranks << 12 | (uint32_t)at_once << 24,
+                       (uint32_t)c.R | (uint32_t)share.ranks << 12,
                        (uint32_t)c.S | (uint32_t)c.policy << 12 | (uint32_t)(nt / 64) << 13 |
                            (uint32_t)share.subs << 18,
                        c.tbl_version, c.slot_of, c.row_of,
