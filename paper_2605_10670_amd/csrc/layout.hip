@@ -733,16 +733,19 @@ __global__ __launch_bounds__(kMapThreads) void k_layout_small(
 // of a branch, and what does not wait for the scan stands between its barriers.
 //
 // Measured (a layout in a graph of 40; 32 ranks x 9 slots, top-8), in brackets k_layout_small, and beyond 512
-// tokens tiles: T = 256 / 512 4.2 / 4.4 us (4.6 / 5.8), 768 / 1024 / 1536 / 2048 4.7 / 4.9 / 5.4 / 5.8 (7.6 / 7.7 / 7.8 / 7.9),
-// 3072 / 4096 7.3 / 8.6 (8.1 / 8.4); with a Zipf router, whose hot slots' counts are one LDS word
-// for many lanes, 2048 7.2 (7.8), 4096 10.7 (8.1).  T = 1024 of 64 ranks x 9 slots 5.8 (12.0), top-2 of
-// 32 ranks 4.1 (7.4), top-6 of 24 ranks 4.2 (7.8).  So up to 16384 pairs.  Shares of about 64 tokens, whole
+// tokens tiles: T = 256 / 512 4.2 / 4.5 us (4.6 / 5.8), 1024 / 1536 / 2048 5.1 / 5.5 / 6.0 (7.6 / 7.8 / 7.9), 3072 / 4096
+// 7.3 / 8.3 (8.0 / 8.3); with a Zipf router, whose hot slots' counts are one LDS word for many lanes, 2048 / 3072 / 4096
+// 6.4 / 7.9 / 9.1 (7.8 / 7.9 / 8.1).  T = 1024 of 64 ranks x 9 slots 5.6 (12.0), top-2 of 32 ranks 3.95 (7.4), T = 768 of 24
+// ranks, top-6, 4.4 (7.8).  So up to 16384 pairs.  Shares of about 64 tokens, whole
 // source ranks or, where a rank has at least 768 pairs, a part of one, whose first then also counts the
-// rank's other tokens for the rank's totals: 8 ranks, T = 1024 / 2048 5.3 / 6.3 (whole ranks 5.5 / 7.3; two
-// launches 8.0 / 8.1), 2 ranks, T = 512 / 1024 / 2048 4.6 / 5.6 / 6.8 (5.4 / 7.1 / - ; 5.9 / 7.2 / 7.8), 4 ranks,
-// top-3, T = 1024 4.2 (4.6; 7.2); with fewer pairs it costs as much as it gives (32 ranks, top-2, T = 4096, 256
-// pairs to a rank: 5.5 in parts, 5.2).  512 threads, 1024 for more than 1024 tokens (T = 256 / 1024 / 2048: 0.3 /
-// -0.1 / -0.2 us with 1024 against 512).
+// rank's other tokens for the rank's totals: 8 ranks, T = 1024 / 2048 5.0 / 6.2 (whole ranks 5.5 / 7.2; tiles
+// 7.9 / 8.1), 2 ranks, T = 512 / 1024 / 2048 4.4 / 5.3 / 7.3 (5.5 / 8.7 / 14.7; 5.9 / 7.2 / 7.8), 4 ranks, top-3,
+// T = 1024 3.9 (4.5; 7.2); with fewer pairs it costs as much as it gives (32 ranks, top-2, T = 4096, 256
+// pairs to a rank: 5.0 in parts, 4.8).  512 threads, 1024 for more than 1024 tokens (T = 256 / 512 / 1024: 4.25 / 4.5 /
+// 5.1 with 512, 4.35 / 4.6 / 5.0 with 1024).
+//
+// What no ordinary router gives: 2048 tokens, 90 % of them without an expert (-1) 5.9 us (17.3 with one sink for all,
+// tiles 8.7), half of all pairs without one 6.2 (11.9; 8.8).
 //
 // Up to 512 tokens and 4096 pairs there are 8 workgroups, however many ranks.
 //
@@ -765,44 +768,52 @@ __device__ __forceinline__ T& at(T* p, uint32_t i) {
 }
 
 // What an expert's pairs need to know, one word per expert: the slot of its pairs from even tokens
-// and << 12 that of those from odd ones.  Pairs without a row go to two sinks behind the P slots, and
-// are counted there: P for experts without a live replica, P + 1 for what is no expert or a repeat.
+// and << 12 that of those from odd ones.  Pairs without a row go to sinks behind the P slots, and
+// are counted there: kDeadSinks for experts without a live replica, an expert to one of them, and kNoneSinks for what is
+// no expert or a repeat, because counts of many lanes in one word come one after the other.
 constexpr uint32_t kEntryMany = 1u << 24;  // more live ones to spread over: list start, count << 12
 constexpr int kEntrySlots = 1 << 12;       // slots, sinks and counts stay below this
-constexpr int kSinks = 2;
+constexpr int kDeadSinks = 16, kNoneLanes = 8, kNoneSinks = kNoneLanes - 1 + kOnceMaxK;
+constexpr int kSinks = kDeadSinks + kNoneSinks;
 
-// Writes the entries of all experts, and for those with more than two live replicas to choose from
+// Writes the entries of all experts and behind them those of no expert, and for those with more than two live replicas to choose from
 // the live ones to the front of the list.  The caller's next barrier makes both readable.
 template <bool LARGE>
 __device__ __forceinline__ void build_entries(const RouteTables& rt, uint32_t* entries, int E, int P,
                                               int policy, int nt) {
 #pragma nounroll
-  for (int e = threadIdx.x; e <= E; e += nt) {  // (one pass unless LARGE)
-    uint32_t even = P + 1, odd = P + 1, many = 0;  // (entry E: not an expert)
-    if (e < E) {
-      const int o = rt.off[e], m = rt.off[e + 1] - o;
-      const uint64_t two = (uint64_t)rt.alive[(o >> 5) + 1] << 32 | rt.alive[o >> 5];
-      const uint32_t bits = (uint32_t)(two >> (o & 31)) & (uint32_t)((1ull << (m & 63)) - 1);
-      const uint32_t rest = policy == EEP_FIRST_LIVE ? 0 : bits & (bits - 1);
-      even = odd = P;
-      if (__builtin_expect(m > 32 || (rest & (rest - 1)) != 0, 0)) {
-        int n = 0;
+  for (int e = threadIdx.x; e < E; e += nt) {  // (one pass unless LARGE)
+    uint32_t even = P + (e & (kDeadSinks - 1)), odd = even, many = 0;
+    const int o = rt.off[e], m = rt.off[e + 1] - o;
+    const uint64_t two = (uint64_t)rt.alive[(o >> 5) + 1] << 32 | rt.alive[o >> 5];
+    const uint32_t bits = (uint32_t)(two >> (o & 31)) & (uint32_t)((1ull << (m & 63)) - 1);
+    const uint32_t rest = policy == EEP_FIRST_LIVE ? 0 : bits & (bits - 1);
+    if (__builtin_expect(m > 32 || (rest & (rest - 1)) != 0, 0)) {
+      int n = 0;
 #pragma nounroll
-        for (int q = o; q < o + m; ++q)
-          if ((rt.alive[q >> 5] >> (q & 31)) & 1) rt.list[o + n++] = rt.list[q];
-        if (n > 0) {
-          many = kEntryMany;
-          even = o;
-          odd = policy == EEP_FIRST_LIVE ? 1 : n;
-        }
-      } else if (bits != 0) {
-        even = odd = rt.list[o + __ffs(bits) - 1];
-        if (rest != 0) odd = rt.list[o + __ffs(rest) - 1];
+      for (int q = o; q < o + m; ++q)
+        if ((rt.alive[q >> 5] >> (q & 31)) & 1) rt.list[o + n++] = rt.list[q];
+      if (n > 0) {
+        many = kEntryMany;
+        even = o;
+        odd = policy == EEP_FIRST_LIVE ? 1 : n;
       }
+    } else if (bits != 0) {
+      even = odd = rt.list[o + __ffs(bits) - 1];
+      if (rest != 0) odd = rt.list[o + __ffs(rest) - 1];
     }
     entries[e] = many | odd << 12 | even;
     if (!LARGE) break;
   }
+  if (threadIdx.x < kNoneSinks) entries[E + threadIdx.x] = (P + kDeadSinks + threadIdx.x) * (1 + (1 << 12));
+}
+
+// A token's experts to their entries.  What is no expert goes to one of the kNoneSinks behind them, another one for each
+// pair, so that it is no repeat either, and in kNoneLanes lanes; `none` is the lane's for the first pair.
+template <uint32_t N>
+__device__ __forceinline__ void entries_of(int (&e)[N], uint32_t none) {
+#pragma unroll
+  for (uint32_t j = 0; j < N; ++j) e[j] = min((uint32_t)e[j], none + j);
 }
 
 // Does a token name an expert twice?
@@ -817,13 +828,13 @@ __device__ __forceinline__ bool any_repeats(const int (&e)[N]) {
   return N > 1 && least == 0;
 }
 
-// The slots (or sinks) p[] of token t's pairs with the experts e[].
+// The slots (or sinks) p[] of token t's pairs with the experts whose entries are e[].
 template <uint32_t N>
-__device__ __forceinline__ void map_token(const RouteTables& rt, const uint32_t* entries, int E, int P,
-                                          int (&e)[N], bool repeats, int t, int (&p)[N]) {
+__device__ __forceinline__ void map_token(const RouteTables& rt, const uint32_t* entries, int P, int (&e)[N],
+                                          bool repeats, int t, int (&p)[N]) {
   uint32_t all = 0;
 #pragma unroll
-  for (uint32_t j = 0; j < N; ++j) p[j] = entries[(uint32_t)e[j] < (uint32_t)E ? e[j] : E];
+  for (uint32_t j = 0; j < N; ++j) p[j] = entries[e[j]];
 #pragma unroll
   for (uint32_t j = 0; j < N; ++j) all |= p[j];
   if (__builtin_expect(__any(all >= kEntryMany), 0)) {
@@ -847,7 +858,7 @@ __device__ __forceinline__ void map_token(const RouteTables& rt, const uint32_t*
     for (uint32_t j = 1; j < N; ++j) {
       asm volatile("" : "+v"(e[j]));  // (or the comparisons would be kept from above)
 #pragma unroll
-      for (uint32_t i = 0; i < j; ++i) p[j] = e[i] == e[j] ? P + 1 : p[j];
+      for (uint32_t i = 0; i < j; ++i) p[j] = e[i] == e[j] ? P + kDeadSinks : p[j];
     }
   }
 }
@@ -875,7 +886,7 @@ __host__ __device__ inline uint32_t once_zeros(uint32_t P, uint32_t stride, bool
 // What starts at zero, tables, entries, offsets, a share's slots.
 inline size_t once_lds_bytes(int E, int P, int R, int tokens, int k, bool parts) {
   return sizeof(int32_t) * ((size_t)once_zeros(P, token_stride(tokens), parts) + route_table_ints(E, P, R) +
-                            (E + 1) + (P + 1) + (size_t)tokens * k);
+                            (E + kNoneSinks) + (P + kSinks + 1) + (size_t)tokens * k);
 }
 
 // Exclusive scan of the slots' totals into s_offset[0..P]: the wavefronts, the last one first, take
@@ -937,10 +948,10 @@ __global__ __launch_bounds__(kOnceThreads) void k_layout_once(
   const uint32_t subs = PARTS ? S_policy_waves_subs >> 18 : 1;
   const uint32_t tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const auto load = [&](uint32_t t, int (&e)[K]) { __builtin_memcpy(e, &at(topk_idx, t * K), sizeof(e)); };
-  // The first tokens from the last thread down: the first threads have the tables to do.
-  uint32_t t = nt - 1 - tid;
+  // From the batch's last tokens, which the last threads take, to its first: the first threads have the tables to do.
+  int t = (int)(T + tid) - (int)nt;
   int e[K];
-  load(t < T ? t : T - 1, e);
+  load(max(t, 0), e);
   RouteTableLoad<LARGE> tables = {l2p_off, l2p_list, active, (int)E, (int)R, (int)P, (int)nt};
   tables.fetch();
   // several contexts in the instance.  (A vector load: a scalar one would be waited for together with
@@ -953,9 +964,9 @@ __global__ __launch_bounds__(kOnceThreads) void k_layout_once(
   int32_t* const s_cnt = smem;                                      // [regions][P2] pairs per slot
   uint32_t* const s_bm = (uint32_t*)(s_cnt + regions(PARTS) * P2);  // [P2][stride] bitmap of the share's tokens per slot
   int32_t* const s_tab = smem + zeros;
-  uint32_t* const s_entry = (uint32_t*)(s_tab + route_table_ints(E, P, R));  // [E+1]
-  int32_t* const s_offset = (int32_t*)s_entry + E + 1;              // [P+1] exclusive scan of the totals
-  int32_t* const s_slot = s_offset + P + 1;                         // [tokens*K] slots of the share's pairs
+  uint32_t* const s_entry = (uint32_t*)(s_tab + route_table_ints(E, P, R));  // [E+kNoneSinks]
+  int32_t* const s_offset = (int32_t*)s_entry + E + kNoneSinks;     // [P2+1] exclusive scan of the totals
+  int32_t* const s_slot = s_offset + P2 + 1;                        // [tokens*K] slots of the share's pairs
   __shared__ uint32_t s_agreed[2];
 #pragma nounroll
   for (uint32_t i = tid * 4; i < zeros; i += nt * 4) *(int4*)(smem + i) = make_int4(0, 0, 0, 0);
@@ -991,21 +1002,25 @@ __global__ __launch_bounds__(kOnceThreads) void k_layout_once(
   const uint32_t hi = min(lo + tokens, PARTS ? rank_end : T);
   __syncthreads();
   build_entries<LARGE>(rt, s_entry, E, P, policy, nt);
+  const uint32_t none = E + (tid & (kNoneLanes - 1));
+  if constexpr (K > 1) entries_of(e, none);
   bool repeats = any_repeats(e);
   __syncthreads();
 #pragma nounroll
-  while (t < T) {
+  while (t >= 0) {
     const uint32_t now = t;
-    t += nt;
+    t -= nt;
     int next[K];
-    if (t < T) load(t, next);
+    if (t >= 0) load(t, next);
     int p[K];
-    map_token<K>(rt, s_entry, E, P, e, repeats, now, p);
+    if constexpr (K == 1) entries_of(e, none);  // (here it needs no branch)
+    map_token<K>(rt, s_entry, P, e, repeats, now, p);
     // counted in the token's region, and if the token is the share's own, kept
     const bool own = now >= lo && now < hi;
-    int32_t* cnt = s_cnt + (own ? P2 : now < lo ? 0 : 2 * P2);
+    uint32_t region = own ? P2 : now < lo ? 0 : 2 * P2;
+    asm volatile("" : "+v"(region));  // (or the tokens of a share would take a branch of their own)
 #pragma unroll
-    for (uint32_t j = 0; j < K; ++j) atomicAdd(&cnt[p[j]], 1);
+    for (uint32_t j = 0; j < K; ++j) atomicAdd(&s_cnt[region + p[j]], 1);
     if (PARTS && sub == 0 && now >= hi && now < rank_end) {
 #pragma unroll
       for (uint32_t j = 0; j < K; ++j) atomicAdd(&s_cnt[3 * P2 + p[j]], 1);
@@ -1022,23 +1037,21 @@ __global__ __launch_bounds__(kOnceThreads) void k_layout_once(
         atomicOr(&bm[__umul24(p[j], stride)], bit);
       }
     }
-    if (t < T) {
+    if (t >= 0) {
 #pragma unroll
       for (uint32_t j = 0; j < K; ++j) e[j] = next[j];
-      repeats = any_repeats(e);
+      if constexpr (K > 1) {
+        entries_of(e, none);
+        repeats = any_repeats(e);
+      }
     }
   }
   __syncthreads();
   // Between two barriers: the scan, and what does not need it.
   const uint32_t n = (hi - lo) * K, g0 = lo * K;
   const auto total = [=](uint32_t p) { return s_cnt[p] + s_cnt[P2 + p] + s_cnt[2 * P2 + p]; };
-  scan_totals(total, s_offset, P, wave, waves);
-  int dead = 0, masked = 0, version = 0;
-  if (share == 0) {
-    dead = total(P);
-    masked = total(P + 1);
-    version = vector_load(tbl_version) + vector_load(mem_version);
-  }
+  scan_totals(total, s_offset, P2, wave, waves);
+  const int version = share == 0 ? vector_load(tbl_version) + vector_load(mem_version) : 0;
   // pairs per (source rank, slot): the tokens of a source rank are a bit range
   if (sub == 0) {
     const uint32_t mine = min(R - rank0, ranks);
@@ -1091,8 +1104,8 @@ __global__ __launch_bounds__(kOnceThreads) void k_layout_once(
     if (i < n) place(i);
   }
   if (share == 0)
-    write_step_tables(nt, s_offset, dead, masked, version, count, offset, rank_count, rank_offset, status,
-                      step_epoch, R, S, P);
+    write_step_tables(nt, s_offset, s_offset[P + kDeadSinks] - rows, s_offset[P2] - s_offset[P + kDeadSinks], version,
+                      count, offset, rank_count, rank_offset, status, step_epoch, R, S, P);
   if (agree.several && wave == 0 && __builtin_amdgcn_readfirstlane(before) == (int)gridDim.x - 1) {
     // every workgroup has the mask: zeros again for the next launch
 #pragma nounroll
