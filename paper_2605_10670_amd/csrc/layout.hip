@@ -744,8 +744,9 @@ __global__ __launch_bounds__(kMapThreads) void k_layout_small(
 // pairs to a rank: 5.0 in parts, 4.8).  512 threads, 1024 for more than 1024 tokens (T = 256 / 512 / 1024: 4.25 / 4.5 /
 // 5.1 with 512, 4.35 / 4.6 / 5.0 with 1024).
 //
-// What no ordinary router gives: 2048 tokens, 90 % of them without an expert (-1) 5.9 us (17.3 with one sink for all,
-// tiles 8.7), half of all pairs without one 6.2 (11.9; 8.8).
+// What no ordinary router gives: 2048 tokens, 90 % of them without an expert (-1) 6.2 us (17.3 with one sink for all,
+// tiles 8.7), half of all pairs without one 6.4 (11.9; 8.8), all tokens alike 6.5 (17.4 lane by lane; 7.7).  Four experts
+// that every token names in the middle of others are not told: 11.1 (7.8).
 //
 // Up to 512 tokens and 4096 pairs there are 8 workgroups, however many ranks.
 //
@@ -861,6 +862,28 @@ __device__ __forceinline__ void map_token(const RouteTables& rt, const uint32_t*
       for (uint32_t i = 0; i < j; ++i) p[j] = e[i] == e[j] ? P + kDeadSinks : p[j];
     }
   }
+}
+
+// Adds the lanes to counts[c], those of up to three different c (an expert's replicas) together, one lane for all: one
+// word of LDS is otherwise added to by one lane after the other.
+__device__ __forceinline__ void count_together(int32_t* counts, int c) {
+  const int lane = threadIdx.x & 63;
+  bool to_do = true;
+#pragma unroll
+  for (int i = 0; i < 3; ++i) {
+    if (to_do) {
+      const bool same = c == __builtin_amdgcn_readfirstlane(c);
+      const int all = __popcll(__ballot(same));
+      if (lane == __builtin_amdgcn_readfirstlane(lane)) atomicAdd(&counts[c], all);
+      to_do = !same;
+    }
+  }
+  if (to_do) atomicAdd(&counts[c], 1);
+}
+// Do all lanes' tokens begin and end with the same experts?
+template <uint32_t N>
+__device__ __forceinline__ bool alike(const int (&e)[N]) {
+  return __all(e[0] == __builtin_amdgcn_readfirstlane(e[0]) && e[N - 1] == __builtin_amdgcn_readfirstlane(e[N - 1]));
 }
 
 // Bits [lo, hi) of a bitmap, lo < hi.
@@ -1002,50 +1025,65 @@ __global__ __launch_bounds__(kOnceThreads) void k_layout_once(
   const uint32_t hi = min(lo + tokens, PARTS ? rank_end : T);
   __syncthreads();
   build_entries<LARGE>(rt, s_entry, E, P, policy, nt);
+  // Tokens that are copies of one another (padding that is routed like any token, a router that has collapsed) are
+  // told by their first and last expert, those of a wavefront's first round for all: padding is last.
+  const bool copies = K > 1 && alike(e);
   const uint32_t none = E + (tid & (kNoneLanes - 1));
   if constexpr (K > 1) entries_of(e, none);
   bool repeats = any_repeats(e);
   __syncthreads();
+  const auto count_tokens = [&](auto together) {
 #pragma nounroll
-  while (t >= 0) {
-    const uint32_t now = t;
-    t -= nt;
-    int next[K];
-    if (t >= 0) load(t, next);
-    int p[K];
-    if constexpr (K == 1) entries_of(e, none);  // (here it needs no branch)
-    map_token<K>(rt, s_entry, P, e, repeats, now, p);
-    // counted in the token's region, and if the token is the share's own, kept
-    const bool own = now >= lo && now < hi;
-    uint32_t region = own ? P2 : now < lo ? 0 : 2 * P2;
-    asm volatile("" : "+v"(region));  // (or the tokens of a share would take a branch of their own)
+    while (t >= 0) {
+      const uint32_t now = t;
+      t -= nt;
+      int next[K];
+      if (t >= 0) load(t, next);
+      int p[K];
+      if constexpr (K == 1) entries_of(e, none);  // (here it needs no branch)
+      const bool at_once = together.value && alike(e);
+      map_token<K>(rt, s_entry, P, e, repeats, now, p);
+      // counted in the token's region, and if the token is the share's own, kept
+      const bool own = now >= lo && now < hi;
+      const auto count = [&](uint32_t region) {
+        if (at_once) {
 #pragma unroll
-    for (uint32_t j = 0; j < K; ++j) atomicAdd(&s_cnt[region + p[j]], 1);
-    if (PARTS && sub == 0 && now >= hi && now < rank_end) {
+          for (uint32_t j = 0; j < K; ++j) count_together(s_cnt, region + p[j]);
+        } else {
 #pragma unroll
-      for (uint32_t j = 0; j < K; ++j) atomicAdd(&s_cnt[3 * P2 + p[j]], 1);
-    }
-    if (own) {
-      const uint32_t tl = now - lo;
-      uint32_t* bm = s_bm + (tl >> 5);
-      int32_t* to = s_slot + tl * K;
-      const uint32_t bit = 1u << (tl & 31);
+          for (uint32_t j = 0; j < K; ++j) atomicAdd(&s_cnt[region + p[j]], 1);
+        }
+      };
+      uint32_t region = own ? P2 : now < lo ? 0 : 2 * P2;
+      asm volatile("" : "+v"(region));  // (or the tokens of a share would take a branch of their own)
+      count(region);
+      if (PARTS && sub == 0 && now >= hi && now < rank_end) count(3 * P2);
+      if (own) {
+        const uint32_t tl = now - lo;
+        uint32_t* bm = s_bm + (tl >> 5);
+        int32_t* to = s_slot + tl * K;
+        const uint32_t bit = 1u << (tl & 31);
 #pragma unroll
-      for (uint32_t j = 0; j < K; ++j) to[j] = p[j];
+        for (uint32_t j = 0; j < K; ++j) to[j] = p[j];
 #pragma unroll
-      for (uint32_t j = 0; j < K; ++j) {
-        atomicOr(&bm[__umul24(p[j], stride)], bit);
+        for (uint32_t j = 0; j < K; ++j) {
+          atomicOr(&bm[__umul24(p[j], stride)], bit);
+        }
+      }
+      if (t >= 0) {
+#pragma unroll
+        for (uint32_t j = 0; j < K; ++j) e[j] = next[j];
+        if constexpr (K > 1) {
+          entries_of(e, none);
+          repeats = any_repeats(e);
+        }
       }
     }
-    if (t >= 0) {
-#pragma unroll
-      for (uint32_t j = 0; j < K; ++j) e[j] = next[j];
-      if constexpr (K > 1) {
-        entries_of(e, none);
-        repeats = any_repeats(e);
-      }
-    }
-  }
+  };
+  if (__builtin_expect(copies, 0))
+    count_tokens(std::true_type());
+  else
+    count_tokens(std::false_type());
   __syncthreads();
   // Between two barriers: the scan, and what does not need it.
   const uint32_t n = (hi - lo) * K, g0 = lo * K;
