@@ -1460,7 +1460,10 @@ __global__ __launch_bounds__(kMapThreads) void k_dedup_position(
 // a launch of its own costs about 2 us beside that, and the host 2.6.  Whole de-duplicated steps in a graph
 // of 8, the one-launch form of the ordinary layout on both sides: 2048 tokens over 8 ranks, 7168 channels,
 // 158.3 us in two launches, 153.5 in one; 512 tokens 52.8 and 49.0.
-constexpr int kDedupShare = 64;
+// Up to 3 ranks only up to 6144 tokens (kDedupFewTokens): the counts of few ranks are few LDS words, added to by one
+// lane after the other.  Top-1, 16384 tokens, 1 / 2 / 4 / 8 ranks 16.4 / 10.3 / 8.8 / 5.9 us, in two launches 9.0 each; top-2,
+// 8192 tokens 10.0 / 9.4 / 7.8 / 6.6, in two 7.5 each; top-3, 5460 tokens 7.8 / 8.2 / 7.3 / 6.4, in two 8.0 each.
+constexpr int kDedupShare = 64, kDedupFewRanks = 3, kDedupFewTokens = 6144;
 
 template <int KC>
 __global__ __launch_bounds__(kOnceThreads) void k_dedup_once(
@@ -1553,7 +1556,8 @@ hipError_t launch_dedup_layout(eep_ctx* c, int T, hipStream_t st) {
     if (e == hipSuccess) e = launch_fill(c->dd_status, 0, 1, st);
     return e;
   }
-  if (c->R <= 64 && c->k <= kOnceMaxK && (int64_t)T * c->k <= kOncePairs) {
+  if (c->R <= 64 && c->k <= kOnceMaxK && (int64_t)T * c->k <= kOncePairs &&
+      (c->R > kDedupFewRanks || T <= kDedupFewTokens)) {
     static const decltype(&k_dedup_once<1>) of[kOnceMaxK] = {
         k_dedup_once<1>, k_dedup_once<2>, k_dedup_once<3>, k_dedup_once<4>, k_dedup_once<5>,
         k_dedup_once<6>, k_dedup_once<7>, k_dedup_once<8>, k_dedup_once<9>, k_dedup_once<10>};
