@@ -138,11 +138,13 @@ def test_dedup_call_order_and_refusals():
         ctx.destroy()
 
 
-def test_rows_withdrawn_before_the_dedup_layout(oracle):
+# one launch; two: beyond 16384 pairs, beyond top-10, beyond 64 ranks
+@pytest.mark.parametrize("R,T,k,small", [(8, 512, 6, 256), (8, 6144, 6, 4096), (8, 1024, 12, 512), (66, 1056, 4, 528)])
+def test_rows_withdrawn_before_the_dedup_layout(oracle, R, T, k, small):
     """Failure detection strikes pairs between the layout and the de-duplicated one: their rows must
     not keep the source of an earlier, larger step."""
-    wl = _workload(R=8, T=512, k=6, sp=4, sr=1, H=64)
-    T, R, S, silent = 256, wl.R, wl.S, 3
+    wl = _workload(R=R, T=T, k=k, sp=4, sr=1, H=64)
+    T, S, silent = small, wl.S, 3
     ctx = gu.make_context(wl, strict=False)
     try:
         gu.apply_tables(ctx, wl.p2l, wl.active)
