@@ -891,7 +891,10 @@ __device__ __forceinline__ int row_if_arrived(const DetectArgs& d, int64_t pair0
 // k is a compile-time number up to 10; a larger one goes in batches of 8 and 4 rows.  One row at a
 // time, each behind its index, top-10 took (whole steps, 4096 channels, T = 32 / 256) 12.5 / 16.9 us instead
 // of 9.7 / 15.5, top-3 9.2 / 10.4 instead of 8.7 / 9.9, top-5 of 512 tokens 21.9 instead of 21.1; at 4096
-// tokens, where other wavefronts fill the time, 124.8 instead of 123.0 and the same.
+// tokens, where other wavefronts fill the time, 124.8 instead of 123.0 and the same; top-32 of 1024 tokens 43.2 instead
+// of 44.7.  With one pair in seven dropped (combine alone, 4096 channels, T = 256 / 1024, top-12 / 24 / 32) one row at a time
+// 10.3 / 17.4, 17.3 / 30.6, 21.7 / 39.1 us, a batch with such a pair one row at a time 9.1 / 17.9, 15.7 / 33.0, 19.6 / 42.1,
+// a branch around each load 8.2 / 17.8, 15.5 / 33.1, 19.4 / 42.0, and in this form 6.2 / 16.6, 9.0 / 30.3, 11.0 / 39.2.
 //
 // DETECT: the wait for the ranks' signals is part of the kernel (DetectArgs above); row_of
 // is then not read-only, because dropped pairs are struck from it, and lane j keeps the row of
@@ -994,11 +997,21 @@ __global__ __launch_bounds__(64) void k_combine(const int32_t* row_of,
 #pragma unroll
         for (int i = 0; i < B; ++i) accumulate<Y_BF16>(acc, d[i], ws[j0 + i]);
       } else {
-        for (int i = 0; i < B; ++i) {
-          const int row = row_at(j0 + i);
-          if (row < 0) continue;
-          accumulate<Y_BF16>(acc, __builtin_nontemporal_load(&y[(int64_t)row * row_vecs + v]), ws[j0 + i]);
+        // Some pairs have no row: they load another one, row 0, or with DETECT one of the token's, which
+        // is known to be there, and only the terms are left out.
+        int other = 0;
+        if constexpr (DETECT) {
+          other = -1;
+#pragma unroll
+          for (int i = 0; i < B; ++i) other = r[i] >= 0 ? r[i] : other;
+          if (other < 0) return;
         }
+#pragma unroll
+        for (int i = 0; i < B; ++i)
+          d[i] = __builtin_nontemporal_load(&y[(int64_t)(r[i] >= 0 ? r[i] : other) * row_vecs + v]);
+#pragma unroll
+        for (int i = 0; i < B; ++i)
+          if (r[i] >= 0) accumulate<Y_BF16>(acc, d[i], ws[j0 + i]);
       }
     };
     int j = 0;
