@@ -408,6 +408,25 @@ __device__ __forceinline__ void wave_exclusive_scan(Value value, int32_t* s_offs
   if (lane == 0) s_offset[n] = run;
 }
 
+// Exclusive scan of the slots' totals into s_offset[0..P]: the wavefronts, the last one first, take
+// 64 slots each and add up what lies ahead of these for themselves, so that nothing has to be
+// exchanged.  The caller's next barrier makes the result readable.
+template <class Total>
+__device__ __forceinline__ void scan_totals(Total total, int32_t* s_offset, int P, int wave,
+                                            int waves) {
+  const int lane = threadIdx.x & 63, chunks = (P >> 6) + 1;
+#pragma nounroll
+  for (int c = waves - 1 - wave; c < chunks; c += waves) {
+    int ahead = 0;
+#pragma unroll 4
+    for (int i = 0; i < c; ++i) ahead += total(i * 64 + lane);
+    const int p = c * 64 + lane, v = p < P ? total(p) : 0;
+    const int incl = wave_inclusive_scan(v);
+    ahead = __builtin_amdgcn_readlane(wave_inclusive_scan(ahead), 63);
+    if (p <= P) s_offset[p] = ahead + incl - v;
+  }
+}
+
 // Per-step tables every consumer needs, written once by one workgroup
 // (`count` may be null when another kernel has already written it).
 __device__ inline void write_step_tables(int nt, const int32_t* s_offset,
@@ -563,13 +582,16 @@ __global__ __launch_bounds__(kFusedThreads) void k_scan_position(
 // workgroup waits for another; one alone spent 1.4 to 2.8 us on storing, mostly the [R][P] matrix of pairs per
 // (source rank, slot).
 //
-// Where k_layout_once below could do it too, this takes batches of up to 128 tokens (kFewTokens), two
-// wavefronts in that form, with a compile-time k.  Measured (a layout in a graph of 40; 32 ranks x 9 slots, in
-// brackets that one): top-8, T = 32 / 64 / 96 / 128 3.6 / 3.7 / 3.7 / 3.8 us (3.9 each), T = 192 / 256 / 512
-// 4.4 / 4.6 / 5.8 (4.1 / 4.2 / 4.4); top-4, T = 64 / 128 / 256 3.6 / 3.7 / 3.8 (3.8 each); top-2, T = 64 / 128 / 512
-// 3.6 / 3.6 / 3.9 (3.6 / 3.6 / 3.65); without a compile-time k, top-6, T = 32 / 64 4.1 / 4.15 (3.8 each); 64 ranks,
-// top-8, T = 64 / 128 4.4 / 4.5 (4.6 each).  Beyond these it takes more than top-10, and tables that do not
-// fit there (8 ranks x 265 slots, T = 32: 8.5 us, in tiles 12.6).
+// Where k_layout_once below could do it too, this takes at most a pair to a thread (kFewPairs), with a compile-time k.
+// Measured (a layout in a graph of 40; 32 ranks x 9 slots, in brackets that one): top-8, T = 32 / 64 / 128 3.55 / 3.6 /
+// 3.7 us (4.1 each), T = 192 / 256 / 512 4.3 / 4.6 / 5.8 (4.2 / 4.3 / 4.5); top-4, T = 64 / 128 / 256 / 512 3.6 / 3.6 / 3.8 / 4.5
+// (3.8 / 3.8 / 3.9 / 4.0); top-2, T = 64 / 128 / 512 3.5 / 3.6 / 3.8 (3.7 / 3.8 / 3.8); top-1, T = 512 3.65 (3.65); without a
+// compile-time k, top-6, T = 32 / 64 / 128 4.0 / 4.05 / 4.2 (4.0 each); 64 ranks, top-8, T = 64 / 128 / 256 3.9 / 4.1 / 5.0
+// (4.9 / 4.9 / 5.0); 24 ranks x 17 slots, T = 120, top-2 3.9 (3.8), top-8 4.0 (4.3); 48 x 10, top-2, T = 144 3.9 (4.15); 6 x 5, top-1,
+// T = 420, five replicas 3.3 (3.9).
+// Beyond these it takes more than top-10, and tables that do not fit there (8 ranks x 265 slots, T = 32: 7.6 us, in
+// tiles 12.6).  With the scan done by one wavefront, and the source ranks' counts by the first workgroups'
+// wavefronts alone, it took 0.05 to 0.3 us more, and most of it with more than 320 slots (64 ranks 4.4 / 4.5; 24 x 17 4.5).
 //
 // The eight results fit together only if all eight workgroups saw one mask.  An
 // instance of one context keeps its mask still while a layout runs: only its own
@@ -578,7 +600,7 @@ __global__ __launch_bounds__(kFusedThreads) void k_scan_position(
 // there ONE workgroup does it all (each entry of the replica lists is found live or
 // dead once, and every pair, count and row follows from that), up to the size from
 // which the tiled path, where each pair is mapped once, is as fast: T = 32 / 128 / 256 / 384
-// 4.1 / 4.4 / 5.7 / 7.2 us, in tiles 7.5.  The launch
+// 4.0 / 4.4 / 5.6 / 7.2 us, in tiles 7.5.  The launch
 // decides by the number of contexts; a launch captured while there was one is
 // overruled by the word behind the membership version, which says that there are more.
 // ---------------------------------------------------------------------------
@@ -588,7 +610,7 @@ constexpr int kSmallPairsPerThread = 4;
 constexpr int kSmallPairs = kMapThreads * kSmallPairsPerThread;
 constexpr int kSoloTokens = 384;  // the limits for one workgroup
 constexpr int kSoloPairs = kMapThreads * 3;
-constexpr int kFewTokens = 128;  // up to here not for k_layout_once
+constexpr int kFewPairs = kMapThreads;  // up to here not for k_layout_once
 constexpr uint32_t kSoloBit = 1u << 31;
 
 __device__ __forceinline__ int vector_load(const int32_t* p) {
@@ -687,7 +709,8 @@ __global__ __launch_bounds__(kMapThreads) void k_layout_small(
                    own_hi, slot_of);
   __syncthreads();
 
-  if (tid < 64) wave_exclusive_scan([=](int p) { return s_count[p]; }, s_offset, P);
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  scan_totals([=](int p) { return s_count[p]; }, s_offset, P, wave, kMapThreads / 64);
   __syncthreads();
 
   const int N = s_offset[P];
@@ -706,9 +729,8 @@ __global__ __launch_bounds__(kMapThreads) void k_layout_small(
     }
   }
   // pairs per (source rank, slot): the tokens of a source rank are a bit range; wavefronts
-  // take source ranks, lanes slots, five sets of 64 slots at once where there are more than one
-  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  for (int b = block * (kMapThreads / 64) + wave; b < R; b += blocks * (kMapThreads / 64)) {
+  // take source ranks, the workgroups in turn, lanes slots, five sets of 64 at once where there are more than one
+  for (int b = wave * blocks + block; b < R; b += blocks * (kMapThreads / 64)) {
     const int lo = b * tokens_per_rank, hi = lo + tokens_per_rank;
     int32_t* cnt = cnt_src + (int64_t)b * P;
     if (P <= 64)
@@ -733,7 +755,7 @@ __global__ __launch_bounds__(kMapThreads) void k_layout_small(
 // of a branch, and what does not wait for the scan stands between its barriers.
 //
 // Measured (a layout in a graph of 40; 32 ranks x 9 slots, top-8), in brackets k_layout_small, and beyond 512
-// tokens tiles: T = 256 / 512 4.2 / 4.5 us (4.6 / 5.8), 1024 / 1536 / 2048 5.1 / 5.5 / 6.0 (7.6 / 7.8 / 7.9), 3072 / 4096
+// tokens tiles: T = 256 / 512 4.3 / 4.5 us (4.6 / 5.8), 1024 / 1536 / 2048 5.1 / 5.5 / 6.0 (7.6 / 7.8 / 7.9), 3072 / 4096
 // 7.3 / 8.3 (8.0 / 8.3); with a Zipf router, whose hot slots' counts are one LDS word for many lanes, 2048 / 3072 / 4096
 // 6.4 / 7.9 / 9.1 (7.8 / 7.9 / 8.1).  T = 1024 of 64 ranks x 9 slots 5.6 (12.0), top-2 of 32 ranks 3.95 (7.4), T = 768 of 24
 // ranks, top-6, 4.4 (7.8).  So up to 16384 pairs.  Shares of about 64 tokens, whole
@@ -754,7 +776,7 @@ __global__ __launch_bounds__(kMapThreads) void k_layout_small(
 // an instance of one context, which keeps its mask still.  One captured then and replayed when there are more
 // learns it from the word behind the membership version; its workgroups use the mask that the first one read
 // (agree_on), for a barrier and a round trip or two through memory more: T = 256 / 512 / 1024 / 2048
-// 5.1 / 5.5 / 6.2 / 7.1 us.  (All of it done by the first workgroup took 8.6 / 11.1 / 19.3 / 29.9, and 65 for 2048 tokens of
+// 5.3 / 5.5 / 6.1 / 7.1 us.  (All of it done by the first workgroup took 8.6 / 11.1 / 19.3 / 29.9, and 65 for 2048 tokens of
 // 8 ranks, and the loop over shares that it needed cost every launch 0.1 to 0.3 us.)
 // ---------------------------------------------------------------------------
 constexpr int kOnceThreads = 1024;
@@ -910,25 +932,6 @@ __host__ __device__ inline uint32_t once_zeros(uint32_t P, uint32_t stride, bool
 inline size_t once_lds_bytes(int E, int P, int R, int tokens, int k, bool parts) {
   return sizeof(int32_t) * ((size_t)once_zeros(P, token_stride(tokens), parts) + route_table_ints(E, P, R) +
                             (E + kNoneSinks) + (P + kSinks + 1) + (size_t)tokens * k);
-}
-
-// Exclusive scan of the slots' totals into s_offset[0..P]: the wavefronts, the last one first, take
-// 64 slots each and add up what lies ahead of these for themselves, so that nothing has to be
-// exchanged.  The caller's next barrier makes the result readable.
-template <class Total>
-__device__ __forceinline__ void scan_totals(Total total, int32_t* s_offset, int P, int wave,
-                                            int waves) {
-  const int lane = threadIdx.x & 63, chunks = (P >> 6) + 1;
-#pragma nounroll
-  for (int c = waves - 1 - wave; c < chunks; c += waves) {
-    int ahead = 0;
-#pragma unroll 4
-    for (int i = 0; i < c; ++i) ahead += total(i * 64 + lane);
-    const int p = c * 64 + lane, v = p < P ? total(p) : 0;
-    const int incl = wave_inclusive_scan(v);
-    ahead = __builtin_amdgcn_readlane(wave_inclusive_scan(ahead), 63);
-    if (p <= P) s_offset[p] = ahead + incl - v;
-  }
 }
 
 // One word of the mask that all workgroups of a launch use where it may change meanwhile: the one that the first
@@ -1664,7 +1667,7 @@ hipError_t launch_layout(const LayoutIO& c, int T, hipStream_t st) {
   const ShareSize share = share_size(c.E, c.P, c.R, g.tokens_per_rank, c.k, small);
   const int tokens = share.tokens(g.tokens_per_rank);
   const bool has_k = c.k == 1 || c.k == 2 || c.k == 4 || c.k == 8;  // an instance of k_layout_small
-  const bool few = small > 0 && has_k && T <= kFewTokens;
+  const bool few = small > 0 && has_k && T * c.k <= kFewPairs;
   if (!solo && !few && c.k <= kOnceMaxK && (int64_t)T * c.k <= kOncePairs && c.P + kSinks <= kEntrySlots &&
       once_lds_bytes(c.E, c.P, c.R, tokens, c.k, share.subs > 1) <= kLayoutLdsLimit) {
     int nt = c.P > c.E ? c.P : c.E + 1;  // threads: for the tables, and for the tokens

@@ -18,7 +18,7 @@ pytestmark = pytest.mark.gpu
 @pytest.mark.parametrize("R,S,E,k,sizes", [
     (32, 9, 256, 8, (256, 2048)), (8, 36, 256, 8, (2048, 512)), (2, 9, 16, 8, (1024, 256)), (1, 16, 16, 3, (5001,)),
     (48, 4, 96, 5, (480, 2496)), (65, 3, 130, 7, (585, 2340)), (200, 6, 1100, 4, (600, 4000)),
-    (1000, 2, 500, 2, (1000, 8000)), (64, 9, 512, 10, (1024,)),
+    (1000, 2, 500, 2, (1000, 8000)), (64, 9, 512, 10, (1024,)), (8, 140, 500, 4, (1024, 520)),
 ], ids=str)
 def test_one_mask_for_all_workgroups(oracle, R, S, E, k, sizes):
     T_max = max(sizes)
