@@ -101,7 +101,7 @@ def bf16_to_f64(bits):
 
 
 def check_combine(got, out_dtype, want64, chain32_bits=None):
-    """north_star gate: 1e-3 relative on the fp32-accumulated sum (row-rms floor);
+    """The gate: 1e-3 relative on the fp32-accumulated sum (row-rms floor);
     bf16 outputs within one bf16 ulp of the exact sum.  If the fp32-chain result
     is given, also demand bit equality with it (same order, same rounding)."""
     rms = np.sqrt((want64 ** 2).mean(axis=1, keepdims=True))

@@ -31,7 +31,7 @@ def _oracle_out(oracle, wl, p2l, active, silent=()):
     return lay, det, chain
 
 
-@pytest.mark.parametrize("T_batch", [1024, 512, 64])   # tiled layout / one launch, large and small
+@pytest.mark.parametrize("T_batch", [4096, 1024, 512, 64])   # tiled layout / one launch, large and small
 @pytest.mark.parametrize("use_graph", [False, True])
 def test_silent_rank_is_dropped_by_the_kernel(oracle, use_graph, T_batch):
     wl = synth.churn_inputs(1, T=T_batch, H=512)[0]

@@ -1,5 +1,5 @@
 """dispatch_layout at the edges of its launch forms: pairs per thread (1024, 2048, 4096 pairs), the
-limit of the one-launch form (512 tokens, 4096 pairs), top-k with and without a lane form, masks in a
+limits of the one-launch form for small batches (512 tokens, 4096 pairs), top-k with and without a lane form, masks in a
 register (up to 64 ranks) and in LDS, experts with more than 32 replicas, slot counts around the
 scan's groups of 64 and 320.  Every field bit-equal to the oracle, with dead ranks, masked, repeated
 and uncovered pairs."""

@@ -2,8 +2,8 @@
 several source ranks and of a part of one (the last part short or empty), every compile-time top-k, batches that a lane takes
 several tokens of, tables larger than a workgroup, experts with none, two, three and more than 32 live
 replicas.  Every field bit-equal to the oracle, with dead ranks, masked, repeated and uncovered pairs;
-and the same after the instance got a second context, when one workgroup does it all: of a launch
-captured before, and of one made then."""
+and the same after the instance got a second context: of a launch captured before, whose workgroups
+then use one mask, and of one made then, which is one workgroup or tiles."""
 import numpy as np
 import pytest
 

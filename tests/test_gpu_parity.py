@@ -108,7 +108,8 @@ def test_decode_shape_ragged_sizes(oracle, T):
 @pytest.mark.parametrize("R,T", [(32, 16384), (32, 20576), (3, 600), (1, 77), (64, 64 * 130)])
 def test_many_tiles_and_odd_rank_counts(oracle, R, T):
     """More than 64 tiles (several tiles per scan lane), ragged tiles inside a
-    source rank, rank counts that are not powers of two, a single rank."""
+    source rank; and rank counts that are not powers of two and a single rank, whose
+    batches are one launch here (in tiles: test_gpu_layout_tiles)."""
     rng = np.random.default_rng(R + T)
     H, k, sp, sr = 128, 8, 4, 1
     E = R * sp
@@ -124,7 +125,7 @@ def test_many_tiles_and_odd_rank_counts(oracle, R, T):
     assert got["N"] == T * k
 
 
-@pytest.mark.parametrize("T", [96, 256, 1024])   # one launch, one and two pairs a thread / tiled layout
+@pytest.mark.parametrize("T", [96, 256, 1024, 4096])   # one launch, a lane to a pair, a lane to a token / tiled layout
 def test_masked_repeated_and_out_of_range_indices(oracle, T):
     wl = synth.decode(T=T, H=256)
     rng = np.random.default_rng(5)
