@@ -583,15 +583,15 @@ __global__ __launch_bounds__(kFusedThreads) void k_scan_position(
 // (source rank, slot).
 //
 // Where k_layout_once below could do it too, this takes at most a pair to a thread (kFewPairs), with a compile-time k.
-// Measured (a layout in a graph of 40; 32 ranks x 9 slots, in brackets that one): top-8, T = 32 / 64 / 128 3.55 / 3.6 /
-// 3.7 us (4.1 each), T = 192 / 256 / 512 4.3 / 4.6 / 5.8 (4.2 / 4.3 / 4.5); top-4, T = 64 / 128 / 256 / 512 3.6 / 3.6 / 3.8 / 4.5
-// (3.8 / 3.8 / 3.9 / 4.0); top-2, T = 64 / 128 / 512 3.5 / 3.6 / 3.8 (3.7 / 3.8 / 3.8); top-1, T = 512 3.65 (3.65); without a
-// compile-time k, top-6, T = 32 / 64 / 128 4.0 / 4.05 / 4.2 (4.0 each); 64 ranks, top-8, T = 64 / 128 / 256 3.9 / 4.1 / 5.0
-// (4.9 / 4.9 / 5.0); 24 ranks x 17 slots, T = 120, top-2 3.9 (3.8), top-8 4.0 (4.3); 48 x 10, top-2, T = 144 3.9 (4.15); 6 x 5, top-1,
-// T = 420, five replicas 3.3 (3.9).
+// Measured (a layout in a graph of 40; 32 ranks x 9 slots, in brackets that one): top-8, T = 32 / 64 / 128 3.55 / 3.6
+// / 3.7 us (4.1 each), T = 192 / 256 / 512 4.3 / 4.6 / 5.8 (4.2 / 4.3 / 4.5); top-4, T = 64 / 128 / 256 / 512 3.6 / 3.6 /
+// 3.8 / 4.5 (3.8 / 3.8 / 3.9 / 4.0); top-2, T = 64 / 128 / 512 3.5 / 3.6 / 3.8 (3.7 / 3.8 / 3.8); top-1, T = 512 3.65 (3.65);
+// without a compile-time k, top-6, T = 32 / 64 / 128 4.0 / 4.05 / 4.2 (4.0 each); 64 ranks, top-8, T = 64 / 128 / 256
+// 3.9 / 4.1 / 5.0 (4.9 / 4.9 / 5.0); 24 ranks x 17 slots, T = 120, top-2 3.9 (3.8), top-8 4.0 (4.3); 48 x 10, top-2,
+// T = 144 3.9 (4.15); 6 x 5, top-1, T = 420, five replicas 3.3 (3.9).
 // Beyond these it takes more than top-10, and tables that do not fit there (8 ranks x 265 slots, T = 32: 7.6 us, in
 // tiles 12.6).  With the scan done by one wavefront, and the source ranks' counts by the first workgroups'
-// wavefronts alone, it took 0.05 to 0.3 us more, and most of it with more than 320 slots (64 ranks 4.4 / 4.5; 24 x 17 4.5).
+// wavefronts alone, it took 0.05 to 0.5 us more, and most with more than 320 slots (64 ranks 4.4 / 4.5, 24 x 17 4.5).
 //
 // The eight results fit together only if all eight workgroups saw one mask.  An
 // instance of one context keeps its mask still while a layout runs: only its own
@@ -751,7 +751,7 @@ __global__ __launch_bounds__(kMapThreads) void k_layout_small(
 // (1.9 us for an empty kernel), one round of global loads, LDS round trips, and, as every
 // workgroup maps all pairs, the instructions per pair.  Hence a lane takes a whole token,
 // whose indices it compares in registers, the routing of an expert is one word that is
-// prepared once (`build_entries`), pairs without a slot have a sink to be counted in instead
+// prepared once (`build_entries`), pairs without a slot have sinks to be counted in instead
 // of a branch, and what does not wait for the scan stands between its barriers.
 //
 // Measured (a layout in a graph of 40; 32 ranks x 9 slots, top-8), in brackets k_layout_small, and beyond 512
@@ -770,7 +770,7 @@ __global__ __launch_bounds__(kMapThreads) void k_layout_small(
 // tiles 8.7), half of all pairs without one 6.4 (11.9; 8.8), all tokens alike 6.5 (17.4 lane by lane; 7.7).  Four experts
 // that every token names in the middle of others are not told: 11.1 (7.8).
 //
-// Up to 512 tokens and 4096 pairs there are 8 workgroups, however many ranks.
+// Up to 512 tokens and 4096 pairs there are at most 8 workgroups, however many ranks.
 //
 // The workgroups' results fit together only if all of them saw one mask, see k_layout_small.  Launches are made for
 // an instance of one context, which keeps its mask still.  One captured then and replayed when there are more
@@ -799,8 +799,8 @@ constexpr int kEntrySlots = 1 << 12;       // slots, sinks and counts stay below
 constexpr int kDeadSinks = 16, kNoneLanes = 8, kNoneSinks = kNoneLanes - 1 + kOnceMaxK;
 constexpr int kSinks = kDeadSinks + kNoneSinks;
 
-// Writes the entries of all experts and behind them those of no expert, and for those with more than two live replicas to choose from
-// the live ones to the front of the list.  The caller's next barrier makes both readable.
+// Writes the entries of all experts and behind them those of no expert, and for experts with more than two live
+// replicas to choose from the live ones to the front of the list.  The caller's next barrier makes both readable.
 template <bool LARGE>
 __device__ __forceinline__ void build_entries(const RouteTables& rt, uint32_t* entries, int E, int P,
                                               int policy, int nt) {
