@@ -767,8 +767,9 @@ __global__ __launch_bounds__(kMapThreads) void k_layout_small(
 // 5.1 with 512, 4.35 / 4.6 / 5.0 with 1024).
 //
 // What no ordinary router gives: 2048 tokens, 90 % of them without an expert (-1) 6.2 us (17.3 with one sink for all,
-// tiles 8.7), half of all pairs without one 6.4 (11.9; 8.8), all tokens alike 6.5 (17.4 lane by lane; 7.7).  Four experts
-// that every token names in the middle of others are not told: 11.1 (7.8).
+// tiles 8.7), half of all pairs without one 6.4 (11.9; 8.8), all tokens alike 6.5 (17.4 lane by lane; 7.7), one / two / four
+// / seven experts that every token names first or last 6.4 / 6.5 / 6.7 / 7.1 (6.6 / 8.1 / 11.2 / 16.0; 7.8 each); 16384
+// tokens of one pair, all the same, 12.3 (11.2): top-1 is not looked at, which would cost it 2 %.
 //
 // Up to 512 tokens and 4096 pairs there are at most 8 workgroups, however many ranks.
 //
@@ -902,11 +903,7 @@ __device__ __forceinline__ void count_together(int32_t* counts, int c) {
   }
   if (to_do) atomicAdd(&counts[c], 1);
 }
-// Do all lanes' tokens begin and end with the same experts?
-template <uint32_t N>
-__device__ __forceinline__ bool alike(const int (&e)[N]) {
-  return __all(e[0] == __builtin_amdgcn_readfirstlane(e[0]) && e[N - 1] == __builtin_amdgcn_readfirstlane(e[N - 1]));
-}
+__device__ __forceinline__ bool same_in_all_lanes(int v) { return __all(v == __builtin_amdgcn_readfirstlane(v)); }
 
 // Bits [lo, hi) of a bitmap, lo < hi.
 __device__ __forceinline__ int bits_between(const uint32_t* bm, int lo, int hi) {
@@ -1028,9 +1025,10 @@ __global__ __launch_bounds__(kOnceThreads) void k_layout_once(
   const uint32_t hi = min(lo + tokens, PARTS ? rank_end : T);
   __syncthreads();
   build_entries<LARGE>(rt, s_entry, E, P, policy, nt);
-  // Tokens that are copies of one another (padding that is routed like any token, a router that has collapsed) are
-  // told by their first and last expert, those of a wavefront's first round for all: padding is last.
-  const bool copies = K > 1 && alike(e);
+  // Tokens that are copies of one another (padding that is routed like any token, a router that has collapsed), or name
+  // some experts all alike, are told by their first and last expert, those of a wavefront's first round for all: padding
+  // is last.
+  const bool copies = K > 1 && (same_in_all_lanes(e[0]) || same_in_all_lanes(e[K - 1]));
   const uint32_t none = E + (tid & (kNoneLanes - 1));
   if constexpr (K > 1) entries_of(e, none);
   bool repeats = any_repeats(e);
@@ -1044,17 +1042,22 @@ __global__ __launch_bounds__(kOnceThreads) void k_layout_once(
       if (t >= 0) load(t, next);
       int p[K];
       if constexpr (K == 1) entries_of(e, none);  // (here it needs no branch)
-      const bool at_once = together.value && alike(e);
       map_token<K>(rt, s_entry, P, e, repeats, now, p);
       // counted in the token's region, and if the token is the share's own, kept
       const bool own = now >= lo && now < hi;
       const auto count = [&](uint32_t region) {
-        if (at_once) {
+        const bool all = together.value && same_in_all_lanes(e[0]) && same_in_all_lanes(e[K - 1]);
+        if (all) {
 #pragma unroll
           for (uint32_t j = 0; j < K; ++j) count_together(s_cnt, region + p[j]);
         } else {
 #pragma unroll
-          for (uint32_t j = 0; j < K; ++j) atomicAdd(&s_cnt[region + p[j]], 1);
+          for (uint32_t j = 0; j < K; ++j) {
+            if (together.value && same_in_all_lanes(e[j]))
+              count_together(s_cnt, region + p[j]);
+            else
+              atomicAdd(&s_cnt[region + p[j]], 1);
+          }
         }
       };
       uint32_t region = own ? P2 : now < lo ? 0 : 2 * P2;

@@ -23,6 +23,8 @@ def batch(kind, idx, E, rng):
         out[:, 0] = E - 1
     elif kind == "last the same":
         out[:, -1] = E // 2
+    elif kind == "most the same":
+        out[:, : k // 2 + 1] = np.arange(k // 2 + 1)
     elif kind == "end padded":
         out[T // 5 + 1:] = -1
     elif kind == "all padded":
@@ -37,8 +39,8 @@ def batch(kind, idx, E, rng):
 
 
 # (T, k, R, S, E): shares of several ranks, of one, of a part of one; a pair to a token; tables larger than a workgroup
-@pytest.mark.parametrize("kind", ["same", "half the same", "first the same", "last the same", "end padded",
-                                  "all padded", "tokens padded", "pairs padded", "repeats"])
+@pytest.mark.parametrize("kind", ["same", "half the same", "first the same", "last the same", "most the same",
+                                  "end padded", "all padded", "tokens padded", "pairs padded", "repeats"])
 @pytest.mark.parametrize("shape", [(1984, 8, 32, 9, 256), (1610, 10, 2, 9, 16), (1024, 5, 4, 6, 16), (8000, 2, 16, 6, 40),
                                    (16384, 1, 64, 2, 100), (600, 2, 150, 8, 1100)], ids=str)
 def test_skewed_layouts(oracle, shape, kind):
