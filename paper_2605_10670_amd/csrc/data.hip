@@ -10,26 +10,15 @@
 #include <type_traits>
 
 #include "eep_internal.hpp"
+#include "rows.hpp"
 
 namespace eep {
 
-typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef float f32x2 __attribute__((ext_vector_type(2)));
 typedef uint16_t u16x2 __attribute__((ext_vector_type(2)));
 typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
-
-// Workgroup index -> (token, part) without a division in front of the first load: n / d is the
-// high word of n * magic, magic = 2^32 / d rounded up, exact while n * d < 2^32 (the rounding
-// is at most d too much).  Magic 0: one part, or a grid so large that it divides.
-static uint32_t part_magic(int parts, int64_t grid) {
-  if (parts <= 1 || grid * parts >= ((int64_t)1 << 32)) return 0;
-  return (uint32_t)((((uint64_t)1 << 32) + parts - 1) / parts);
-}
-__device__ __forceinline__ uint32_t token_of(uint32_t n, uint32_t parts, uint32_t magic) {
-  return magic != 0 ? __umulhi(n, magic) : parts == 1 ? n : n / parts;
-}
 
 // ---------------------------------------------------------------------------
 // pack: recv[row_of[t, j]] = x[t].  One wavefront per token reads the row once
@@ -52,32 +41,12 @@ constexpr int kPackSplitBelow = 1024;
 constexpr int kPackNarrowBelow = 512;
 constexpr int kExpandSplitBelow = 4096;  // the same for rows that are read and written once
 
-// The data registers of a store of more than 8 bytes may not be rewritten by the next two
-// wait states' vector instructions.  The compiler keeps that distance for its own stores but
-// does not look into the asm, so the distance is part of it.
-__device__ inline void store_through(u32x4* p, u32x4 v) {
-  asm volatile("global_store_dwordx4 %0, %1, off sc0 sc1\n\ts_nop 1" ::"v"(p), "v"(v) : "memory");
-}
-
-// The same to `offset` bytes behind base + row, both scalar.  A vector memory instruction may not read
-// a scalar register within five wait states of a vector instruction that wrote it (v_readfirstlane, or
-// a spilled register's v_readlane); the compiler does not keep that distance for asm either, so
-// the address is added up by scalar instructions that are part of it.
-__device__ __forceinline__ void store_through_at(void* base, int64_t row, uint32_t offset, u32x4 v) {
-  asm volatile(
-      "s_add_u32 s98, %2, %4\n\ts_addc_u32 s99, %3, %5\n\t"
-      "global_store_dwordx4 %0, %1, s[98:99] sc0 sc1\n\ts_nop 1" ::"v"(offset), "v"(v),
-      "s"((uint32_t)(uintptr_t)base), "s"((uint32_t)((uintptr_t)base >> 32)), "s"((uint32_t)row),
-      "s"((uint32_t)((uint64_t)row >> 32))
-      : "memory", "scc", "s98", "s99");
-}
-
 // One wavefront per token.  U = 16-byte vectors per lane per pass.  EXACT: the row is a whole number of
 // passes (row_vecs % (64 * U) == 0), so no access needs a bounds check;
 // otherwise loads past the row's end read its last vector again, so that all U
 // loads of a pass are in flight here too (a branch around each would make it
 // wait for the ones before), and stores are guarded.
-template <int U, bool EXACT>
+template <int U, bool EXACT, bool HELD>
 __global__ __launch_bounds__(64) void k_pack(const u32x4* __restrict__ x,
                                              const int32_t* __restrict__ row_of, int k,
                                              int row_vecs, u32x4* __restrict__ recv) {
@@ -105,7 +74,7 @@ __global__ __launch_bounds__(64) void k_pack(const u32x4* __restrict__ x,
 #pragma unroll
       for (int u = 0; u < U; ++u) {
         int v = v0 + u * 64 + lane;
-        if (EXACT || v < row_vecs) store_through(&dst[v], buf[u]);
+        if (EXACT || v < row_vecs) store_row<HELD>(&dst[v], buf[u]);
       }
     }
   }
@@ -121,7 +90,7 @@ __global__ __launch_bounds__(64) void k_pack(const u32x4* __restrict__ x,
 // (k_scale_rows), T = 32 / 128 / 512 / 1000 in 16.3 / 19.9 / 42.4 / 70.7 us, 13.2 / 17.2 / 38.6 / 67.0 now.
 constexpr int kSplitMaxK = 8;
 
-template <int U, bool EXACT, int K, bool SCALES>
+template <int U, bool EXACT, int K, bool SCALES, bool HELD>
 __global__ __launch_bounds__(64) void k_pack_split(const u32x4* __restrict__ x,
                                                    const int32_t* __restrict__ row_of, int k_rt,
                                                    uint32_t row_vecs, uint32_t parts, uint32_t magic,
@@ -161,7 +130,7 @@ __global__ __launch_bounds__(64) void k_pack_split(const u32x4* __restrict__ x,
       const u32x4 d = x_scale[(int64_t)t * scale_vecs + v];
       for_rows([&]() { asm volatile("" ::"v"(d)); }, [&](int row) {
         if (v0 + lane < scale_vecs)
-          store_through_at(recv_scale, (int64_t)row * (scale_vecs * 16), v * 16, d);
+          store_row_at<HELD>(recv_scale, (int64_t)row * (scale_vecs * 16), v * 16, d);
       });
     }
     return;
@@ -184,7 +153,7 @@ __global__ __launch_bounds__(64) void k_pack_split(const u32x4* __restrict__ x,
 #pragma unroll
     for (int u = 0; u < U; ++u)
       if (EXACT || v0 + u * 64 < row_vecs)
-        store_through_at(recv, at, ((K > 0 ? v0 : lane) + u * 64) * 16, buf[u]);
+        store_row_at<HELD>(recv, at, ((K > 0 ? v0 : lane) + u * 64) * 16, buf[u]);
   });
 }
 
@@ -222,7 +191,7 @@ __global__ __launch_bounds__(64) void k_pack_multi(const u32x4* __restrict__ x,
       if (row < 0) continue;
       u32x4* dst = recv + (int64_t)row * row_vecs;
 #pragma unroll
-      for (int u = 0; u < U; ++u) store_through(&dst[u * 64 + lane], buf[q][u]);
+      for (int u = 0; u < U; ++u) store_row(&dst[u * 64 + lane], buf[q][u]);
     }
   }
 }
@@ -270,7 +239,7 @@ __global__ __launch_bounds__(kScaleThreads) void k_scale_rows(
   }
 #pragma unroll
   for (int u = 0; u < kScaleVecs; ++u)
-    if (pair[u] >= 0) store_through(&recv_scale[v0 + u * kScaleThreads], val[u]);
+    if (pair[u] >= 0) store_row(&recv_scale[v0 + u * kScaleThreads], val[u]);
 }
 
 // How a row of row_vecs 16-byte vectors is cut into passes of 64 * u vectors, and over how many
@@ -319,25 +288,31 @@ static PassShape pass_shape(int row_vecs, int split, int64_t rows, int max_vecs)
 
 template <int U, bool EXACT>
 static hipError_t launch_pack_t(eep_ctx* c, const int32_t* rows, const void* x, void* recv_x,
-                                int T, hipStream_t st) {
-  hipLaunchKernelGGL((k_pack<U, EXACT>), dim3(T), dim3(64), 0, st, (const u32x4*)x, rows, c->k,
-                     (int)(c->x_row_bytes / 16), (u32x4*)recv_x);
+                                int T, bool held, hipStream_t st) {
+  hipLaunchKernelGGL((held ? k_pack<U, EXACT, true> : k_pack<U, EXACT, false>), dim3(T), dim3(64), 0, st,
+                     (const u32x4*)x, rows, c->k, (int)(c->x_row_bytes / 16), (u32x4*)recv_x);
   return hipGetLastError();
+}
+
+template <int U, bool EXACT, bool SCALES, bool HELD>
+static auto pack_split_for(int k) {
+#define EEP_SPLIT(K) k_pack_split<U, EXACT, K, SCALES, HELD>
+  static const decltype(&EEP_SPLIT(0)) of[kSplitMaxK + 1] = {EEP_SPLIT(0), EEP_SPLIT(1), EEP_SPLIT(2),
+                                                             EEP_SPLIT(3), EEP_SPLIT(4), EEP_SPLIT(5),
+                                                             EEP_SPLIT(6), EEP_SPLIT(7), EEP_SPLIT(8)};
+#undef EEP_SPLIT
+  return of[k];
 }
 
 template <int U, bool EXACT, bool SCALES>
 static hipError_t launch_pack_split_t(eep_ctx* c, const int32_t* rows, const void* x,
                                       const float* x_scale, void* recv_x, float* recv_scale, int T,
-                                      int parts, hipStream_t st) {
-  static const decltype(&k_pack_split<U, EXACT, 0, SCALES>) of[kSplitMaxK + 1] = {
-      k_pack_split<U, EXACT, 0, SCALES>, k_pack_split<U, EXACT, 1, SCALES>,
-      k_pack_split<U, EXACT, 2, SCALES>, k_pack_split<U, EXACT, 3, SCALES>,
-      k_pack_split<U, EXACT, 4, SCALES>, k_pack_split<U, EXACT, 5, SCALES>,
-      k_pack_split<U, EXACT, 6, SCALES>, k_pack_split<U, EXACT, 7, SCALES>,
-      k_pack_split<U, EXACT, 8, SCALES>};
+                                      int parts, bool held, hipStream_t st) {
   const int64_t grid = (int64_t)T * parts;
   const bool compiled = c->k <= kSplitMaxK && c->x_row_bytes < (int64_t)1 << 32;  // (32-bit offsets there)
-  hipLaunchKernelGGL(of[compiled ? c->k : 0], dim3((unsigned)grid), dim3(64), 0, st,
+  const int k = compiled ? c->k : 0;
+  auto kern = held ? pack_split_for<U, EXACT, SCALES, true>(k) : pack_split_for<U, EXACT, SCALES, false>(k);
+  hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3(64), 0, st,
                      (const u32x4*)x, rows, c->k, (uint32_t)(c->x_row_bytes / 16), (uint32_t)parts,
                      part_magic(parts, grid), (u32x4*)recv_x, (const u32x4*)x_scale,
                      (u32x4*)recv_scale, (uint32_t)(c->scale_row_bytes / 16));
@@ -370,18 +345,29 @@ static int pack_tokens_per_wave(const PassShape& ps, int row_vecs, int T) {
   return tpw;
 }
 
+// Are a dispatch's stores held in the L2s (rows.hpp)?  Measured as whole steps in graphs of 4 (T = 32 to 8192, rows of 1 to
+// 14 KiB, top-1 to 8), the receive rows' MiB first, write-through's time over that of held stores.  Combine reads the receive
+// rows: top-8 4 0.97-0.99, 8 1.00-1.06, 16 1.00-1.05, 24 1.04-1.09, 28 1.04-1.07, 36 1.00-1.05, 44 0.98-1.04, 64 0.91-0.94; top-6 and
+// top-4 12 1.01-1.02, 24 1.03-1.05, 36 0.95-1.06; top-2 0.95-1.01 and top-1 0.90-0.99 at any size.  Another kernel writes what
+// combine reads: 8 0.95-0.98, 16 1.01-1.02, 24 1.00-1.01, 28 0.98-1.00, 36 0.97-0.99.  fp8 payloads, whose experts' rows
+// are twice as large: 2 0.99-1.01, 4 1.02, 8 1.01-1.03, 12 1.01-1.03, 16 0.97, 24 0.94.
+static bool pack_holds(const eep_ctx* c, int64_t T) {
+  const int64_t bytes = T * c->k * c->x_row_bytes;
+  return c->cfg.x_dtype == EEP_FP8_E4M3 ? mib_between(bytes, 4, 13) : c->k >= 4 && mib_between(bytes, 14, 26);
+}
+
 // (x_scale null: no scale rows, or not here)
 static hipError_t launch_pack_payload(eep_ctx* c, const int32_t* rows, const void* x,
                                       const float* x_scale, void* recv_x, float* recv_scale, int T,
-                                      hipStream_t st) {
+                                      bool held, hipStream_t st) {
   const int row_vecs = (int)(c->x_row_bytes / 16);
   const PassShape ps = pass_shape(row_vecs, pack_split(T), T, kPackVecs);
   if (x_scale != nullptr || ps.parts > 1) {
 #define EEP_PACK_SPLIT(U, SCALES)                                                                 \
   return ps.exact ? launch_pack_split_t<U, true, SCALES>(c, rows, x, x_scale, recv_x, recv_scale, \
-                                                         T, ps.parts + SCALES, st)                \
+                                                         T, ps.parts + SCALES, held, st)          \
                   : launch_pack_split_t<U, false, SCALES>(c, rows, x, x_scale, recv_x, recv_scale, \
-                                                          T, ps.parts + SCALES, st)
+                                                          T, ps.parts + SCALES, held, st)
     if (x_scale != nullptr) {
       if (ps.u == 1) EEP_PACK_SPLIT(1, true);
       EEP_PACK_SPLIT(2, true);
@@ -411,8 +397,8 @@ static hipError_t launch_pack_payload(eep_ctx* c, const int32_t* rows, const voi
   switch (ps.u) {
 #define EEP_PACK_CASE(U)                                                                \
   case U:                                                                               \
-    return ps.exact ? launch_pack_t<U, true>(c, rows, x, recv_x, T, st)                 \
-                    : launch_pack_t<U, false>(c, rows, x, recv_x, T, st);
+    return ps.exact ? launch_pack_t<U, true>(c, rows, x, recv_x, T, held, st)           \
+                    : launch_pack_t<U, false>(c, rows, x, recv_x, T, held, st);
     EEP_PACK_CASE(14) EEP_PACK_CASE(13) EEP_PACK_CASE(12) EEP_PACK_CASE(11) EEP_PACK_CASE(10)
     EEP_PACK_CASE(9) EEP_PACK_CASE(8) EEP_PACK_CASE(7) EEP_PACK_CASE(6) EEP_PACK_CASE(5)
     EEP_PACK_CASE(4) EEP_PACK_CASE(3) EEP_PACK_CASE(2) EEP_PACK_CASE(1)
@@ -423,14 +409,14 @@ static hipError_t launch_pack_payload(eep_ctx* c, const int32_t* rows, const voi
 
 static hipError_t launch_pack_any(eep_ctx* c, const int32_t* rows, const void* x,
                                   const float* x_scale, void* recv_x, float* recv_scale, int T,
-                                  hipStream_t st) {
+                                  bool held, hipStream_t st) {
   if (T == 0) return hipSuccess;
   // Small batches: the scale rows go with the payload, in wavefronts of their own.
   const bool together = x_scale != nullptr && T < kPackSplitBelow &&
                         pass_shape((int)(c->x_row_bytes / 16), pack_split(T), T, kPackVecs).u <= 2;
   hipError_t e = in_launches(T, max_blocks(64), [&](int64_t t0, int64_t n) {
     return launch_pack_payload(c, rows + t0 * c->k, (const char*)x + t0 * c->x_row_bytes,
-                               together ? x_scale : nullptr, recv_x, recv_scale, (int)n, st);
+                               together ? x_scale : nullptr, recv_x, recv_scale, (int)n, held, st);
   });
   if (e != hipSuccess || x_scale == nullptr || together) return e;
   const int scale_vecs = (int)(c->scale_row_bytes / 16);
@@ -448,12 +434,12 @@ static hipError_t launch_pack_any(eep_ctx* c, const int32_t* rows, const void* x
 
 hipError_t launch_pack(eep_ctx* c, const void* x, const float* x_scale, void* recv_x,
                        float* recv_scale, int T, hipStream_t st) {
-  return launch_pack_any(c, c->row_of, x, x_scale, recv_x, recv_scale, T, st);
+  return launch_pack_any(c, c->row_of, x, x_scale, recv_x, recv_scale, T, pack_holds(c, T), st);
 }
 
 hipError_t launch_pack_rows(eep_ctx* c, const int32_t* rows, const void* x, void* recv, int T,
                             hipStream_t st) {
-  return launch_pack_any(c, rows, x, nullptr, recv, nullptr, T, st);
+  return launch_pack_any(c, rows, x, nullptr, recv, nullptr, T, false, st);
 }
 
 // ---------------------------------------------------------------------------
@@ -472,7 +458,7 @@ hipError_t launch_pack_rows(eep_ctx* c, const int32_t* rows, const void* x, void
 constexpr int kExpandVecs = 7, kExpandManyVecs = 2, kExpandWideVecs = 8;
 constexpr int kExpandManyRows = 8192, kExpandWideRow = 16384 / 16;
 
-template <int U, bool EXACT>
+template <int U, bool EXACT, bool HELD>
 __global__ __launch_bounds__(64) void k_expand(const int32_t* __restrict__ expand_of,
                                                const u32x4* __restrict__ recv_d, int row_vecs,
                                                uint32_t parts, uint32_t magic,
@@ -493,7 +479,7 @@ __global__ __launch_bounds__(64) void k_expand(const int32_t* __restrict__ expan
     }
 #pragma unroll
     for (int u = 0; u < U; ++u)
-      if (EXACT || v0 + u * 64 < row_vecs) store_through(&dst[v0 + u * 64], buf[u]);
+      if (EXACT || v0 + u * 64 < row_vecs) store_row<HELD>(&dst[v0 + u * 64], buf[u]);
   }
 }
 
@@ -505,13 +491,16 @@ hipError_t launch_expand(eep_ctx* c, const void* recv_dedup, void* recv_x, int T
                                   rows < kExpandManyRows       ? kExpandVecs
                                   : row_vecs <= kExpandWideRow ? kExpandManyVecs
                                                                : kExpandWideVecs);
+  // Held stores (rows.hpp), by the receive rows' MiB, as above: 8 0.97-0.99, 16 1.05-1.10, 28 1.01-1.06, 36 1.00-1.03, 56 0.91-0.95.
+  const bool held = mib_between(rows * c->x_row_bytes, 12, 32);
   return in_launches(rows, max_blocks(64) / ps.parts, [&](int64_t r0, int64_t n) {
     const uint32_t magic = part_magic(ps.parts, n * ps.parts);
     u32x4* to = (u32x4*)recv_x + r0 * row_vecs;
     switch (ps.u) {
 #define EEP_EXPAND_CASE(U)                                                                     \
   case U:                                                                                      \
-    hipLaunchKernelGGL((ps.exact ? k_expand<U, true> : k_expand<U, false>),                    \
+    hipLaunchKernelGGL((held ? (ps.exact ? k_expand<U, true, true> : k_expand<U, false, true>)   \
+                             : (ps.exact ? k_expand<U, true, false> : k_expand<U, false, false>)), \
                        dim3((unsigned)(n * ps.parts)), dim3(64), 0, st, c->dd_expand + r0,     \
                        (const u32x4*)recv_dedup, row_vecs, (uint32_t)ps.parts, magic, to);     \
     return hipGetLastError();
@@ -614,7 +603,7 @@ __device__ __forceinline__ uint32_t quant4(const uint32_t (&d)[2], float scale, 
   return (uint32_t)__builtin_amdgcn_cvt_pk_fp8_f32(q[2], q[3], o, true);
 }
 
-template <int U>
+template <int U, bool HELD>
 __global__ __launch_bounds__(64) void k_pack_quant(const u32x4* __restrict__ x,
                                                    const int32_t* __restrict__ row_of, int k,
                                                    int out_vecs, uint32_t parts, uint32_t magic,
@@ -668,7 +657,7 @@ __global__ __launch_bounds__(64) void k_pack_quant(const u32x4* __restrict__ x,
 #pragma unroll
       for (int u = 0; u < U; ++u) {
         int w = w0 + u * 64 + lane;
-        if (w < out_vecs) store_through(&dst[w], q[u]);
+        if (w < out_vecs) store_row<HELD>(&dst[w], q[u]);
       }
     }
     if (__any(odd != 0)) {
@@ -699,7 +688,7 @@ __global__ __launch_bounds__(64) void k_pack_quant(const u32x4* __restrict__ x,
                  (f32_to_e4m3(v[4 * i + 2] / scale) << 16) |
                  (f32_to_e4m3(v[4 * i + 3] / scale) << 24);
         for (int j = 0; j < k; ++j)
-          if (rows[j] >= 0) store_through(&recv_q[(int64_t)rows[j] * out_vecs + w], o);
+          if (rows[j] >= 0) store_row(&recv_q[(int64_t)rows[j] * out_vecs + w], o);
       }
     }
     __syncthreads();
@@ -723,8 +712,11 @@ hipError_t launch_pack_quant(eep_ctx* c, const void* x_bf16, void* recv_q, float
   const int passes = (out_vecs + 63) / 64;
   const bool split = T < kQuantSplitBelow && (int64_t)T * passes <= max_blocks(64);
   const int parts = split ? passes : 1;
+  // Held stores (rows.hpp), by the codes' MiB, as for dispatch: 4 0.97, 8 1.04-1.06, 16 0.96, 24 0.93-0.95.
+  const bool held = mib_between((int64_t)T * c->k * c->H, 7, 12);
   return in_launches(T, max_blocks(64) / parts, [&](int64_t t0, int64_t n) {
-    hipLaunchKernelGGL((split ? k_pack_quant<1> : k_pack_quant<kQuantVecs>),
+    hipLaunchKernelGGL((held ? (split ? k_pack_quant<1, true> : k_pack_quant<kQuantVecs, true>)
+                             : (split ? k_pack_quant<1, false> : k_pack_quant<kQuantVecs, false>)),
                        dim3((unsigned)(n * parts)), dim3(64), 0, st,
                        (const u32x4*)x_bf16 + t0 * out_vecs * 2, c->row_of + t0 * c->k, c->k,
                        out_vecs, (uint32_t)parts, part_magic(parts, n * parts),
@@ -1101,7 +1093,7 @@ __global__ __launch_bounds__(256) void k_stub_copy(const u32x4* __restrict__ rec
   const int row = row0 + blockIdx.x;
   if (row >= status[0]) return;
   for (int v = threadIdx.x; v < row_vecs; v += blockDim.x)
-    store_through(&y[(int64_t)row * row_vecs + v],
+    store_row(&y[(int64_t)row * row_vecs + v],
                   __builtin_nontemporal_load(&recv[(int64_t)row * row_vecs + v]));
 }
 
@@ -1111,7 +1103,7 @@ __global__ __launch_bounds__(256) void k_stub_copy(const u32x4* __restrict__ rec
 // steps: 764 us against 771 with the row's loads after the lookups (8 steps of 2048 tokens,
 // 4096 channels), 11.05 against 11.55 (64 tokens, 2048 channels, top-4).  One wavefront per row or per
 // 64 to 512 vectors of one, with non-temporal stores: 787 to 793 (write-through 776), 11.2 to 11.9.
-template <bool BF16>
+template <bool BF16, bool HELD>
 __global__ __launch_bounds__(256) void k_stub_scale(
     const int32_t* __restrict__ src_of, const u32x4* __restrict__ recv, int row_vecs,
     const int32_t* __restrict__ slot_of, const int32_t* __restrict__ p2l,
@@ -1131,7 +1123,7 @@ __global__ __launch_bounds__(256) void k_stub_scale(
       if constexpr (BF16) o[i] = pack_bf16x2(s * bf16_lo(d[i]), s * bf16_hi(d[i]));
       else o[i] = __float_as_uint(s * __uint_as_float(d[i]));
     }
-    store_through(&y[base + v], o);
+    store_row<HELD>(&y[base + v], o);
     v += 256;
     if (v < row_vecs) d = __builtin_nontemporal_load(&recv[base + v]);
   }
@@ -1231,7 +1223,11 @@ hipError_t launch_stub(eep_ctx* c, int kind, const void* recv_x, const float* re
         hipLaunchKernelGGL(k_stub_copy, grid, block, 0, st, (const u32x4*)recv_x, (u32x4*)y,
                            c->status, row_vecs, (int)r0);
       } else {
-        auto kern = c->cfg.x_dtype == EEP_BF16 ? k_stub_scale<true> : k_stub_scale<false>;
+        // Held stores (rows.hpp), by the rows' MiB, as for dispatch: 4 0.96, 8 1.00-1.05, 12 1.07-1.10, 16 1.08-1.17, 24 1.10-1.12,
+        // 32 1.06-1.08, 36 1.03-1.05, 44 1.00, 52 0.98.
+        const bool held = mib_between(rows * c->x_row_bytes, 10, 36), bf16 = c->cfg.x_dtype == EEP_BF16;
+        auto kern = held ? (bf16 ? k_stub_scale<true, true> : k_stub_scale<false, true>)
+                         : (bf16 ? k_stub_scale<true, false> : k_stub_scale<false, false>);
         hipLaunchKernelGGL(kern, grid, block, 0, st, c->src_of + r0, (const u32x4*)recv_x + v0,
                            row_vecs, c->slot_of, c->p2l, expert_scale, (u32x4*)y + v0);
       }

@@ -1,0 +1,63 @@
+// Device code that every kernel which moves rows shares: pieces of rows, stores.
+#pragma once
+
+#include "eep_internal.hpp"
+
+namespace eep {
+
+typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+
+// Workgroup index -> (token, part) without a division in front of the first load: n / d is the
+// high word of n * magic, magic = 2^32 / d rounded up, exact while n * d < 2^32 (the rounding
+// is at most d too much).  Magic 0: one part, or a grid so large that it divides.
+inline uint32_t part_magic(int parts, int64_t grid) {
+  if (parts <= 1 || grid * parts >= ((int64_t)1 << 32)) return 0;
+  return (uint32_t)((((uint64_t)1 << 32) + parts - 1) / parts);
+}
+__device__ __forceinline__ uint32_t token_of(uint32_t n, uint32_t parts, uint32_t magic) {
+  return magic != 0 ? __umulhi(n, magic) : parts == 1 ? n : n / parts;
+}
+
+// Stores of receive rows and of what else one kernel writes and the next one reads, in one of two ways.  Write-through
+// (sc0 sc1): a line goes on to memory at once, and stays in the XCD's L2.  HELD (nt): it stays in the L2 until it is
+// evicted or the kernel ends, which writes it back.  With the eight L2s of 4 MiB in mind: what fits them is best held, since
+// the stores then end in the L2 and the write-back runs at its own pace; larger ones are evicted in the middle of the
+// kernel, line by line, and write-through is better; and of a few MB there is nothing to gain, but the write-back at
+// the end takes longer than stores that have long arrived.  The limits at the launches are measured.
+//
+// The data registers of a store of more than 8 bytes may not be rewritten by the next two
+// wait states' vector instructions.  The compiler keeps that distance for its own stores but
+// does not look into the asm, so the distance is part of it.
+template <bool HELD = false>
+__device__ __forceinline__ void store_row(u32x4* p, u32x4 v) {
+  if constexpr (HELD)
+    asm volatile("global_store_dwordx4 %0, %1, off nt\n\ts_nop 1" ::"v"(p), "v"(v) : "memory");
+  else
+    asm volatile("global_store_dwordx4 %0, %1, off sc0 sc1\n\ts_nop 1" ::"v"(p), "v"(v) : "memory");
+}
+
+// The same to `offset` bytes behind base + row, both scalar.  A vector memory instruction may not read
+// a scalar register within five wait states of a vector instruction that wrote it (v_readfirstlane, or
+// a spilled register's v_readlane); the compiler does not keep that distance for asm either, so
+// the address is added up by scalar instructions that are part of it.
+template <bool HELD>
+__device__ __forceinline__ void store_row_at(void* base, int64_t row, uint32_t offset, u32x4 v) {
+#define EEP_STORE_AT(HOW)                                                                                  \
+  asm volatile("s_add_u32 s98, %2, %4\n\ts_addc_u32 s99, %3, %5\n\t"                                       \
+               "global_store_dwordx4 %0, %1, s[98:99] " HOW "\n\ts_nop 1" ::"v"(offset), "v"(v),            \
+               "s"((uint32_t)(uintptr_t)base), "s"((uint32_t)((uintptr_t)base >> 32)), "s"((uint32_t)row), \
+               "s"((uint32_t)((uint64_t)row >> 32))                                                        \
+               : "memory", "scc", "s98", "s99")
+  if constexpr (HELD)
+    EEP_STORE_AT("nt");
+  else
+    EEP_STORE_AT("sc0 sc1");
+#undef EEP_STORE_AT
+}
+
+// Are `bytes` within [lo, hi] MiB?
+inline bool mib_between(int64_t bytes, int lo, int hi) {
+  return bytes >= (int64_t)lo << 20 && bytes <= (int64_t)hi << 20;
+}
+
+}  // namespace eep
