@@ -32,8 +32,8 @@ typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
 // ---------------------------------------------------------------------------
 constexpr int kPackVecs = 14;
 constexpr int kRowBatch = 8;  // row indices fetched together
-// Batches below this many tokens split a row over wavefronts, and below the second many in pieces
-// as narrow as combine's.  Counts of tokens, not of bytes: where they were checked (rows of 0.5, 1,
+// Batches below this many tokens split a row over wavefronts, and below the second many, and those of few bytes (pack_split),
+// in pieces as narrow as combine's.  Counts of tokens, where they were checked (rows of 0.5, 1,
 // 2, 4, 5.6, 8, 14 and 16 KiB and fp32 rows of 8 and 32 KiB, T = 32 to 4096, identity and scaling
 // experts) no step is more than 1 % slower than with 2 KiB pieces below 1024 tokens and 2 KiB parts
 // in combine, and most are faster.
@@ -259,7 +259,19 @@ __global__ __launch_bounds__(kScaleThreads) void k_scale_rows(
 // Measured on whole steps with rows that are no whole number of passes (bf16, 2880 channels,
 // 360 vectors; T = 32 / 256 / 2048): 26 / 30 / 52 us with a bounds check around each of 14
 // accesses and one wavefront per token at every T, 9.3 / 15.7 / 42.7 us in this form.
-static int pack_split(int T) { return T < kPackNarrowBelow ? 1 : T < kPackSplitBelow ? 2 : 0; }
+//
+// Larger batches of few bytes keep the pieces that combine reads too: the receive rows are then still in the L2s when it
+// does.  Measured as whole steps in graphs of 4, the time without over that with narrow pieces: combine reads the receive rows,
+// by their MiB, top-4 to 8 of 512 to 3072 tokens 8 1.04-1.08, 12 1.06-1.13, top-2 and 3 of up to 6 MiB of tokens 1.02-1.16, of
+// more 0.95-1.04, top-1 0.97-1.04, top-10 (run-time top-k) 0.94; with a kernel between that writes other rows for combine to read
+// 0.99-1.03, but 0.95-0.99 from 16 MiB on for top-4 to 8 (where the other gives 1.03-1.17).
+static int pack_split_of_tokens(int T) { return T < kPackNarrowBelow ? 1 : T < kPackSplitBelow ? 2 : 0; }
+static int pack_split(const eep_ctx* c, int T) {
+  const int64_t x_bytes = T * c->x_row_bytes;
+  const bool narrow = c->cfg.x_dtype != EEP_FP8_E4M3 && c->k >= 2 && c->k <= kSplitMaxK && x_bytes <= 6 << 20 &&
+                      (c->k < 4 || x_bytes * c->k <= 14 << 20);
+  return narrow ? 1 : pack_split_of_tokens(T);
+}
 struct PassShape {
   int u, parts;
   bool exact;
@@ -359,9 +371,9 @@ static bool pack_holds(const eep_ctx* c, int64_t T) {
 // (x_scale null: no scale rows, or not here)
 static hipError_t launch_pack_payload(eep_ctx* c, const int32_t* rows, const void* x,
                                       const float* x_scale, void* recv_x, float* recv_scale, int T,
-                                      bool held, hipStream_t st) {
+                                      int split, bool held, hipStream_t st) {
   const int row_vecs = (int)(c->x_row_bytes / 16);
-  const PassShape ps = pass_shape(row_vecs, pack_split(T), T, kPackVecs);
+  const PassShape ps = pass_shape(row_vecs, split, T, kPackVecs);
   if (x_scale != nullptr || ps.parts > 1) {
 #define EEP_PACK_SPLIT(U, SCALES)                                                                 \
   return ps.exact ? launch_pack_split_t<U, true, SCALES>(c, rows, x, x_scale, recv_x, recv_scale, \
@@ -409,14 +421,14 @@ static hipError_t launch_pack_payload(eep_ctx* c, const int32_t* rows, const voi
 
 static hipError_t launch_pack_any(eep_ctx* c, const int32_t* rows, const void* x,
                                   const float* x_scale, void* recv_x, float* recv_scale, int T,
-                                  bool held, hipStream_t st) {
+                                  int split, bool held, hipStream_t st) {
   if (T == 0) return hipSuccess;
   // Small batches: the scale rows go with the payload, in wavefronts of their own.
   const bool together = x_scale != nullptr && T < kPackSplitBelow &&
-                        pass_shape((int)(c->x_row_bytes / 16), pack_split(T), T, kPackVecs).u <= 2;
+                        pass_shape((int)(c->x_row_bytes / 16), split, T, kPackVecs).u <= 2;
   hipError_t e = in_launches(T, max_blocks(64), [&](int64_t t0, int64_t n) {
     return launch_pack_payload(c, rows + t0 * c->k, (const char*)x + t0 * c->x_row_bytes,
-                               together ? x_scale : nullptr, recv_x, recv_scale, (int)n, held, st);
+                               together ? x_scale : nullptr, recv_x, recv_scale, (int)n, split, held, st);
   });
   if (e != hipSuccess || x_scale == nullptr || together) return e;
   const int scale_vecs = (int)(c->scale_row_bytes / 16);
@@ -434,12 +446,12 @@ static hipError_t launch_pack_any(eep_ctx* c, const int32_t* rows, const void* x
 
 hipError_t launch_pack(eep_ctx* c, const void* x, const float* x_scale, void* recv_x,
                        float* recv_scale, int T, hipStream_t st) {
-  return launch_pack_any(c, c->row_of, x, x_scale, recv_x, recv_scale, T, pack_holds(c, T), st);
+  return launch_pack_any(c, c->row_of, x, x_scale, recv_x, recv_scale, T, pack_split(c, T), pack_holds(c, T), st);
 }
 
 hipError_t launch_pack_rows(eep_ctx* c, const int32_t* rows, const void* x, void* recv, int T,
                             hipStream_t st) {
-  return launch_pack_any(c, rows, x, nullptr, recv, nullptr, T, false, st);
+  return launch_pack_any(c, rows, x, nullptr, recv, nullptr, T, pack_split_of_tokens(T), false, st);
 }
 
 // ---------------------------------------------------------------------------
@@ -1023,7 +1035,7 @@ static hipError_t launch_combine_t(eep_ctx* c, const void* y, const float* w, vo
   int row_vecs = (int)(c->y_row_bytes / 16);
   int parts = (row_vecs + 63) / 64;
   // (y can be the receive buffer only if its rows are of the same size)
-  const PassShape packed = pass_shape(row_vecs, pack_split(T), T, kPackVecs);
+  const PassShape packed = pass_shape(row_vecs, pack_split(c, T), T, kPackVecs);
   const bool paired = c->x_row_bytes == c->y_row_bytes && parts > 1 &&
                       (parts + 1) / 2 == packed.parts && pack_tokens_per_wave(packed, row_vecs, T) == 1;
   if (paired) parts = packed.parts;
