@@ -152,6 +152,7 @@ void host_replica_lists(int P, int E, int S, int S_prim, const int32_t* p2l, int
 struct LayoutIO {
   int R, S, P, E, k, policy;
   bool mask_may_change;  // while the layout runs: other contexts, or nobody knows whose mask it is
+  bool can_agree;        // the words behind step_epoch are there
   const int32_t *topk_idx, *l2p_off, *l2p_list, *active, *tbl_version, *mem_version;
   int32_t *slot_of, *row_of, *src_of, *count, *offset, *rank_count, *rank_offset, *cnt_src, *status;
   // scratch: per-tile slot counts and prefixes [tiles][P], per-tile drop counters [tiles],

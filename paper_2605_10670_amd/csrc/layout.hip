@@ -773,8 +773,8 @@ __global__ __launch_bounds__(kMapThreads) void k_layout_small(
 //
 // Up to 512 tokens and 4096 pairs there are at most 8 workgroups, however many ranks.
 //
-// The workgroups' results fit together only if all of them saw one mask, see k_layout_small.  Launches are made for
-// an instance of one context, which keeps its mask still.  One captured then and replayed when there are more
+// The workgroups' results fit together only if all of them saw one mask, see k_layout_small.  An instance of one
+// context keeps its mask still.  A launch for an instance of several, or one captured before there were,
 // learns it from the word behind the membership version; its workgroups use the mask that the first one read
 // (agree_on), for a barrier and a round trip or two through memory more: T = 256 / 512 / 1024 / 2048
 // 5.3 / 5.5 / 6.1 / 7.1 us.  (All of it done by the first workgroup took 8.6 / 11.1 / 19.3 / 29.9, and 65 for 2048 tokens of
@@ -1665,13 +1665,18 @@ hipError_t launch_layout(const LayoutIO& c, int T, hipStream_t st) {
   }
   if (g.num_tiles > max_blocks(kMapThreads)) return hipErrorInvalidValue;
   const float inv_S = 1.0f / (float)c.S;
-  const bool solo = c.mask_may_change || writes_its_input(c, T);
+  const bool overlaps = writes_its_input(c, T), solo = c.mask_may_change || overlaps;
   const int small = layout_small_workgroups(c.E, c.P, c.R, T, c.k, solo);
-  const ShareSize share = share_size(c.E, c.P, c.R, g.tokens_per_rank, c.k, small);
+  // Several contexts: beyond what one workgroup does, k_layout_once with its workgroups' agreement on a mask is
+  // faster than tiles (32 ranks x 9 slots, a layout in a graph of 40; top-8, T = 416 / 512 / 1024 / 2048: 5.6 / 5.4 / 6.1 / 7.05 us,
+  // in tiles 7.75 / 7.5 / 7.7 / 7.8; top-2, T = 512 / 4096 4.8 / 5.85 (7.4 / 7.7); all tokens alike, T = 2048 7.65 (7.6)).
+  const bool agree = c.mask_may_change && c.can_agree && !overlaps && small == 0;
+  const ShareSize share = share_size(c.E, c.P, c.R, g.tokens_per_rank, c.k,
+                                     agree ? layout_small_workgroups(c.E, c.P, c.R, T, c.k, false) : small);
   const int tokens = share.tokens(g.tokens_per_rank);
   const bool has_k = c.k == 1 || c.k == 2 || c.k == 4 || c.k == 8;  // an instance of k_layout_small
   const bool few = small > 0 && has_k && T * c.k <= kFewPairs;
-  if (!solo && !few && c.k <= kOnceMaxK && (int64_t)T * c.k <= kOncePairs && c.P + kSinks <= kEntrySlots &&
+  if ((!solo || agree) && !few && c.k <= kOnceMaxK && (int64_t)T * c.k <= kOncePairs && c.P + kSinks <= kEntrySlots &&
       once_lds_bytes(c.E, c.P, c.R, tokens, c.k, share.subs > 1) <= kLayoutLdsLimit) {
     int nt = c.P > c.E ? c.P : c.E + 1;  // threads: for the tables, and for the tokens
     const int most = T > kOnceThreads ? kOnceThreads : kOnceThreads / 2;
@@ -1742,6 +1747,7 @@ hipError_t launch_layout(eep_ctx* c, const int32_t* topk_idx, int T, hipStream_t
   io.R = c->R; io.S = c->S; io.P = c->P; io.E = c->E; io.k = c->k; io.policy = c->cfg.policy;
   io.topk_idx = topk_idx;
   io.mask_may_change = c->mem->members.size() > 1;
+  io.can_agree = true;
   io.l2p_off = c->l2p_off; io.l2p_list = c->l2p_list; io.active = c->active;
   io.tbl_version = c->tbl_version; io.mem_version = c->mem->mem_version;
   io.slot_of = c->slot_of; io.row_of = c->row_of; io.src_of = c->src_of;

@@ -91,6 +91,7 @@ int eep_dispatch_layout_noalloc(const eep_layout_shape* shape, const int32_t* to
   io.R = R; io.S = S; io.P = P; io.E = E; io.k = k; io.policy = shape->policy;
   io.topk_idx = topk_idx;
   io.mask_may_change = true;  // `active` may be a live instance's
+  io.can_agree = false;
   io.l2p_off = l2p_off; io.l2p_list = l2p_list; io.active = active;
   // status[3] = *table_version, or 0 without one: the kernels add two words
   io.tbl_version = table_version ? table_version : base + kZeroWord;

@@ -1,6 +1,7 @@
 """Which form a layout takes when its mask may change while it runs: with several contexts in an
 instance, and without a context, one workgroup or tiles (each pair is mapped once), never the
-form in which eight workgroups map every pair for themselves."""
+form in which eight workgroups map every pair for themselves; beyond one workgroup, with several contexts,
+workgroups that agree on a mask first."""
 import numpy as np
 import pytest
 
