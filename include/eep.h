@@ -262,7 +262,9 @@ int64_t eep_noalloc_scratch_needed(int32_t num_ranks, int32_t slots_per_rank, in
  * recv_x: device [T*k, H] x_dtype; rows >= N are left untouched.  With fp8
  * payloads x_scale is device float[T, H/group] and recv_scale device
  * float[T*k, H/group], moved the same way; otherwise both are NULL.
- * Needs eep_dispatch_layout with the same T queued before it. */
+ * Needs eep_dispatch_layout with the same T queued before it.
+ * Captured right behind it on the same stream, the two may become one node of the graph,
+ * in the layout's place; what waits for the layout then waits for both. */
 int eep_dispatch(eep_ctx* ctx, const void* x, const float* x_scale, void* recv_x,
                  float* recv_scale, int32_t T, void* stream);
 

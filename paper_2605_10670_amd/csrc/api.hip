@@ -28,6 +28,56 @@ hipError_t set_shared_word(eep_membership* m, int32_t several) {
 
 bool aligned16(const void* p) { return ((uintptr_t)p & 15u) == 0; }
 
+bool overlap(const void* a, int64_t na, const void* b, int64_t nb) {
+  return a != nullptr && b != nullptr && (uintptr_t)a < (uintptr_t)b + nb && (uintptr_t)b < (uintptr_t)a + na;
+}
+
+// Is `st` being captured, and is one node all that what comes next in it waits for?
+bool captured_node(hipStream_t st, unsigned long long* capture, hipGraphNode_t* node) {
+  if (st == nullptr) return false;  // (cannot be captured)
+  hipStreamCaptureStatus status = hipStreamCaptureStatusNone;
+  const hipGraphNode_t* nodes = nullptr;
+  size_t n = 0;
+  if (hipStreamGetCaptureInfo_v2(st, &status, capture, nullptr, &nodes, &n) != hipSuccess) {
+    (void)hipGetLastError();
+    return false;
+  }
+  if (status != hipStreamCaptureStatusActive || n != 1) return false;
+  *node = nodes[0];
+  return true;
+}
+
+// A dispatch that is captured right behind its layout, with nothing else that waits for the layout, becomes part of the
+// layout's node, where there is a kernel for both: whatever the dispatch waits for, the layout waits for too, and so
+// nothing can tell the difference, but for the time.  Buffers that the two launches could share are refused: in one launch the
+// router indices are read while receive rows are written, and the layout's tables are written while tokens are read.
+bool dispatch_with_layout(eep_ctx* c, const int32_t* topk_idx, const void* x, const float* x_scale, void* recv_x,
+                          float* recv_scale, int T, hipStream_t st) {
+  unsigned long long capture;
+  hipGraphNode_t node;
+  size_t followers = 0;
+  PackPieces pieces;
+  if (topk_idx == nullptr || st != c->captured_on || !captured_node(st, &capture, &node) ||
+      capture != c->captured_in || node != c->captured_node)
+    return false;
+  if (hipGraphNodeGetDependentNodes(node, nullptr, &followers) != hipSuccess) {
+    (void)hipGetLastError();
+    return false;
+  }
+  const int64_t pairs = (int64_t)T * c->k;
+  const struct { const void* p; int64_t bytes; bool written; } buffers[] = {
+      {x, T * c->x_row_bytes, false}, {x_scale, T * c->scale_row_bytes, false},
+      {recv_x, pairs * c->x_row_bytes, true}, {recv_scale, pairs * c->scale_row_bytes, true}};
+  for (const auto& b : buffers)
+    if (overlap(b.p, b.bytes, c->slab, c->slab_bytes) || (b.written && overlap(b.p, b.bytes, topk_idx, pairs * 4)))
+      return false;
+  if (followers != 0 || !pack_pieces(c, x, x_scale, recv_x, recv_scale, T, &pieces) ||
+      !layout_pack_node(c, topk_idx, pieces, T, node))
+    return false;
+  c->dispatched_split = pieces.vecs <= 2 ? pieces.vecs : 0;
+  return true;
+}
+
 }  // namespace
 
 extern "C" {
@@ -95,6 +145,8 @@ int create_impl(const eep_config* cfg, eep_ctx* parent, void* workspace, int64_t
   c->out_row_bytes = (int64_t)c->H * dtype_bytes(f.out_dtype);
   c->scale_row_bytes = f.x_dtype == EEP_FP8_E4M3 ? (int64_t)(c->H / f.scale_group) * 4 : 0;
   c->layout_T = -1;
+  c->captured_idx = nullptr;
+  c->dispatched_split = -1;
   c->last_hip_error = 0;
   c->slab = nullptr;
   if (c->x_row_bytes % 16 || c->y_row_bytes % 16 || c->out_row_bytes % 16 ||
@@ -133,7 +185,8 @@ int create_impl(const eep_config* cfg, eep_ctx* parent, void* workspace, int64_t
   int64_t total = 0;
   for (int i = 0; i < EEP_V_NUM_FIELDS; ++i) total += round_up(n[i] > 0 ? n[i] : 1);
   const int64_t n_tile = (int64_t)c->max_tiles * c->P;
-  const int64_t n_epoch = kAgreeMask + 2 * mask_words(c->R);  // the step counter and what stands behind it
+  // the step counter and what stands behind it
+  const int64_t n_epoch = round_up(kAgreeMask + 2 * mask_words(c->R)) + kAgreeGroups * kAgreeGroupInts;
   total += 2 * round_up(n_tile) + 2 * round_up(c->max_tiles) + 4 * round_up(1) + round_up(n_epoch) +
            3 * round_up(c->R) + 4 * round_up(c->P);
   const int64_t n_dd_tile = (int64_t)c->max_tiles * c->R;
@@ -169,6 +222,7 @@ int create_impl(const eep_config* cfg, eep_ctx* parent, void* workspace, int64_t
     if (e != hipSuccess) { delete c; return EEP_ERR_HIP; }
     c->owns_slab = true;
   }
+  c->slab_bytes = total * (int64_t)sizeof(int32_t);
   int32_t* cur = (int32_t*)c->slab;
   for (int i = 0; i < EEP_V_NUM_FIELDS; ++i) {
     *field_ptr[i] = cur;
@@ -371,8 +425,13 @@ int eep_update_placement(eep_ctx* c, const int32_t* p2l_host, void* stream) {
 int eep_dispatch_layout(eep_ctx* c, const int32_t* topk_idx, int32_t T, void* stream) {
   if (!c || T < 0 || T > c->T_max || T % c->R != 0) return EEP_ERR_INVALID_ARG;
   if (T > 0 && !topk_idx) return EEP_ERR_INVALID_ARG;
-  hipError_t e = launch_layout(c, topk_idx, T, (hipStream_t)stream);
+  bool one_launch = false;
+  hipError_t e = launch_layout(c, topk_idx, T, (hipStream_t)stream, &one_launch);
   if (e != hipSuccess) return fail_hip(c, e);
+  c->captured_on = (hipStream_t)stream;
+  c->captured_idx =
+      one_launch && captured_node(c->captured_on, &c->captured_in, &c->captured_node) ? topk_idx : nullptr;
+  c->dispatched_split = -1;
   c->layout_T = T;
   c->dedup_T = -1;  // the de-duplicated tables belong to the previous layout
   return EEP_OK;
@@ -388,6 +447,9 @@ int eep_dispatch(eep_ctx* c, const void* x, const float* x_scale, void* recv_x, 
   if (fp8 != (x_scale != nullptr) || fp8 != (recv_scale != nullptr)) return EEP_ERR_INVALID_ARG;
   if (!aligned16(x) || !aligned16(recv_x) || !aligned16(x_scale) || !aligned16(recv_scale))
     return EEP_ERR_ALIGN;
+  const int32_t* captured_idx = c->captured_idx;
+  c->captured_idx = nullptr;
+  if (dispatch_with_layout(c, captured_idx, x, x_scale, recv_x, recv_scale, T, (hipStream_t)stream)) return EEP_OK;
   hipError_t e = launch_pack(c, x, x_scale, recv_x, recv_scale, T, (hipStream_t)stream);
   return e == hipSuccess ? EEP_OK : fail_hip(c, e);
 }

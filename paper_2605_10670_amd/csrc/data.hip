@@ -444,6 +444,31 @@ static hipError_t launch_pack_any(eep_ctx* c, const int32_t* rows, const void* x
   return hipGetLastError();
 }
 
+// With the layout in one launch the narrow pieces are the better ones up to larger sizes, also where another kernel writes what
+// combine reads (top-8, T = 1024 to 1536 of 1024 channels, 16 to 24 MiB of receive rows: 1.17-1.20 times as fast as two launches,
+// 1.09-1.12 with wider pieces; with a scaling stage 1.03-1.10 and 1.02-1.10), and so are held stores (the time with
+// write-through over that with them, combine reads the rows / another kernel writes others: 4 MiB 0.94-1.00 / 0.93-1.03, 8 0.97-1.05 /
+// 0.97-1.03, 12 1.00-1.08 / 0.97-1.01, 16 1.03-1.05 / 1.02-1.05, 24 1.02-1.10 / 1.01-1.05, 32 1.06-1.10 / 0.99-1.01, 36 1.06-1.09 / 1.00,
+// 44 0.98-1.06 / 1.00; fp8 2 0.99, 4 1.02-1.03, 8 1.02-1.05, 12 1.02-1.06, 16 0.99, 19 0.95).
+bool pack_pieces(const eep_ctx* c, const void* x, const float* x_scale, void* recv_x, float* recv_scale, int T,
+                 PackPieces* out) {
+  const int row_vecs = (int)(c->x_row_bytes / 16), scale_vecs = x_scale != nullptr ? (int)(c->scale_row_bytes / 16) : 0;
+  // (scale rows of larger batches are a launch of their own; a piece holds 64 vectors of one)
+  if (scale_vecs > 64 || (scale_vecs > 0 && T >= kPackSplitBelow) || c->x_row_bytes >= (int64_t)1 << 32) return false;
+  const int chunks = (row_vecs + 63) / 64;
+  const int64_t x_bytes = T * c->x_row_bytes;
+  int vecs = pack_split(c, T);
+  if (scale_vecs == 0 && c->k >= 2 && x_bytes <= 6 << 20 && x_bytes * c->k <= 36 << 20) vecs = 1;
+  if (vecs == 0) {  // (whole rows): as few parts as 7 vectors per lane allow
+    const int parts = (chunks + 6) / 7, even = (chunks + parts - 1) / parts;
+    vecs = even <= 2 ? even : even <= 4 ? 4 : 7;
+  }
+  const bool held = scale_vecs > 0 ? mib_between(x_bytes * c->k, 4, 13) : mib_between(x_bytes * c->k, 12, 36);
+  *out = {x, x_scale, recv_x, recv_scale, (uint32_t)row_vecs, (uint32_t)scale_vecs,
+          (uint32_t)((chunks + vecs - 1) / vecs + (scale_vecs > 0)), vecs, held};
+  return true;
+}
+
 hipError_t launch_pack(eep_ctx* c, const void* x, const float* x_scale, void* recv_x,
                        float* recv_scale, int T, hipStream_t st) {
   return launch_pack_any(c, c->row_of, x, x_scale, recv_x, recv_scale, T, pack_split(c, T), pack_holds(c, T), st);
@@ -1035,7 +1060,8 @@ static hipError_t launch_combine_t(eep_ctx* c, const void* y, const float* w, vo
   int row_vecs = (int)(c->y_row_bytes / 16);
   int parts = (row_vecs + 63) / 64;
   // (y can be the receive buffer only if its rows are of the same size)
-  const PassShape packed = pass_shape(row_vecs, pack_split(c, T), T, kPackVecs);
+  const int split = c->dispatched_split >= 0 ? c->dispatched_split : pack_split(c, T);
+  const PassShape packed = pass_shape(row_vecs, split, T, kPackVecs);
   const bool paired = c->x_row_bytes == c->y_row_bytes && parts > 1 &&
                       (parts + 1) / 2 == packed.parts && pack_tokens_per_wave(packed, row_vecs, T) == 1;
   if (paired) parts = packed.parts;

@@ -24,6 +24,9 @@ constexpr int kPatchParts = 3;  // arrays one update may patch together
 // Behind a context's step counter, for the workgroups of a layout launch that agree on a mask (k_layout_once):
 // how many of them have it, and the mask, 32 entries and a 1 to every 8 bytes.  All zero between launches.
 constexpr int kAgreeCount = 1, kAgreeMask = 2;
+// And behind these, for launches of many workgroups (SpreadAgreedMask), a place for every eighth of them, 256 bytes each.
+// (It begins there up to 992 ranks; those launches are for up to 64.)
+constexpr int kAgreeGroups = 8, kAgreeGroupInts = 64, kAgreeGroupsAt = 64;
 __host__ __device__ inline int mask_words(int R) { return (R + 31) / 32; }
 constexpr size_t kLayoutLdsLimit = 60 * 1024;  // the layout kernels keep their tables in LDS
 
@@ -99,6 +102,7 @@ struct eep_ctx {
   int max_tiles;
 
   void* slab;  // the one device allocation everything below points into
+  int64_t slab_bytes;
   bool owns_slab;  // false: the caller supplied it (eep_create_with_workspace)
   // tables (fixed addresses, contents patched in place)
   int32_t *active;  // == mem->active
@@ -135,6 +139,13 @@ struct eep_ctx {
   int n_staging;
   hipEvent_t ev_fork, ev_join;  // created on first use by eep_staging_fork
   int layout_T;  // T of the last dispatch_layout, -1 if none yet
+  // The node that the last dispatch_layout left in a capture and nothing has followed yet: its capture, stream and router
+  // indices (null: none).
+  const int32_t* captured_idx;
+  hipStream_t captured_on;
+  unsigned long long captured_in;
+  hipGraphNode_t captured_node;
+  int dispatched_split;  // how the last dispatch since then cut its rows (pack_split in data.hip), -1 if none
   int last_hip_error;
   int64_t field_ints[EEP_V_NUM_FIELDS];
 };
@@ -161,8 +172,23 @@ struct LayoutIO {
 };
 int layout_small_workgroups(int E, int P, int R, int T, int k, bool solo);
 bool layout_shape_fits(int E, int P, int R, int k);  // tables fit the kernels' LDS budget
-hipError_t launch_layout(const LayoutIO& io, int T, hipStream_t st);
-hipError_t launch_layout(eep_ctx* c, const int32_t* topk_idx, int T, hipStream_t st);
+// (*one_launch, if asked for: whether it was one)
+hipError_t launch_layout(const LayoutIO& io, int T, hipStream_t st, bool* one_launch = nullptr);
+hipError_t launch_layout(eep_ctx* c, const int32_t* topk_idx, int T, hipStream_t st, bool* one_launch);
+// A dispatch in pieces of `vecs` * 64 vectors of a row, `parts` to a token; for payloads with scales the last of these is
+// the scale row.  held: rows.hpp.
+struct PackPieces {
+  const void *x, *x_scale;
+  void *recv, *recv_scale;
+  uint32_t row_vecs, scale_vecs, parts;
+  int vecs;
+  bool held;
+};
+// Those of a dispatch that goes with its layout; false: it goes in a launch of its own.
+bool pack_pieces(const eep_ctx* c, const void* x, const float* x_scale, void* recv_x, float* recv_scale, int T,
+                 PackPieces* out);
+// Makes the captured node of a layout one of layout and dispatch, if there is a kernel for both.
+bool layout_pack_node(eep_ctx* c, const int32_t* topk_idx, PackPieces pk, int T, hipGraphNode_t node);
 hipError_t launch_check_layout(eep_ctx* c, int T, int32_t* bad /* device [4] */, hipStream_t st);
 // data.hip
 hipError_t launch_pack(eep_ctx* c, const void* x, const float* x_scale, void* recv_x,

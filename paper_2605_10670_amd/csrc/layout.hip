@@ -37,6 +37,7 @@
 #include <type_traits>
 
 #include "eep_internal.hpp"
+#include "rows.hpp"
 
 namespace eep {
 
@@ -905,6 +906,37 @@ __device__ __forceinline__ void count_together(int32_t* counts, int c) {
 }
 __device__ __forceinline__ bool same_in_all_lanes(int v) { return __all(v == __builtin_amdgcn_readfirstlane(v)); }
 
+// Adds a token's pairs, of experts e[] in slots p[], to the counts from `region` on.  TOGETHER: lanes that have an
+// expert in common are added by one of them.
+template <uint32_t K, bool TOGETHER>
+__device__ __forceinline__ void count_pairs(int32_t* s_cnt, uint32_t region, const int (&e)[K], const int (&p)[K]) {
+  const bool all = TOGETHER && same_in_all_lanes(e[0]) && same_in_all_lanes(e[K - 1]);
+  if (all) {
+#pragma unroll
+    for (uint32_t j = 0; j < K; ++j) count_together(s_cnt, region + p[j]);
+  } else {
+#pragma unroll
+    for (uint32_t j = 0; j < K; ++j) {
+      if (TOGETHER && same_in_all_lanes(e[j]))
+        count_together(s_cnt, region + p[j]);
+      else
+        atomicAdd(&s_cnt[region + p[j]], 1);
+    }
+  }
+}
+// Keeps the slots p[] of a share's token tl, and marks it in their bitmaps.
+template <uint32_t K>
+__device__ __forceinline__ void keep_pairs(uint32_t* s_bm, uint32_t stride, int32_t* s_slot, uint32_t tl,
+                                           const int (&p)[K]) {
+  uint32_t* bm = s_bm + (tl >> 5);
+  int32_t* to = s_slot + tl * K;
+  const uint32_t bit = 1u << (tl & 31);
+#pragma unroll
+  for (uint32_t j = 0; j < K; ++j) to[j] = p[j];
+#pragma unroll
+  for (uint32_t j = 0; j < K; ++j) atomicOr(&bm[__umul24(p[j], stride)], bit);
+}
+
 // Bits [lo, hi) of a bitmap, lo < hi.
 __device__ __forceinline__ int bits_between(const uint32_t* bm, int lo, int hi) {
   const int w0 = lo >> 5, w1 = (hi - 1) >> 5;
@@ -1045,37 +1077,12 @@ __global__ __launch_bounds__(kOnceThreads) void k_layout_once(
       map_token<K>(rt, s_entry, P, e, repeats, now, p);
       // counted in the token's region, and if the token is the share's own, kept
       const bool own = now >= lo && now < hi;
-      const auto count = [&](uint32_t region) {
-        const bool all = together.value && same_in_all_lanes(e[0]) && same_in_all_lanes(e[K - 1]);
-        if (all) {
-#pragma unroll
-          for (uint32_t j = 0; j < K; ++j) count_together(s_cnt, region + p[j]);
-        } else {
-#pragma unroll
-          for (uint32_t j = 0; j < K; ++j) {
-            if (together.value && same_in_all_lanes(e[j]))
-              count_together(s_cnt, region + p[j]);
-            else
-              atomicAdd(&s_cnt[region + p[j]], 1);
-          }
-        }
-      };
       uint32_t region = own ? P2 : now < lo ? 0 : 2 * P2;
       asm volatile("" : "+v"(region));  // (or the tokens of a share would take a branch of their own)
-      count(region);
-      if (PARTS && sub == 0 && now >= hi && now < rank_end) count(3 * P2);
-      if (own) {
-        const uint32_t tl = now - lo;
-        uint32_t* bm = s_bm + (tl >> 5);
-        int32_t* to = s_slot + tl * K;
-        const uint32_t bit = 1u << (tl & 31);
-#pragma unroll
-        for (uint32_t j = 0; j < K; ++j) to[j] = p[j];
-#pragma unroll
-        for (uint32_t j = 0; j < K; ++j) {
-          atomicOr(&bm[__umul24(p[j], stride)], bit);
-        }
-      }
+      count_pairs<K, decltype(together)::value>(s_cnt, region, e, p);
+      if (PARTS && sub == 0 && now >= hi && now < rank_end)
+        count_pairs<K, decltype(together)::value>(s_cnt, 3 * P2, e, p);
+      if (own) keep_pairs<K>(s_bm, stride, s_slot, now - lo, p);
       if (t >= 0) {
 #pragma unroll
         for (uint32_t j = 0; j < K; ++j) e[j] = next[j];
@@ -1157,6 +1164,333 @@ __global__ __launch_bounds__(kOnceThreads) void k_layout_once(
       __hip_atomic_store(agree.words + i, (uint64_t)0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     if (tid == 0) __hip_atomic_store(step_epoch + kAgreeCount, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   }
+}
+
+// ---------------------------------------------------------------------------
+// Layout and dispatch in ONE launch, for captured steps of up to 2048 tokens: eep_dispatch makes the node that its layout
+// left in the graph one of these (layout_pack_node).  Bound by latency: a launch of its own costs the dispatch 1.9 us and,
+// behind it, a round trip for the row indices and the tokens.  Here every workgroup lays the whole batch out for itself,
+// which all of them do at once, with its pieces of the tokens on their way meanwhile, and stores these as soon as it knows
+// their rows; the layout's results are written by whoever has them at hand: a token's by the wavefront of its first
+// piece, the pairs per source rank a rank to a workgroup.
+//
+// Measured, whole steps in graphs of 4 (32 ranks x 9 slots, top-8, bf16), in two launches and in one: 7168 channels, T = 32 / 96 /
+// 256 / 320 / 640 / 2048 10.0 / 13.6 / 22.1 / 23.0 / 34.5 / 84.4 us and 8.8 / 12.3 / 19.1 / 20.3 / 31.6 / 82.9; 2048 channels, T = 32 / 256 / 512 /
+// 1024 / 2048 8.95 / 12.0 / 15.4 / 24.4 / 32.1 and 7.9 / 10.4 / 13.1 / 18.3 / 31.1; fp8, 4096 channels, T = 128 / 448 / 960
+// 17.2 / 26.9 / 41.3 and 15.1 / 25.9 / 39.2; top-2, 2048 channels, T = 160 / 992 9.05 / 12.2 and 7.6 / 10.6.  Part of it is
+// that the receive rows are held in the L2s (rows.hpp) up to a larger size here, since all wavefronts store at once.
+// ---------------------------------------------------------------------------
+// The agreement on a mask, as in k_layout_once, for launches of hundreds of workgroups, up to 64 ranks: the first workgroup leaves the mask in eight places, one
+// for the workgroups of each XCD (kAgreeGroups, kAgreeGroupInts), which are counted there too.  (In one place the loads and the
+// counting come one after the other: a step with two contexts, 7168 channels, T = 32 / 256 / 640 10.6 / 21.1 / 38.9 us, 8.5 / 18.5 /
+// 32.6 in this form; with one context 7.9 / 17.6 / 30.8.)
+struct SpreadAgreedMask {
+  int32_t* groups;  // [kAgreeGroups][kAgreeGroupInts]: workgroups counted, groups counted (in the first one), mask words
+  bool several;
+  uint32_t* s_agreed;
+  __device__ __forceinline__ uint64_t* words(uint32_t group) const {
+    return (uint64_t*)(groups + group * kAgreeGroupInts + 2);
+  }
+  __device__ __forceinline__ uint64_t operator()(uint64_t mask) const {
+    if (!several) return mask;
+    const uint32_t tid = threadIdx.x, word = tid & 1;
+    const uint64_t mine = (uint64_t)1 << 32 | (uint32_t)(mask >> (word * 32));
+    if (blockIdx.x == 0) {
+      if (tid < 2 * kAgreeGroups) {
+        __hip_atomic_store(words(tid >> 1) + word, mine, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        __builtin_amdgcn_s_waitcnt(0x0f70);  // vmcnt(0): it is there before this workgroup counts itself
+      }
+      return mask;
+    }
+    if (tid < 2) {
+      uint64_t v = mine;  // (after the bound, as in agree_on)
+      for (int polls = 0; polls < kAgreePolls; ++polls) {
+        v = __hip_atomic_load(words(blockIdx.x & (kAgreeGroups - 1)) + word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        if (v >> 32 != 0) break;
+        __builtin_amdgcn_s_sleep(1);
+      }
+      s_agreed[tid] = (uint32_t)(v >> 32 != 0 ? v : mine);
+    }
+    __syncthreads();
+    return (uint64_t)s_agreed[1] << 32 | s_agreed[0];
+  }
+  __device__ __forceinline__ void operator()(uint32_t*) const {}  // (more than 64 ranks: not here)
+  // Thread 0, once the workgroup has the mask.  The last one of the last group: true.
+  __device__ __forceinline__ bool arrive_last() const {
+    const uint32_t group = blockIdx.x & (kAgreeGroups - 1);
+    const int size = (int)(gridDim.x / kAgreeGroups);
+    if (__hip_atomic_fetch_add(groups + group * kAgreeGroupInts, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != size - 1)
+      return false;
+    return __hip_atomic_fetch_add(groups + 1, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == kAgreeGroups - 1;
+  }
+  // Zeros again for the next launch, by one wavefront of the workgroup that was the last.
+  __device__ __forceinline__ void clear() const {
+    const uint32_t lane = threadIdx.x & 63, group = lane >> 3, word = lane & 7;
+    if (word < 6)
+      __hip_atomic_store(groups + group * kAgreeGroupInts + word, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  }
+};
+
+// The piece of a wavefront of a launch that moves rows, see PackPieces: of token t, `vecs` vectors of a row of the
+// payload or of the scales, the lane's from v on.
+struct Piece {
+  uint32_t t, part, v, vecs;
+  bool any, scales;
+};
+// Pieces, counted token by token, go to the XCDs in turn as the workgroups do: workgroup b takes every eighth one from
+// b mod 8 on, one to each of its first `waves` wavefronts.
+__device__ __forceinline__ uint32_t piece_token(uint32_t wave, uint32_t waves, uint32_t parts, uint32_t magic) {
+  return token_of((((blockIdx.x >> 3) * waves + wave) << 3) + (blockIdx.x & 7), parts, magic);
+}
+template <uint32_t U>
+__device__ __forceinline__ Piece piece_of(uint32_t wave, uint32_t waves, uint32_t T, uint32_t parts, uint32_t magic,
+                                          uint32_t row_vecs, uint32_t scale_vecs) {
+  const uint32_t m = (((blockIdx.x >> 3) * waves + wave) << 3) + (blockIdx.x & 7), lane = threadIdx.x & 63;
+  Piece p;
+  p.t = token_of(m, parts, magic);
+  p.part = m - p.t * parts;
+  p.any = wave < waves && p.t < T;
+  p.scales = scale_vecs > 0 && p.part == parts - 1;
+  p.v = p.scales ? lane : p.part * (64 * U) + lane;
+  p.vecs = p.scales ? scale_vecs : row_vecs;
+  return p;
+}
+template <uint32_t U>
+__device__ __forceinline__ void load_piece(const Piece& pc, const u32x4* x, const u32x4* x_scale, u32x4 (&d)[U]) {
+  if (!pc.any) return;
+  const u32x4* src = (pc.scales ? x_scale : x) + (int64_t)pc.t * pc.vecs;
+#pragma unroll
+  for (uint32_t u = 0; u < U; ++u) d[u] = __builtin_nontemporal_load(&src[min(pc.v + u * 64, pc.vecs - 1)]);
+}
+// Stores the piece to the token's K rows, lane j's `row` for pair j (-1: none).
+template <uint32_t K, uint32_t U>
+__device__ __forceinline__ void store_piece(const Piece& pc, int row, const u32x4 (&d)[U], u32x4* recv,
+                                            u32x4* recv_scale, bool held) {
+  u32x4* to = pc.scales ? recv_scale : recv;
+  int r[K];
+#pragma unroll
+  for (uint32_t j = 0; j < K; ++j) r[j] = __builtin_amdgcn_readlane(row, j);
+#pragma unroll
+  for (uint32_t u = 0; u < U; ++u) asm volatile("" ::"v"(d[u]));
+  const auto stores = [&](auto h) {
+#pragma unroll
+    for (uint32_t j = 0; j < K; ++j) {
+      if (r[j] < 0) continue;
+#pragma unroll
+      for (uint32_t u = 0; u < U; ++u)
+        if (pc.v + u * 64 < pc.vecs)
+          store_row_at<decltype(h)::value>(to, (int64_t)r[j] * (pc.vecs * 16), (pc.v + u * 64) * 16, d[u]);
+    }
+  };
+  if (held)
+    stores(std::true_type());
+  else
+    stores(std::false_type());
+}
+
+// Few pairs, built like k_layout_small.  T_waves: T, and << 16 the wavefronts with a piece, and << 31 `held`.
+template <int K>
+__global__ __launch_bounds__(kMapThreads) void k_layout_pack_small(
+    const int32_t* __restrict__ topk_idx, const int32_t* __restrict__ l2p_off,
+    const int32_t* __restrict__ l2p_list, const int32_t* __restrict__ active,
+    const int32_t* __restrict__ mem_version, uint32_t T_waves, int E, int P, int R,
+    const u32x4* __restrict__ x, uint32_t row_vecs, uint32_t parts, uint32_t magic,
+    const u32x4* __restrict__ x_scale, uint32_t scale_vecs, float inv_S, int policy, int tokens_per_rank, int S,
+    u32x4* __restrict__ recv, u32x4* __restrict__ recv_scale, const int32_t* __restrict__ tbl_version,
+    int32_t* __restrict__ slot_of, int32_t* __restrict__ row_of, int32_t* __restrict__ src_of,
+    int32_t* __restrict__ count, int32_t* __restrict__ offset, int32_t* __restrict__ rank_count,
+    int32_t* __restrict__ rank_offset, int32_t* __restrict__ cnt_src,
+    int32_t* __restrict__ status, int32_t* __restrict__ step_epoch) {
+  const int T = T_waves & 0xffff, waves = T_waves >> 16 & 31;
+  const bool held = T_waves >> 31 != 0;
+  const int npairs = T * K;
+  const int stride = token_stride(T);
+  extern __shared__ int32_t smem[];
+  int32_t* s_count = smem;                        // [P] pairs per slot
+  uint32_t* s_bm = (uint32_t*)(s_count + P);      // [P][stride] token bitmap per slot
+  int32_t* s_offset = (int32_t*)(s_bm + P * stride);  // [P+1] exclusive scan of s_count
+  int32_t* s_slot = s_offset + P + 1;             // [T*K] slots of the pairs
+  int32_t* s_tab = s_slot + npairs;
+  __shared__ int32_t s_drop[2];
+  __shared__ uint32_t s_agreed[2];
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+
+  // every global read of this kernel is issued here, none depends on another
+  int my_e[1], slot[1];
+  my_e[0] = tid < npairs ? topk_idx[tid] : -1;
+  const int version = blockIdx.x == 0 && tid == 0 ? *tbl_version + *mem_version : 0;
+  const int several_v = vector_load(&mem_version[1]);  // several contexts in the instance
+  RouteTableLoad<false> tables = {l2p_off, l2p_list, active, E, R, P, kMapThreads};
+  tables.fetch();
+  const Piece pc = piece_of<1>(wave, waves, T, parts, magic, row_vecs, scale_vecs);
+  u32x4 d[1];
+  load_piece(pc, x, x_scale, d);
+#pragma nounroll
+  for (int i = tid; i < P * (stride + 1); i += kMapThreads) s_count[i] = 0;  // and s_bm
+  if (tid < 2) s_drop[tid] = 0;
+  const SpreadAgreedMask agree = {step_epoch + kAgreeGroupsAt, __builtin_amdgcn_readfirstlane(several_v) != 0, s_agreed};
+  const RouteTables rt = tables.fill(s_tab, inv_S, agree);
+  bool last = false;  // of the workgroups to have the mask (thread 0)
+  if (agree.several && tid == 0) last = agree.arrive_last();
+  __syncthreads();
+  map_pairs<K, 1>(rt, my_e, s_slot, slot, s_bm, stride, s_count, s_drop, npairs, K, E, 0, policy, 0, 0, slot_of);
+  if (tid < npairs) s_slot[tid] = slot[0];
+  __syncthreads();
+  scan_totals([=](int p) { return s_count[p]; }, s_offset, P, wave, kMapThreads / 64);
+  __syncthreads();
+
+  const int N = s_offset[P];
+  if (pc.any) {
+    const int i = pc.t * K + (lane < K ? lane : K - 1);
+    const int p = s_slot[i];
+    const int row = p >= 0 ? s_offset[p] + rank_in_slot(&s_bm[p * stride], pc.t) : -1;
+    store_piece<K>(pc, row, d, recv, recv_scale, held);
+    if (pc.part == 0 && lane < K) {
+      slot_of[i] = p;
+      row_of[i] = row;
+      if (p >= 0) src_of[row] = i;
+      if (i >= N) src_of[i] = -1;  // rows past the last routed pair
+    }
+  }
+  // pairs per (source rank, slot): the tokens of a source rank are a bit range
+  for (int b = wave * gridDim.x + blockIdx.x; b < R; b += gridDim.x * (kMapThreads / 64)) {
+    const int lo = b * tokens_per_rank, hi = lo + tokens_per_rank;
+    int32_t* cnt = cnt_src + (int64_t)b * P;
+    if (P <= 64)
+      store_src_counts<1>(s_bm, stride, 0, P, lo, hi, cnt);
+    else
+      for (int p0 = 0; p0 < P; p0 += 320) store_src_counts<5>(s_bm, stride, p0, P, lo, hi, cnt);
+  }
+  if (blockIdx.x == 0)
+    write_step_tables(kMapThreads, s_offset, s_drop[0], s_drop[1], version, count, offset, rank_count,
+                      rank_offset, status, step_epoch, R, S, P);
+  if (agree.several && wave == 0 && __builtin_amdgcn_readfirstlane(last)) agree.clear();
+}
+
+// More pairs, built like k_layout_once: a workgroup's share are the tokens that its pieces belong to, at most `window`,
+// and for the pairs per source rank workgroup b counts rank b's beside it.  Words: T and tokens per
+// rank; E and P; R and S << 12; `window`, policy << 12, wavefronts << 13, those with a piece << 18, `held` << 31.
+template <uint32_t K, uint32_t U>
+__global__ __launch_bounds__(kOnceThreads) void k_layout_pack_once(
+    const int32_t* __restrict__ topk_idx, const int32_t* __restrict__ l2p_off,
+    const int32_t* __restrict__ l2p_list, const int32_t* __restrict__ active,
+    const int32_t* __restrict__ mem_version, uint32_t T_rank, uint32_t E_P, uint32_t R_S, uint32_t window_waves,
+    const u32x4* __restrict__ x, uint32_t row_vecs, uint32_t parts, uint32_t magic,
+    const u32x4* __restrict__ x_scale, uint32_t scale_vecs, u32x4* __restrict__ recv,
+    u32x4* __restrict__ recv_scale, const int32_t* __restrict__ tbl_version, int32_t* __restrict__ slot_of,
+    int32_t* __restrict__ row_of, int32_t* __restrict__ src_of, int32_t* __restrict__ cnt_src,
+    int32_t* __restrict__ count, int32_t* __restrict__ offset, int32_t* __restrict__ rank_count,
+    int32_t* __restrict__ rank_offset, int32_t* __restrict__ status,
+    int32_t* __restrict__ step_epoch) {
+  const uint32_t T = T_rank & 0xffff, tokens_per_rank = T_rank >> 16;
+  const uint32_t E = E_P & 0xffff, P = E_P >> 16, P2 = P + kSinks;
+  const uint32_t R = R_S & 0xfff, S = R_S >> 12;
+  const uint32_t window = window_waves & 0xfff, policy = window_waves >> 12 & 1;
+  const uint32_t waves = window_waves >> 13 & 31, nt = waves * 64, moving = window_waves >> 18 & 31;
+  const uint32_t tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const auto load = [&](uint32_t t, int (&e)[K]) { __builtin_memcpy(e, &at(topk_idx, t * K), sizeof(e)); };
+  // From the batch's last tokens, which the last threads take, to its first: the first threads have the tables to do.
+  int t = (int)(T + tid) - (int)nt;
+  int e[K];
+  load(max(t, 0), e);
+  RouteTableLoad<false> tables = {l2p_off, l2p_list, active, (int)E, (int)R, (int)P, (int)nt};
+  tables.fetch();
+  const int several_v = vector_load(&mem_version[1]);  // several contexts in the instance
+  const Piece pc = piece_of<U>(wave, moving, T, parts, magic, row_vecs, scale_vecs);
+  u32x4 d[U];
+  load_piece(pc, x, x_scale, d);
+
+  extern __shared__ __align__(16) int32_t smem[];
+  const uint32_t stride = token_stride(window);
+  const uint32_t zeros = once_zeros(P, stride, true);
+  int32_t* const s_cnt = smem;                                      // [regions][P2] pairs per slot
+  uint32_t* const s_bm = (uint32_t*)(s_cnt + regions(true) * P2);   // [P2][stride] bitmap of the share's tokens per slot
+  int32_t* const s_tab = smem + zeros;
+  uint32_t* const s_entry = (uint32_t*)(s_tab + route_table_ints(E, P, R));  // [E+kNoneSinks]
+  int32_t* const s_offset = (int32_t*)s_entry + E + kNoneSinks;     // [P2+1] exclusive scan of the totals
+  int32_t* const s_slot = s_offset + P2 + 1;                        // [window*K] slots of the share's pairs
+  __shared__ uint32_t s_agreed[2];
+#pragma nounroll
+  for (uint32_t i = tid * 4; i < zeros; i += nt * 4) *(int4*)(smem + i) = make_int4(0, 0, 0, 0);
+  const SpreadAgreedMask agree = {step_epoch + kAgreeGroupsAt, __builtin_amdgcn_readfirstlane(several_v) != 0, s_agreed};
+  const RouteTables rt = tables.fill(s_tab, __builtin_amdgcn_rcpf((float)S), agree);
+  bool last = false;  // of the workgroups to have the mask (thread 0)
+  if (agree.several && tid == 0) last = agree.arrive_last();
+  const uint32_t lo = min(piece_token(0, moving, parts, magic), T);
+  const uint32_t hi = min(piece_token(moving - 1, moving, parts, magic) + 1, T);
+  const uint32_t rank_lo = blockIdx.x * tokens_per_rank, rank_hi = rank_lo + tokens_per_rank;  // (beyond T: none)
+  __syncthreads();
+  build_entries<false>(rt, s_entry, E, P, policy, nt);
+  const bool copies = K > 1 && (same_in_all_lanes(e[0]) || same_in_all_lanes(e[K - 1]));  // see k_layout_once
+  const uint32_t none = E + (tid & (kNoneLanes - 1));
+  if constexpr (K > 1) entries_of(e, none);
+  bool repeats = any_repeats(e);
+  __syncthreads();
+  const auto count_tokens = [&](auto together) {
+#pragma nounroll
+    while (t >= 0) {
+      const uint32_t now = t;
+      t -= nt;
+      int next[K];
+      if (t >= 0) load(t, next);
+      int p[K];
+      if constexpr (K == 1) entries_of(e, none);  // (here it needs no branch)
+      map_token<K>(rt, s_entry, P, e, repeats, now, p);
+      const bool own = now >= lo && now < hi;
+      uint32_t region = own ? P2 : now < lo ? 0 : 2 * P2;
+      asm volatile("" : "+v"(region));  // (or the tokens of a share would take a branch of their own)
+      count_pairs<K, decltype(together)::value>(s_cnt, region, e, p);
+      if (now >= rank_lo && now < rank_hi) count_pairs<K, decltype(together)::value>(s_cnt, 3 * P2, e, p);
+      if (own) keep_pairs<K>(s_bm, stride, s_slot, now - lo, p);
+      if (t >= 0) {
+#pragma unroll
+        for (uint32_t j = 0; j < K; ++j) e[j] = next[j];
+        if constexpr (K > 1) {
+          entries_of(e, none);
+          repeats = any_repeats(e);
+        }
+      }
+    }
+  };
+  if (__builtin_expect(copies, 0))
+    count_tokens(std::true_type());
+  else
+    count_tokens(std::false_type());
+  __syncthreads();
+  // Between two barriers: the scan, and what does not need it.
+  const auto total = [=](uint32_t p) { return s_cnt[p] + s_cnt[P2 + p] + s_cnt[2 * P2 + p]; };
+  scan_totals(total, s_offset, P2, wave, waves);
+  const int version = blockIdx.x == 0 ? vector_load(tbl_version) + vector_load(mem_version) : 0;
+  const uint32_t j = lane < K ? lane : K - 1;
+  uint32_t p = P;
+  int row = -1;
+  if (pc.any) {  // slot of the token's pair j, its row less the slot's offset
+    const uint32_t tl = pc.t - lo;
+    p = s_slot[tl * K + j];
+    row = s_cnt[p] + rank_in_slot(&s_bm[p * stride], tl);
+  }
+  __syncthreads();
+  const int rows = s_offset[P];
+  if (pc.any) {
+    row = p < P ? row + s_offset[p] : -1;
+    store_piece<K>(pc, row, d, recv, recv_scale, window_waves >> 31 != 0);
+    if (pc.part == 0 && lane < K) {
+      const uint32_t g = pc.t * K + j;
+      at(slot_of, g) = p < P ? (int)p : -1;
+      at(row_of, g) = row;
+      if (p < P) at(src_of, row) = g;
+      if ((int)g >= rows) at(src_of, g) = -1;  // rows past the last routed pair
+    }
+  }
+  if (blockIdx.x < R) {
+#pragma nounroll
+    for (uint32_t q = tid; q < P; q += nt) at(cnt_src, blockIdx.x * P + q) = s_cnt[3 * P2 + q];
+  }
+  if (blockIdx.x == 0)
+    write_step_tables(nt, s_offset, s_offset[P + kDeadSinks] - rows, s_offset[P2] - s_offset[P + kDeadSinks], version,
+                      count, offset, rank_count, rank_offset, status, step_epoch, R, S, P);
+  if (agree.several && wave == 0 && __builtin_amdgcn_readfirstlane(last)) agree.clear();
 }
 
 // What a share holds: source ranks, or a part of one.
@@ -1654,9 +1988,10 @@ int layout_small_workgroups(int E, int P, int R, int T, int k, bool solo) {
   return solo ? 1 : kSmallBlocks;
 }
 
-hipError_t launch_layout(const LayoutIO& c, int T, hipStream_t st) {
+hipError_t launch_layout(const LayoutIO& c, int T, hipStream_t st, bool* one_launch) {
   Tiling g = make_tiling(T, c.R);
   const bool k8 = c.k == 8;
+  if (one_launch != nullptr) *one_launch = true;
   if (g.num_tiles == 0) {
     hipLaunchKernelGGL(k_empty_step, dim3(1), dim3(256), 0, st, c.tbl_version, c.mem_version,
                        c.count, c.offset, c.rank_count, c.rank_offset, c.cnt_src, c.status,
@@ -1705,6 +2040,7 @@ hipError_t launch_layout(const LayoutIO& c, int T, hipStream_t st) {
                        c.rank_offset, c.cnt_src, c.status, c.step_epoch);
     return hipGetLastError();
   }
+  if (one_launch != nullptr) *one_launch = false;
   {
     size_t lds = sizeof(int32_t) * map_lds_ints(c.E, c.P, c.R, g.tile_tokens, c.k);
     auto kern = large_tables(c.E, c.P, c.R, kMapThreads) ? map_count_for<true>(c.k, g.tile_tokens * c.k) : map_count_for<false>(c.k, g.tile_tokens * c.k);
@@ -1742,7 +2078,7 @@ hipError_t launch_layout(const LayoutIO& c, int T, hipStream_t st) {
   return hipGetLastError();
 }
 
-hipError_t launch_layout(eep_ctx* c, const int32_t* topk_idx, int T, hipStream_t st) {
+static LayoutIO layout_io(eep_ctx* c, const int32_t* topk_idx) {
   LayoutIO io;
   io.R = c->R; io.S = c->S; io.P = c->P; io.E = c->E; io.k = c->k; io.policy = c->cfg.policy;
   io.topk_idx = topk_idx;
@@ -1755,7 +2091,89 @@ hipError_t launch_layout(eep_ctx* c, const int32_t* topk_idx, int T, hipStream_t
   io.rank_offset = c->rank_offset; io.cnt_src = c->cnt_src; io.status = c->status;
   io.cnt_tile = c->cnt_tile; io.base_tile = c->base_tile; io.blk_unc = c->blk_unc;
   io.blk_msk = c->blk_msk; io.step_epoch = c->step_epoch;
-  return launch_layout(io, T, st);
+  return io;
+}
+
+hipError_t launch_layout(eep_ctx* c, const int32_t* topk_idx, int T, hipStream_t st, bool* one_launch) {
+  return launch_layout(layout_io(c, topk_idx), T, st, one_launch);
+}
+
+static bool set_node(hipGraphNode_t node, const void* kernel, int grid, int threads, size_t lds, void** args) {
+  hipKernelNodeParams p = {};
+  p.func = const_cast<void*>(kernel);
+  p.gridDim = dim3((unsigned)grid);
+  p.blockDim = dim3((unsigned)threads);
+  p.sharedMemBytes = (unsigned)lds;
+  p.kernelParams = args;
+  if (hipGraphKernelNodeSetParams(node, &p) == hipSuccess) return true;
+  (void)hipGetLastError();
+  return false;
+}
+
+template <uint32_t U>
+static const void* layout_pack_once_for(int k) {
+  static const decltype(&k_layout_pack_once<1, U>) of[kOnceMaxK] = {
+      k_layout_pack_once<1, U>, k_layout_pack_once<2, U>, k_layout_pack_once<3, U>, k_layout_pack_once<4, U>,
+      k_layout_pack_once<5, U>, k_layout_pack_once<6, U>, k_layout_pack_once<7, U>, k_layout_pack_once<8, U>,
+      k_layout_pack_once<9, U>, k_layout_pack_once<10, U>};
+  return (const void*)of[k - 1];
+}
+
+// How many pieces a workgroup takes.  More pieces than 8 wavefronts of every CU make further rounds of workgroups, which are
+// resident together up to three (the top-8 kernel has 69 registers), and in these all CUs are to get the same: with 16
+// wavefronts in 280 workgroups 320 tokens of 7168 channels took 25.6 us a step, with 10 in 448 21.9, with 6 in 752 21.7, with 9 in
+// 504 21.6.  Beyond three rounds (768 pieces to an XCD; 896 tokens of 7168 channels) two launches are as fast.
+constexpr int kLayoutPackTokens = 2048, kXcdCus = 32, kPieceWaves = 8, kPieceRounds = 3;
+
+bool layout_pack_node(eep_ctx* ctx, const int32_t* topk_idx, PackPieces pk, int T, hipGraphNode_t node) {
+  LayoutIO io = layout_io(ctx, topk_idx);
+  const Tiling g = make_tiling(T, io.R);
+  if (T < 1 || T > kLayoutPackTokens || io.k > kOnceMaxK || T * io.k > kOncePairs || io.P + kSinks > kEntrySlots ||
+      writes_its_input(io, T))
+    return false;
+  const int pieces = (int)((T * (int64_t)pk.parts + 7) / 8);  // of an XCD
+  if (pieces > kXcdCus * kPieceWaves * kPieceRounds) return false;
+  // As k_layout_small up to the same size for top-4 and 8 (7168 channels, top-8, T = 32 / 96: 8.75 / 12.3 us, as k_layout_once
+  // 9.0 / 12.6; for top-1 and 2 the latter is faster: T = 32 7.7 and 7.5); its workgroups have 16 wavefronts.
+  const bool few = (io.k == 4 || io.k == 8) && T * io.k <= kFewPairs && pk.vecs == 1 && pieces <= kXcdCus * 16 &&
+                   !large_tables(io.E, io.P, io.R, kMapThreads) &&
+                   small_lds_bytes(io.E, io.P, io.R, T, io.k) <= kLayoutLdsLimit;
+  const int rounds = few ? 1 : (pieces + kXcdCus * kPieceWaves - 1) / (kXcdCus * kPieceWaves);
+  const int waves = (pieces + kXcdCus * rounds - 1) / (kXcdCus * rounds);
+  int grid = (pieces + waves - 1) / waves * 8;
+  if (grid < io.R) grid = (io.R + 7) / 8 * 8;
+  const uint32_t held = pk.held ? 1u << 31 : 0;
+  uint32_t magic = part_magic((int)pk.parts, (int64_t)(grid + 8) * waves);
+  if (few) {
+    uint32_t T_waves = (uint32_t)T | (uint32_t)waves << 16 | held;
+    int tokens_per_rank = g.tokens_per_rank;
+    float inv_S = 1.0f / (float)io.S;
+    void* args[] = {&io.topk_idx, &io.l2p_off, &io.l2p_list, &io.active, &io.mem_version, &T_waves, &io.E, &io.P, &io.R,
+                    &pk.x, &pk.row_vecs, &pk.parts, &magic, &pk.x_scale, &pk.scale_vecs, &inv_S, &io.policy,
+                    &tokens_per_rank, &io.S, &pk.recv, &pk.recv_scale, &io.tbl_version, &io.slot_of, &io.row_of,
+                    &io.src_of, &io.count, &io.offset, &io.rank_count, &io.rank_offset, &io.cnt_src, &io.status,
+                    &io.step_epoch};
+    return set_node(node, io.k == 8 ? (const void*)k_layout_pack_small<8> : (const void*)k_layout_pack_small<4>, grid,
+                    kMapThreads, small_lds_bytes(io.E, io.P, io.R, T, io.k), args);
+  }
+  int nt = kOnceThreads / 2;  // threads: for the tables too
+  while (nt < kOnceThreads && large_tables(io.E, io.P, io.R, nt)) nt += 64;
+  const int window = 8 * (waves - 1) / (int)pk.parts + 2;  // the most tokens that a workgroup's pieces belong to
+  const size_t lds = once_lds_bytes(io.E, io.P, io.R, window, io.k, true);
+  if (lds > kLayoutLdsLimit || large_tables(io.E, io.P, io.R, nt)) return false;
+  uint32_t T_rank = (uint32_t)T | (uint32_t)g.tokens_per_rank << 16, E_P = (uint32_t)io.E | (uint32_t)io.P << 16;
+  uint32_t R_S = (uint32_t)io.R | (uint32_t)io.S << 12;
+  uint32_t window_waves = (uint32_t)window | (uint32_t)io.policy << 12 | (uint32_t)(nt / 64) << 13 |
+                          (uint32_t)waves << 18 | held;
+  void* args[] = {&io.topk_idx, &io.l2p_off, &io.l2p_list, &io.active, &io.mem_version, &T_rank, &E_P, &R_S,
+                  &window_waves, &pk.x, &pk.row_vecs, &pk.parts, &magic, &pk.x_scale, &pk.scale_vecs, &pk.recv,
+                  &pk.recv_scale, &io.tbl_version, &io.slot_of, &io.row_of, &io.src_of, &io.cnt_src, &io.count,
+                  &io.offset, &io.rank_count, &io.rank_offset, &io.status, &io.step_epoch};
+  return set_node(node,
+                  pk.vecs == 1   ? layout_pack_once_for<1>(io.k)
+                  : pk.vecs == 2 ? layout_pack_once_for<2>(io.k)
+                  : pk.vecs == 4 ? layout_pack_once_for<4>(io.k) : layout_pack_once_for<7>(io.k),
+                  grid, nt, lds, args);
 }
 
 }  // namespace eep
