@@ -1800,12 +1800,18 @@ __global__ __launch_bounds__(kMapThreads) void k_dedup_position(
 // a launch of its own costs about 2 us beside that, and the host 2.6.  Whole de-duplicated steps in a graph
 // of 8, the one-launch form of the ordinary layout on both sides: 2048 tokens over 8 ranks, 7168 channels,
 // 158.3 us in two launches, 153.5 in one; 512 tokens 52.8 and 49.0.
-// Up to 3 ranks only up to 6144 tokens (kDedupFewTokens): the counts of few ranks are few LDS words, added to by one
-// lane after the other.  Top-1, 16384 tokens, 1 / 2 / 4 / 8 ranks 16.4 / 10.3 / 8.8 / 5.9 us, in two launches 9.0 each; top-2,
-// 8192 tokens 10.0 / 9.4 / 7.8 / 6.6, in two 7.5 each; top-3, 5460 tokens 7.8 / 8.2 / 7.3 / 6.4, in two 8.0 each.
-constexpr int kDedupShare = 64, kDedupFewRanks = 3, kDedupFewTokens = 6144;
+// Few ranks are few LDS words, added to by one lane after the other.  There (BALLOT) a wavefront counts its 64 tokens by a
+// ballot for each rank, which costs as much for every rank whatever its tokens: layout alone in a graph of 40, by lane / by
+// ballot, top-1, 16320 tokens, 1 / 2 / 3 / 4 / 8 ranks 16.3 / 10.3 / 9.5 / 8.8 / 5.9 and 8.1 / 8.9 / 9.7 / 10.6 / 14.1 us; top-2, 8160
+// tokens 10.1 / 9.4 / 8.4 / 7.7 / 6.5 and 5.8 / 6.2 / 6.7 / 7.1 / 8.8; top-4, 512 tokens 3.0 / 3.0 / 2.9 / 2.9 / 2.8 and 2.65 / 2.7 / 2.7 /
+// 2.75 / 2.9; top-8, 2048 tokens, 1 / 2 / 4 / 8 / 12 / 16 ranks 5.5 / 5.95 / 6.1 / 5.95 / 5.7 / 5.5 and 4.4 / 4.5 / 4.7 / 5.1 / 5.6 / 5.9, 1024
+// tokens of 8 ranks 4.2 and 4.3.  (In two launches top-1, 16320 tokens of up to 3 ranks took 9.0 to 10.1.)
+constexpr int kDedupShare = 64;
+static bool dedup_by_ballot(int R, int k, int T) {
+  return R <= 4 ? R <= k + 1 : R <= 8 && k >= 6 && T > 1024;
+}
 
-template <int KC>
+template <int KC, bool BALLOT>
 __global__ __launch_bounds__(kOnceThreads) void k_dedup_once(
     const int32_t* __restrict__ slot_of, const int32_t* __restrict__ row_of,
     const int32_t* __restrict__ status, int T, int R, int nt, float inv_S,
@@ -1829,23 +1835,39 @@ __global__ __launch_bounds__(kOnceThreads) void k_dedup_once(
   }
   __syncthreads();
 #pragma nounroll
-  for (int t = tid; t < T;) {
+  for (int t = tid; (BALLOT ? t - (tid & 63) : t) < T;) {
     const bool own = t >= lo && t < hi;
-    int32_t* cnt = s_cnt[own ? 1 : t < lo ? 0 : 2];
+    // (with BALLOT whole wavefronts stay, whose tokens lie in one share)
+    const int t0 = BALLOT ? __builtin_amdgcn_readfirstlane(t) : t;
+    int32_t* cnt = s_cnt[t0 >= lo && t0 < hi ? 1 : t0 < lo ? 0 : 2];
     uint64_t mask = 0;
 #pragma unroll
     for (int j = 0; j < KC; ++j) {
       bool lead = false;
-      if (p[j] >= 0) {
+      if (p[j] >= 0 && (!BALLOT || t < T)) {
         const int r = rank_of_slot(p[j], inv_S);
         lead = ((mask >> r) & 1) == 0;
         mask |= 1ull << r;
-        if (lead) {
+        if (!BALLOT && lead) {
           atomicAdd(&cnt[r], 1);
           if (own) atomicOr((unsigned long long*)&s_bm[r], 1ull << (t - lo));
         }
       }
       if (own) s_pair[(t - lo) * KC + j] = p[j] < 0 ? -1 : p[j] << 1 | lead;
+    }
+    if constexpr (BALLOT) {
+      // A wavefront's 64 tokens lie in one share, so a ballot is a rank's count, and in the own share its bitmap;
+      // lane r keeps rank r's.
+      uint64_t mine = 0;
+#pragma nounroll
+      for (int r = 0; r < R; ++r) {
+        const uint64_t has = __ballot((mask >> r) & 1);
+        if ((tid & 63) == r) mine = has;
+      }
+      if ((tid & 63) < R) {
+        if (t0 >= lo && t0 < hi) s_bm[tid & 63] = mine;
+        atomicAdd(&cnt[tid & 63], __popcll(mine));
+      }
     }
     t += nt;
     if (t < T) __builtin_memcpy(p, &at(slot_of, t * KC), sizeof(p));
@@ -1896,13 +1918,14 @@ hipError_t launch_dedup_layout(eep_ctx* c, int T, hipStream_t st) {
     if (e == hipSuccess) e = launch_fill(c->dd_status, 0, 1, st);
     return e;
   }
-  if (c->R <= 64 && c->k <= kOnceMaxK && (int64_t)T * c->k <= kOncePairs &&
-      (c->R > kDedupFewRanks || T <= kDedupFewTokens)) {
-    static const decltype(&k_dedup_once<1>) of[kOnceMaxK] = {
-        k_dedup_once<1>, k_dedup_once<2>, k_dedup_once<3>, k_dedup_once<4>, k_dedup_once<5>,
-        k_dedup_once<6>, k_dedup_once<7>, k_dedup_once<8>, k_dedup_once<9>, k_dedup_once<10>};
+  if (c->R <= 64 && c->k <= kOnceMaxK && (int64_t)T * c->k <= kOncePairs) {
+#define EEP_DEDUP(B) {k_dedup_once<1, B>, k_dedup_once<2, B>, k_dedup_once<3, B>, k_dedup_once<4, B>, k_dedup_once<5, B>, \
+                      k_dedup_once<6, B>, k_dedup_once<7, B>, k_dedup_once<8, B>, k_dedup_once<9, B>, k_dedup_once<10, B>}
+    static const decltype(&k_dedup_once<1, false>) of[2][kOnceMaxK] = {EEP_DEDUP(false), EEP_DEDUP(true)};
+#undef EEP_DEDUP
+    const bool ballot = dedup_by_ballot(c->R, c->k, T);
     const int nt = T > kOnceThreads ? kOnceThreads : kOnceThreads / 2;
-    hipLaunchKernelGGL(of[c->k - 1], dim3((T + kDedupShare - 1) / kDedupShare), dim3(nt), 0, st, c->slot_of,
+    hipLaunchKernelGGL(of[ballot][c->k - 1], dim3((T + kDedupShare - 1) / kDedupShare), dim3(nt), 0, st, c->slot_of,
                        c->row_of, c->status, T, c->R, nt, 1.0f / (float)c->S, c->src_of, c->offset,
                        c->dd_row, c->dd_dst, c->dd_expand, c->dd_count, c->dd_offset, c->dd_status);
     return hipGetLastError();
