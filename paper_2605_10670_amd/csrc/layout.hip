@@ -1288,9 +1288,9 @@ __device__ __forceinline__ void store_piece(const Piece& pc, int row, const u32x
     stores(std::false_type());
 }
 
-// Few pairs, built like k_layout_small.  T_waves: T, and << 16 the wavefronts with a piece, and << 31 `held`.
-template <int K>
-__global__ __launch_bounds__(kMapThreads) void k_layout_pack_small(
+// Few pairs, at most one to each of the NT threads, built like k_layout_small.  T_waves: T, and << 16 the wavefronts with a piece, and << 31 `held`.
+template <int K, int NT>
+__global__ __launch_bounds__(NT) void k_layout_pack_small(
     const int32_t* __restrict__ topk_idx, const int32_t* __restrict__ l2p_off,
     const int32_t* __restrict__ l2p_list, const int32_t* __restrict__ active,
     const int32_t* __restrict__ mem_version, uint32_t T_waves, int E, int P, int R,
@@ -1321,13 +1321,13 @@ __global__ __launch_bounds__(kMapThreads) void k_layout_pack_small(
   my_e[0] = tid < npairs ? topk_idx[tid] : -1;
   const int version = blockIdx.x == 0 && tid == 0 ? *tbl_version + *mem_version : 0;
   const int several_v = vector_load(&mem_version[1]);  // several contexts in the instance
-  RouteTableLoad<false> tables = {l2p_off, l2p_list, active, E, R, P, kMapThreads};
+  RouteTableLoad<false> tables = {l2p_off, l2p_list, active, E, R, P, NT};
   tables.fetch();
   const Piece pc = piece_of<1>(wave, waves, T, parts, magic, row_vecs, scale_vecs);
   u32x4 d[1];
   load_piece(pc, x, x_scale, d);
 #pragma nounroll
-  for (int i = tid; i < P * (stride + 1); i += kMapThreads) s_count[i] = 0;  // and s_bm
+  for (int i = tid; i < P * (stride + 1); i += NT) s_count[i] = 0;  // and s_bm
   if (tid < 2) s_drop[tid] = 0;
   const SpreadAgreedMask agree = {step_epoch + kAgreeGroupsAt, __builtin_amdgcn_readfirstlane(several_v) != 0, s_agreed};
   const RouteTables rt = tables.fill(s_tab, inv_S, agree);
@@ -1337,7 +1337,7 @@ __global__ __launch_bounds__(kMapThreads) void k_layout_pack_small(
   map_pairs<K, 1>(rt, my_e, s_slot, slot, s_bm, stride, s_count, s_drop, npairs, K, E, 0, policy, 0, 0, slot_of);
   if (tid < npairs) s_slot[tid] = slot[0];
   __syncthreads();
-  scan_totals([=](int p) { return s_count[p]; }, s_offset, P, wave, kMapThreads / 64);
+  scan_totals([=](int p) { return s_count[p]; }, s_offset, P, wave, NT / 64);
   __syncthreads();
 
   const int N = s_offset[P];
@@ -1354,7 +1354,7 @@ __global__ __launch_bounds__(kMapThreads) void k_layout_pack_small(
     }
   }
   // pairs per (source rank, slot): the tokens of a source rank are a bit range
-  for (int b = wave * gridDim.x + blockIdx.x; b < R; b += gridDim.x * (kMapThreads / 64)) {
+  for (int b = wave * gridDim.x + blockIdx.x; b < R; b += gridDim.x * (NT / 64)) {
     const int lo = b * tokens_per_rank, hi = lo + tokens_per_rank;
     int32_t* cnt = cnt_src + (int64_t)b * P;
     if (P <= 64)
@@ -1363,7 +1363,7 @@ __global__ __launch_bounds__(kMapThreads) void k_layout_pack_small(
       for (int p0 = 0; p0 < P; p0 += 320) store_src_counts<5>(s_bm, stride, p0, P, lo, hi, cnt);
   }
   if (blockIdx.x == 0)
-    write_step_tables(kMapThreads, s_offset, s_drop[0], s_drop[1], version, count, offset, rank_count,
+    write_step_tables(NT, s_offset, s_drop[0], s_drop[1], version, count, offset, rank_count,
                       rank_offset, status, step_epoch, R, S, P);
   if (agree.several && wave == 0 && __builtin_amdgcn_readfirstlane(last)) agree.clear();
 }
@@ -2157,7 +2157,7 @@ bool layout_pack_node(eep_ctx* ctx, const int32_t* topk_idx, PackPieces pk, int 
   const int pieces = (int)((T * (int64_t)pk.parts + 7) / 8);  // of an XCD
   if (pieces > kXcdCus * kPieceWaves * kPieceRounds) return false;
   // As k_layout_small up to the same size for top-4 and 8 (7168 channels, top-8, T = 32 / 96: 8.75 / 12.3 us, as k_layout_once
-  // 9.0 / 12.6; for top-1 and 2 the latter is faster: T = 32 7.7 and 7.5); its workgroups have 16 wavefronts.
+  // 9.0 / 12.6; for top-1 and 2 the latter is faster: T = 32 7.7 and 7.5).
   const bool few = (io.k == 4 || io.k == 8) && T * io.k <= kFewPairs && pk.vecs == 1 && pieces <= kXcdCus * 16 &&
                    !large_tables(io.E, io.P, io.R, kMapThreads) &&
                    small_lds_bytes(io.E, io.P, io.R, T, io.k) <= kLayoutLdsLimit;
@@ -2176,8 +2176,15 @@ bool layout_pack_node(eep_ctx* ctx, const int32_t* topk_idx, PackPieces pk, int 
                     &tokens_per_rank, &io.S, &pk.recv, &pk.recv_scale, &io.tbl_version, &io.slot_of, &io.row_of,
                     &io.src_of, &io.count, &io.offset, &io.rank_count, &io.rank_offset, &io.cnt_src, &io.status,
                     &io.step_epoch};
-    return set_node(node, io.k == 8 ? (const void*)k_layout_pack_small<8> : (const void*)k_layout_pack_small<4>, grid,
-                    kMapThreads, small_lds_bytes(io.E, io.P, io.R, T, io.k), args);
+    // (half the threads where there is a pair to each: T = 32 / 64 7.65 / 9.5 us a step, 7.85 / 9.75 with 16 wavefronts)
+    const bool half = T * io.k <= kMapThreads / 2 && waves <= kMapThreads / 128 &&
+                      !large_tables(io.E, io.P, io.R, kMapThreads / 2);
+    return set_node(node,
+                    half ? (io.k == 8 ? (const void*)k_layout_pack_small<8, kMapThreads / 2>
+                                      : (const void*)k_layout_pack_small<4, kMapThreads / 2>)
+                         : (io.k == 8 ? (const void*)k_layout_pack_small<8, kMapThreads>
+                                      : (const void*)k_layout_pack_small<4, kMapThreads>),
+                    grid, half ? kMapThreads / 2 : kMapThreads, small_lds_bytes(io.E, io.P, io.R, T, io.k), args);
   }
   int nt = kOnceThreads / 2;  // threads: for the tables too
   while (nt < kOnceThreads && large_tables(io.E, io.P, io.R, nt)) nt += 64;

@@ -110,6 +110,9 @@ CASES = ([((40, k, 1032, 4, 6, 20, "bf16"), 1) for k in range(1, 11)] +         
           ((1300, 1, 3584, 4, 8, 30, "bf16"), 1), ((2048, 7, 1536, 16, 3, 40, "bf16"), 1), ((1280, 10, 640, 5, 8, 30, "f32"), 1),
           ((160, 8, 7168, 32, 9, 256, "fp8"), 1), ((32, 4, 512, 8, 3, 20, "fp8"), 1), ((700, 3, 1536, 4, 9, 30, "fp8"), 1),
           ((1023, 8, 1024, 1, 24, 20, "fp8"), 1), ((184, 2, 8192, 8, 3, 20, "f32"), 1),
+          ((63, 8, 1024, 1, 24, 20, "bf16"), 1), ((64, 8, 7168, 2, 12, 20, "bf16"), 1),      # a pair to each of 512 threads or 1024
+          ((65, 8, 7168, 1, 24, 20, "bf16"), 1), ((128, 4, 8192, 2, 12, 20, "f32"), 1), ((128, 4, 1024, 4, 128, 500, "bf16"), 1),
+          ((128, 4, 1024, 4, 129, 500, "bf16"), 1), ((128, 4, 1024, 4, 128, 513, "bf16"), 1),
           # in two or more: tokens, pairs, top-k, ranks, pieces, scale rows
           ((2050, 7, 64, 2, 12, 20, "bf16"), 2), ((2048, 9, 64, 2, 12, 20, "bf16"), 3), ((64, 11, 64, 2, 12, 20, "bf16"), 2),
           ((130, 8, 64, 65, 2, 80, "bf16"), 2), ((440, 8, 8192, 2, 12, 20, "f32"), 2), ((1024, 8, 512, 2, 12, 20, "fp8"), 3),
@@ -231,6 +234,35 @@ def test_what_becomes_one_node(oracle):
         for graph in graphs:
             graph.destroy()
         other.ctx.destroy()
+        step.ctx.destroy()
+
+
+@pytest.mark.parametrize("mode", ["global", "thread_local", "relaxed"])
+def test_captured_by_torch(oracle, mode):
+    """torch's own capture, in each of its modes, with its kernels around the two calls."""
+    step = Step(96, 8, 1024, 4, 9, 30)
+    try:
+        pairs = torch.zeros_like(step.idx_dev)
+        seen = torch.zeros_like(step.recv[:1])
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph, stream=step.stream, capture_error_mode=mode):
+            mine, step.idx_dev = step.idx_dev, pairs
+            pairs.copy_(mine)
+            step.layout()
+            step.dispatch()
+            n = nodes_captured(step.stream)
+            seen.copy_(step.recv[:1])
+        assert n == 2
+        for _ in range(3):
+            step.renew()
+            pairs.zero_()
+            torch.cuda.synchronize()
+            with torch.cuda.stream(step.stream):
+                graph.replay()
+            step.check(oracle)
+            assert torch.equal(seen, step.recv[:1])
+        del graph
+    finally:
         step.ctx.destroy()
 
 
