@@ -46,7 +46,7 @@ constexpr int kExpandSplitBelow = 4096;  // the same for rows that are read and 
 // otherwise loads past the row's end read its last vector again, so that all U
 // loads of a pass are in flight here too (a branch around each would make it
 // wait for the ones before), and stores are guarded.
-template <int U, bool EXACT, bool HELD>
+template <int U, bool EXACT>
 __global__ __launch_bounds__(64) void k_pack(const u32x4* __restrict__ x,
                                              const int32_t* __restrict__ row_of, int k,
                                              int row_vecs, u32x4* __restrict__ recv) {
@@ -74,7 +74,7 @@ __global__ __launch_bounds__(64) void k_pack(const u32x4* __restrict__ x,
 #pragma unroll
       for (int u = 0; u < U; ++u) {
         int v = v0 + u * 64 + lane;
-        if (EXACT || v < row_vecs) store_row<HELD>(&dst[v], buf[u]);
+        if (EXACT || v < row_vecs) store_row(&dst[v], buf[u]);
       }
     }
   }
@@ -90,7 +90,7 @@ __global__ __launch_bounds__(64) void k_pack(const u32x4* __restrict__ x,
 // (k_scale_rows), T = 32 / 128 / 512 / 1000 in 16.3 / 19.9 / 42.4 / 70.7 us, 13.2 / 17.2 / 38.6 / 67.0 now.
 constexpr int kSplitMaxK = 8;
 
-template <int U, bool EXACT, int K, bool SCALES, bool HELD>
+template <int U, bool EXACT, int K, bool SCALES>
 __global__ __launch_bounds__(64) void k_pack_split(const u32x4* __restrict__ x,
                                                    const int32_t* __restrict__ row_of, int k_rt,
                                                    uint32_t row_vecs, uint32_t parts, uint32_t magic,
@@ -130,7 +130,7 @@ __global__ __launch_bounds__(64) void k_pack_split(const u32x4* __restrict__ x,
       const u32x4 d = x_scale[(int64_t)t * scale_vecs + v];
       for_rows([&]() { asm volatile("" ::"v"(d)); }, [&](int row) {
         if (v0 + lane < scale_vecs)
-          store_row_at<HELD>(recv_scale, (int64_t)row * (scale_vecs * 16), v * 16, d);
+          store_row_at(recv_scale, (int64_t)row * (scale_vecs * 16), v * 16, d);
       });
     }
     return;
@@ -153,7 +153,7 @@ __global__ __launch_bounds__(64) void k_pack_split(const u32x4* __restrict__ x,
 #pragma unroll
     for (int u = 0; u < U; ++u)
       if (EXACT || v0 + u * 64 < row_vecs)
-        store_row_at<HELD>(recv, at, ((K > 0 ? v0 : lane) + u * 64) * 16, buf[u]);
+        store_row_at(recv, at, ((K > 0 ? v0 : lane) + u * 64) * 16, buf[u]);
   });
 }
 
@@ -300,15 +300,15 @@ static PassShape pass_shape(int row_vecs, int split, int64_t rows, int max_vecs)
 
 template <int U, bool EXACT>
 static hipError_t launch_pack_t(eep_ctx* c, const int32_t* rows, const void* x, void* recv_x,
-                                int T, bool held, hipStream_t st) {
-  hipLaunchKernelGGL((held ? k_pack<U, EXACT, true> : k_pack<U, EXACT, false>), dim3(T), dim3(64), 0, st,
+                                int T, hipStream_t st) {
+  hipLaunchKernelGGL((k_pack<U, EXACT>), dim3(T), dim3(64), 0, st,
                      (const u32x4*)x, rows, c->k, (int)(c->x_row_bytes / 16), (u32x4*)recv_x);
   return hipGetLastError();
 }
 
-template <int U, bool EXACT, bool SCALES, bool HELD>
+template <int U, bool EXACT, bool SCALES>
 static auto pack_split_for(int k) {
-#define EEP_SPLIT(K) k_pack_split<U, EXACT, K, SCALES, HELD>
+#define EEP_SPLIT(K) k_pack_split<U, EXACT, K, SCALES>
   static const decltype(&EEP_SPLIT(0)) of[kSplitMaxK + 1] = {EEP_SPLIT(0), EEP_SPLIT(1), EEP_SPLIT(2),
                                                              EEP_SPLIT(3), EEP_SPLIT(4), EEP_SPLIT(5),
                                                              EEP_SPLIT(6), EEP_SPLIT(7), EEP_SPLIT(8)};
@@ -319,11 +319,11 @@ static auto pack_split_for(int k) {
 template <int U, bool EXACT, bool SCALES>
 static hipError_t launch_pack_split_t(eep_ctx* c, const int32_t* rows, const void* x,
                                       const float* x_scale, void* recv_x, float* recv_scale, int T,
-                                      int parts, bool held, hipStream_t st) {
+                                      int parts, hipStream_t st) {
   const int64_t grid = (int64_t)T * parts;
   const bool compiled = c->k <= kSplitMaxK && c->x_row_bytes < (int64_t)1 << 32;  // (32-bit offsets there)
   const int k = compiled ? c->k : 0;
-  auto kern = held ? pack_split_for<U, EXACT, SCALES, true>(k) : pack_split_for<U, EXACT, SCALES, false>(k);
+  auto kern = pack_split_for<U, EXACT, SCALES>(k);
   hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3(64), 0, st,
                      (const u32x4*)x, rows, c->k, (uint32_t)(c->x_row_bytes / 16), (uint32_t)parts,
                      part_magic(parts, grid), (u32x4*)recv_x, (const u32x4*)x_scale,
@@ -357,29 +357,18 @@ static int pack_tokens_per_wave(const PassShape& ps, int row_vecs, int T) {
   return tpw;
 }
 
-// Are a dispatch's stores held in the L2s (rows.hpp)?  Measured as whole steps in graphs of 4 (T = 32 to 8192, rows of 1 to
-// 14 KiB, top-1 to 8), the receive rows' MiB first, write-through's time over that of held stores.  Combine reads the receive
-// rows: top-8 4 0.97-0.99, 8 1.00-1.06, 16 1.00-1.05, 24 1.04-1.09, 28 1.04-1.07, 36 1.00-1.05, 44 0.98-1.04, 64 0.91-0.94; top-6 and
-// top-4 12 1.01-1.02, 24 1.03-1.05, 36 0.95-1.06; top-2 0.95-1.01 and top-1 0.90-0.99 at any size.  Another kernel writes what
-// combine reads: 8 0.95-0.98, 16 1.01-1.02, 24 1.00-1.01, 28 0.98-1.00, 36 0.97-0.99.  fp8 payloads, whose experts' rows
-// are twice as large: 2 0.99-1.01, 4 1.02, 8 1.01-1.03, 12 1.01-1.03, 16 0.97, 24 0.94.
-static bool pack_holds(const eep_ctx* c, int64_t T) {
-  const int64_t bytes = T * c->k * c->x_row_bytes;
-  return c->cfg.x_dtype == EEP_FP8_E4M3 ? mib_between(bytes, 4, 13) : c->k >= 4 && mib_between(bytes, 14, 26);
-}
-
 // (x_scale null: no scale rows, or not here)
 static hipError_t launch_pack_payload(eep_ctx* c, const int32_t* rows, const void* x,
                                       const float* x_scale, void* recv_x, float* recv_scale, int T,
-                                      int split, bool held, hipStream_t st) {
+                                      int split, hipStream_t st) {
   const int row_vecs = (int)(c->x_row_bytes / 16);
   const PassShape ps = pass_shape(row_vecs, split, T, kPackVecs);
   if (x_scale != nullptr || ps.parts > 1) {
 #define EEP_PACK_SPLIT(U, SCALES)                                                                 \
   return ps.exact ? launch_pack_split_t<U, true, SCALES>(c, rows, x, x_scale, recv_x, recv_scale, \
-                                                         T, ps.parts + SCALES, held, st)          \
+                                                         T, ps.parts + SCALES, st)          \
                   : launch_pack_split_t<U, false, SCALES>(c, rows, x, x_scale, recv_x, recv_scale, \
-                                                          T, ps.parts + SCALES, held, st)
+                                                          T, ps.parts + SCALES, st)
     if (x_scale != nullptr) {
       if (ps.u == 1) EEP_PACK_SPLIT(1, true);
       EEP_PACK_SPLIT(2, true);
@@ -409,8 +398,8 @@ static hipError_t launch_pack_payload(eep_ctx* c, const int32_t* rows, const voi
   switch (ps.u) {
 #define EEP_PACK_CASE(U)                                                                \
   case U:                                                                               \
-    return ps.exact ? launch_pack_t<U, true>(c, rows, x, recv_x, T, held, st)           \
-                    : launch_pack_t<U, false>(c, rows, x, recv_x, T, held, st);
+    return ps.exact ? launch_pack_t<U, true>(c, rows, x, recv_x, T, st)           \
+                    : launch_pack_t<U, false>(c, rows, x, recv_x, T, st);
     EEP_PACK_CASE(14) EEP_PACK_CASE(13) EEP_PACK_CASE(12) EEP_PACK_CASE(11) EEP_PACK_CASE(10)
     EEP_PACK_CASE(9) EEP_PACK_CASE(8) EEP_PACK_CASE(7) EEP_PACK_CASE(6) EEP_PACK_CASE(5)
     EEP_PACK_CASE(4) EEP_PACK_CASE(3) EEP_PACK_CASE(2) EEP_PACK_CASE(1)
@@ -421,14 +410,14 @@ static hipError_t launch_pack_payload(eep_ctx* c, const int32_t* rows, const voi
 
 static hipError_t launch_pack_any(eep_ctx* c, const int32_t* rows, const void* x,
                                   const float* x_scale, void* recv_x, float* recv_scale, int T,
-                                  int split, bool held, hipStream_t st) {
+                                  int split, hipStream_t st) {
   if (T == 0) return hipSuccess;
   // Small batches: the scale rows go with the payload, in wavefronts of their own.
   const bool together = x_scale != nullptr && T < kPackSplitBelow &&
                         pass_shape((int)(c->x_row_bytes / 16), split, T, kPackVecs).u <= 2;
   hipError_t e = in_launches(T, max_blocks(64), [&](int64_t t0, int64_t n) {
     return launch_pack_payload(c, rows + t0 * c->k, (const char*)x + t0 * c->x_row_bytes,
-                               together ? x_scale : nullptr, recv_x, recv_scale, (int)n, split, held, st);
+                               together ? x_scale : nullptr, recv_x, recv_scale, (int)n, split, st);
   });
   if (e != hipSuccess || x_scale == nullptr || together) return e;
   const int scale_vecs = (int)(c->scale_row_bytes / 16);
@@ -446,10 +435,15 @@ static hipError_t launch_pack_any(eep_ctx* c, const int32_t* rows, const void* x
 
 // With the layout in one launch the narrow pieces are the better ones up to larger sizes, also where another kernel writes what
 // combine reads (top-8, T = 1024 to 1536 of 1024 channels, 16 to 24 MiB of receive rows: 1.17-1.20 times as fast as two launches,
-// 1.09-1.12 with wider pieces; with a scaling stage 1.03-1.10 and 1.02-1.10), and so are held stores (the time with
-// write-through over that with them, combine reads the rows / another kernel writes others: 4 MiB 0.94-1.00 / 0.93-1.03, 8 0.97-1.05 /
-// 0.97-1.03, 12 1.00-1.08 / 0.97-1.01, 16 1.03-1.05 / 1.02-1.05, 24 1.02-1.10 / 1.01-1.05, 32 1.06-1.10 / 0.99-1.01, 36 1.06-1.09 / 1.00,
-// 44 0.98-1.06 / 1.00; fp8 2 0.99, 4 1.02-1.03, 8 1.02-1.05, 12 1.02-1.06, 16 0.99, 19 0.95).
+// 1.09-1.12 with wider pieces; with a scaling stage 1.03-1.10 and 1.02-1.10).  Held stores (rows.hpp): write-through's time over
+// theirs, graphs of 4 steps, one / two / three sets of buffers in turn, by MiB of receive rows.  Combine reads the rows: 12 1.00-1.05 /
+// 1.00-1.08 / 1.00-1.07, 16 1.01-1.07 / 1.04-1.08 / 1.03-1.06, 20 1.03-1.08 / 1.02-1.07 / 1.01-1.04, 28 1.06-1.12 / 0.99-1.05 / 0.97-1.02,
+// 36 1.07-1.11 / 0.95-1.01 / 0.95-0.99.  A scaling stage writes others: 12 1.00-1.06 / 0.99-1.06 / 0.98-1.01, 16 1.01-1.10 / 0.98-1.01 /
+// 0.97-0.98, 20 0.99-1.06 / 0.96-0.99 / 0.95-0.98, 28 0.95-1.00 / 0.95-0.98 / 0.94-0.97.  fp8: 4 1.00-1.03 / 1.00-1.06 / 1.00-1.06,
+// 8 1.02-1.10 / 1.05-1.07 / 0.99-1.02, 10 1.03-1.08 / 0.98-1.02 / 0.96-0.98, 13 1.01-1.05 / 0.94-0.97 / 0.94-0.95.  (In a dispatch
+// of its own they gain where the layout's node does, but lose there too: three sets in turn, call by call, 14 / 20 / 26 MiB 0.96-1.06 /
+// 0.97-1.05 / 0.95-1.03 with the rows read by combine, 0.97-0.99 / 0.94-0.98 / 0.93-1.00 with a scaling stage; quantised, 7 / 9 / 12 MiB
+// of codes 0.98 / 0.95 / 0.92.  No such dispatch holds them.)
 bool pack_pieces(const eep_ctx* c, const void* x, const float* x_scale, void* recv_x, float* recv_scale, int T,
                  PackPieces* out) {
   const int row_vecs = (int)(c->x_row_bytes / 16), scale_vecs = x_scale != nullptr ? (int)(c->scale_row_bytes / 16) : 0;
@@ -463,7 +457,7 @@ bool pack_pieces(const eep_ctx* c, const void* x, const float* x_scale, void* re
     const int parts = (chunks + 6) / 7, even = (chunks + parts - 1) / parts;
     vecs = even <= 2 ? even : even <= 4 ? 4 : 7;
   }
-  const bool held = scale_vecs > 0 ? mib_between(x_bytes * c->k, 4, 13) : mib_between(x_bytes * c->k, 12, 36);
+  const bool held = scale_vecs > 0 ? mib_between(x_bytes * c->k, 4, 8) : mib_between(x_bytes * c->k, 12, 28);
   *out = {x, x_scale, recv_x, recv_scale, (uint32_t)row_vecs, (uint32_t)scale_vecs,
           (uint32_t)((chunks + vecs - 1) / vecs + (scale_vecs > 0)), vecs, held};
   return true;
@@ -471,12 +465,12 @@ bool pack_pieces(const eep_ctx* c, const void* x, const float* x_scale, void* re
 
 hipError_t launch_pack(eep_ctx* c, const void* x, const float* x_scale, void* recv_x,
                        float* recv_scale, int T, hipStream_t st) {
-  return launch_pack_any(c, c->row_of, x, x_scale, recv_x, recv_scale, T, pack_split(c, T), pack_holds(c, T), st);
+  return launch_pack_any(c, c->row_of, x, x_scale, recv_x, recv_scale, T, pack_split(c, T), st);
 }
 
 hipError_t launch_pack_rows(eep_ctx* c, const int32_t* rows, const void* x, void* recv, int T,
                             hipStream_t st) {
-  return launch_pack_any(c, rows, x, nullptr, recv, nullptr, T, pack_split_of_tokens(T), false, st);
+  return launch_pack_any(c, rows, x, nullptr, recv, nullptr, T, pack_split_of_tokens(T), st);
 }
 
 // ---------------------------------------------------------------------------
@@ -528,8 +522,10 @@ hipError_t launch_expand(eep_ctx* c, const void* recv_dedup, void* recv_x, int T
                                   rows < kExpandManyRows       ? kExpandVecs
                                   : row_vecs <= kExpandWideRow ? kExpandManyVecs
                                                                : kExpandWideVecs);
-  // Held stores (rows.hpp), by the receive rows' MiB, as above: 8 0.97-0.99, 16 1.05-1.10, 28 1.01-1.06, 36 1.00-1.03, 56 0.91-0.95.
-  const bool held = mib_between(rows * c->x_row_bytes, 12, 32);
+  // Held stores (rows.hpp), in a captured step only: write-through's time over theirs, whole steps, 14 / 18 / 24 / 30 MiB of
+  // receive rows: in graphs 1.11 / 1.05 / 1.06-1.09 / 1.04, three sets of buffers in turn 1.02 / 1.03-1.04 / 1.03 / 1.01-1.02; call
+  // by call 1.06-1.15 / 1.03-1.06 / 1.06-1.11 / 1.04, but three sets in turn 0.98-1.00 / 0.98 / 0.94-0.96 / 0.93-0.95.
+  const bool held = mib_between(rows * c->x_row_bytes, 12, 32) && is_captured(st);
   return in_launches(rows, max_blocks(64) / ps.parts, [&](int64_t r0, int64_t n) {
     const uint32_t magic = part_magic(ps.parts, n * ps.parts);
     u32x4* to = (u32x4*)recv_x + r0 * row_vecs;
@@ -640,7 +636,7 @@ __device__ __forceinline__ uint32_t quant4(const uint32_t (&d)[2], float scale, 
   return (uint32_t)__builtin_amdgcn_cvt_pk_fp8_f32(q[2], q[3], o, true);
 }
 
-template <int U, bool HELD>
+template <int U>
 __global__ __launch_bounds__(64) void k_pack_quant(const u32x4* __restrict__ x,
                                                    const int32_t* __restrict__ row_of, int k,
                                                    int out_vecs, uint32_t parts, uint32_t magic,
@@ -694,7 +690,7 @@ __global__ __launch_bounds__(64) void k_pack_quant(const u32x4* __restrict__ x,
 #pragma unroll
       for (int u = 0; u < U; ++u) {
         int w = w0 + u * 64 + lane;
-        if (w < out_vecs) store_row<HELD>(&dst[w], q[u]);
+        if (w < out_vecs) store_row(&dst[w], q[u]);
       }
     }
     if (__any(odd != 0)) {
@@ -749,11 +745,8 @@ hipError_t launch_pack_quant(eep_ctx* c, const void* x_bf16, void* recv_q, float
   const int passes = (out_vecs + 63) / 64;
   const bool split = T < kQuantSplitBelow && (int64_t)T * passes <= max_blocks(64);
   const int parts = split ? passes : 1;
-  // Held stores (rows.hpp), by the codes' MiB, as for dispatch: 4 0.97, 8 1.04-1.06, 16 0.96, 24 0.93-0.95.
-  const bool held = mib_between((int64_t)T * c->k * c->H, 7, 12);
   return in_launches(T, max_blocks(64) / parts, [&](int64_t t0, int64_t n) {
-    hipLaunchKernelGGL((held ? (split ? k_pack_quant<1, true> : k_pack_quant<kQuantVecs, true>)
-                             : (split ? k_pack_quant<1, false> : k_pack_quant<kQuantVecs, false>)),
+    hipLaunchKernelGGL((split ? k_pack_quant<1> : k_pack_quant<kQuantVecs>),
                        dim3((unsigned)(n * parts)), dim3(64), 0, st,
                        (const u32x4*)x_bf16 + t0 * out_vecs * 2, c->row_of + t0 * c->k, c->k,
                        out_vecs, (uint32_t)parts, part_magic(parts, n * parts),
@@ -1261,9 +1254,12 @@ hipError_t launch_stub(eep_ctx* c, int kind, const void* recv_x, const float* re
         hipLaunchKernelGGL(k_stub_copy, grid, block, 0, st, (const u32x4*)recv_x, (u32x4*)y,
                            c->status, row_vecs, (int)r0);
       } else {
-        // Held stores (rows.hpp), by the rows' MiB, as for dispatch: 4 0.96, 8 1.00-1.05, 12 1.07-1.10, 16 1.08-1.17, 24 1.10-1.12,
-        // 32 1.06-1.08, 36 1.03-1.05, 44 1.00, 52 0.98.
-        const bool held = mib_between(rows * c->x_row_bytes, 10, 36), bf16 = c->cfg.x_dtype == EEP_BF16;
+        // Held stores (rows.hpp), for more rows in a captured step: write-through's time over theirs, whole steps, 10-16 / 18 / 24 / 30 MiB:
+        // in graphs 1.11-1.18 / 1.08-1.15 / 1.04-1.10 / 1.02-1.04, three sets of buffers in turn 0.99-1.03 / 0.99-1.04 / 1.00-1.03 /
+        // 0.98; call by call 1.02-1.16 / 1.04-1.10 / 1.06-1.12 / 1.05, three sets in turn 0.97-1.02 / 0.98-1.00 / 0.97-0.98 / 0.97.
+        const int64_t bytes = rows * c->x_row_bytes;
+        const bool held = mib_between(bytes, 10, 16) || (mib_between(bytes, 16, 26) && is_captured(st));
+        const bool bf16 = c->cfg.x_dtype == EEP_BF16;
         auto kern = held ? (bf16 ? k_stub_scale<true, true> : k_stub_scale<false, true>)
                          : (bf16 ? k_stub_scale<true, false> : k_stub_scale<false, false>);
         hipLaunchKernelGGL(kern, grid, block, 0, st, c->src_of + r0, (const u32x4*)recv_x + v0,

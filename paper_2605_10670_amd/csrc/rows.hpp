@@ -23,7 +23,10 @@ __device__ __forceinline__ uint32_t token_of(uint32_t n, uint32_t parts, uint32_
 // evicted or the kernel ends, which writes it back.  With the eight L2s of 4 MiB in mind: what fits them is best held, since
 // the stores then end in the L2 and the write-back runs at its own pace; larger ones are evicted in the middle of the
 // kernel, line by line, and write-through is better; and of a few MB there is nothing to gain, but the write-back at
-// the end takes longer than stores that have long arrived.  The limits at the launches are measured.
+// the end takes longer than stores that have long arrived.  A buffer whose lines the L2s still hold from the step before gains
+// most, one that was not touched lately least: stores that are held then take the place of other lines, and write-through
+// ones have no line in another L2 to end.  A captured step is replayed on its own buffers, so more is held there; calls
+// one by one may have other buffers each time.  The limits at the launches are measured with both.
 //
 // The data registers of a store of more than 8 bytes may not be rewritten by the next two
 // wait states' vector instructions.  The compiler keeps that distance for its own stores but
@@ -40,7 +43,7 @@ __device__ __forceinline__ void store_row(u32x4* p, u32x4 v) {
 // a scalar register within five wait states of a vector instruction that wrote it (v_readfirstlane, or
 // a spilled register's v_readlane); the compiler does not keep that distance for asm either, so
 // the address is added up by scalar instructions that are part of it.
-template <bool HELD>
+template <bool HELD = false>
 __device__ __forceinline__ void store_row_at(void* base, int64_t row, uint32_t offset, u32x4 v) {
 #define EEP_STORE_AT(HOW)                                                                                  \
   asm volatile("s_add_u32 s98, %2, %4\n\ts_addc_u32 s99, %3, %5\n\t"                                       \
@@ -53,6 +56,15 @@ __device__ __forceinline__ void store_row_at(void* base, int64_t row, uint32_t o
   else
     EEP_STORE_AT("sc0 sc1");
 #undef EEP_STORE_AT
+}
+
+// Is a kernel launched on this stream now part of a capture?
+inline bool is_captured(hipStream_t st) {
+  hipStreamCaptureStatus status = hipStreamCaptureStatusNone;
+  if (st == nullptr) return false;  // (cannot be)
+  if (hipStreamIsCapturing(st, &status) == hipSuccess) return status == hipStreamCaptureStatusActive;
+  (void)hipGetLastError();
+  return false;
 }
 
 // Are `bytes` within [lo, hi] MiB?

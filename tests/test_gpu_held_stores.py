@@ -1,7 +1,7 @@
-"""Dispatch, expansion, quantisation and the scaling stand-in at the sizes between which their stores are held in the
-L2s, and one step to either side of them: every form of each kernel (whole rows, pieces of one and two kilobytes, rows
-with a remainder, scale rows, a group that needs the division).  Moved bytes equal, rows past the last routed pair
-untouched."""
+"""Dispatch, expansion, quantisation and the scaling stand-in at the sizes between which stores are held in the
+L2s, and one step to either side of them (expansion holds its own in captured steps only, the stand-in more of them
+there): every form of each kernel (whole rows, pieces of one and two kilobytes, rows with a remainder, scale rows, a
+group that needs the division).  Moved bytes equal, rows past the last routed pair untouched."""
 import re
 import subprocess
 
@@ -32,6 +32,20 @@ def context(T, k, H, R=1, **kw):
 def random_rows(T, H, dtype):
     size = {"f32": 4, "bf16": 2, "fp8": 1}[dtype]
     return torch.randint(0, 256, (T, H * size), dtype=torch.uint8, device="cuda")
+
+
+def launch(ctx, captured, call):
+    """The call by itself, or captured and replayed."""
+    if not captured:
+        return call(None)
+    stream = torch.cuda.Stream()
+    torch.cuda.synchronize()
+    ctx.graph_begin(stream)
+    call(stream)
+    graph = ctx.graph_end(stream)
+    graph.launch(stream)
+    stream.synchronize()
+    graph.destroy()
 
 
 # (T, k, H, x dtype): receive rows of 13.9 to 26.1 MiB (fp8 3.9 to 13.1), around 512 and 1024 tokens
@@ -72,8 +86,10 @@ def test_expansion(T, H):
             (T * k, 2 * H), 0x5A, dtype=torch.uint8, device="cuda")
         ctx.dedup_layout(T)
         ctx.dispatch_dedup(x, recv_d, T)
-        ctx.expand(recv_d, recv, T)
-        assert torch.equal(recv[:N], x[src[:N] // k]) and bool((recv[N:] == 0x5A).all())
+        for captured in (False, True):
+            recv.fill_(0x5A)
+            launch(ctx, captured, lambda st: ctx.expand(recv_d, recv, T, stream=st))
+            assert torch.equal(recv[:N], x[src[:N] // k]) and bool((recv[N:] == 0x5A).all())
     finally:
         ctx.destroy()
 
@@ -101,20 +117,23 @@ def test_quantisation(oracle, T, H):
 
 @gpu
 @pytest.mark.parametrize("T,H,dtype", [(80, 8184, "bf16"), (81, 8192, "bf16"), (256, 2048, "f32"), (700, 3080, "bf16"),
-                                       (576, 4096, "bf16"), (580, 4096, "bf16")])
+                                       (576, 4096, "bf16"), (580, 4096, "bf16"),
+                                       (128, 8192, "bf16"), (130, 8192, "bf16"), (416, 4096, "bf16"), (418, 4096, "bf16")])
 def test_scaling_stand_in(T, H, dtype):
     k, E = 8, 20
     ctx, src, N = context(T, k, H, x_dtype=dtype, y_dtype=dtype, out_dtype=dtype)
     try:
         tdt = {"f32": torch.float32, "bf16": torch.bfloat16}[dtype]
         recv = torch.randn((T * k, H), device="cuda").to(tdt)
-        y = torch.full((T * k, H), 7.0, device="cuda", dtype=tdt)
+        y = torch.empty((T * k, H), device="cuda", dtype=tdt)
         s = torch.rand(E, device="cuda") + 0.5
-        ctx.expert_stub("scale", recv, y, T, expert_scale=s)
         p2l = torch.from_numpy(ctx.read("phys_to_logical", 24)).cuda().long()
         slot = torch.from_numpy(ctx.read("slot_of", T * k)).cuda().long()
         want = (recv[:N].float() * s[p2l[slot[src[:N]]]][:, None]).to(tdt)
-        assert torch.equal(y[:N], want) and bool((y[N:] == 7.0).all())
+        for captured in (False, True):
+            y.fill_(7.0)
+            launch(ctx, captured, lambda st: ctx.expert_stub("scale", recv, y, T, expert_scale=s, stream=st))
+            assert torch.equal(y[:N], want) and bool((y[N:] == 7.0).all())
     finally:
         ctx.destroy()
 
@@ -122,10 +141,14 @@ def test_scaling_stand_in(T, H, dtype):
 def test_held_stores_make_their_scalar_address(tmp_path):
     """As the write-through ones (test_scalar_addresses.py): the address of a store from scalar registers is added up
     by the two scalar instructions right ahead of it."""
-    out = tmp_path / "data.s"
+    src, out = tmp_path / "store.hip", tmp_path / "store.s"
+    src.write_text('#include "rows.hpp"\n'
+                   "__global__ void k(char* p, const eep::u32x4* v, const int* rows) {\n"
+                   "  for (int j = 0; j < 4; ++j)\n"
+                   "    eep::store_row_at<true>(p, (int64_t)rows[j] * 7168, threadIdx.x * 16, v[threadIdx.x]);\n}\n")
     flags = [f for f in build.FLAGS if f not in ("-shared", "-fPIC")]
-    subprocess.run([build.HIPCC, *flags, "-w", "-S", "--cuda-device-only", "-o", str(out),
-                    build.HERE + "/csrc/data.hip"], check=True)
+    subprocess.run([build.HIPCC, *flags, "-w", "-I", build.HERE + "/csrc", "-S", "--cuda-device-only", "-o", str(out),
+                    str(src)], check=True)
     lines = [s for s in (line.split(";")[0].strip() for line in out.read_text().splitlines()) if s]
     stores = 0
     for i, line in enumerate(lines):
