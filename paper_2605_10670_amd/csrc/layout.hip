@@ -2143,10 +2143,28 @@ static const void* layout_pack_once_for(int k) {
 }
 
 // How many pieces a workgroup takes.  More pieces than 8 wavefronts of every CU make further rounds of workgroups, which are
-// resident together up to three (the top-8 kernel has 69 registers), and in these all CUs are to get the same: with 16
+// resident together up to three (stay_resident), and in these all CUs are to get the same: with 16
 // wavefronts in 280 workgroups 320 tokens of 7168 channels took 25.6 us a step, with 10 in 448 21.9, with 6 in 752 21.7, with 9 in
-// 504 21.6.  Beyond three rounds (768 pieces to an XCD; 896 tokens of 7168 channels) two launches are as fast.
-constexpr int kLayoutPackTokens = 2048, kXcdCus = 32, kPieceWaves = 8, kPieceRounds = 3;
+// 504 21.6.  Beyond three rounds (768 pieces to an XCD; 896 tokens of 7168 channels) two launches are as fast, and with three
+// rounds of many pairs, all of which every workgroup lays out: two launches' time over that of one, 1088 channels, 288 slots,
+// top-4 1536 / 2048 tokens 1.09 / 1.06, top-8 1.05 / 1.01; with a skewed router 1.03 / 0.975 and 0.98 / 0.935.
+constexpr int kLayoutPackTokens = 2048, kXcdCus = 32, kPieceWaves = 8, kPieceRounds = 3, kThirdRoundPairs = 6144;
+
+// Are `rounds` workgroups of nt threads resident on a CU together?  A round that has to wait for the one before lays the
+// batch out again when that has ended: three rounds of top-10 (83 registers, 5 wavefronts to a SIMD), 1536 tokens of 1088
+// channels 25.0 us a step, in two launches 22.1; of 576 slots (9 wavefronts, 3 of them on one SIMD) top-4 17.0 and 15.9; two rounds
+// of both, 1024 tokens, 21.3 and 19.8.
+static bool stay_resident(const void* kernel, int nt, int rounds) {
+  hipFuncAttributes a;
+  if (rounds <= 1) return true;
+  if (hipFuncGetAttributes(&a, kernel) != hipSuccess) {
+    (void)hipGetLastError();
+    return false;
+  }
+  // wavefronts of a SIMD: 512 vector registers in eights, and the scalar ones are enough for 7
+  const int waves = std::min(7, 512 / std::max(8, (a.numRegs + 7) / 8 * 8));
+  return rounds * ((nt + 255) / 256) <= waves;
+}
 
 bool layout_pack_node(eep_ctx* ctx, const int32_t* topk_idx, PackPieces pk, int T, hipGraphNode_t node) {
   LayoutIO io = layout_io(ctx, topk_idx);
@@ -2190,7 +2208,12 @@ bool layout_pack_node(eep_ctx* ctx, const int32_t* topk_idx, PackPieces pk, int 
   while (nt < kOnceThreads && large_tables(io.E, io.P, io.R, nt)) nt += 64;
   const int window = 8 * (waves - 1) / (int)pk.parts + 2;  // the most tokens that a workgroup's pieces belong to
   const size_t lds = once_lds_bytes(io.E, io.P, io.R, window, io.k, true);
-  if (lds > kLayoutLdsLimit || large_tables(io.E, io.P, io.R, nt)) return false;
+  const void* const kernel = pk.vecs == 1   ? layout_pack_once_for<1>(io.k)
+                             : pk.vecs == 2 ? layout_pack_once_for<2>(io.k)
+                             : pk.vecs == 4 ? layout_pack_once_for<4>(io.k) : layout_pack_once_for<7>(io.k);
+  if (lds > kLayoutLdsLimit || large_tables(io.E, io.P, io.R, nt) ||
+      (rounds == kPieceRounds && T * io.k > kThirdRoundPairs) || !stay_resident(kernel, nt, rounds))
+    return false;
   uint32_t T_rank = (uint32_t)T | (uint32_t)g.tokens_per_rank << 16, E_P = (uint32_t)io.E | (uint32_t)io.P << 16;
   uint32_t R_S = (uint32_t)io.R | (uint32_t)io.S << 12;
   uint32_t window_waves = (uint32_t)window | (uint32_t)io.policy << 12 | (uint32_t)(nt / 64) << 13 |
@@ -2199,11 +2222,7 @@ bool layout_pack_node(eep_ctx* ctx, const int32_t* topk_idx, PackPieces pk, int 
                   &window_waves, &pk.x, &pk.row_vecs, &pk.parts, &magic, &pk.x_scale, &pk.scale_vecs, &pk.recv,
                   &pk.recv_scale, &io.tbl_version, &io.slot_of, &io.row_of, &io.src_of, &io.cnt_src, &io.count,
                   &io.offset, &io.rank_count, &io.rank_offset, &io.status, &io.step_epoch};
-  return set_node(node,
-                  pk.vecs == 1   ? layout_pack_once_for<1>(io.k)
-                  : pk.vecs == 2 ? layout_pack_once_for<2>(io.k)
-                  : pk.vecs == 4 ? layout_pack_once_for<4>(io.k) : layout_pack_once_for<7>(io.k),
-                  grid, nt, lds, args);
+  return set_node(node, kernel, grid, nt, lds, args);
 }
 
 }  // namespace eep

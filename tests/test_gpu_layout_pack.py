@@ -106,13 +106,17 @@ CASES = ([((40, k, 1032, 4, 6, 20, "bf16"), 1) for k in range(1, 11)] +         
          [((T, 8, 1024, 1, 24, 20, "bf16"), 1) for T in (1, 31, 127, 128, 129, 511, 512, 1023, 1024, 1025, 2047, 2048)] +
          [((T, 4, 7168, 2, 12, 20, "bf16"), 1) for T in (2, 254, 256, 258, 512, 768)] +  # few pairs, many pieces, rounds
          [((32, 8, 24, 32, 9, 256, "bf16"), 1), ((64, 8, 520, 64, 9, 512, "bf16"), 1), ((600, 6, 2880, 24, 5, 96, "bf16"), 1),
-          ((1152, 2, 4608, 48, 2, 48, "bf16"), 1), ((1200, 4, 2560, 8, 100, 700, "bf16"), 1), ((96, 8, 1024, 2, 500, 900, "f32"), 1),
+          ((1152, 2, 4608, 48, 2, 48, "bf16"), 1), ((400, 4, 2560, 8, 100, 700, "bf16"), 1), ((96, 8, 1024, 2, 500, 900, "f32"), 1),
           ((1300, 1, 3584, 4, 8, 30, "bf16"), 1), ((2048, 7, 1536, 16, 3, 40, "bf16"), 1), ((1280, 10, 640, 5, 8, 30, "f32"), 1),
           ((160, 8, 7168, 32, 9, 256, "fp8"), 1), ((32, 4, 512, 8, 3, 20, "fp8"), 1), ((700, 3, 1536, 4, 9, 30, "fp8"), 1),
           ((1023, 8, 1024, 1, 24, 20, "fp8"), 1), ((184, 2, 8192, 8, 3, 20, "f32"), 1),
           ((63, 8, 1024, 1, 24, 20, "bf16"), 1), ((64, 8, 7168, 2, 12, 20, "bf16"), 1),      # a pair to each of 512 threads or 1024
           ((65, 8, 7168, 1, 24, 20, "bf16"), 1), ((128, 4, 8192, 2, 12, 20, "f32"), 1), ((128, 4, 1024, 4, 128, 500, "bf16"), 1),
           ((128, 4, 1024, 4, 129, 500, "bf16"), 1), ((128, 4, 1024, 4, 128, 513, "bf16"), 1),
+          # rounds of workgroups that fit a CU together, and not: pairs, top-10's registers, threads for many slots
+          ((1536, 4, 1088, 32, 9, 256, "bf16"), 1), ((1568, 4, 1088, 32, 9, 256, "bf16"), 2), ((512, 10, 3584, 8, 9, 64, "bf16"), 1),
+          ((608, 10, 3080, 8, 9, 64, "bf16"), 2), ((640, 4, 2560, 64, 9, 512, "bf16"), 1), ((1344, 4, 1088, 64, 9, 512, "bf16"), 1),
+          ((1408, 4, 1088, 64, 9, 512, "bf16"), 2), ((640, 10, 1088, 64, 9, 512, "bf16"), 1), ((704, 10, 1088, 64, 9, 512, "bf16"), 2),
           # in two or more: tokens, pairs, top-k, ranks, pieces, scale rows
           ((2050, 7, 64, 2, 12, 20, "bf16"), 2), ((2048, 9, 64, 2, 12, 20, "bf16"), 3), ((64, 11, 64, 2, 12, 20, "bf16"), 2),
           ((130, 8, 64, 65, 2, 80, "bf16"), 2), ((440, 8, 8192, 2, 12, 20, "f32"), 2), ((1024, 8, 512, 2, 12, 20, "fp8"), 3),
