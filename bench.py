@@ -35,11 +35,11 @@ STAGE_KERNELS = {"dispatch": ("k_pack", "k_pack_multi", "k_pack_quant", "k_scale
 
 
 def source_hash():
-    """Hash of the HIP sources that hold every kernel of the step (layout.hip, data.hip); the
+    """Hash of the HIP sources that hold every kernel of the step (layout.hip, data.hip, rows.hpp); the
     built .so travels with them."""
     import hashlib
     h = hashlib.sha256()
-    for name in ("data.hip", "layout.hip"):
+    for name in ("data.hip", "layout.hip", "rows.hpp"):
         h.update(name.encode())
         h.update(open(os.path.join(ROOT, "paper_2605_10670_amd", "csrc", name), "rb").read())
     return h.hexdigest()[:16]

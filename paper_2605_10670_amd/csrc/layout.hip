@@ -1178,7 +1178,7 @@ __global__ __launch_bounds__(kOnceThreads) void k_layout_once(
 // 256 / 320 / 640 / 2048 10.0 / 13.6 / 22.1 / 23.0 / 34.5 / 84.4 us and 8.8 / 12.3 / 19.1 / 20.3 / 31.6 / 82.9; 2048 channels, T = 32 / 256 / 512 /
 // 1024 / 2048 8.95 / 12.0 / 15.4 / 24.4 / 32.1 and 7.9 / 10.4 / 13.1 / 18.3 / 31.1; fp8, 4096 channels, T = 128 / 448 / 960
 // 17.2 / 26.9 / 41.3 and 15.1 / 25.9 / 39.2; top-2, 2048 channels, T = 160 / 992 9.05 / 12.2 and 7.6 / 10.6.  Part of it is
-// that the receive rows are held in the L2s (rows.hpp) up to a larger size here, since all wavefronts store at once.
+// that mid-sized receive rows are held in the L2s (rows.hpp) here, where all wavefronts store at once.
 // ---------------------------------------------------------------------------
 // The agreement on a mask, as in k_layout_once, for launches of hundreds of workgroups, up to 64 ranks: the first workgroup leaves the mask in eight places, one
 // for the workgroups of each XCD (kAgreeGroups, kAgreeGroupInts), which are counted there too.  (In one place the loads and the
