@@ -493,8 +493,10 @@ int eep_plan_transition(int32_t R, int32_t S, int32_t S_prim, int32_t E,
 /* Carry out a planned repair (Sec. 3.5: local reuse / batched GPU-to-GPU
  * relocation / reload from the DRAM backup; Sec. 5.1: the weights are moved to
  * where the new placement wants them, the active mask being looked up when
- * each transfer is issued), then publish the placement (as
- * eep_update_placement does), all in stream order.
+ * each transfer is issued) and publish the placement (as
+ * eep_update_placement does), in stream order: what is queued behind it on the
+ * stream sees the weights and the placement both.  There is no order between the
+ * two before that, so work on other streams that uses either waits for the whole call.
  *   weights  device memory, [P][slot_bytes]: the expert weight store, slot-major
  *            (rank r owns slots [r*S, (r+1)*S)); updated in place.
  *   backup   [E][slot_bytes], readable by the GPU: device memory, or host memory
@@ -505,13 +507,15 @@ int eep_plan_transition(int32_t R, int32_t S, int32_t S_prim, int32_t E,
  *   new_phys_to_logical, source_kind, source_slot  host int32[P], as written by
  *            eep_plan_repair for the placement this context holds now.
  *            (eep_plan_transition's output is accepted as well).
- * One kernel does the whole batch.  For each PEER slot p it reads the DEVICE
+ * One kernel moves the whole batch.  For each PEER slot p it reads the DEVICE
  * copy of the active mask: source rank active -> copy from source_slot[p];
  * source rank dropped out after planning -> copy backup[new_phys_to_logical[p]]
  * instead.  DRAM slots copy from the backup.  Only the source is looked up: the
  * destination may be a rank that is not active yet (Sec. 3.6: a relaunched rank
  * loads its experts before it joins).  What happened is recorded per slot
- * (eep_repair_outcome) and read back with eep_read_repair_outcome.
+ * (eep_repair_outcome) and read back with eep_read_repair_outcome.  A large slot
+ * is copied in pieces, each of which looks the mask up when its turn comes: if a source
+ * leaves the mask meanwhile, the outcome says where the slot's first piece came from.
  * Checked on the host before anything is queued (EEP_ERR_INVALID_ARG):
  * a LOCAL slot keeps the expert the context's current placement gives it; a PEER
  * source is another slot that holds that expert now and is not itself rewritten

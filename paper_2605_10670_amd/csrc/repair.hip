@@ -73,41 +73,42 @@ __device__ __forceinline__ int outcome_of(int src, bool from_peer) {
 }
 
 // One workgroup's part of the moves.  Of n moves the last n_link go over the host link, by the first kLinkBlocks workgroups (if
-// there are any); each of the others copies one chunk, a move's chunks one after the other.
+// there are any); each of the others copies one chunk, a move's chunks one after the other.  The outcome of a move is
+// written by whoever copies its first vectors, from the look at the mask that chose their source: one of its own would be at
+// another time, and another context's combine may drop the rank in between.
 __device__ __forceinline__ void move_weights(int block, u32x4* weights, const u32x4* backup, int64_t slot_vecs,
                                              int chunks_per_move, const int32_t* mv_dst, const int32_t* mv_src,
-                                             const int32_t* mv_expert, int n, int n_link, const int32_t* active, int S) {
+                                             const int32_t* mv_expert, int n, int n_link, const int32_t* active, int S,
+                                             int32_t* outcome) {
   if (n_link > 0) {
     if (block < kLinkBlocks) {
       const int first = n - n_link;
+      if (block == 0)
+        for (int m = first + threadIdx.x; m < n; m += kMoveThreads) outcome[mv_dst[m]] = EEP_REPAIR_FROM_DRAM;
       copy_over_link(weights, backup, slot_vecs, block, mv_dst + first, mv_expert + first, n_link);
       return;
     }
     block -= kLinkBlocks;
   }
   const int m = block / chunks_per_move, chunk = block - m * chunks_per_move;
-  const int src = mv_src[m];
-  copy_chunk(weights, backup, slot_vecs, chunk, mv_dst[m], src, mv_expert[m], is_from_peer(src, active, S));
+  const int src = mv_src[m], dst = mv_dst[m];
+  const bool from_peer = is_from_peer(src, active, S);
+  if (chunk == 0 && threadIdx.x == 0) outcome[dst] = outcome_of(src, from_peer);
+  copy_chunk(weights, backup, slot_vecs, chunk, dst, src, mv_expert[m], from_peer);
 }
 
-// Workgroup 0 writes the outcomes, the others move.
 __global__ __launch_bounds__(kMoveThreads) void k_relocate(
     u32x4* weights, const u32x4* backup, int64_t slot_vecs, int chunks_per_move, int n, int n_link,
     const int32_t* __restrict__ mv_dst, const int32_t* __restrict__ mv_src,
     const int32_t* __restrict__ mv_expert, const int32_t* __restrict__ active, int S,
     int32_t* __restrict__ outcome) {
-  if (blockIdx.x > 0) {
-    move_weights(blockIdx.x - 1, weights, backup, slot_vecs, chunks_per_move, mv_dst, mv_src, mv_expert, n, n_link,
-                 active, S);
-    return;
-  }
-  for (int m = threadIdx.x; m < n; m += kMoveThreads)
-    outcome[mv_dst[m]] = outcome_of(mv_src[m], is_from_peer(mv_src[m], active, S));
+  move_weights(blockIdx.x, weights, backup, slot_vecs, chunks_per_move, mv_dst, mv_src, mv_expert, n, n_link, active, S,
+               outcome);
 }
 
 // The whole repair in one launch, where its move list and the new tables fit the kernel's arguments: workgroup 0 writes the
-// outcomes and the tables (nothing in the launch reads these, and what comes behind it on the stream sees both them and the
-// weights), the others move.  Bound by the copies; a launch for the move list and one for the tables cost some 2.2 us each
+// tables and the outcomes of slots that nothing moves to (nothing in the launch reads these, and what comes behind it on
+// the stream sees both them and the weights), the others move.  Bound by the copies; a launch for the move list and one for the tables cost some 2.2 us each
 // (a repair, a return with 28 MB over the host link and the way back to the preferred placement: 593.7 us with
 // them, 582.6 without, 530.0 with few workgroups on the link).
 constexpr int kRepairInts = 960, kRepairSmallInts = 320;
@@ -125,14 +126,13 @@ __global__ __launch_bounds__(kMoveThreads) void k_repair(
   const int32_t *mv_src = mv_dst + n, *mv_expert = mv_src + n, *tables = mv_expert + n;
   if (blockIdx.x > 0) {
     move_weights(blockIdx.x - 1, weights, backup, slot_vecs, chunks_per_move, mv_dst, mv_src, mv_expert, n, n_link,
-                 active, S);
+                 active, S, outcome);
     return;
   }
-  __shared__ int32_t s_outcome[N];
-  for (int p = threadIdx.x; p < P; p += kMoveThreads) s_outcome[p] = EEP_REPAIR_UNTOUCHED;
+  __shared__ int32_t s_moved[N];
+  for (int p = threadIdx.x; p < P; p += kMoveThreads) s_moved[p] = 0;
   __syncthreads();
-  for (int m = threadIdx.x; m < n; m += kMoveThreads)
-    s_outcome[mv_dst[m]] = outcome_of(mv_src[m], is_from_peer(mv_src[m], active, S));
+  for (int m = threadIdx.x; m < n; m += kMoveThreads) s_moved[mv_dst[m]] = 1;
   for (int i = threadIdx.x; i < 2 * P + E + 1; i += kMoveThreads) {
     const int32_t v = tables[i];
     if (i < P) p2l[i] = v;
@@ -140,7 +140,8 @@ __global__ __launch_bounds__(kMoveThreads) void k_repair(
     else l2p_list[i - P - E - 1] = v;
   }
   __syncthreads();
-  for (int p = threadIdx.x; p < P; p += kMoveThreads) outcome[p] = s_outcome[p];
+  for (int p = threadIdx.x; p < P; p += kMoveThreads)
+    if (s_moved[p] == 0) outcome[p] = EEP_REPAIR_UNTOUCHED;
   if (threadIdx.x == 0) *version = *version + 1;
 }
 
@@ -253,7 +254,7 @@ int eep_apply_repair(eep_ctx* c, void* weights, const void* backup, int64_t slot
   hipStream_t st = (hipStream_t)stream;
   hipError_t e;
   const int n_link = backup_on_host ? (int)link_dst.size() : 0;
-  const int64_t blocks = 1 + (n_link > 0 ? kLinkBlocks : 0) + (n_moves - n_link) * chunks;
+  const int64_t blocks = (n_link > 0 ? kLinkBlocks : 0) + (n_moves - n_link) * chunks;  // that move
   const int64_t n_words = (int64_t)3 * n_moves + 2 * (int64_t)P + c->E + 1;
   if (n_words <= kRepairInts) {
     // (what publish_placement checks has been checked above)
@@ -265,7 +266,7 @@ int eep_apply_repair(eep_ctx* c, void* weights, const void* backup, int64_t slot
     std::copy(new_p2l, new_p2l + P, tables);
     host_replica_lists(P, c->E, S, c->S_prim, new_p2l, tables + P, tables + P + c->E + 1);
     const auto launch = n_words <= kRepairSmallInts ? launch_repair<kRepairSmallInts> : launch_repair<kRepairInts>;
-    e = launch(c, (u32x4*)weights_dev, (const u32x4*)backup_dev, slot_vecs, (int)chunks, (int)blocks, words, n_moves,
+    e = launch(c, (u32x4*)weights_dev, (const u32x4*)backup_dev, slot_vecs, (int)chunks, (int)blocks + 1, words, n_moves,
                n_link, st);
     if (e != hipSuccess) return fail_hip(c, e);
     c->h_p2l.assign(new_p2l, new_p2l + P);
