@@ -1,11 +1,14 @@
 """Weight movement in each of its forms: the whole repair in one launch (shorter and longer move lists and tables) and as
 three, reloads from host memory by few workgroups and from device memory by many, slots of less than a workgroup's
-vectors, of whole chunks and with a ragged tail, sources that dropped out, nothing to move.  Byte-exact, and the tables."""
+vectors, of whole chunks and with a ragged tail, sources that dropped out, nothing to move.  Byte-exact, the tables, their
+version, and the layout that follows from them."""
 import numpy as np
 import pytest
+import torch
 
 from paper_2605_10670_amd import binding
 
+import gpu_util as gu
 from test_gpu_repair_moves import _context, _expect, _run, _store
 
 pytestmark = pytest.mark.gpu
@@ -18,7 +21,7 @@ pytestmark = pytest.mark.gpu
     (8, 10, 120, 4, 9, 4096 * 63), (8, 10, 120, 4, 10, 4096 * 64 + 16), (8, 10, 120, 5, 11, 4096 * 65 - 16),
     (16, 20, 301, 2, 4, 65552), (16, 20, 301, 3, 4, 65552), (16, 20, 301, 0, 9, 1 << 18), (16, 20, 301, 9, 0, 1 << 18),
     (16, 40, 400, 20, 70, 4112)])
-def test_forms(R, S, E, peers, reloads, slot_bytes, pinned):
+def test_forms(oracle, R, S, E, peers, reloads, slot_bytes, pinned):
     rng = np.random.default_rng(R + E + peers + reloads)
     P = R * S
     cur = rng.permutation(np.concatenate([np.arange(min(E, P // 2)), np.full(P - min(E, P // 2), -1)])).astype(np.int32)
@@ -37,7 +40,9 @@ def test_forms(R, S, E, peers, reloads, slot_bytes, pinned):
     try:
         ctx.update_placement(cur)
         ctx.set_membership(active)
-        version = ctx.read("status", 4)
+        idx = torch.from_numpy(rng.integers(0, E, size=(4 * R, min(2, E)), dtype=np.int32)).cuda()
+        ctx.dispatch_layout(idx, 4 * R)
+        version = int(ctx.read("status", 4)[3])
         plan = dict(p2l=p2l, kind=kind, src_slot=src)
         got_w, got_o = _run(ctx, weights, backup, plan, slot_bytes, pinned)
         want_w, want_o = _expect(weights, backup, plan, active, S)
@@ -51,6 +56,9 @@ def test_forms(R, S, E, peers, reloads, slot_bytes, pinned):
                 assert np.array_equal(got, other.read(field, got.size)), field
         finally:
             other.destroy()
-        assert np.array_equal(version, ctx.read("status", 4))      # (no layout has run)
+        ctx.dispatch_layout(idx, 4 * R)
+        gu.assert_layout_equal(ctx.read_layout(4 * R), oracle.step_layout(idx.cpu().numpy(), p2l, active, E, R, S, S,
+                                                                          oracle.SPREAD), 4 * R, min(2, E))
+        assert int(ctx.read("status", 4)[3]) == version + 1
     finally:
         ctx.destroy()
