@@ -449,6 +449,7 @@ int eep_dispatch(eep_ctx* c, const void* x, const float* x_scale, void* recv_x, 
     return EEP_ERR_ALIGN;
   const int32_t* captured_idx = c->captured_idx;
   c->captured_idx = nullptr;
+  c->dispatched_split = -1;
   if (dispatch_with_layout(c, captured_idx, x, x_scale, recv_x, recv_scale, T, (hipStream_t)stream)) return EEP_OK;
   hipError_t e = launch_pack(c, x, x_scale, recv_x, recv_scale, T, (hipStream_t)stream);
   return e == hipSuccess ? EEP_OK : fail_hip(c, e);
@@ -492,6 +493,7 @@ int eep_dispatch_quant(eep_ctx* c, const void* x_bf16, void* recv_x, float* recv
   if (!x_bf16 || !recv_x || !recv_scale) return EEP_ERR_INVALID_ARG;
   if (!aligned16(x_bf16) || !aligned16(recv_x) || ((uintptr_t)recv_scale & 3u))
     return EEP_ERR_ALIGN;
+  c->dispatched_split = -1;
   hipError_t e = launch_pack_quant(c, x_bf16, recv_x, recv_scale, T, (hipStream_t)stream);
   return e == hipSuccess ? EEP_OK : fail_hip(c, e);
 }
@@ -623,6 +625,7 @@ int eep_expand(eep_ctx* c, const void* recv_dedup, void* recv_x, int32_t T, void
   if (T == 0) return EEP_OK;
   if (!recv_dedup || !recv_x || recv_dedup == recv_x) return EEP_ERR_INVALID_ARG;
   if (!aligned16(recv_dedup) || !aligned16(recv_x)) return EEP_ERR_ALIGN;
+  c->dispatched_split = -1;
   hipError_t e = launch_expand(c, recv_dedup, recv_x, T, (hipStream_t)stream);
   return e == hipSuccess ? EEP_OK : fail_hip(c, e);
 }

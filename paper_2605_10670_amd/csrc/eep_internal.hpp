@@ -145,7 +145,9 @@ struct eep_ctx {
   hipStream_t captured_on;
   unsigned long long captured_in;
   hipGraphNode_t captured_node;
-  int dispatched_split;  // how the last dispatch since then cut its rows (pack_split in data.hip), -1 if none
+  // How the receive rows were cut last, if by a dispatch in one launch with its layout (0 or 1 or 2, as pack_split in
+  // data.hip), else -1.
+  int dispatched_split;
   int last_hip_error;
   int64_t field_ints[EEP_V_NUM_FIELDS];
 };

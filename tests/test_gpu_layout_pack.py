@@ -149,6 +149,48 @@ def test_layout_and_dispatch(oracle, shape, nodes):
         step.ctx.destroy()
 
 
+class KernelNodeParams(ctypes.Structure):
+    _fields_ = [("block", ctypes.c_uint32 * 3), ("extra", ctypes.c_void_p), ("func", ctypes.c_void_p),
+                ("grid", ctypes.c_uint32 * 3), ("args", ctypes.c_void_p), ("lds", ctypes.c_uint32)]
+
+
+def last_grid(stream):
+    """Workgroups of the kernel that the running capture of `stream` holds last."""
+    lib, status, node, n = hip(), ctypes.c_int(), ctypes.POINTER(ctypes.c_void_p)(), ctypes.c_size_t()
+    assert lib.hipStreamGetCaptureInfo_v2(ctypes.c_void_p(stream.cuda_stream), ctypes.byref(status), None, None,
+                                          ctypes.byref(node), ctypes.byref(n)) == 0 and n.value == 1
+    params = KernelNodeParams()
+    assert lib.hipGraphKernelNodeGetParams(ctypes.c_void_p(node[0]), ctypes.byref(params)) == 0
+    return params.grid[0]
+
+
+def test_combine_takes_the_rows_as_the_last_dispatch_cut_them():
+    """A dispatch in one node with its layout may cut the rows in another way than one of its own does, and combine
+    goes by the last one that wrote them."""
+    T, k, H = 1028, 8, 1024                            # pieces of 1 KiB in the one, whole rows in the other
+    step = Step(T, k, H, 4, 6, 20)
+    w, out = torch.rand((T, k), device="cuda"), torch.zeros((T, H), dtype=torch.bfloat16, device="cuda")
+    recv_d = torch.zeros_like(step.recv)
+    dedup = lambda: step.ctx.dedup_layout(T, step.stream)
+    packed = lambda: step.ctx.dispatch_dedup(step.x, recv_d, T, step.stream)
+    expand = lambda: step.ctx.expand(recv_d, step.recv, T, step.stream)
+    grids = []
+
+    def combine():
+        step.ctx.combine(step.recv.view(torch.bfloat16), w, out, T, step.stream)
+        grids.append(last_grid(step.stream))
+
+    try:
+        for calls in ((step.layout, step.dispatch), (step.layout, step.dispatch, step.dispatch),
+                      (step.layout, step.dispatch, dedup, packed, expand), (step.layout, step.dispatch, dedup, packed)):
+            step.capture(*calls, combine)[0].destroy()
+        step.layout()
+        step.capture(step.dispatch, combine)[0].destroy()
+        assert grids == [T * 2, T // 8 * 16 + 16, T // 8 * 16 + 16, T * 2, T // 8 * 16 + 16]
+    finally:
+        step.ctx.destroy()
+
+
 @pytest.mark.parametrize("router", ["repeats", "padding", "copies", "outside", "first live"])
 @pytest.mark.parametrize("T,k", [(96, 8), (640, 8), (320, 3), (64, 4)])
 def test_routers(oracle, router, T, k):
