@@ -149,6 +149,49 @@ def test_layout_and_dispatch(oracle, shape, nodes):
         step.ctx.destroy()
 
 
+# pieces of 1 and 2 KiB, and whole rows in passes of four and seven vectors
+@pytest.mark.parametrize("T,k,H", [(256, 8, 7168), (1028, 8, 1024), (1536, 2, 2048), (640, 8, 5120), (600, 3, 5768),
+                                   (1600, 2, 2048), (1024, 6, 3096), (1100, 5, 7168), (1300, 1, 3584)])
+def test_combine_behind_one_node(T, k, H):
+    """A step whose layout and dispatch are one node: the sums of the receive rows, and of other rows of the same size, as
+    the calls one by one give them."""
+    step = Step(T, k, H, 4, 6, 20)
+    graph = None
+    try:
+        w = torch.rand((T, k), device="cuda")
+        y = torch.randn((T * k, H), device="cuda").to(torch.bfloat16)
+        out = [torch.zeros((T, H), dtype=torch.bfloat16, device="cuda") for _ in range(2)]
+
+        def combine():
+            step.ctx.combine(step.recv.view(torch.bfloat16), w, out[0], T, step.stream)
+            step.ctx.combine(y, w, out[1], T, step.stream)
+
+        def renew():
+            step.renew()
+            step.x.copy_(torch.randn((T, H), device="cuda").to(torch.bfloat16).view(torch.uint8))
+            torch.cuda.synchronize()
+
+        graph, n = step.capture(step.layout, step.dispatch, combine)
+        assert n == 3
+        for _ in range(2):
+            renew()
+            graph.launch(step.stream)
+            step.stream.synchronize()
+            got = [o.clone() for o in out]
+            for o in out:
+                o.zero_()
+            step.recv.fill_(0x5A)
+            torch.cuda.synchronize()
+            for call in (step.layout, step.dispatch, combine):
+                call()
+            step.stream.synchronize()
+            assert all(torch.equal(a, b) and bool(a.any()) for a, b in zip(got, out))
+    finally:
+        if graph is not None:
+            graph.destroy()
+        step.ctx.destroy()
+
+
 class KernelNodeParams(ctypes.Structure):
     _fields_ = [("block", ctypes.c_uint32 * 3), ("extra", ctypes.c_void_p), ("func", ctypes.c_void_p),
                 ("grid", ctypes.c_uint32 * 3), ("args", ctypes.c_void_p), ("lds", ctypes.c_uint32)]
