@@ -435,15 +435,7 @@ static hipError_t launch_pack_any(eep_ctx* c, const int32_t* rows, const void* x
 
 // With the layout in one launch the narrow pieces are the better ones up to larger sizes, also where another kernel writes what
 // combine reads (top-8, T = 1024 to 1536 of 1024 channels, 16 to 24 MiB of receive rows: 1.17-1.20 times as fast as two launches,
-// 1.09-1.12 with wider pieces; with a scaling stage 1.03-1.10 and 1.02-1.10).  Held stores (rows.hpp): write-through's time over
-// theirs, graphs of 4 steps, one / two / three sets of buffers in turn, by MiB of receive rows.  Combine reads the rows: 12 1.00-1.05 /
-// 1.00-1.08 / 1.00-1.07, 16 1.01-1.07 / 1.04-1.08 / 1.03-1.06, 20 1.03-1.08 / 1.02-1.07 / 1.01-1.04, 28 1.06-1.12 / 0.99-1.05 / 0.97-1.02,
-// 36 1.07-1.11 / 0.95-1.01 / 0.95-0.99.  A scaling stage writes others: 12 1.00-1.06 / 0.99-1.06 / 0.98-1.01, 16 1.01-1.10 / 0.98-1.01 /
-// 0.97-0.98, 20 0.99-1.06 / 0.96-0.99 / 0.95-0.98, 28 0.95-1.00 / 0.95-0.98 / 0.94-0.97.  fp8: 4 1.00-1.03 / 1.00-1.06 / 1.00-1.06,
-// 8 1.02-1.10 / 1.05-1.07 / 0.99-1.02, 10 1.03-1.08 / 0.98-1.02 / 0.96-0.98, 13 1.01-1.05 / 0.94-0.97 / 0.94-0.95.  (In a dispatch
-// of its own they gain where the layout's node does, but lose there too: three sets in turn, call by call, 14 / 20 / 26 MiB 0.96-1.06 /
-// 0.97-1.05 / 0.95-1.03 with the rows read by combine, 0.97-0.99 / 0.94-0.98 / 0.93-1.00 with a scaling stage; quantised, 7 / 9 / 12 MiB
-// of codes 0.98 / 0.95 / 0.92.  No such dispatch holds them.)
+// 1.09-1.12 with wider pieces; with a scaling stage 1.03-1.10 and 1.02-1.10).  Held stores: pack_holds_rows in rows.hpp.
 bool pack_pieces(const eep_ctx* c, const void* x, const float* x_scale, void* recv_x, float* recv_scale, int T,
                  PackPieces* out) {
   const int row_vecs = (int)(c->x_row_bytes / 16), scale_vecs = x_scale != nullptr ? (int)(c->scale_row_bytes / 16) : 0;
@@ -457,7 +449,7 @@ bool pack_pieces(const eep_ctx* c, const void* x, const float* x_scale, void* re
     const int parts = (chunks + 6) / 7, even = (chunks + parts - 1) / parts;
     vecs = even <= 2 ? even : even <= 4 ? 4 : 7;
   }
-  const bool held = scale_vecs > 0 ? mib_between(x_bytes * c->k, 4, 8) : mib_between(x_bytes * c->k, 12, 28);
+  const bool held = pack_holds_rows(x_bytes * c->k, scale_vecs > 0);
   *out = {x, x_scale, recv_x, recv_scale, (uint32_t)row_vecs, (uint32_t)scale_vecs,
           (uint32_t)((chunks + vecs - 1) / vecs + (scale_vecs > 0)), vecs, held};
   return true;

@@ -1,6 +1,6 @@
-"""Dispatch, expansion, quantisation and the scaling stand-in at the sizes between which stores are held in the
-L2s, and one step to either side of them (expansion holds its own in captured steps only, the stand-in more of them
-there): every form of each kernel (whole rows, pieces of one and two kilobytes, rows with a remainder, scale rows, a
+"""Stores that are held in the L2s: a dispatch in one node with its layout, expansion and the scaling stand-in at the limits
+of the sizes at which they hold theirs, and one step to either side.  Beside them a dispatch of its own and quantisation, which
+never do, at the same sizes, in every form (whole rows, pieces of one and two kilobytes, rows with a remainder, scale rows, a
 group that needs the division).  Moved bytes equal, rows past the last routed pair untouched."""
 import re
 import subprocess
@@ -13,6 +13,7 @@ from paper_2605_10670_amd import binding, build
 
 import gpu_util as gu
 from test_gpu_layout_edges import instance
+from test_gpu_layout_pack import Step, last_kernel
 
 gpu = pytest.mark.gpu
 
@@ -73,6 +74,29 @@ def test_dispatch(T, k, H, dtype):
             assert torch.equal(got[:N], scales["x_scale"][src[:N] // k]) and bool((got[N:] == -1.0).all())
     finally:
         ctx.destroy()
+
+
+# receive rows of 12 to 28 MiB, fp8 4 to 8: both limits and the next size
+@gpu
+@pytest.mark.parametrize("T,H,dtype,want", [
+    (384, 2048, "bf16", True), (383, 2048, "bf16", False), (896, 2048, "bf16", True), (897, 2048, "bf16", False),
+    (256, 7168, "bf16", True), (500, 2888, "bf16", True), (600, 3080, "bf16", False), (192, 2048, "f32", True),
+    (256, 2048, "fp8", True), (255, 2048, "fp8", False), (512, 2048, "fp8", True), (513, 2048, "fp8", False)])
+def test_dispatch_with_its_layout(oracle, T, H, dtype, want):
+    step = Step(T, 8, H, 1, 24, 20, dtype)
+    graph = None
+    try:
+        kernel = {}
+        graph, n = step.capture(step.layout, step.dispatch, lambda: kernel.update(flags=last_kernel(step.stream).word(8)))
+        assert n == 1 and kernel["flags"] >> 31 == want
+        for _ in range(2):
+            step.renew()
+            graph.launch(step.stream)
+            step.check(oracle)
+    finally:
+        if graph is not None:
+            graph.destroy()
+        step.ctx.destroy()
 
 
 @gpu

@@ -194,17 +194,22 @@ def test_combine_behind_one_node(T, k, H):
 
 class KernelNodeParams(ctypes.Structure):
     _fields_ = [("block", ctypes.c_uint32 * 3), ("extra", ctypes.c_void_p), ("func", ctypes.c_void_p),
-                ("grid", ctypes.c_uint32 * 3), ("args", ctypes.c_void_p), ("lds", ctypes.c_uint32)]
+                ("grid", ctypes.c_uint32 * 3), ("args", ctypes.POINTER(ctypes.POINTER(ctypes.c_uint32))),
+                ("lds", ctypes.c_uint32)]
+
+    def word(self, i):
+        """Argument i, a 32-bit word."""
+        return self.args[i][0]
 
 
-def last_grid(stream):
-    """Workgroups of the kernel that the running capture of `stream` holds last."""
+def last_kernel(stream):
+    """The kernel that the running capture of `stream` holds last."""
     lib, status, node, n = hip(), ctypes.c_int(), ctypes.POINTER(ctypes.c_void_p)(), ctypes.c_size_t()
     assert lib.hipStreamGetCaptureInfo_v2(ctypes.c_void_p(stream.cuda_stream), ctypes.byref(status), None, None,
                                           ctypes.byref(node), ctypes.byref(n)) == 0 and n.value == 1
     params = KernelNodeParams()
     assert lib.hipGraphKernelNodeGetParams(ctypes.c_void_p(node[0]), ctypes.byref(params)) == 0
-    return params.grid[0]
+    return params
 
 
 def test_combine_takes_the_rows_as_the_last_dispatch_cut_them():
@@ -221,7 +226,7 @@ def test_combine_takes_the_rows_as_the_last_dispatch_cut_them():
 
     def combine():
         step.ctx.combine(step.recv.view(torch.bfloat16), w, out, T, step.stream)
-        grids.append(last_grid(step.stream))
+        grids.append(last_kernel(step.stream).grid[0])
 
     try:
         for calls in ((step.layout, step.dispatch), (step.layout, step.dispatch, step.dispatch),
