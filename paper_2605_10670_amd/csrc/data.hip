@@ -1246,11 +1246,12 @@ hipError_t launch_stub(eep_ctx* c, int kind, const void* recv_x, const float* re
         hipLaunchKernelGGL(k_stub_copy, grid, block, 0, st, (const u32x4*)recv_x, (u32x4*)y,
                            c->status, row_vecs, (int)r0);
       } else {
-        // Held stores (rows.hpp), for more rows in a captured step: write-through's time over theirs, whole steps, 10-16 / 18 / 24 / 30 MiB:
+        // Held stores (rows.hpp), in a captured step only: write-through's time over theirs, whole steps, 10-16 / 18 / 24 / 30 MiB:
         // in graphs 1.11-1.18 / 1.08-1.15 / 1.04-1.10 / 1.02-1.04, three sets of buffers in turn 0.99-1.03 / 0.99-1.04 / 1.00-1.03 /
-        // 0.98; call by call 1.02-1.16 / 1.04-1.10 / 1.06-1.12 / 1.05, three sets in turn 0.97-1.02 / 0.98-1.00 / 0.97-0.98 / 0.97.
-        const int64_t bytes = rows * c->x_row_bytes;
-        const bool held = mib_between(bytes, 10, 16) || (mib_between(bytes, 16, 26) && is_captured(st));
+        // 0.98.  Call by call a program may have other buffers each time, and then held stores lose (8 shapes, rows of 2 to 16 KiB,
+        // top-2 to 8): one set of buffers, 10-11 / 12 / 14 / 16 MiB 1.02-1.09 / 1.01-1.09 / 1.03-1.13 / 1.06-1.17, two in turn
+        // 0.95-1.06 / 0.96-1.05 / 0.97-1.04 / 0.97-1.02, three 0.97-1.01 / 0.97-1.01 / 0.96-1.00 / 0.95-1.00.
+        const bool held = mib_between(rows * c->x_row_bytes, 10, 26) && is_captured(st);
         const bool bf16 = c->cfg.x_dtype == EEP_BF16;
         auto kern = held ? (bf16 ? k_stub_scale<true, true> : k_stub_scale<false, true>)
                          : (bf16 ? k_stub_scale<true, false> : k_stub_scale<false, false>);

@@ -25,8 +25,8 @@ __device__ __forceinline__ uint32_t token_of(uint32_t n, uint32_t parts, uint32_
 // kernel, line by line, and write-through is better; and of a few MB there is nothing to gain, but the write-back at
 // the end takes longer than stores that have long arrived.  A buffer whose lines the L2s still hold from the step before gains
 // most, one that was not touched lately least: stores that are held then take the place of other lines, and write-through
-// ones have no line in another L2 to end.  A captured step is replayed on its own buffers, so more is held there; calls
-// one by one may have other buffers each time.  The limits at the launches are measured with both.
+// ones have no line in another L2 to end.  A captured step is replayed on its own buffers, so stores are held only
+// there; calls one by one may have other buffers each time.  The limits at the launches are measured with both.
 //
 // The data registers of a store of more than 8 bytes may not be rewritten by the next two
 // wait states' vector instructions.  The compiler keeps that distance for its own stores but

@@ -1,5 +1,5 @@
 """Stores that are held in the L2s: a dispatch in one node with its layout, expansion and the scaling stand-in at the limits
-of the sizes at which they hold theirs, and one step to either side.  Beside them a dispatch of its own and quantisation, which
+of the sizes at which they hold theirs (in captured steps only), and one step to either side.  Beside them a dispatch of its own and quantisation, which
 never do, at the same sizes, in every form (whole rows, pieces of one and two kilobytes, rows with a remainder, scale rows, a
 group that needs the division).  Moved bytes equal, rows past the last routed pair untouched."""
 import re
@@ -158,6 +158,34 @@ def test_scaling_stand_in(T, H, dtype):
             y.fill_(7.0)
             launch(ctx, captured, lambda st: ctx.expert_stub("scale", recv, y, T, expert_scale=s, stream=st))
             assert torch.equal(y[:N], want) and bool((y[N:] == 7.0).all())
+    finally:
+        ctx.destroy()
+
+
+@gpu
+@pytest.mark.parametrize("call", ["stand-in", "expansion"])
+def test_held_only_in_a_captured_step(call):
+    """Call by call the next buffers may be other ones, and held stores lose there."""
+    T, k, H = 256, 8, 4096                             # 16 MiB of receive rows
+    ctx, _, _ = context(T, k, H)
+    try:
+        recv, y = (torch.zeros((T * k, H), device="cuda", dtype=torch.bfloat16) for _ in range(2))
+        scale = torch.ones(20, device="cuda")
+        ctx.dedup_layout(T)
+
+        def run(st):
+            if call == "stand-in":
+                ctx.expert_stub("scale", recv, y, T, expert_scale=scale, stream=st)
+            else:
+                ctx.expand(recv, y, T, stream=st)
+
+        launch(ctx, True, run)
+        for captured in (False, True):
+            with torch.profiler.profile(activities=[torch.profiler.ProfilerActivity.CUDA]) as prof:
+                launch(ctx, captured, run)
+                torch.cuda.synchronize()
+            names = [e.key for e in prof.key_averages() if "k_stub_scale" in e.key or "k_expand" in e.key]
+            assert len(names) == 1 and re.search(r"(true|false)>\(", names[0])[1] == str(captured).lower(), names
     finally:
         ctx.destroy()
 
