@@ -301,30 +301,24 @@ static PassShape pass_shape(int row_vecs, int split, int64_t rows, int max_vecs)
 template <int U, bool EXACT>
 static hipError_t launch_pack_t(eep_ctx* c, const int32_t* rows, const void* x, void* recv_x,
                                 int T, hipStream_t st) {
-  hipLaunchKernelGGL((k_pack<U, EXACT>), dim3(T), dim3(64), 0, st,
-                     (const u32x4*)x, rows, c->k, (int)(c->x_row_bytes / 16), (u32x4*)recv_x);
+  hipLaunchKernelGGL((k_pack<U, EXACT>), dim3(T), dim3(64), 0, st, (const u32x4*)x, rows, c->k,
+                     (int)(c->x_row_bytes / 16), (u32x4*)recv_x);
   return hipGetLastError();
-}
-
-template <int U, bool EXACT, bool SCALES>
-static auto pack_split_for(int k) {
-#define EEP_SPLIT(K) k_pack_split<U, EXACT, K, SCALES>
-  static const decltype(&EEP_SPLIT(0)) of[kSplitMaxK + 1] = {EEP_SPLIT(0), EEP_SPLIT(1), EEP_SPLIT(2),
-                                                             EEP_SPLIT(3), EEP_SPLIT(4), EEP_SPLIT(5),
-                                                             EEP_SPLIT(6), EEP_SPLIT(7), EEP_SPLIT(8)};
-#undef EEP_SPLIT
-  return of[k];
 }
 
 template <int U, bool EXACT, bool SCALES>
 static hipError_t launch_pack_split_t(eep_ctx* c, const int32_t* rows, const void* x,
                                       const float* x_scale, void* recv_x, float* recv_scale, int T,
                                       int parts, hipStream_t st) {
+  static const decltype(&k_pack_split<U, EXACT, 0, SCALES>) of[kSplitMaxK + 1] = {
+      k_pack_split<U, EXACT, 0, SCALES>, k_pack_split<U, EXACT, 1, SCALES>,
+      k_pack_split<U, EXACT, 2, SCALES>, k_pack_split<U, EXACT, 3, SCALES>,
+      k_pack_split<U, EXACT, 4, SCALES>, k_pack_split<U, EXACT, 5, SCALES>,
+      k_pack_split<U, EXACT, 6, SCALES>, k_pack_split<U, EXACT, 7, SCALES>,
+      k_pack_split<U, EXACT, 8, SCALES>};
   const int64_t grid = (int64_t)T * parts;
   const bool compiled = c->k <= kSplitMaxK && c->x_row_bytes < (int64_t)1 << 32;  // (32-bit offsets there)
-  const int k = compiled ? c->k : 0;
-  auto kern = pack_split_for<U, EXACT, SCALES>(k);
-  hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3(64), 0, st,
+  hipLaunchKernelGGL(of[compiled ? c->k : 0], dim3((unsigned)grid), dim3(64), 0, st,
                      (const u32x4*)x, rows, c->k, (uint32_t)(c->x_row_bytes / 16), (uint32_t)parts,
                      part_magic(parts, grid), (u32x4*)recv_x, (const u32x4*)x_scale,
                      (u32x4*)recv_scale, (uint32_t)(c->scale_row_bytes / 16));
@@ -366,7 +360,7 @@ static hipError_t launch_pack_payload(eep_ctx* c, const int32_t* rows, const voi
   if (x_scale != nullptr || ps.parts > 1) {
 #define EEP_PACK_SPLIT(U, SCALES)                                                                 \
   return ps.exact ? launch_pack_split_t<U, true, SCALES>(c, rows, x, x_scale, recv_x, recv_scale, \
-                                                         T, ps.parts + SCALES, st)          \
+                                                         T, ps.parts + SCALES, st)                \
                   : launch_pack_split_t<U, false, SCALES>(c, rows, x, x_scale, recv_x, recv_scale, \
                                                           T, ps.parts + SCALES, st)
     if (x_scale != nullptr) {
@@ -398,7 +392,7 @@ static hipError_t launch_pack_payload(eep_ctx* c, const int32_t* rows, const voi
   switch (ps.u) {
 #define EEP_PACK_CASE(U)                                                                \
   case U:                                                                               \
-    return ps.exact ? launch_pack_t<U, true>(c, rows, x, recv_x, T, st)           \
+    return ps.exact ? launch_pack_t<U, true>(c, rows, x, recv_x, T, st)                 \
                     : launch_pack_t<U, false>(c, rows, x, recv_x, T, st);
     EEP_PACK_CASE(14) EEP_PACK_CASE(13) EEP_PACK_CASE(12) EEP_PACK_CASE(11) EEP_PACK_CASE(10)
     EEP_PACK_CASE(9) EEP_PACK_CASE(8) EEP_PACK_CASE(7) EEP_PACK_CASE(6) EEP_PACK_CASE(5)
@@ -1117,7 +1111,7 @@ __global__ __launch_bounds__(256) void k_stub_copy(const u32x4* __restrict__ rec
   if (row >= status[0]) return;
   for (int v = threadIdx.x; v < row_vecs; v += blockDim.x)
     store_row(&y[(int64_t)row * row_vecs + v],
-                  __builtin_nontemporal_load(&recv[(int64_t)row * row_vecs + v]));
+              __builtin_nontemporal_load(&recv[(int64_t)row * row_vecs + v]));
 }
 
 // y[row] = round(s[expert of row] * recv[row]).  The way to the row's scale is four dependent
