@@ -253,12 +253,12 @@ __device__ __forceinline__ bool repeats_earlier(int e, int j, const int32_t* tok
 // that nobody has to walk the words for it.
 constexpr int kMaxPairsPerThread = kTileTokens * kMaxTopk / kMapThreads;
 
-// Maps this thread's pairs tid, tid + kMapThreads, ... of a batch of `npairs` (first token t0):
+// Maps this thread's pairs tid, tid + NT, ... (NT threads) of a batch of `npairs` (first token t0):
 // slots to slot[] (-1: not routed), token bits to s_bm
 // ([P][stride], zeroed), counts to s_count (zeroed), dropped pairs to s_drop {uncovered, masked}
 // (zeroed).  my_e holds the router indices already loaded; s_idx the same in LDS when KC == 0.  Slots of
 // the pairs [own_lo, own_hi) are written to slot_of.
-template <int KC, int U>
+template <int KC, int U, int NT = kMapThreads>
 __device__ __forceinline__ void map_pairs(const RouteTables& rt, const int (&my_e)[U],
                                           const int32_t* s_idx, int (&slot)[U], uint32_t* s_bm,
                                           int stride, int32_t* s_count, int32_t* s_drop, int npairs,
@@ -267,9 +267,9 @@ __device__ __forceinline__ void map_pairs(const RouteTables& rt, const int (&my_
   const int wave0 = __builtin_amdgcn_readfirstlane(threadIdx.x & ~63);
 #pragma unroll
   for (int u = 0; u < U; ++u) {
-    const int i = threadIdx.x + u * kMapThreads;
+    const int i = threadIdx.x + u * NT;
     slot[u] = -1;
-    if (wave0 + u * kMapThreads >= npairs) break;  // a wavefront without pairs stays out of the others' way
+    if (wave0 + u * NT >= npairs) break;  // a wavefront without pairs stays out of the others' way
     const int tl = i / k, j = i - tl * k;
     const int e = my_e[u];
     const bool repeated = repeats_earlier<KC>(e, j, KC == 0 && i < npairs ? s_idx + tl * k : s_idx);
@@ -1334,7 +1334,7 @@ __global__ __launch_bounds__(NT) void k_layout_pack_small(
   bool last = false;  // of the workgroups to have the mask (thread 0)
   if (agree.several && tid == 0) last = agree.arrive_last();
   __syncthreads();
-  map_pairs<K, 1>(rt, my_e, s_slot, slot, s_bm, stride, s_count, s_drop, npairs, K, E, 0, policy, 0, 0, slot_of);
+  map_pairs<K, 1, NT>(rt, my_e, s_slot, slot, s_bm, stride, s_count, s_drop, npairs, K, E, 0, policy, 0, 0, slot_of);
   if (tid < npairs) s_slot[tid] = slot[0];
   __syncthreads();
   scan_totals([=](int p) { return s_count[p]; }, s_offset, P, wave, NT / 64);
