@@ -601,7 +601,11 @@ __global__ __launch_bounds__(kFusedThreads) void k_scan_position(
 // there ONE workgroup does it all (each entry of the replica lists is found live or
 // dead once, and every pair, count and row follows from that), up to the size from
 // which the tiled path, where each pair is mapped once, is as fast: T = 32 / 128 / 256 / 384
-// 4.0 / 4.4 / 5.6 / 7.2 us, in tiles 7.5.  The launch
+// 4.0 / 4.4 / 5.6 / 7.2 us, in tiles 7.5.  Tiles are what comes next without a context, where nobody can agree on a
+// mask; the limit is the same with several, where k_layout_once comes next.  (That one is the faster already from about 2048 pairs
+// on, with many slots earlier and with few later, a layout in a graph of 40, one workgroup / agreement: 32 ranks x 9 slots, top-8, T = 160 / 224 / 256 /
+// 320 / 384 4.8 / 5.1 / 5.5 / 6.25 / 7.05 and 5.05 / 5.3 / 4.9 / 5.1 / 5.3 us; 64 x 9, T = 192 / 384 7.8 / 10.1 and 5.5 / 5.6; 4 x 6, T = 256 / 320 / 384
+// 4.3 / 4.9 / 5.2 and 4.8 / 4.9 / 4.95.)  The launch
 // decides by the number of contexts; a launch captured while there was one is
 // overruled by the word behind the membership version, which says that there are more.
 // ---------------------------------------------------------------------------
@@ -2025,7 +2029,7 @@ hipError_t launch_layout(const LayoutIO& c, int T, hipStream_t st, bool* one_lau
   const float inv_S = 1.0f / (float)c.S;
   const bool overlaps = writes_its_input(c, T), solo = c.mask_may_change || overlaps;
   const int small = layout_small_workgroups(c.E, c.P, c.R, T, c.k, solo);
-  // Several contexts: beyond what one workgroup does, k_layout_once with its workgroups' agreement on a mask is
+  // Several contexts: beyond the sizes for one workgroup, k_layout_once with its workgroups' agreement on a mask is
   // faster than tiles (32 ranks x 9 slots, a layout in a graph of 40; top-8, T = 416 / 512 / 1024 / 2048: 5.6 / 5.4 / 6.1 / 7.05 us,
   // in tiles 7.75 / 7.5 / 7.7 / 7.8; top-2, T = 512 / 4096 4.8 / 5.85 (7.4 / 7.7); all tokens alike, T = 2048 7.65 (7.6)).
   const bool agree = c.mask_may_change && c.can_agree && !overlaps && small == 0;
@@ -2133,6 +2137,10 @@ static bool set_node(hipGraphNode_t node, const void* kernel, int grid, int thre
   return false;
 }
 
+// The widths of a piece, us a step in graphs of 4 with 1 / 2 / 4 / 7 KiB: top-8, 512 tokens of 10 KiB 23.25 / 24.4 / 24.4 / 23.8, 640 of
+// 14 KiB 34.2 / 31.2 / 32.05 / 31.7, 768 of 8 KiB 23.0 / 23.9 / 27.0 / 30.0, 1024 of 7 KiB 28.6 / 27.7 / 27.7 / 27.3; top-4, 1024 of 14 KiB
+// 29.6 / 29.6 / 28.2 / 28.1; top-2, 1536 of 8 KiB 19.3 / 16.6 / 17.4 / 18.7, 2048 of 4 KiB 17.3 / 14.9 / 15.8 / 15.9.  A top-k that is
+// not here would take two launches, 1.14 times as long over 360 shapes of top-1 to 10.
 template <uint32_t U>
 static const void* layout_pack_once_for(int k) {
   static const decltype(&k_layout_pack_once<1, U>) of[kOnceMaxK] = {
@@ -2143,9 +2151,11 @@ static const void* layout_pack_once_for(int k) {
 }
 
 // How many pieces a workgroup takes.  More pieces than 8 wavefronts of every CU make further rounds of workgroups, which are
-// resident together up to three (stay_resident), and in these all CUs are to get the same: with 16
-// wavefronts in 280 workgroups 320 tokens of 7168 channels took 25.6 us a step, with 10 in 448 21.9, with 6 in 752 21.7, with 9 in
-// 504 21.6.  Beyond three rounds (768 pieces to an XCD; 896 tokens of 7168 channels) two launches are as fast, and with three
+// resident together up to three (stay_resident), and in these all CUs are to get the same: 320 tokens of 7168 channels took
+// 25.6 us a step with 16 wavefronts in 280 workgroups (35 for the 32 CUs of an XCD), 21.9 with 10 in 448, 21.7 with 6 in 752, 21.6 with 9 in
+// 504.  One even round of more wavefronts is no better, though the batch is then laid out once on a CU: T = 160 / 192 / 224 / 256 / 288 (9 to 16
+// wavefronts, 1024 threads) 16.15 / 17.3 / 18.6 / 19.3 / 21.8 us, two rounds of 512 threads 15.8 / 16.9 / 18.1 / 18.8 / 21.3, three 15.7 /
+// 16.8 / 18.0 / 18.7 / 21.4; with a skewed router the same (T = 256 19.15 / 18.8 / 18.7).  Beyond three rounds (768 pieces to an XCD; 896 tokens of 7168 channels) two launches are as fast, and with three
 // rounds of many pairs, all of which every workgroup lays out: two launches' time over that of one, 1088 channels, 288 slots,
 // top-4 1536 / 2048 tokens 1.09 / 1.06, top-8 1.05 / 1.01; with a skewed router 1.03 / 0.975 and 0.98 / 0.935.
 constexpr int kLayoutPackTokens = 2048, kXcdCus = 32, kPieceWaves = 8, kPieceRounds = 3, kThirdRoundPairs = 6144;

@@ -46,7 +46,10 @@ __device__ __forceinline__ void copy_chunk(u32x4* weights, const u32x4* backup, 
 // Moves that only the backup can serve, where it is in host memory: kLinkBlocks workgroups take 4 KiB of them in turn.  Bound by
 // the host link, which wants few requests in flight: 28.3 MB in one launch of 64 KiB to a workgroup, all of it asked for
 // at once, take 558 us (50.7 GB/s); a vector per thread of 32 / 64 / 128 / 256 / 512 / 1024 workgroups 502 / 500 / 504 / 503 / 509 / 544,
-// four of 64 / 256 503 / 542, eight of 16 / 64 / 256 504 / 510 / 549; the copy engine 508.
+// four of 64 / 256 503 / 542, eight of 16 / 64 / 256 504 / 510 / 549; the copy engine 508.  Whole calls, a full grid / these: 8 experts
+// of 1 MB 50.3 / 55.7 GB/s, 6 and 12 of 4.7 MB 51.5 and 53.6 / 56.9 and 57.2, 7 of 18.9 MB 55.0 / 57.5, 7 and 14 of 44 MB 55.6 and
+// 55.8 / 57.5 and 57.6.  (A move whose peer has dropped out meanwhile is seen on the GPU only, and takes the backup's copy at the full
+// grid's rate.)
 constexpr int kLinkBlocks = 64;
 __device__ __forceinline__ void copy_over_link(u32x4* weights, const u32x4* backup, int64_t slot_vecs, int block,
                                                const int32_t* mv_dst, const int32_t* mv_expert, int n) {
