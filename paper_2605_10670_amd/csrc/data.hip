@@ -429,7 +429,7 @@ static hipError_t launch_pack_any(eep_ctx* c, const int32_t* rows, const void* x
 
 // With the layout in one launch the narrow pieces are the better ones up to larger sizes, also where another kernel writes what
 // combine reads (top-8, T = 1024 to 1536 of 1024 channels, 16 to 24 MiB of receive rows: 1.17-1.20 times as fast as two launches,
-// 1.09-1.12 with wider pieces; with a scaling stage 1.03-1.10 and 1.02-1.10).  Held stores: pack_holds_rows in rows.hpp.
+// 1.09-1.12 with wider pieces; with a scaling stage 1.03-1.10 and 1.02-1.10).  Held stores: the call that reads the rows says so (hold_rows in api.hip).
 bool pack_pieces(const eep_ctx* c, const void* x, const float* x_scale, void* recv_x, float* recv_scale, int T,
                  PackPieces* out) {
   const int row_vecs = (int)(c->x_row_bytes / 16), scale_vecs = x_scale != nullptr ? (int)(c->scale_row_bytes / 16) : 0;
@@ -443,9 +443,8 @@ bool pack_pieces(const eep_ctx* c, const void* x, const float* x_scale, void* re
     const int parts = (chunks + 6) / 7, even = (chunks + parts - 1) / parts;
     vecs = even <= 2 ? even : even <= 4 ? 4 : 7;
   }
-  const bool held = pack_holds_rows(x_bytes * c->k, scale_vecs > 0);
   *out = {x, x_scale, recv_x, recv_scale, (uint32_t)row_vecs, (uint32_t)scale_vecs,
-          (uint32_t)((chunks + vecs - 1) / vecs + (scale_vecs > 0)), vecs, held};
+          (uint32_t)((chunks + vecs - 1) / vecs + (scale_vecs > 0)), vecs, false};
   return true;
 }
 

@@ -75,6 +75,16 @@ struct PatchArray {
   int n;
 };
 
+// A dispatch in pieces of `vecs` * 64 vectors of a row, `parts` to a token; for payloads with scales the last of these is
+// the scale row.  held: rows.hpp.
+struct PackPieces {
+  const void *x, *x_scale;
+  void *recv, *recv_scale;
+  uint32_t row_vecs, scale_vecs, parts;
+  int vecs;
+  bool held;
+};
+
 }  // namespace eep
 
 // The membership of one EP instance (the peer table's `active` column, Fig. 7):
@@ -148,6 +158,12 @@ struct eep_ctx {
   // How the receive rows were cut last, if by a dispatch in one launch with its layout (0 or 1 or 2, as pack_split in
   // data.hip), else -1.
   int dispatched_split;
+  // Then also that launch's node, for the call that reads the rows (hold_rows in api.hip): its capture, router indices (null: no
+  // such node), pieces, and the node that a call directly behind it waits for.
+  const int32_t* packed_idx;
+  unsigned long long packed_in;
+  hipGraphNode_t packed_node, packed_last;
+  eep::PackPieces packed;
   int last_hip_error;
   int64_t field_ints[EEP_V_NUM_FIELDS];
 };
@@ -177,15 +193,6 @@ bool layout_shape_fits(int E, int P, int R, int k);  // tables fit the kernels' 
 // (*one_launch, if asked for: whether it was one)
 hipError_t launch_layout(const LayoutIO& io, int T, hipStream_t st, bool* one_launch = nullptr);
 hipError_t launch_layout(eep_ctx* c, const int32_t* topk_idx, int T, hipStream_t st, bool* one_launch);
-// A dispatch in pieces of `vecs` * 64 vectors of a row, `parts` to a token; for payloads with scales the last of these is
-// the scale row.  held: rows.hpp.
-struct PackPieces {
-  const void *x, *x_scale;
-  void *recv, *recv_scale;
-  uint32_t row_vecs, scale_vecs, parts;
-  int vecs;
-  bool held;
-};
 // Those of a dispatch that goes with its layout; false: it goes in a launch of its own.
 bool pack_pieces(const eep_ctx* c, const void* x, const float* x_scale, void* recv_x, float* recv_scale, int T,
                  PackPieces* out);

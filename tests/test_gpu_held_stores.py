@@ -1,4 +1,4 @@
-"""Stores that are held in the L2s: a dispatch in one node with its layout, expansion and the scaling stand-in at the limits
+"""Stores that are held in the L2s: a dispatch in one node with its layout, by who reads its rows; expansion and the scaling stand-in at the limits
 of the sizes at which they hold theirs (in captured steps only), and one step to either side.  Beside them a dispatch of its own and quantisation, which
 never do, at the same sizes, in every form (whole rows, pieces of one and two kilobytes, rows with a remainder, scale rows, a
 group that needs the division).  Moved bytes equal, rows past the last routed pair untouched."""
@@ -13,7 +13,7 @@ from paper_2605_10670_amd import binding, build
 
 import gpu_util as gu
 from test_gpu_layout_edges import instance
-from test_gpu_layout_pack import Step, last_kernel
+from test_gpu_layout_pack import Step, kernel_of, last_node
 
 gpu = pytest.mark.gpu
 
@@ -76,27 +76,60 @@ def test_dispatch(T, k, H, dtype):
         ctx.destroy()
 
 
-# receive rows of 12 to 28 MiB, fp8 4 to 8: both limits and the next size
+# who reads the receive rows: combine, of 12 to 28 MiB; a stand-in, of 12 to 16, fp8 4 to 8 (both limits and the next size);
+# and calls that do not, or not directly behind the dispatch
 @gpu
-@pytest.mark.parametrize("T,H,dtype,want", [
-    (384, 2048, "bf16", True), (383, 2048, "bf16", False), (896, 2048, "bf16", True), (897, 2048, "bf16", False),
-    (256, 7168, "bf16", True), (500, 2888, "bf16", True), (600, 3080, "bf16", False), (192, 2048, "f32", True),
-    (256, 2048, "fp8", True), (255, 2048, "fp8", False), (512, 2048, "fp8", True), (513, 2048, "fp8", False)])
-def test_dispatch_with_its_layout(oracle, T, H, dtype, want):
-    step = Step(T, 8, H, 1, 24, 20, dtype)
-    graph = None
+@pytest.mark.parametrize("T,H,dtype,reader,want", [
+    (384, 2048, "bf16", "combine", True), (383, 2048, "bf16", "combine", False), (896, 2048, "bf16", "combine", True),
+    (897, 2048, "bf16", "combine", False), (256, 7168, "bf16", "combine", True), (500, 2888, "bf16", "combine", True),
+    (600, 3080, "bf16", "combine", False), (192, 2048, "f32", "combine", True),
+    (384, 2048, "bf16", "stand-in", True), (383, 2048, "bf16", "stand-in", False), (512, 2048, "bf16", "stand-in", True),
+    (513, 2048, "bf16", "stand-in", False), (256, 2048, "fp8", "stand-in", True), (255, 2048, "fp8", "stand-in", False),
+    (512, 2048, "fp8", "stand-in", True), (513, 2048, "fp8", "stand-in", False),
+    (256, 7168, "bf16", "nobody", False), (256, 2048, "fp8", "nobody", False), (256, 7168, "bf16", "other rows", False),
+    (256, 7168, "bf16", "after a kernel", False), (256, 7168, "bf16", "after the signals", True),
+    (256, 7168, "bf16", "after a dispatch", False)])
+def test_dispatch_with_its_layout(oracle, T, H, dtype, reader, want):
+    k = 8
+    step = Step(T, k, H, 1, 24, 20, dtype)
+    ctx, st = step.ctx, step.stream
+    y_type = torch.float32 if dtype == "f32" else torch.bfloat16
+    rows = step.recv if dtype == "fp8" else step.recv.view(y_type)
+    y, w = torch.zeros((T * k, H), device="cuda", dtype=y_type), torch.rand((T, k), device="cuda")
+    out, scale = torch.zeros((T, H), device="cuda", dtype=torch.bfloat16), torch.ones(20, device="cuda")
+    torch.cuda.synchronize()
+    graph, fused = None, {}
+
+    def read():
+        if reader == "nobody":
+            return
+        if reader == "stand-in":
+            ctx.expert_stub("dequant" if dtype == "fp8" else "scale", rows, y, T,
+                            recv_scale=step.scales.get("recv_scale"), expert_scale=scale, stream=st)
+        elif reader == "after a kernel":
+            with torch.cuda.stream(st):
+                w.mul_(1.0)
+        elif reader == "after the signals":
+            ctx.signal_experts_done(st)
+        elif reader == "after a dispatch":
+            step.dispatch()
+        ctx.combine(y if reader in ("stand-in", "other rows") else rows, w, out, T, st)
+
     try:
-        kernel = {}
-        graph, n = step.capture(step.layout, step.dispatch, lambda: kernel.update(flags=last_kernel(step.stream).word(8)))
-        assert n == 1 and kernel["flags"] >> 31 == want
+        if reader == "after the signals":
+            ctx.set_detection(1_000_000_000)
+        graph, n = step.capture(step.layout, step.dispatch, lambda: fused.update(node=last_node(st)), read,
+                                lambda: fused.update(flags=kernel_of(fused["node"]).word(8)))
+        assert n == {"nobody": 1, "stand-in": 3, "after a kernel": 3, "after the signals": 3, "after a dispatch": 3}.get(reader, 2)
+        assert fused["flags"] >> 31 == want
         for _ in range(2):
             step.renew()
-            graph.launch(step.stream)
+            graph.launch(st)
             step.check(oracle)
     finally:
         if graph is not None:
             graph.destroy()
-        step.ctx.destroy()
+        ctx.destroy()
 
 
 @gpu

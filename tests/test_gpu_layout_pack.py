@@ -202,14 +202,23 @@ class KernelNodeParams(ctypes.Structure):
         return self.args[i][0]
 
 
-def last_kernel(stream):
-    """The kernel that the running capture of `stream` holds last."""
+def last_node(stream):
+    """The node that the running capture of `stream` holds last."""
     lib, status, node, n = hip(), ctypes.c_int(), ctypes.POINTER(ctypes.c_void_p)(), ctypes.c_size_t()
     assert lib.hipStreamGetCaptureInfo_v2(ctypes.c_void_p(stream.cuda_stream), ctypes.byref(status), None, None,
                                           ctypes.byref(node), ctypes.byref(n)) == 0 and n.value == 1
+    return node[0]
+
+
+def kernel_of(node):
     params = KernelNodeParams()
-    assert lib.hipGraphKernelNodeGetParams(ctypes.c_void_p(node[0]), ctypes.byref(params)) == 0
+    assert hip().hipGraphKernelNodeGetParams(ctypes.c_void_p(node), ctypes.byref(params)) == 0
     return params
+
+
+def last_kernel(stream):
+    """The kernel that the running capture of `stream` holds last."""
+    return kernel_of(last_node(stream))
 
 
 def test_combine_takes_the_rows_as_the_last_dispatch_cut_them():
