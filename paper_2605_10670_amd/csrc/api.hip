@@ -48,6 +48,18 @@ bool captured_node(hipStream_t st, unsigned long long* capture, hipGraphNode_t* 
   return true;
 }
 
+// Nothing is known of who wrote the receive rows, or no more.
+void forget_rows(eep_ctx* c) {
+  c->dispatched_split = -1;
+  c->rows_node = nullptr;
+}
+void note_rows(eep_ctx* c, hipGraphNode_t node, unsigned long long capture, const int32_t* topk_idx, const PackPieces& rows) {
+  c->rows_node = c->rows_last = node;
+  c->rows_in = capture;
+  c->rows_idx = topk_idx;
+  c->rows = rows;
+}
+
 // A dispatch that is captured right behind its layout, with nothing else that waits for the layout, becomes part of the
 // layout's node, where there is a kernel for both: whatever the dispatch waits for, the layout waits for too, and so
 // nothing can tell the difference, but for the time.  Buffers that the two launches could share are refused: in one launch the
@@ -76,43 +88,37 @@ bool dispatch_with_layout(eep_ctx* c, const int32_t* topk_idx, const void* x, co
       !layout_pack_node(c, topk_idx, pieces, T, node))
     return false;
   c->dispatched_split = pieces.vecs <= 2 ? pieces.vecs : 0;
-  c->packed_idx = topk_idx;
-  c->packed_in = capture;
-  c->packed_node = c->packed_last = node;
-  c->packed = pieces;
+  note_rows(c, node, capture, topk_idx, pieces);
   return true;
 }
 
-// Nothing is known of the receive rows, or no more.
-void forget_dispatch(eep_ctx* c) {
-  c->dispatched_split = -1;
-  c->packed_idx = nullptr;
-}
-
-// Is what comes next in `st` captured directly behind a layout and dispatch in one node?
-bool behind_dispatch(eep_ctx* c, hipStream_t st) {
+// Is what comes next in `st` captured directly behind the node that wrote the receive rows?
+bool behind_rows(eep_ctx* c, hipStream_t st) {
   unsigned long long capture;
   hipGraphNode_t node;
-  return c->packed_idx != nullptr && captured_node(st, &capture, &node) && capture == c->packed_in &&
-         node == c->packed_last;
+  return c->rows_node != nullptr && captured_node(st, &capture, &node) && capture == c->rows_in && node == c->rows_last;
 }
 
-// The call that is captured now reads `rows`: if a layout and dispatch in one node directly ahead of it writes them, and `hold`
-// says so for the bytes that they have, its node is made to hold its stores in the L2s (rows.hpp).
-void hold_rows(eep_ctx* c, const void* rows, bool (*hold)(int64_t, bool), hipStream_t st) {
-  if (c->packed_idx == nullptr || rows != c->packed.recv || c->packed.held ||
-      !hold(c->layout_T * c->k * c->x_row_bytes, c->packed.scale_vecs > 0) || !behind_dispatch(c, st))
-    return;
-  c->packed.held = true;
-  layout_pack_node(c, c->packed_idx, c->packed, c->layout_T, c->packed_node);
+// The call that is captured now reads `rows`: if the node directly ahead of it writes them, and `holds` says so for their bytes,
+// that one is made to hold its stores in the L2s (rows.hpp).
+void hold_rows(eep_ctx* c, const void* rows, bool (*holds)(int64_t, RowWriter), hipStream_t st) {
+  if (c->rows_node == nullptr || rows != c->rows.recv || c->rows.held) return;
+  const RowWriter by = c->rows_idx == nullptr    ? RowWriter::kExpand
+                       : c->rows.scale_vecs > 0 ? RowWriter::kPackScales : RowWriter::kPack;
+  if (!holds(c->layout_T * c->k * c->x_row_bytes, by) || !behind_rows(c, st)) return;
+  c->rows.held = true;
+  if (by == RowWriter::kExpand)
+    (void)launch_expand(c, c->rows.x, c->rows.recv, c->layout_T, st, c->rows_node);
+  else
+    layout_pack_node(c, c->rows_idx, c->rows, c->layout_T, c->rows_node);
 }
 
-// The expert stage's signals, which stand between a dispatch and the combine of its rows.
+// The expert stage's signals, which stand between the receive rows and their combine.
 hipError_t signal_step(eep_ctx* c, hipStream_t st) {
-  const bool behind = behind_dispatch(c, st);
+  const bool behind = behind_rows(c, st);
   const hipError_t e = launch_signal(c, st);
   unsigned long long capture;
-  if (behind && (e != hipSuccess || !captured_node(st, &capture, &c->packed_last))) c->packed_idx = nullptr;
+  if (behind && (e != hipSuccess || !captured_node(st, &capture, &c->rows_last))) c->rows_node = nullptr;
   return e;
 }
 
@@ -184,7 +190,7 @@ int create_impl(const eep_config* cfg, eep_ctx* parent, void* workspace, int64_t
   c->scale_row_bytes = f.x_dtype == EEP_FP8_E4M3 ? (int64_t)(c->H / f.scale_group) * 4 : 0;
   c->layout_T = -1;
   c->captured_idx = nullptr;
-  forget_dispatch(c);
+  forget_rows(c);
   c->last_hip_error = 0;
   c->slab = nullptr;
   if (c->x_row_bytes % 16 || c->y_row_bytes % 16 || c->out_row_bytes % 16 ||
@@ -469,7 +475,7 @@ int eep_dispatch_layout(eep_ctx* c, const int32_t* topk_idx, int32_t T, void* st
   c->captured_on = (hipStream_t)stream;
   c->captured_idx =
       one_launch && captured_node(c->captured_on, &c->captured_in, &c->captured_node) ? topk_idx : nullptr;
-  forget_dispatch(c);
+  forget_rows(c);
   c->layout_T = T;
   c->dedup_T = -1;  // the de-duplicated tables belong to the previous layout
   return EEP_OK;
@@ -487,7 +493,7 @@ int eep_dispatch(eep_ctx* c, const void* x, const float* x_scale, void* recv_x, 
     return EEP_ERR_ALIGN;
   const int32_t* captured_idx = c->captured_idx;
   c->captured_idx = nullptr;
-  forget_dispatch(c);
+  forget_rows(c);
   if (dispatch_with_layout(c, captured_idx, x, x_scale, recv_x, recv_scale, T, (hipStream_t)stream)) return EEP_OK;
   hipError_t e = launch_pack(c, x, x_scale, recv_x, recv_scale, T, (hipStream_t)stream);
   return e == hipSuccess ? EEP_OK : fail_hip(c, e);
@@ -531,7 +537,7 @@ int eep_dispatch_quant(eep_ctx* c, const void* x_bf16, void* recv_x, float* recv
   if (!x_bf16 || !recv_x || !recv_scale) return EEP_ERR_INVALID_ARG;
   if (!aligned16(x_bf16) || !aligned16(recv_x) || ((uintptr_t)recv_scale & 3u))
     return EEP_ERR_ALIGN;
-  forget_dispatch(c);
+  forget_rows(c);
   hipError_t e = launch_pack_quant(c, x_bf16, recv_x, recv_scale, T, (hipStream_t)stream);
   return e == hipSuccess ? EEP_OK : fail_hip(c, e);
 }
@@ -545,7 +551,7 @@ int eep_combine(eep_ctx* c, const void* y, const float* topk_w, void* out, int32
   if (!aligned16(y) || !aligned16(out)) return EEP_ERR_ALIGN;
   // with detection on, the kernel itself waits for the ranks' signals and may drop one
   if (c->detect_timeout_ticks > 0) c->mem->unread_round = true;  // until eep_read_failures
-  hold_rows(c, y, pack_holds_for_combine, (hipStream_t)stream);
+  hold_rows(c, y, holds_for_combine, (hipStream_t)stream);
   hipError_t e = launch_combine(c, y, topk_w, out, T, (hipStream_t)stream);
   return e == hipSuccess ? EEP_OK : fail_hip(c, e);
 }
@@ -571,7 +577,7 @@ int eep_expert_stub(eep_ctx* c, int32_t kind, const void* recv_x, const float* r
     default:
       return EEP_ERR_INVALID_ARG;
   }
-  hold_rows(c, recv_x, pack_holds_for_stub, (hipStream_t)stream);
+  hold_rows(c, recv_x, holds_for_stub, (hipStream_t)stream);
   hipError_t e =
       launch_stub(c, kind, recv_x, recv_scale, expert_scale, y, T, (hipStream_t)stream);
   if (e == hipSuccess && c->detect_timeout_ticks > 0) e = signal_step(c, (hipStream_t)stream);
@@ -665,9 +671,18 @@ int eep_expand(eep_ctx* c, const void* recv_dedup, void* recv_x, int32_t T, void
   if (T == 0) return EEP_OK;
   if (!recv_dedup || !recv_x || recv_dedup == recv_x) return EEP_ERR_INVALID_ARG;
   if (!aligned16(recv_dedup) || !aligned16(recv_x)) return EEP_ERR_ALIGN;
-  forget_dispatch(c);
+  forget_rows(c);
   hipError_t e = launch_expand(c, recv_dedup, recv_x, T, (hipStream_t)stream);
-  return e == hipSuccess ? EEP_OK : fail_hip(c, e);
+  if (e != hipSuccess) return fail_hip(c, e);
+  unsigned long long capture;
+  hipGraphNode_t node;
+  if (captured_node((hipStream_t)stream, &capture, &node)) {
+    PackPieces rows = {};
+    rows.x = recv_dedup;
+    rows.recv = recv_x;
+    note_rows(c, node, capture, nullptr, rows);
+  }
+  return EEP_OK;
 }
 
 int eep_read_dedup(eep_ctx* c, int32_t field, int32_t* host_dst, int64_t n, void* stream) {

@@ -499,7 +499,7 @@ __global__ __launch_bounds__(64) void k_expand(const int32_t* __restrict__ expan
   }
 }
 
-hipError_t launch_expand(eep_ctx* c, const void* recv_dedup, void* recv_x, int T, hipStream_t st) {
+hipError_t launch_expand(eep_ctx* c, const void* recv_dedup, void* recv_x, int T, hipStream_t st, hipGraphNode_t held) {
   const int64_t rows = (int64_t)T * c->k;
   if (rows == 0) return hipSuccess;
   const int row_vecs = (int)(c->x_row_bytes / 16);
@@ -507,20 +507,23 @@ hipError_t launch_expand(eep_ctx* c, const void* recv_dedup, void* recv_x, int T
                                   rows < kExpandManyRows       ? kExpandVecs
                                   : row_vecs <= kExpandWideRow ? kExpandManyVecs
                                                                : kExpandWideVecs);
-  // Held stores (rows.hpp), in a captured step only: write-through's time over theirs, whole steps, 14 / 18 / 24 / 30 MiB of
-  // receive rows: in graphs 1.11 / 1.05 / 1.06-1.09 / 1.04, three sets of buffers in turn 1.02 / 1.03-1.04 / 1.03 / 1.01-1.02; call
-  // by call 1.06-1.15 / 1.03-1.06 / 1.06-1.11 / 1.04, but three sets in turn 0.98-1.00 / 0.98 / 0.94-0.96 / 0.93-0.95.
-  const bool held = mib_between(rows * c->x_row_bytes, 12, 32) && is_captured(st);
   return in_launches(rows, max_blocks(64) / ps.parts, [&](int64_t r0, int64_t n) {
-    const uint32_t magic = part_magic(ps.parts, n * ps.parts);
+    const int32_t* expand_of = c->dd_expand + r0;
+    const u32x4* from = (const u32x4*)recv_dedup;
+    int vecs = row_vecs;
+    uint32_t parts = (uint32_t)ps.parts, magic = part_magic(ps.parts, n * ps.parts);
     u32x4* to = (u32x4*)recv_x + r0 * row_vecs;
+    const unsigned grid = (unsigned)(n * ps.parts);
+    void* args[] = {&expand_of, &from, &vecs, &parts, &magic, &to};
     switch (ps.u) {
-#define EEP_EXPAND_CASE(U)                                                                     \
-  case U:                                                                                      \
-    hipLaunchKernelGGL((held ? (ps.exact ? k_expand<U, true, true> : k_expand<U, false, true>)   \
-                             : (ps.exact ? k_expand<U, true, false> : k_expand<U, false, false>)), \
-                       dim3((unsigned)(n * ps.parts)), dim3(64), 0, st, c->dd_expand + r0,     \
-                       (const u32x4*)recv_dedup, row_vecs, (uint32_t)ps.parts, magic, to);     \
+#define EEP_EXPAND_CASE(U)                                                                                      \
+  case U:                                                                                                       \
+    if (held != nullptr) {                                                                                      \
+      const auto kern = ps.exact ? k_expand<U, true, true> : k_expand<U, false, true>;                          \
+      return set_node(held, (const void*)kern, grid, 64, 0, args) ? hipSuccess : hipErrorInvalidValue;          \
+    }                                                                                                           \
+    hipLaunchKernelGGL((ps.exact ? k_expand<U, true, false> : k_expand<U, false, false>), dim3(grid), dim3(64), \
+                       0, st, expand_of, from, vecs, parts, magic, to);                                         \
     return hipGetLastError();
       EEP_EXPAND_CASE(8) EEP_EXPAND_CASE(7) EEP_EXPAND_CASE(6) EEP_EXPAND_CASE(5) EEP_EXPAND_CASE(4)
       EEP_EXPAND_CASE(3) EEP_EXPAND_CASE(2) EEP_EXPAND_CASE(1)

@@ -158,12 +158,13 @@ struct eep_ctx {
   // How the receive rows were cut last, if by a dispatch in one launch with its layout (0 or 1 or 2, as pack_split in
   // data.hip), else -1.
   int dispatched_split;
-  // Then also that launch's node, for the call that reads the rows (hold_rows in api.hip): its capture, router indices (null: no
-  // such node), pieces, and the node that a call directly behind it waits for.
-  const int32_t* packed_idx;
-  unsigned long long packed_in;
-  hipGraphNode_t packed_node, packed_last;
-  eep::PackPieces packed;
+  // The captured node that wrote the receive rows last, for the call that reads them (hold_rows in api.hip), if it is one that can
+  // hold its stores (else null): its capture, the node that a call directly behind it waits for, and what it was made of: of a
+  // layout and dispatch the router indices and pieces, of an expansion (null indices) the two buffers in the pieces' place.
+  hipGraphNode_t rows_node, rows_last;
+  unsigned long long rows_in;
+  const int32_t* rows_idx;
+  eep::PackPieces rows;
   int last_hip_error;
   int64_t field_ints[EEP_V_NUM_FIELDS];
 };
@@ -205,7 +206,9 @@ hipError_t launch_pack(eep_ctx* c, const void* x, const float* x_scale, void* re
 // pack through another row table (the de-duplicated dispatch's), payload rows only
 hipError_t launch_pack_rows(eep_ctx* c, const int32_t* rows, const void* x, void* recv, int T,
                             hipStream_t st);
-hipError_t launch_expand(eep_ctx* c, const void* recv_dedup, void* recv_x, int T, hipStream_t st);
+// (`held`: nothing is launched; this captured node of such a launch is made to hold its stores)
+hipError_t launch_expand(eep_ctx* c, const void* recv_dedup, void* recv_x, int T, hipStream_t st,
+                         hipGraphNode_t held = nullptr);
 hipError_t launch_dedup_layout(eep_ctx* c, int T, hipStream_t st);
 hipError_t launch_pack_quant(eep_ctx* c, const void* x_bf16, void* recv_q, float* recv_scale, int T,
                              hipStream_t st);

@@ -2125,18 +2125,6 @@ hipError_t launch_layout(eep_ctx* c, const int32_t* topk_idx, int T, hipStream_t
   return launch_layout(layout_io(c, topk_idx), T, st, one_launch);
 }
 
-static bool set_node(hipGraphNode_t node, const void* kernel, int grid, int threads, size_t lds, void** args) {
-  hipKernelNodeParams p = {};
-  p.func = const_cast<void*>(kernel);
-  p.gridDim = dim3((unsigned)grid);
-  p.blockDim = dim3((unsigned)threads);
-  p.sharedMemBytes = (unsigned)lds;
-  p.kernelParams = args;
-  if (hipGraphKernelNodeSetParams(node, &p) == hipSuccess) return true;
-  (void)hipGetLastError();
-  return false;
-}
-
 // The widths of a piece, us a step in graphs of 4 with 1 / 2 / 4 / 7 KiB: top-8, 512 tokens of 10 KiB 23.25 / 24.4 / 24.4 / 23.8, 640 of
 // 14 KiB 34.2 / 31.2 / 32.05 / 31.7, 768 of 8 KiB 23.0 / 23.9 / 27.0 / 30.0, 1024 of 7 KiB 28.6 / 27.7 / 27.7 / 27.3; top-4, 1024 of 14 KiB
 // 29.6 / 29.6 / 28.2 / 28.1; top-2, 1536 of 8 KiB 19.3 / 16.6 / 17.4 / 18.7, 2048 of 4 KiB 17.3 / 14.9 / 15.8 / 15.9.  A top-k that is

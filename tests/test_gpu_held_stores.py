@@ -143,9 +143,16 @@ def test_expansion(T, H):
             (T * k, 2 * H), 0x5A, dtype=torch.uint8, device="cuda")
         ctx.dedup_layout(T)
         ctx.dispatch_dedup(x, recv_d, T)
-        for captured in (False, True):
+        w, out = torch.rand((T, k), device="cuda"), torch.zeros((T, H), dtype=torch.bfloat16, device="cuda")
+
+        def run(st, combined):
+            ctx.expand(recv_d, recv, T, stream=st)
+            if combined:
+                ctx.combine(recv.view(torch.bfloat16), w, out, T, st)
+
+        for captured, combined in ((False, False), (True, False), (True, True)):
             recv.fill_(0x5A)
-            launch(ctx, captured, lambda st: ctx.expand(recv_d, recv, T, stream=st))
+            launch(ctx, captured, lambda st: run(st, combined))
             assert torch.equal(recv[:N], x[src[:N] // k]) and bool((recv[N:] == 0x5A).all())
     finally:
         ctx.destroy()
@@ -196,21 +203,29 @@ def test_scaling_stand_in(T, H, dtype):
 
 
 @gpu
-@pytest.mark.parametrize("call", ["stand-in", "expansion"])
-def test_held_only_in_a_captured_step(call):
-    """Call by call the next buffers may be other ones, and held stores lose there."""
-    T, k, H = 256, 8, 4096                             # 16 MiB of receive rows
+@pytest.mark.parametrize("call,T,want", [("stand-in", 256, True), ("expansion", 256, True), ("expansion", 191, False),
+                                         ("expansion", 192, True), ("expansion", 512, True), ("expansion", 513, False),
+                                         ("expansion, other rows", 256, False), ("expansion, after a kernel", 256, False)])
+def test_held_only_in_a_captured_step(call, T, want):
+    """Call by call the next buffers may be other ones, and held stores lose there; an expansion's do so too where another
+    kernel reads its rows."""
+    k, H = 8, 4096                                     # 16 MiB of receive rows for 256 tokens
     ctx, _, _ = context(T, k, H)
     try:
         recv, y = (torch.zeros((T * k, H), device="cuda", dtype=torch.bfloat16) for _ in range(2))
-        scale = torch.ones(20, device="cuda")
+        scale, w = torch.ones(20, device="cuda"), torch.rand((T, k), device="cuda")
+        out = torch.zeros((T, H), device="cuda", dtype=torch.bfloat16)
         ctx.dedup_layout(T)
 
         def run(st):
             if call == "stand-in":
                 ctx.expert_stub("scale", recv, y, T, expert_scale=scale, stream=st)
-            else:
-                ctx.expand(recv, y, T, stream=st)
+                return
+            ctx.expand(recv, y, T, stream=st)
+            if call.endswith("kernel"):
+                with torch.cuda.stream(st):
+                    scale.mul_(1.0)
+            ctx.combine(recv if call.endswith("rows") else y, w, out, T, st)
 
         launch(ctx, True, run)
         for captured in (False, True):
@@ -218,7 +233,7 @@ def test_held_only_in_a_captured_step(call):
                 launch(ctx, captured, run)
                 torch.cuda.synchronize()
             names = [e.key for e in prof.key_averages() if "k_stub_scale" in e.key or "k_expand" in e.key]
-            assert len(names) == 1 and re.search(r"(true|false)>\(", names[0])[1] == str(captured).lower(), names
+            assert len(names) == 1 and re.search(r"(true|false)>\(", names[0])[1] == str(captured and want).lower(), names
     finally:
         ctx.destroy()
 
