@@ -429,7 +429,8 @@ static hipError_t launch_pack_any(eep_ctx* c, const int32_t* rows, const void* x
 
 // With the layout in one launch the narrow pieces are the better ones up to larger sizes, also where another kernel writes what
 // combine reads (top-8, T = 1024 to 1536 of 1024 channels, 16 to 24 MiB of receive rows: 1.17-1.20 times as fast as two launches,
-// 1.09-1.12 with wider pieces; with a scaling stage 1.03-1.10 and 1.02-1.10).  Held stores: the call that reads the rows says so (hold_rows in api.hip).
+// 1.09-1.12 with wider pieces; with a scaling stage 1.03-1.10 and 1.02-1.10).  Whether stores are held is for the call that
+// reads the rows to say (hold_rows in api.hip).
 bool pack_pieces(const eep_ctx* c, const void* x, const float* x_scale, void* recv_x, float* recv_scale, int T,
                  PackPieces* out) {
   const int row_vecs = (int)(c->x_row_bytes / 16), scale_vecs = x_scale != nullptr ? (int)(c->scale_row_bytes / 16) : 0;
